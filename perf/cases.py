@@ -213,3 +213,106 @@ def tolerance(case):
     if LAYOUTS[case["layout"]][3] == "f32":
         return {"rel": 1e-6, "max": 1e-5}
     return {"rel": 1e-2, "max": 0.1}
+
+
+# ---- the same results in 64 bits, from the definitions -------------------------------------------------------
+MAX_EXACT_FLOPS = 4e13  # beyond this the 64-bit products take too long
+
+
+def _attend64(q, k, v, ck, cv, out, lse=None):
+    """Rows of a group over the kept entries and, causally, the group itself, head by head in blocks of rows."""
+    n, hq, d = q.shape
+    r, c = hq // k.shape[1], ck.shape[1]
+    for h in range(hq):
+        kk = torch.cat((ck[h // r].double(), k[:, h // r].double()))
+        vv = torch.cat((cv[h // r].double(), v[:, h // r].double()))
+        step = max(1, (1 << 27) // kk.shape[0])
+        for t in range(0, n, step):
+            e = min(n, t + step)
+            s = (q[t:e, h].double() @ kk[:c + e].T) / math.sqrt(d)
+            later = torch.arange(e, device=q.device)[None, :] > torch.arange(t, e, device=q.device)[:, None]
+            s[:, c:].masked_fill_(later, -math.inf)
+            if lse is not None:
+                lse[h, t:e] = torch.logsumexp(s, -1)
+            out[t:e, h] = torch.softmax(s, -1) @ vv[:c + e]
+
+
+def _kept64(case, k, v, qw, keep):
+    """Indices [h_kv][keep] that Eq. 2 keeps of a group, ascending."""
+    if case["rule"] == "key_norm_small":
+        s = -k.norm(dim=-1).T
+    elif case["rule"] == "value_norm":
+        s = v.norm(dim=-1).T
+    else:
+        w, hq, d = qw.shape
+        hkv = k.shape[1]
+        rows = qw.reshape(w, hkv, hq // hkv, d).permute(1, 0, 2, 3).reshape(hkv, -1, d)
+        s = torch.softmax(torch.matmul(rows, k.permute(1, 2, 0).contiguous()) / math.sqrt(d), -1).sum(1)
+    order = torch.sort(s, dim=-1, descending=True, stable=True).indices[:, :keep]
+    return order.sort(-1).values
+
+
+def _gather(x, idx):
+    return torch.stack([x[idx[h], h] for h in range(idx.shape[0])])
+
+
+def _cached64(t, fp8):
+    """A kept row as the cache's format holds it (8-bit: nearest E4M3 value, saturating at 448)."""
+    return t.clamp(-448, 448).float().to(torch.float8_e4m3fn).double() if fp8 else t
+
+
+def _rms64(x, w, eps):
+    return x / torch.sqrt((x * x).mean(-1, keepdim=True) + eps) * w.double()
+
+
+def _rope64(x, pos, dims):
+    """Rotary embedding with three position axes: halves of the head dimension pair up."""
+    half = x.shape[-1] // 2
+    axis = torch.tensor([0] * dims.mrope_section[0] + [1] * dims.mrope_section[1] + [2] * dims.mrope_section[2], device=x.device)
+    freq = dims.rope_theta ** (-torch.arange(half, device=x.device, dtype=torch.float64) / half)
+    ang = (pos.double()[axis].T * freq)[:, None, :]
+    a, b = x[..., :half], x[..., half:]
+    return torch.cat((a * ang.cos() - b * ang.sin(), b * ang.cos() + a * ang.sin()), -1)
+
+
+def exact(case, seed):
+    """What `run` returns, in 64 bits throughout. Where entries are pruned, the kept rows themselves are left out: at a
+    near-tie more than one selection is right, and it shifts the rows behind it."""
+    if work(case)["flops"] > MAX_EXACT_FLOPS:
+        return None
+    s = prepare(case, seed)
+    hq, hkv, d, _ = LAYOUTS[case["layout"]]
+    if case["kind"] == "prefill":
+        q, k, v = s["q"], s["k"], s["v"]
+        out = torch.empty(q.shape, dtype=torch.float64, device="cuda")
+        ck = cv = torch.empty(hkv, 0, d, dtype=torch.float64, device="cuda")
+        first = 0
+        for n, keep in _groups(case):
+            g = slice(first, first + n)
+            _attend64(q[g], k[g], v[g], ck, cv, out[g])
+            kg, vg = k[g].double(), v[g].double()
+            idx = _kept64(case, kg, vg, s["qw"].double() if case["window"] else None, keep)
+            ck = torch.cat((ck, _cached64(_gather(kg, idx), case["fp8_cache"])), 1)
+            cv = torch.cat((cv, _cached64(_gather(vg, idx), case["fp8_cache"])), 1)
+            first += n
+        return dict(out=out, k=None, v=None, pos=None)
+    cache, c, n = s["cache"], case["cache"], case["tokens"]
+    ck, cv = cache.k[:, :c], cache.v[:, :c]
+    if case["kind"] == "attend":
+        out = torch.empty(s["q"].shape, dtype=torch.float64, device="cuda")
+        lse = torch.empty(hq, n, dtype=torch.float64, device="cuda")
+        _attend64(s["q"], s["k"], s["v"], ck, cv, out, lse)
+        return dict(out=out, lse=lse)
+    dims = W.LAYER_DIMS[case["layout"]]
+    w, x = s["weights"].tensors, s["x"].double()
+    qkv = (_rms64(x, w["ln1_w"], dims.rms_eps) @ w["w_qkv"].double().T + w["b_qkv"].double()).view(n, hq + 2 * hkv, d)
+    q, k, v = _rope64(qkv[:, :hq], s["pos"], dims), _rope64(qkv[:, hq:hq + hkv], s["pos"], dims), qkv[:, hq + hkv:]
+    att = torch.empty(n, hq, d, dtype=torch.float64, device="cuda")
+    _attend64(q, k, v, ck, cv, att)
+    x1 = x + att.view(n, hq * d) @ w["w_o"].double().T
+    gate, up = (_rms64(x1, w["ln2_w"], dims.rms_eps) @ w["w_gate_up"].double().T).split(dims.d_ff, -1)
+    out = x1 + (torch.nn.functional.silu(gate) * up) @ w["w_down"].double().T
+    if s["keep"] < n:
+        return dict(out=out, k=None, v=None, pos=None, kept=None)
+    return dict(out=out, k=torch.cat((ck.double(), k.transpose(0, 1)), 1), v=torch.cat((cv.double(), v.transpose(0, 1)), 1),
+                pos=None, kept=None)
