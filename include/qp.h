@@ -218,15 +218,17 @@ qp_status qp_topk_compact(const qp_layout* layout, const float* scores, const vo
  *   cache: appended starting at cache->len (normally 0); entries already in it are visible
  *     to every group. Needs capacity >= len + qp_cache_capacity(...).
  *   out [N][H_q][d]
- * All arguments are validated before the first launch. Scoring and compaction of a group do not
- * depend on its attention, and the attention of group g+1 depends on the compaction of group g but
- * not on the attention of group g; the call uses two library-owned streams per device (created on
- * first use on the current device, default priority) for the scoring/compaction chain and for every
- * other group's attention (the latter only when a group's attention launch is under two rounds of
- * workgroups; larger launches all run on hip_stream). They are forked from hip_stream at entry and joined back into it before
- * the call returns: work the caller enqueues on hip_stream afterwards is ordered after all of this
- * call's work. The call only enqueues (it never waits for the GPU); calls from several host threads
- * are serialised while they enqueue, because they share those streams.
+ * All arguments are validated before the first launch. Scoring and compaction depend on the groups' K and V only, which
+ * are all there when the call starts, and a group's attention reads the cache rows appended by the groups before it.
+ * Videos whose attention fills the GPU at least twice are therefore served in runs of groups (as many as the workspace
+ * holds scores for): one launch per step scores, selects and attends for a whole run. Shorter videos, and groups of at
+ * most 32 stacked rows per KV head, take the steps group by group, with the key splits of qp_group_attend; a row's
+ * result may differ between the two in the last bits (a split adds a merge of partial sums), kept entries never do.
+ * Where it pays, the call uses two library-owned streams per device (created on first use on the current device,
+ * default priority) for scoring / compaction and for part of the attention. They are forked from hip_stream at entry
+ * and joined back into it before the call returns: work the caller enqueues on hip_stream afterwards is ordered after
+ * all of this call's work. The call only enqueues (it never waits for the GPU); calls from several host threads
+ * are serialised while they enqueue on those streams.
  * Failure after the first launch (QP_ERR_HIP from a launch or a stream call): nothing further is enqueued, the
  * library's streams are still joined back into hip_stream, the groups already enqueued run to completion, and
  * cache->len is restored to its value at entry (rows beyond it, and `out`, then hold unspecified data). */
@@ -264,7 +266,7 @@ qp_status qp_attend_plan(const qp_layout* layout, int32_t n_group_tokens, int32_
 qp_status qp_select_attend_kernel(int32_t which);
 
 /* Test seam for the error paths: the n_checks-th launch check from now on (every entry point of this header checks
- * once after it has enqueued its launches; qp_prefill_video checks three times per group) reports QP_ERR_HIP with
+ * once after it has enqueued its launches; qp_prefill_video checks three times per group or run of groups) reports QP_ERR_HIP with
  * hipErrorLaunchFailure although the GPU work was enqueued and runs normally. 0 switches it off. Process-wide. */
 qp_status qp_debug_fail_after(int32_t n_checks);
 

@@ -188,13 +188,17 @@ __global__ __launch_bounds__(MF_NT, 2) void attend_mfma_kernel(AttendArgs a) {
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // wave-uniform for the compiler too: scalar address and branch work
   const int l32 = lane & 31, g = lane >> 5;
   const int r_heads = a.h_q / a.h_kv;
-  const int n_rows = a.n_g * r_heads;
-  const int n_hb = (n_rows + MF_HB - 1) / MF_HB;  // half blocks of 128 rows
-  const int n_rb = (n_hb + 1) / 2;                // workgroups per KV head (256 rows or a pair of half blocks)
+  int n_rows = a.n_g * r_heads;
+  int n_hb = (n_rows + MF_HB - 1) / MF_HB;  // half blocks of 128 rows
+  int n_rb = (n_hb + 1) / 2;                // workgroups per KV head (256 rows or a pair of half blocks)
   // Work items of a KV head: the row blocks that one workgroup serves whole (longest first), then the chunks of the
   // split row blocks (the shortest ones), chunk by chunk.
   const int n_whole = n_rb - (a.n_split > 1 ? a.split_rb : 0);
-  const int n_items = n_whole + (n_rb - n_whole) * a.n_split;
+  int n_items = n_whole + (n_rb - n_whole) * a.n_split;
+  // A run of groups is never split: its items are the row blocks of the last group (longest key range), then those of
+  // the group before it, and so on.
+  const int n_rb_last = a.groups > 1 ? ((a.n_last * r_heads + MF_HB - 1) / MF_HB + 1) / 2 : 0;
+  if (a.groups > 1) n_items = n_rb_last + (a.groups - 1) * n_rb;
   // workgroup id -> (KV head, item): ids go round-robin over the 8 XCDs
   int h, item;
   {
@@ -213,8 +217,24 @@ __global__ __launch_bounds__(MF_NT, 2) void attend_mfma_kernel(AttendArgs a) {
     }
   }
   if (item >= n_items) return;    // padding workgroups of the XCD mapping (whole workgroup, before any barrier)
+  const int tokens = a.n_g;  // of a full group
+  size_t t0 = 0;             // first token of this item's group
   int rbi = item, chunk = 0, my_split = 1;  // row block (0 = latest tokens), key chunk, chunks of this row block
-  if (item >= n_whole) {
+  if (a.groups > 1) {  // from here on: this item's group
+    int grp = a.groups - 1;
+    if (item < n_rb_last) {
+      a.n_g = a.n_last;
+      n_rows = a.n_g * r_heads;
+      n_hb = (n_rows + MF_HB - 1) / MF_HB;
+      n_rb = n_rb_last;
+    } else {
+      const int e = item - n_rb_last, back = e / n_rb;
+      grp -= 1 + back;
+      rbi = e - back * n_rb;
+    }
+    a.c += grp * a.keep;
+    t0 += (size_t)grp * tokens;
+  } else if (item >= n_whole) {
     const int e = item - n_whole, n_sp = n_rb - n_whole;
     chunk = e / n_sp;
     rbi = n_whole + (e - chunk * n_sp);
@@ -235,7 +255,7 @@ __global__ __launch_bounds__(MF_NT, 2) void attend_mfma_kernel(AttendArgs a) {
   const int rowc = row_ok ? row : n_rows - 1;
   const int t_lane = rowc / r_heads;
   const int j_lane = rowc - t_lane * r_heads;
-  const bf16_t* qrow = (const bf16_t*)a.q + ((size_t)t_lane * a.h_q + (size_t)h * r_heads + j_lane) * MF_D;
+  const bf16_t* qrow = (const bf16_t*)a.q + ((t0 + t_lane) * a.h_q + (size_t)h * r_heads + j_lane) * MF_D;
   // wave-uniform token horizons
   const int t_w_max = min(row0 + 31, n_rows - 1) / r_heads;
   const int t_w_min = min(row0, n_rows - 1) / r_heads;
@@ -250,8 +270,8 @@ __global__ __launch_bounds__(MF_NT, 2) void attend_mfma_kernel(AttendArgs a) {
   constexpr int CROW = F8 ? MF_D : MF_D * 2;  // bytes of one cached row
   const unsigned char* ck = (const unsigned char*)a.ck + (size_t)h * a.cap * CROW;
   const unsigned char* cv = (const unsigned char*)a.cv + (size_t)h * a.cap * CROW;
-  const unsigned char* gk = (const unsigned char*)a.k + (size_t)h * (MF_D * 2);
-  const unsigned char* gv = (const unsigned char*)a.v + (size_t)h * (MF_D * 2);
+  const unsigned char* gk = (const unsigned char*)a.k + (t0 * a.h_kv + h) * (MF_D * 2);
+  const unsigned char* gv = (const unsigned char*)a.v + (t0 * a.h_kv + h) * (MF_D * 2);
   const unsigned gstride_b = (unsigned)a.h_kv * (MF_D * 2);
 
   // staging: this wavefront's two load instructions per tensor cover keys 8*wave .. 8*wave+7 of the tile;
@@ -416,7 +436,7 @@ __global__ __launch_bounds__(MF_NT, 2) void attend_mfma_kernel(AttendArgs a) {
     if (g == 0) a.part_lse[prow] = m_run * c2 + log2f(l_tot);
     return;
   }
-  bf16_t* orow = (bf16_t*)a.out + ((size_t)t_lane * a.h_q + (size_t)h * r_heads + j_lane) * MF_D;
+  bf16_t* orow = (bf16_t*)a.out + ((t0 + t_lane) * a.h_q + (size_t)h * r_heads + j_lane) * MF_D;
 #pragma unroll
   for (int n = 0; n < 4; ++n)
 #pragma unroll
@@ -633,16 +653,41 @@ AttendPlan plan_attend_mfma(const AttendArgs& a, size_t split_ws_bytes) {
   return p;
 }
 
-void launch_attend_mfma(const AttendArgs& a_in, void* split_ws, size_t split_ws_bytes, hipStream_t s) {
+static void set_lds_limit() {
   static bool attr_set[QP_MAX_DEVICES] = {};
   const int dev = current_device();
-  if (dev < 0 || !attr_set[dev]) {
-    (void)hipFuncSetAttribute((const void*)attend_mfma_kernel<false>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                              MF_STAGES * MF_SLOT);
-    (void)hipFuncSetAttribute((const void*)attend_mfma_kernel<true>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                              MF_STAGES * MF_SLOT);
-    if (dev >= 0) attr_set[dev] = true;
+  if (dev >= 0 && attr_set[dev]) return;
+  (void)hipFuncSetAttribute((const void*)attend_mfma_kernel<false>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                            MF_STAGES * MF_SLOT);
+  (void)hipFuncSetAttribute((const void*)attend_mfma_kernel<true>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                            MF_STAGES * MF_SLOT);
+  if (dev >= 0) attr_set[dev] = true;
+}
+
+long attend_mfma_row_blocks(int n_g, int h_q, int h_kv) {
+  return (((long)n_g * (h_q / h_kv) + MF_HB - 1) / MF_HB + 1) / 2;
+}
+
+void launch_attend_mfma_run(const AttendArgs& a_in, hipStream_t s) {
+  set_lds_limit();
+  AttendArgs a = a_in;
+  a.mirrored = 0;
+  a.n_split = 1;
+  a.split_rb = a.split_tiles = a.part_rows = 0;
+  const long items = attend_mfma_row_blocks(a.n_last, a.h_q, a.h_kv) + (a.groups - 1) * attend_mfma_row_blocks(a.n_g, a.h_q, a.h_kv);
+  long wgs = items * a.h_kv;
+  if (8 % a.h_kv == 0) {
+    const int per = 8 / a.h_kv;
+    wgs = (items + per - 1) / per * 8;
   }
+  if (a.cache_fp8)
+    hipLaunchKernelGGL(attend_mfma_kernel<true>, dim3((unsigned)wgs), dim3(MF_NT), MF_STAGES * MF_SLOT, s, a);
+  else
+    hipLaunchKernelGGL(attend_mfma_kernel<false>, dim3((unsigned)wgs), dim3(MF_NT), MF_STAGES * MF_SLOT, s, a);
+}
+
+void launch_attend_mfma(const AttendArgs& a_in, void* split_ws, size_t split_ws_bytes, hipStream_t s) {
+  set_lds_limit();
   AttendArgs a = a_in;
   const AttendPlan p = plan_attend_mfma(a, split_ws != nullptr ? split_ws_bytes : 0);
   a.mirrored = p.mirrored;

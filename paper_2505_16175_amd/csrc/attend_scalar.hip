@@ -24,6 +24,15 @@ __global__ __launch_bounds__(256) void attend_scalar_kernel(AttendArgs a) {
   const int qh = blockIdx.y;
   const int r = a.h_q / a.h_kv;
   const int h = qh / r;
+  if (a.groups > 1) {  // this workgroup's group of a run (grid.z)
+    const size_t t0 = (size_t)blockIdx.z * a.n_g;
+    a.q = (const T*)a.q + t0 * a.h_q * D;
+    a.k = (const T*)a.k + t0 * a.h_kv * D;
+    a.v = (const T*)a.v + t0 * a.h_kv * D;
+    a.out = (T*)a.out + t0 * a.h_q * D;
+    a.c += blockIdx.z * a.keep;
+    if ((int)blockIdx.z == a.groups - 1) a.n_g = a.n_last;
+  }
   const bool active = i < a.n_g;            // whole wave agrees
 
   if (active) {
@@ -112,7 +121,7 @@ __global__ __launch_bounds__(256) void attend_scalar_kernel(AttendArgs a) {
 }
 
 void launch_attend_scalar(const AttendArgs& a, int dtype, hipStream_t s) {
-  dim3 grid((a.n_g + 3) / 4, a.h_q), block(256);
+  dim3 grid((a.n_g + 3) / 4, a.h_q, a.groups > 1 ? a.groups : 1), block(256);
   if (dtype == QP_F32) {
     if (a.d == 64) hipLaunchKernelGGL((attend_scalar_kernel<float, 64>), grid, block, 0, s, a);
     else hipLaunchKernelGGL((attend_scalar_kernel<float, 128>), grid, block, 0, s, a);

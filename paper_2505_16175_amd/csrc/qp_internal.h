@@ -128,10 +128,15 @@ struct AttendArgs {
   int mirrored;       // MFMA kernel's row mapping: 1 = mirrored half blocks (balanced), 0 = consecutive, longest first
   float* part_o;      // [n_split][h_kv * part_rows][d] f32
   float* part_lse;    // [n_split][h_kv * part_rows]    f32, log2 units
+  // Run of groups: `groups` consecutive groups of n_g tokens each (the last one n_last) in one launch. q, k, v and out
+  // point at the first one's first token; group i sees c + i * keep cache entries. groups <= 1: one group of n_g tokens.
+  int groups, n_last, keep;
 };
 
 // Launchers (defined next to their kernels). They only enqueue; hipGetLastError is checked by the caller.
-void launch_attend_scalar(const AttendArgs& a, int dtype, hipStream_t s);
+void launch_attend_scalar(const AttendArgs& a, int dtype, hipStream_t s);  // a run of groups if a.groups > 1
+void launch_attend_mfma_run(const AttendArgs& a, hipStream_t s);            // a run of groups, never split
+long attend_mfma_row_blocks(int n_g, int h_q, int h_kv);                    // workgroups per KV head of an unsplit group
 bool attend_mfma_supported(const AttendArgs& a, int dtype);
 // How launch_attend_mfma lays a call out: grid (one-dimensional), key split, row mapping, scratch it takes.
 struct AttendPlan {
@@ -163,20 +168,31 @@ void note_hip_error(int e);  // what qp_last_hip_error() reports on this thread
 hipStream_t side_fork(hipStream_t main);
 void side_join(hipStream_t main);
 
-void launch_score_norm(const void* x, int dtype, int n_g, int h_kv, int d, float sign, float* scores, hipStream_t s);
+// Scoring and selection take runs of groups too: `count` consecutive groups of the call's n_g tokens, the last one of
+// n_last; group i's scores are at scores + i * score_stride (floats). One launch serves all of them (a grid dimension).
+struct GroupRun {
+  int count, n_last;
+  size_t score_stride;
+};
+constexpr int QP_MAX_RUN_GROUPS = 32768;  // a grid dimension
+
+void launch_score_norm(const void* x, int dtype, int n_g, int h_kv, int d, float sign, float* scores, const GroupRun& run,
+                       hipStream_t s);
 
 struct WindowArgs {
   const void* k;      // [n_g][h_kv][d]
   const void* q_win;  // [w][h_q][d]
   float* scores;      // [h_kv][n_g]
   void* workspace;
+  size_t workspace_stride;  // bytes between the groups' scratch areas of a run
   int n_g, h_q, h_kv, d, w;
   float scale_log2;
+  GroupRun run;
 };
 size_t window_workspace_bytes(int h_q, int h_kv, int n_g, int w);
 size_t window_logit_workspace_bytes(int h_kv, int d);  // the summed window rows, [h_kv][d] f32
 void launch_score_window_logit(const WindowArgs& a, int dtype, float scale, hipStream_t s);
-void launch_share_heads(float* scores, int h_kv, int n_g, hipStream_t s);
+void launch_share_heads(float* scores, int h_kv, int n_g, const GroupRun& run, hipStream_t s);
 void launch_score_window(const WindowArgs& a, int dtype, hipStream_t s);
 bool window_mfma_supported(int dtype, int h_q, int h_kv, int d, int w);
 size_t window_mfma_workspace_bytes(int h_q, int h_kv, int n_g, int w);
@@ -191,6 +207,8 @@ struct TopkArgs {
   int32_t* pos;         // [h_kv][cap]
   int n_g, h_kv, d, keep, base, cap, len;
   int cache_fp8;        // 1: ck / cv take one E4M3 byte per element (bf16 inputs only)
+  int keep_last;        // keep of the run's last group; group i appends at len + i * keep, its tokens start at base + i * n_g
+  GroupRun run;
 };
 size_t topk_workspace_bytes(int h_kv, int keep);
 hipError_t launch_topk_compact(const TopkArgs& a, int dtype, int32_t* kept_ws, hipStream_t s);

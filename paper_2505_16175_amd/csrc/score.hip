@@ -24,7 +24,10 @@ constexpr int NORM_UNROLL = 4;  // rows in flight per lane group: four independe
 
 template <typename T, int D>
 __global__ __launch_bounds__(256) void score_norm_kernel(const T* __restrict__ x, int n_g, int h_kv, float sign,
-                                                         float* __restrict__ scores) {
+                                                         float* __restrict__ scores, GroupRun run) {
+  x += (size_t)blockIdx.y * n_g * h_kv * D;  // this workgroup's group of the run
+  scores += blockIdx.y * run.score_stride;
+  if ((int)blockIdx.y == run.count - 1) n_g = run.n_last;
   constexpr int PER = Elem<T>::kPer16B;
   constexpr int LPR = D / PER;             // lanes per row, power of two in 8..32
   constexpr int TW = 64 / LPR * NORM_UNROLL;  // tokens per wavefront item
@@ -59,22 +62,23 @@ __global__ __launch_bounds__(256) void score_norm_kernel(const T* __restrict__ x
 }
 
 template <typename T, int D>
-static void launch_norm(const void* x, int n_g, int h_kv, float sign, float* scores, hipStream_t s) {
+static void launch_norm(const void* x, int n_g, int h_kv, float sign, float* scores, const GroupRun& run, hipStream_t s) {
   constexpr int TW = 64 / (D / Elem<T>::kPer16B) * NORM_UNROLL;
   const long items = (long)((n_g + TW - 1) / TW) * h_kv;
   long wgs = (items + 3) / 4;  // four wavefronts per workgroup, one item each
   if (wgs > 8192) wgs = 8192;  // wavefronts stride over the items beyond 32 workgroups per CU
-  hipLaunchKernelGGL((score_norm_kernel<T, D>), dim3((unsigned)wgs), dim3(256), 0, s, (const T*)x, n_g, h_kv, sign, scores);
+  hipLaunchKernelGGL((score_norm_kernel<T, D>), dim3((unsigned)wgs, run.count), dim3(256), 0, s, (const T*)x, n_g, h_kv, sign,
+                     scores, run);
 }
 
-void launch_score_norm(const void* x, int dtype, int n_g, int h_kv, int d, float sign, float* scores,
+void launch_score_norm(const void* x, int dtype, int n_g, int h_kv, int d, float sign, float* scores, const GroupRun& run,
                        hipStream_t s) {
   if (dtype == QP_F32) {
-    if (d == 64) launch_norm<float, 64>(x, n_g, h_kv, sign, scores, s);
-    else launch_norm<float, 128>(x, n_g, h_kv, sign, scores, s);
+    if (d == 64) launch_norm<float, 64>(x, n_g, h_kv, sign, scores, run, s);
+    else launch_norm<float, 128>(x, n_g, h_kv, sign, scores, run, s);
   } else {
-    if (d == 64) launch_norm<bf16_t, 64>(x, n_g, h_kv, sign, scores, s);
-    else launch_norm<bf16_t, 128>(x, n_g, h_kv, sign, scores, s);
+    if (d == 64) launch_norm<bf16_t, 64>(x, n_g, h_kv, sign, scores, run, s);
+    else launch_norm<bf16_t, 128>(x, n_g, h_kv, sign, scores, run, s);
   }
 }
 
@@ -116,7 +120,10 @@ __global__ __launch_bounds__(256) void window_qsum_kernel(const T* __restrict__ 
 
 template <typename T, int D>
 __global__ __launch_bounds__(256) void score_dot_kernel(const T* __restrict__ x, const float* __restrict__ qsum, int n_g,
-                                                        int h_kv, float scale, float* __restrict__ scores) {
+                                                        int h_kv, float scale, float* __restrict__ scores, GroupRun run) {
+  x += (size_t)blockIdx.y * n_g * h_kv * D;
+  scores += blockIdx.y * run.score_stride;
+  if ((int)blockIdx.y == run.count - 1) n_g = run.n_last;
   constexpr int PER = Elem<T>::kPer16B;
   constexpr int LPR = D / PER;
   constexpr int TW = 64 / LPR * NORM_UNROLL;
@@ -159,8 +166,8 @@ static void launch_logit(const WindowArgs& a, float scale, hipStream_t s) {
   const long items = (long)((a.n_g + TW - 1) / TW) * a.h_kv;
   long wgs = (items + 3) / 4;
   if (wgs > 8192) wgs = 8192;
-  hipLaunchKernelGGL((score_dot_kernel<T, D>), dim3((unsigned)wgs), dim3(256), 0, s, (const T*)a.k, qsum, a.n_g, a.h_kv,
-                     scale, a.scores);
+  hipLaunchKernelGGL((score_dot_kernel<T, D>), dim3((unsigned)wgs, a.run.count), dim3(256), 0, s, (const T*)a.k, qsum, a.n_g,
+                     a.h_kv, scale, a.scores, a.run);
 }
 
 size_t window_logit_workspace_bytes(int h_kv, int d) { return ((size_t)h_kv * d * sizeof(float) + 255) / 256 * 256; }
@@ -177,7 +184,9 @@ void launch_score_window_logit(const WindowArgs& a, int dtype, float scale, hipS
 }
 
 // Head-shared selection: scores[h][j] <- sum over h' of scores[h'][j], in head order, for every h.
-__global__ __launch_bounds__(256) void share_heads_kernel(float* __restrict__ scores, int h_kv, int n_g) {
+__global__ __launch_bounds__(256) void share_heads_kernel(float* __restrict__ scores, int h_kv, int n_g, GroupRun run) {
+  scores += blockIdx.y * run.score_stride;
+  if ((int)blockIdx.y == run.count - 1) n_g = run.n_last;
   const int j = blockIdx.x * 256 + threadIdx.x;
   if (j >= n_g) return;
   float tot = 0.f;
@@ -186,8 +195,8 @@ __global__ __launch_bounds__(256) void share_heads_kernel(float* __restrict__ sc
   for (int h = 0; h < h_kv; ++h) scores[(size_t)h * n_g + j] = tot;
 }
 
-void launch_share_heads(float* scores, int h_kv, int n_g, hipStream_t s) {
-  hipLaunchKernelGGL(share_heads_kernel, dim3((n_g + 255) / 256), dim3(256), 0, s, scores, h_kv, n_g);
+void launch_share_heads(float* scores, int h_kv, int n_g, const GroupRun& run, hipStream_t s) {
+  hipLaunchKernelGGL(share_heads_kernel, dim3((n_g + 255) / 256, run.count), dim3(256), 0, s, scores, h_kv, n_g, run);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -200,6 +209,8 @@ __global__ __launch_bounds__(256) void window_rowstats_kernel(WindowArgs a, floa
   constexpr int PER = Elem<T>::kPer16B;
   constexpr int CHUNKS = D / PER;
   __shared__ float q_lds[WAVES][D];
+  const int n_g = (int)blockIdx.z == a.run.count - 1 ? a.run.n_last : a.n_g;
+  lse2 += blockIdx.z * (a.workspace_stride / sizeof(float));
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int t = blockIdx.x * WAVES + wave;
   const int qh = blockIdx.y;
@@ -218,9 +229,9 @@ __global__ __launch_bounds__(256) void window_rowstats_kernel(WindowArgs a, floa
   __syncthreads();
   if (!active) return;
   float m = -INFINITY, l = 0.f;
-  const T* gk = (const T*)a.k + (size_t)h * D;
+  const T* gk = (const T*)a.k + ((size_t)blockIdx.z * a.n_g * a.h_kv + h) * D;
   const size_t gstride = (size_t)a.h_kv * D;
-  for (int j = lane; j < a.n_g; j += 64) {
+  for (int j = lane; j < n_g; j += 64) {
     const T* krow = gk + (size_t)j * gstride;
     float s = 0.f;
 #pragma unroll
@@ -250,10 +261,12 @@ __global__ __launch_bounds__(64) void window_colsum_kernel(WindowArgs a, const f
   constexpr int CHUNKS = D / PER;
   const int j = blockIdx.x * blockDim.x + threadIdx.x;
   const int h = blockIdx.y;
-  if (j >= a.n_g) return;
+  const int n_g = (int)blockIdx.z == a.run.count - 1 ? a.run.n_last : a.n_g;
+  if (j >= n_g) return;
+  lse2 += blockIdx.z * (a.workspace_stride / sizeof(float));
   const int r = a.h_q / a.h_kv;
   float kv[D];
-  const T* krow = (const T*)a.k + ((size_t)j * a.h_kv + h) * D;
+  const T* krow = (const T*)a.k + (((size_t)blockIdx.z * a.n_g + j) * a.h_kv + h) * D;
 #pragma unroll
   for (int c = 0; c < CHUNKS; ++c) {
     uint4 raw = *(const uint4*)(krow + c * PER);
@@ -275,7 +288,7 @@ __global__ __launch_bounds__(64) void window_colsum_kernel(WindowArgs a, const f
       total += exp2f(s * a.scale_log2 - lse2[(size_t)qh * a.w + t]);
     }
   }
-  a.scores[(size_t)h * a.n_g + j] = total;
+  a.scores[blockIdx.z * a.run.score_stride + (size_t)h * n_g + j] = total;
 }
 
 size_t window_workspace_bytes(int h_q, int h_kv, int n_g, int w) {
@@ -287,8 +300,8 @@ size_t window_workspace_bytes(int h_q, int h_kv, int n_g, int w) {
 template <typename T, int D>
 static void launch_window_t(const WindowArgs& a, hipStream_t s) {
   float* lse2 = (float*)a.workspace;
-  hipLaunchKernelGGL((window_rowstats_kernel<T, D>), dim3((a.w + 3) / 4, a.h_q), dim3(256), 0, s, a, lse2);
-  hipLaunchKernelGGL((window_colsum_kernel<T, D>), dim3((a.n_g + 63) / 64, a.h_kv), dim3(64), 0, s, a, lse2);
+  hipLaunchKernelGGL((window_rowstats_kernel<T, D>), dim3((a.w + 3) / 4, a.h_q, a.run.count), dim3(256), 0, s, a, lse2);
+  hipLaunchKernelGGL((window_colsum_kernel<T, D>), dim3((a.n_g + 63) / 64, a.h_kv, a.run.count), dim3(64), 0, s, a, lse2);
 }
 
 void launch_score_window(const WindowArgs& a, int dtype, hipStream_t s) {

@@ -52,7 +52,8 @@ static int win_chunk_keys(int n_g) {
 //         exp2 around it.
 // PASS 2: scores[h][j] for the chunk's keys from the merged partials.
 template <int PASS>
-__global__ __launch_bounds__(WIN_NT) void window_kernel(WindowArgs a, float2* __restrict__ partial, int kc_keys, int n_kc) {
+__global__ __launch_bounds__(WIN_NT) void window_kernel(WindowArgs a, float2* __restrict__ partial, int kc_keys, int n_kc,
+                                                        int kc_last, int n_kc_last) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];  // [kc_keys x 256 B of K][pass 2: lse, column sums]
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -61,6 +62,11 @@ __global__ __launch_bounds__(WIN_NT) void window_kernel(WindowArgs a, float2* __
   const int n_rows = r_heads * a.w;
   const int n_rows_pad = win_rows_padded(a.h_q, a.h_kv, a.w);
   const int n_rbk = n_rows_pad / 32;
+  // this workgroup's group of the run (grid.y); the last one may be shorter and has its own chunk length
+  a.k = (const bf16_t*)a.k + (size_t)blockIdx.y * a.n_g * a.h_kv * WIN_D;
+  a.scores += blockIdx.y * a.run.score_stride;
+  partial += blockIdx.y * (a.workspace_stride / sizeof(float2));
+  if ((int)blockIdx.y == a.run.count - 1) a.n_g = a.run.n_last, kc_keys = kc_last, n_kc = n_kc_last;
   // workgroup id -> (KV head, key chunk), one head's workgroups on the same XCDs
   int h, kc;
   {
@@ -255,10 +261,12 @@ void launch_score_window_mfma(const WindowArgs& a, hipStream_t s) {
   const int kc_keys = win_chunk_keys(a.n_g);
   const int n_kc = (a.n_g + kc_keys - 1) / kc_keys;
   float2* partial = (float2*)a.workspace;
-  int wgs = n_kc * a.h_kv;
+  const int kc_last = win_chunk_keys(a.run.n_last), n_kc_last = (a.run.n_last + kc_last - 1) / kc_last;
+  const int n_most = n_kc > n_kc_last ? n_kc : n_kc_last;  // a shorter group may be dealt to more, shorter chunks
+  int wgs = n_most * a.h_kv;
   if (8 % a.h_kv == 0) {
     const int per = 8 / a.h_kv;
-    wgs = (n_kc + per - 1) / per * 8;
+    wgs = (n_most + per - 1) / per * 8;
   }
   const size_t lds1 = (size_t)kc_keys * 256;
   const size_t lds2 = lds1 + (size_t)WIN_NW * 32 * sizeof(float) + (size_t)WIN_NW * kc_keys * sizeof(float);
@@ -270,8 +278,8 @@ void launch_score_window_mfma(const WindowArgs& a, hipStream_t s) {
     (void)hipFuncSetAttribute((const void*)window_kernel<2>, hipFuncAttributeMaxDynamicSharedMemorySize, max2);
     if (dev >= 0) attr_set[dev] = true;
   }
-  hipLaunchKernelGGL(window_kernel<1>, dim3(wgs), dim3(WIN_NT), lds1, s, a, partial, kc_keys, n_kc);
-  hipLaunchKernelGGL(window_kernel<2>, dim3(wgs), dim3(WIN_NT), lds2, s, a, partial, kc_keys, n_kc);
+  hipLaunchKernelGGL(window_kernel<1>, dim3(wgs, a.run.count), dim3(WIN_NT), lds1, s, a, partial, kc_keys, n_kc, kc_last, n_kc_last);
+  hipLaunchKernelGGL(window_kernel<2>, dim3(wgs, a.run.count), dim3(WIN_NT), lds2, s, a, partial, kc_keys, n_kc, kc_last, n_kc_last);
 }
 
 }  // namespace qp

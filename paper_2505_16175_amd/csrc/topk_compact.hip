@@ -61,6 +61,17 @@ __device__ __forceinline__ uint2 pack8_e4m3(const u32x4& b) {
   return r;
 }
 
+// Turns the arguments of a run into those of this workgroup's group (grid.z).
+__device__ __forceinline__ void run_group(TopkArgs& a, size_t token_bytes) {
+  const int i = blockIdx.z;
+  a.scores += i * a.run.score_stride;
+  a.k = (const unsigned char*)a.k + (size_t)i * a.n_g * token_bytes;
+  a.v = (const unsigned char*)a.v + (size_t)i * a.n_g * token_bytes;
+  a.base += i * a.n_g;
+  a.len += i * a.keep;
+  if (i == a.run.count - 1) a.n_g = a.run.n_last, a.keep = a.keep_last;
+}
+
 // keep == n_g (retention 1, and the single tokens and text chunks that follow the video, Sec. 2.1): every token
 // survives whatever its score, so the selection is the identity and the compaction a plain append. One lane per 16
 // bytes of a row; grid (row runs, KV heads).
@@ -70,6 +81,7 @@ __global__ __launch_bounds__(APPEND_THREADS) void append_all_kernel(TopkArgs a, 
   constexpr int PER = Elem<T>::kPer16B;
   constexpr int LPR = D / PER;  // lanes per row
   const int h = blockIdx.y;
+  run_group(a, (size_t)a.h_kv * D * sizeof(T));
   const int idx = blockIdx.x * APPEND_THREADS + threadIdx.x;
   const int j = idx / LPR, sub = idx - j * LPR;
   if (j >= a.n_g) return;
@@ -97,6 +109,7 @@ __global__ __launch_bounds__(TOPK_THREADS) void topk_compact_kernel(TopkArgs a, 
   __shared__ uint32_t wave_a[TOPK_WAVES], wave_b[TOPK_WAVES], wave_min[TOPK_WAVES], wave_max[TOPK_WAVES];
   __shared__ uint32_t sel_bucket, sel_need, sel_count, sel_key, list_n;
 
+  run_group(a, (size_t)a.h_kv * D * sizeof(T));
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int h = blockIdx.y, n = a.n_g;
   uint32_t* sl_idx = keys + n;
@@ -351,13 +364,13 @@ __global__ __launch_bounds__(TOPK_THREADS) void topk_compact_kernel(TopkArgs a, 
 size_t topk_workspace_bytes(int h_kv, int keep) { return ((size_t)h_kv * keep * sizeof(int32_t) + 255) / 256 * 256; }
 
 // Tokens per slice: about SLICE_WANT_KEEP survivors each, at most SLICES_MAX slices and about one workgroup per
-// compute unit over all heads, at most SLICE_MAX tokens, whole batches of 64.
-static int slice_tokens_for(int n_g, int keep, int h_kv) {
+// compute unit over all heads (of all groups of a run), at most SLICE_MAX tokens, whole batches of 64.
+static int slice_tokens_for(int n_g, int keep, int heads) {
   int slices = (keep + SLICE_WANT_KEEP - 1) / SLICE_WANT_KEEP;
   if (slices > SLICES_MAX) slices = SLICES_MAX;
   // every workgroup repeats the head's threshold search: with many heads there are enough workgroups without
   // slicing, and more than one per compute unit only multiplies that search
-  const int per_head = device_cu_count() / h_kv;
+  const int per_head = device_cu_count() / heads;
   if (slices > per_head) slices = per_head;
   const int at_least = (n_g + SLICE_MAX - 1) / SLICE_MAX;
   if (slices < at_least) slices = at_least;
@@ -369,11 +382,11 @@ template <typename T, int D>
 static hipError_t launch_fused(const TopkArgs& a, int32_t* kept_out, hipStream_t s) {
   if (a.keep == a.n_g) {  // nothing to select
     constexpr int LPR = D / Elem<T>::kPer16B;
-    hipLaunchKernelGGL((append_all_kernel<T, D>), dim3((a.n_g * LPR + APPEND_THREADS - 1) / APPEND_THREADS, a.h_kv),
+    hipLaunchKernelGGL((append_all_kernel<T, D>), dim3((a.n_g * LPR + APPEND_THREADS - 1) / APPEND_THREADS, a.h_kv, a.run.count),
                        dim3(APPEND_THREADS), 0, s, a, kept_out);
     return hipSuccess;
   }
-  const int slice_tokens = slice_tokens_for(a.n_g, a.keep, a.h_kv);
+  const int slice_tokens = slice_tokens_for(a.n_g, a.keep, a.h_kv * a.run.count);
   const int slices = (a.n_g + slice_tokens - 1) / slice_tokens;
   const size_t lds_bytes = ((size_t)a.n_g + slice_tokens) * sizeof(uint32_t);
   static bool attr_set[QP_MAX_DEVICES] = {};
@@ -384,7 +397,7 @@ static hipError_t launch_fused(const TopkArgs& a, int32_t* kept_out, hipStream_t
     if (e != hipSuccess) return e;
     if (dev >= 0) attr_set[dev] = true;
   }
-  hipLaunchKernelGGL((topk_compact_kernel<T, D>), dim3(slices, a.h_kv), dim3(TOPK_THREADS), lds_bytes, s, a, kept_out,
+  hipLaunchKernelGGL((topk_compact_kernel<T, D>), dim3(slices, a.h_kv, a.run.count), dim3(TOPK_THREADS), lds_bytes, s, a, kept_out,
                      slice_tokens);
   return hipSuccess;
 }

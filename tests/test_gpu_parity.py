@@ -683,6 +683,56 @@ def test_prefill_can_be_resumed_from_the_cache():
     assert torch.equal(cache.pos[:, :n], want_cache.pos[:, :n])
 
 
+RUNS = [  # layout (H_q, H_kv, d, dtype), frames, tokens per frame, frames per group, rho, rule, window, 8-bit cache, entries before
+    ((28, 4, 128, "bf16"), 67, 121, 4, 0.3, "window_attn", 64, False, 0),       # short last group, odd rows; group 0 in the run
+    ((28, 4, 128, "bf16"), 66, 128, 16, 0.2, "key_norm_small", 0, False, 0),    # group 0 beside the scoring
+    ((28, 4, 128, "bf16"), 67, 121, 4, 0.5, "value_norm", 0, True, 0),          # 8-bit cache, none of it for group 0
+    ((28, 4, 128, "bf16"), 41, 128, 2, 1.0, "key_norm_small", 0, True, 77),     # everything kept, entries from before
+    ((28, 4, 128, "bf16"), 321, 128, 16, 0.1, "window_attn", 1170, False, 0),   # more window scratch than one run holds
+    ((28, 4, 128, "bf16"), 65, 65, 65, 0.5, "window_logit", 8, False, 3),       # one group: the per-group loop
+    ((12, 3, 128, "bf16"), 250, 64, 1, 0.5, "window_logit", 9, False, 5),       # many small groups, heads that do not divide the XCDs
+    ((4, 2, 64, "f32"), 9, 16, 2, 0.5, "window_attn", 16, False, 0),            # scalar kernel
+    ((4, 2, 64, "bf16"), 7, 13, 3, 0.4, "key_norm_small", 0, False, 9),
+]
+
+
+@pytest.mark.parametrize("layout,frames,tpf,group,rho,rule,window,fp8,before", RUNS)
+def test_prefill_video_in_runs_equals_the_step_calls(layout, frames, tpf, group, rho, rule, window, fp8, before):
+    """qp_prefill_video serves runs of groups with one launch per step; group by group through the three step calls
+    (no scratch for the attention, so that nothing is split there either) every output bit is the same."""
+    h_q, h_kv, d, dtype = layout
+    gen = torch.Generator(device=DEV).manual_seed(11)
+    mk = lambda *s: torch.randn(*s, generator=gen, device=DEV).to(torch.float32 if dtype == "f32" else torch.bfloat16)
+    n = frames * tpf
+    q, k, v = mk(n, h_q, d), mk(n, h_kv, d), mk(n, h_kv, d)
+    qw = mk(window, h_q, d) if window else None
+    L = B.make_layout(h_q, h_kv, d, dtype)
+    ws = B.make_workspace(L, min(group, frames) * tpf, window)
+    caches = [B.Cache(L, before + B.cache_capacity(frames, tpf, group, rho),
+                      fmt=B.QP_CACHE_FP8_E4M3 if fp8 else B.QP_CACHE_SAME) for _ in range(2)]
+    old = mk(h_kv, before, d), mk(h_kv, before, d)
+    for c in caches:
+        c.k[:, :before].copy_(old[0])
+        c.v[:, :before].copy_(old[1])
+        c.c.len = before
+    outs = [torch.full_like(q, float("nan")) for _ in range(2)]
+    B.prefill_video(L, frames, tpf, group, rho, rule, q, k, v, qw, caches[0], outs[0], ws)
+    for base, n_g in B.group_bounds(frames, tpf, group):
+        sl = slice(base, base + n_g)
+        keep = B.keep_count(n_g, rho)
+        scores = torch.zeros(h_kv, n_g, device=DEV)
+        B.group_attend(L, q[sl], k[sl], v[sl], caches[1], outs[1][sl], None, None)
+        if keep < n_g:
+            B.score_kv(L, rule, k[sl], v[sl], qw, scores, ws)
+        B.topk_compact(L, scores, k[sl], v[sl], keep, base, caches[1], None, ws)
+    torch.cuda.synchronize()
+    assert caches[0].len == caches[1].len == caches[0].k.shape[1]
+    assert torch.equal(caches[0].pos, caches[1].pos)
+    assert torch.equal(caches[0].k.float(), caches[1].k.float()) and torch.equal(caches[0].v.float(), caches[1].v.float())
+    if frames > group:
+        assert torch.equal(outs[0], outs[1])
+
+
 @pytest.mark.parametrize("group_frames", [5, 1])
 def test_prefill_video_replays_from_a_hip_graph(group_frames):
     """A caller may capture qp_prefill_video (its forked library streams included) into a HIP graph: every replay,
