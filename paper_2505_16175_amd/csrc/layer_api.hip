@@ -225,9 +225,8 @@ qp_status qp_layer_group(const qp_layout* layout, const qp_layer_shape* shape, c
   void* score_ws = ws + c.path;
   const size_t score_bytes = path_bytes - kSplit;
   void* split_ws = ws + c.path + (path_bytes - kSplit) / 256 * 256;
-  qp::launch_rms_norm(x_g, weights->ln1_w, ws + c.h, n_g, dm, shape->rms_eps, s);
-  qp::launch_rope_table(pos, (long)axis_stride, n_g, shape->rope_theta, shape->mrope_section[0], shape->mrope_section[1],
-                        (float*)(ws + c.cs), s);
+  qp::launch_norm_rope(x_g, weights->ln1_w, ws + c.h, n_g, dm, shape->rms_eps, pos, (long)axis_stride, shape->rope_theta,
+                       shape->mrope_section[0], shape->mrope_section[1], (float*)(ws + c.cs), s);
   st = finish(qp::launch_gemm_bf16(qkv, qp::GEMM_QKV_ROPE, ws + c.gemm, kGemmSplitBytes, s));
   if (st != QP_OK) return st;
   // Scoring, top-k and compaction need the group's K and V only, not its attention: they run on the library's side
@@ -282,9 +281,8 @@ qp_status qp_layer_window_queries(const qp_layout* layout, const qp_layer_shape*
   qkv.h_q = layout->n_q_heads, qkv.h_kv = layout->n_kv_heads;
   if (!qp::gemm_supported(qkv, qp::GEMM_QKV_ROPE)) return QP_ERR_UNSUPPORTED;
   hipStream_t s = (hipStream_t)hip_stream;
-  qp::launch_rms_norm(x_win, weights->ln1_w, ws + c.h, n_window, shape->d_model, shape->rms_eps, s);
-  qp::launch_rope_table(pos, (long)axis_stride, n_window, shape->rope_theta, shape->mrope_section[0],
-                        shape->mrope_section[1], (float*)(ws + c.cs), s);
+  qp::launch_norm_rope(x_win, weights->ln1_w, ws + c.h, n_window, shape->d_model, shape->rms_eps, pos, (long)axis_stride,
+                       shape->rope_theta, shape->mrope_section[0], shape->mrope_section[1], (float*)(ws + c.cs), s);
   return finish(qp::launch_gemm_bf16(qkv, qp::GEMM_QKV_ROPE, ws + c.gemm, kGemmSplitBytes, s));
 }
 

@@ -248,5 +248,8 @@ void gemm_force_tile_rows(int rows);      // 0 = choose per launch (default), 12
 void launch_rms_norm(const void* x, const void* w, void* out, int n_tokens, int d_model, float eps, hipStream_t s);
 void launch_rope_table(const int32_t* pos, long axis_stride, int n_tokens, float theta, int s0, int s1, float* cos_sin,
                        hipStream_t s);
+// launch_rms_norm and launch_rope_table as one launch
+void launch_norm_rope(const void* x, const void* w, void* out, int n_tokens, int d_model, float eps, const int32_t* pos,
+                      long axis_stride, float theta, int s0, int s1, float* cos_sin, hipStream_t s);
 
 }  // namespace qp
