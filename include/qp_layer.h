@@ -93,7 +93,8 @@ qp_status qp_select_linear_tile(int32_t token_rows);
  * token_rows_per_tile is then 1 or 2 (the tokens it computes) and workgroups = n / 4; a tiling pinned with
  * qp_select_linear_tile keeps such calls on the tiled kernel. */
 typedef struct {
-  int32_t token_rows_per_tile; /* 128 or 256; 1 or 2 for the weight-streaming kernel */
+  int32_t token_rows_per_tile; /* 128 or 256; 1 or 2 for the weight-streaming kernel. A split call of at most 64 tokens
+                                  may leave out the upper 64 rows of its one tile */
   int32_t workgroups;
   int32_t k_chunks;
   int32_t k_steps_per_chunk;   /* the last chunk may have fewer */

@@ -34,31 +34,36 @@ typedef __attribute__((__vector_size__(4 * sizeof(__bf16)))) __bf16 bf16x4;
 typedef __attribute__((__vector_size__(16 * sizeof(float)))) float f32x16;
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 
-#ifndef GM_BK
-#define GM_BK 64
-#endif
-constexpr int GM_BN = 256;  // weight rows per tile
-constexpr int GM_NW = 8;
-// Token rows per tile BM: 256, or 128 for launches that would leave compute units idle with 256-row tiles.
-// k per ring slot BK: 64 or 32. The ring is as deep as 160 KB of LDS allow; all its free slots are in flight.
-template <int BM, int BK>
+constexpr int GM_BK = 64;   // k per ring slot
+constexpr int GM_BN = 256;  // weight rows per tile of the wide tilings
+// BM token rows x BN weight rows per workgroup, dealt to wavefronts of 32 MI tokens x 64 outputs. STG: depth of the ring
+// of LDS slots, all of whose free slots are in flight.
+template <int BM_, int BN_, int MI_, int STG>
 struct Tile {
+  static constexpr int BM = BM_, BN = BN_, MI = MI_;        // MI: 32-token blocks per wavefront
+  static constexpr int WN = BN / 64, WM = BM / (32 * MI);   // wavefronts across the outputs / the tokens
+  static constexpr int NW = WN * WM;
+  static constexpr int BK = GM_BK;
   static constexpr int ROWB = BK * 2;                       // bytes per tile row
   static constexpr int CPR = ROWB / 16;                     // 16-byte chunks per row
   static constexpr int RPI = 64 / CPR;                      // rows one load instruction covers
   static constexpr int RPL = 256 / ROWB;                    // rows per 256 bytes of LDS (one sweep of the banks)
   static constexpr int KS = BK / 16;                        // k-steps of the MFMA per slot
   static constexpr int XT = BM * ROWB;                      // bytes of the activation tile
-  static constexpr int STAGE = (BM + GM_BN) * ROWB;         // one ring slot: activation tile + weight tile
-  static constexpr int STAGES = (160 * 1024) / STAGE < 6 ? (160 * 1024) / STAGE : 6;
-  static constexpr int MI = BM / 64;                        // 32-token blocks per wavefront (wavefront rows: BM / 2)
-  static constexpr int XQ = BM / 8 / RPI;                   // activation load instructions per wavefront and slot
-  static constexpr int WQ = 32 / RPI;                       // weight load instructions per wavefront and slot
+  static constexpr int STAGE = (BM + BN) * ROWB;            // one ring slot: activation tile + weight tile
+  static constexpr int STAGES = STG;
+  static constexpr int XQ = BM / NW / RPI;                  // activation load instructions per wavefront and slot
+  static constexpr int WQ = BN / NW / RPI;                  // weight load instructions per wavefront and slot
   static constexpr int PER_WAVE = XQ + WQ;
+  static_assert(XQ * NW * RPI == BM && WQ * NW * RPI == BN && STAGE * STG <= 160 * 1024, "tile shape");
   // chunk c of row r sits at position c ^ swizzle(r): 16 consecutive rows' reads of one chunk index, and the 1 KB
   // written by one load instruction, then touch every bank group once
   __device__ static constexpr int swizzle(int r) { return (r / RPL) & (CPR - 1); }
 };
+typedef Tile<256, 256, 4, 2> Tile256;     // 8 wavefronts, one workgroup per CU
+typedef Tile<128, 256, 2, 3> Tile128;
+typedef Tile<128, 64, 2, 3> Narrow128;    // 2 wavefronts, two workgroups per CU
+typedef Tile<64, 64, 1, 3> Narrow64;      // ... three
 
 // 64 lanes x 16 bytes global -> LDS at the wave-uniform LDS byte address lds_addr (lane L lands at lds_addr + 16 L);
 // m0 is clobbered on purpose (see lds_dma16)
@@ -83,21 +88,23 @@ __device__ __forceinline__ void gm_wait_vmcnt() {
 // LDS row j of the weight tile <- which weight row (relative to the tile's first), per mode
 template <int MODE>
 __device__ __forceinline__ int weight_row(int j, int n0, int d_ff) {
-  if (MODE == GEMM_QKV_ROPE) return n0 + (j & ~127) + ((j >> 5) & 1) * 64 + ((j >> 6) & 1) * 32 + (j & 31);
+  if (MODE == GEMM_QKV_ROPE) {  // runs of 64: half a head's rotary pairs
+    const int u = (n0 + j) >> 6;
+    return (u >> 1) * 128 + ((j >> 5) & 1) * 64 + (u & 1) * 32 + (j & 31);
+  }
   if (MODE == GEMM_SWIGLU) return ((j >> 5) & 1) * d_ff + (n0 >> 1) + (j >> 6) * 32 + (j & 31);
   return n0 + j;
 }
 
-template <int MODE, int BM, int BK>
-__global__ __launch_bounds__(GM_NW * 64) void gemm_bf16_kernel(GemmArgs a) {
-  typedef Tile<BM, BK> T;
-  constexpr int ROWB = T::ROWB;
+template <int MODE, typename T>
+__global__ __launch_bounds__(T::NW * 64) void gemm_bf16_kernel(GemmArgs a) {
+  constexpr int ROWB = T::ROWB, BM = T::BM, BN = T::BN, BK = T::BK;
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l32 = lane & 31, g = lane >> 5;
-  const int wm = wave >> 2, wn = wave & 3;
+  const int wm = wave / T::WN, wn = wave % T::WN;
 
   // workgroup id -> (weight tile, token tile). Ids go round-robin over the 8 XCDs; the 32 workgroups that an XCD
   // runs side by side form a block of up to 8 token tiles x 4 weight tiles, so that per k-step the XCD's L2 fetches
@@ -108,26 +115,26 @@ __global__ __launch_bounds__(GM_NW * 64) void gemm_bf16_kernel(GemmArgs a) {
   const int mc = b / a.n_quads, nq = b - mc * a.n_quads;
   const int tm = mc * a.m_block + mi, tn = xcd + 8 * (nq * 4 + ni);
   if (tm >= a.tiles_m || tn >= a.tiles_n) return;  // padding of the mapping (whole workgroup, before any barrier)
-  const int m0 = tm * BM, n0 = tn * GM_BN;
+  const int m0 = tm * BM, n0 = tn * BN;
   const int d_ff = a.n >> 1;
 
-  // staging: activation load q of this wavefront covers tile rows (BM/8) wave + RPI q + lane / CPR, weight load q
-  // rows 32 wave + RPI q + lane / CPR; LDS position lane % CPR of the row holds chunk position ^ swizzle(row)
+  // staging: activation load q of this wavefront covers tile rows (BM/NW) wave + RPI q + lane / CPR, weight load q
+  // rows (BN/NW) wave + RPI q + lane / CPR; LDS position lane % CPR of the row holds chunk position ^ swizzle(row)
   const unsigned char* xg = (const unsigned char*)a.x;
   const unsigned char* wg = (const unsigned char*)a.w;
   const size_t row_b = (size_t)a.k * 2;
   unsigned x_off[T::XQ], w_off[T::WQ];
-  const int wb = MODE == GEMM_SWIGLU ? (n0 >> 1) : n0;  // first weight row this tile touches
+  const int wb = MODE == GEMM_SWIGLU ? (n0 >> 1) : MODE == GEMM_QKV_ROPE ? n0 & ~127 : n0;  // first weight row this tile may touch
   // offsets relative to the tile's first row (the launcher checks that they fit 32 bits)
 #pragma unroll
   for (int q = 0; q < T::XQ; ++q) {
-    const int r = (BM / 8) * wave + T::RPI * q + lane / T::CPR;
+    const int r = (BM / T::NW) * wave + T::RPI * q + lane / T::CPR;
     const int xr = min(m0 + r, a.m - 1);  // rows past the end: computed, not stored
     x_off[q] = (unsigned)((size_t)(xr - m0) * row_b) + (unsigned)((lane % T::CPR) ^ T::swizzle(r)) * 16;
   }
 #pragma unroll
   for (int q = 0; q < T::WQ; ++q) {
-    const int r = 32 * wave + T::RPI * q + lane / T::CPR;
+    const int r = (BN / T::NW) * wave + T::RPI * q + lane / T::CPR;
     const int wr = min(weight_row<MODE>(r, n0, d_ff), a.n - 1);
     w_off[q] = (unsigned)((size_t)(wr - wb) * row_b) + (unsigned)((lane % T::CPR) ^ T::swizzle(r)) * 16;
   }
@@ -136,7 +143,7 @@ __global__ __launch_bounds__(GM_NW * 64) void gemm_bf16_kernel(GemmArgs a) {
   const unsigned char* x_base = xg + (size_t)m0 * row_b + (size_t)step_begin * ROWB;
   const unsigned char* w_base = wg + (size_t)wb * row_b + (size_t)step_begin * ROWB;
   const unsigned smem_lds = (unsigned)(size_t)(__attribute__((address_space(3))) unsigned char*)smem;
-  const unsigned x_lds = smem_lds + wave * (BM / 8) * ROWB, w_lds = smem_lds + T::XT + wave * 32 * ROWB;
+  const unsigned x_lds = smem_lds + wave * (BM / T::NW) * ROWB, w_lds = smem_lds + T::XT + wave * (BN / T::NW) * ROWB;
 
   // load instruction p_ of a step (activation loads first, then weight loads) into ring slot slot_
 #define GM_ISSUE_ONE(p_, step_, slot_)                                                                          \
@@ -152,7 +159,7 @@ __global__ __launch_bounds__(GM_NW * 64) void gemm_bf16_kernel(GemmArgs a) {
   int f_off[T::KS];
 #pragma unroll
   for (int s = 0; s < T::KS; ++s) f_off[s] = l32 * ROWB + (((2 * s + g) ^ T::swizzle(l32)) << 4);
-  const int x_frag = wm * (BM / 2) * ROWB;
+  const int x_frag = wm * (32 * T::MI) * ROWB;
   const int w_frag = T::XT + wn * 64 * ROWB;
 
   f32x16 acc[2][T::MI];
@@ -266,6 +273,7 @@ __global__ __launch_bounds__(GM_NW * 64) void gemm_bf16_kernel(GemmArgs a) {
 #undef GM_ISSUE
 
   // ---- store: lane owns token m = m0 + (BM/2) wm + 32 i + l32 and, in block j, outputs 8 (r >> 2) + 4 g + (r & 3)
+  const int u64 = (n0 >> 6) + wn;  // QKV_ROPE: which run of 64 outputs (half a head's rotary pairs) this wavefront has
   if (a.split_k > 1) {
     // partial sums of this k chunk, f32 [chunk][m][n] with n the output's logical column (for QKV: head * 128 + dim);
     // gemm_reduce_kernel adds the chunks in order and applies the mode's store
@@ -275,12 +283,12 @@ __global__ __launch_bounds__(GM_NW * 64) void gemm_bf16_kernel(GemmArgs a) {
 #pragma unroll
       for (int q4 = 0; q4 < 4; ++q4) {
         int n;
-        if (MODE == GEMM_QKV_ROPE) n = ((n0 >> 7) + (wn >> 1)) * 128 + (wn & 1) * 32 + j * 64 + 8 * q4 + 4 * g;
+        if (MODE == GEMM_QKV_ROPE) n = (u64 >> 1) * 128 + (u64 & 1) * 32 + j * 64 + 8 * q4 + 4 * g;
         else n = n0 + wn * 64 + j * 32 + 8 * q4 + 4 * g;
         if (n >= a.n) continue;
 #pragma unroll
         for (int i = 0; i < T::MI; ++i) {
-          const int m = m0 + wm * (BM / 2) + i * 32 + l32;
+          const int m = m0 + wm * (32 * T::MI) + i * 32 + l32;
           if (m >= a.m) continue;
           *(float4*)(part + (size_t)m * a.n + n) =
               make_float4(acc[j][i][4 * q4], acc[j][i][4 * q4 + 1], acc[j][i][4 * q4 + 2], acc[j][i][4 * q4 + 3]);
@@ -305,7 +313,7 @@ __global__ __launch_bounds__(GM_NW * 64) void gemm_bf16_kernel(GemmArgs a) {
         }
 #pragma unroll
         for (int i = 0; i < T::MI; ++i) {
-          const int m = m0 + wm * (BM / 2) + i * 32 + l32;
+          const int m = m0 + wm * (32 * T::MI) + i * 32 + l32;
           if (m >= a.m) continue;
           float y[4];
 #pragma unroll
@@ -322,8 +330,8 @@ __global__ __launch_bounds__(GM_NW * 64) void gemm_bf16_kernel(GemmArgs a) {
       }
   } else if (MODE == GEMM_QKV_ROPE) {
     // head of this wavefront and where its rows go
-    const int head = (n0 >> 7) + (wn >> 1);
-    const int dim0 = (wn & 1) * 32;  // block 0: dims dim0 + ..., block 1: dim0 + 64 + ...
+    const int head = u64 >> 1;
+    const int dim0 = (u64 & 1) * 32;  // block 0: dims dim0 + ..., block 1: dim0 + 64 + ...
     const bf16_t* bias = (const bf16_t*)a.bias + (size_t)head * 128;
     bf16_t* dst;
     int heads_dst, head_dst;
@@ -342,7 +350,7 @@ __global__ __launch_bounds__(GM_NW * 64) void gemm_bf16_kernel(GemmArgs a) {
       }
 #pragma unroll
       for (int i = 0; i < T::MI; ++i) {
-        const int m = m0 + wm * (BM / 2) + i * 32 + l32;
+        const int m = m0 + wm * (32 * T::MI) + i * 32 + l32;
         if (m >= a.m) continue;
         float lo[4], hi[4];
 #pragma unroll
@@ -373,7 +381,7 @@ __global__ __launch_bounds__(GM_NW * 64) void gemm_bf16_kernel(GemmArgs a) {
       const int n = (n0 >> 1) + wn * 32 + 8 * q4 + 4 * g;
 #pragma unroll
       for (int i = 0; i < T::MI; ++i) {
-        const int m = m0 + wm * (BM / 2) + i * 32 + l32;
+        const int m = m0 + wm * (32 * T::MI) + i * 32 + l32;
         if (m >= a.m) continue;
         bf16x4 pk;
 #pragma unroll
@@ -390,6 +398,7 @@ __global__ __launch_bounds__(GM_NW * 64) void gemm_bf16_kernel(GemmArgs a) {
 // Second launch of a split contraction: sums the chunks' partial tiles in chunk order and applies the mode's store.
 // One thread per token and run of 4 outputs (QKV_ROPE: per run of 4 dims of a head's first half and their rotary
 // partners).
+constexpr int RD_BATCH = 4;  // chunks whose loads are in flight together
 template <int MODE>
 __global__ __launch_bounds__(256) void gemm_reduce_kernel(GemmArgs a) {
   const long id = (long)blockIdx.x * 256 + threadIdx.x;
@@ -400,10 +409,14 @@ __global__ __launch_bounds__(256) void gemm_reduce_kernel(GemmArgs a) {
   if (MODE == GEMM_PLAIN) {
     const int n = 4 * r;
     const float* p = a.partial + (size_t)m * a.n + n;
-    float4 y = *(const float4*)p;
-    for (int c = 1; c < a.split_k; ++c) {
-      const float4 t = *(const float4*)(p + c * stride);
-      y.x += t.x, y.y += t.y, y.z += t.z, y.w += t.w;
+    float4 y = make_float4(0.f, 0.f, 0.f, 0.f);
+    for (int c0 = 0; c0 < a.split_k; c0 += RD_BATCH) {
+      float4 t[RD_BATCH];
+#pragma unroll
+      for (int u = 0; u < RD_BATCH; ++u) t[u] = *(const float4*)(p + min(c0 + u, a.split_k - 1) * stride);
+#pragma unroll
+      for (int u = 0; u < RD_BATCH; ++u)
+        if (c0 + u < a.split_k) y.x += t[u].x, y.y += t[u].y, y.z += t[u].z, y.w += t[u].w;
     }
     if (a.bias != nullptr) {
       const uint2 raw = *(const uint2*)((const bf16_t*)a.bias + n);
@@ -419,11 +432,20 @@ __global__ __launch_bounds__(256) void gemm_reduce_kernel(GemmArgs a) {
   } else if (MODE == GEMM_QKV_ROPE) {
     const int head = r / 16, f = 4 * (r % 16);  // f: first of 4 rotary frequencies
     const float* p = a.partial + (size_t)m * a.n + head * 128 + f;
-    float4 lo4 = *(const float4*)p, hi4 = *(const float4*)(p + 64);
-    for (int c = 1; c < a.split_k; ++c) {
-      const float4 t = *(const float4*)(p + c * stride), u = *(const float4*)(p + c * stride + 64);
-      lo4.x += t.x, lo4.y += t.y, lo4.z += t.z, lo4.w += t.w;
-      hi4.x += u.x, hi4.y += u.y, hi4.z += u.z, hi4.w += u.w;
+    float4 lo4 = make_float4(0.f, 0.f, 0.f, 0.f), hi4 = lo4;
+    for (int c0 = 0; c0 < a.split_k; c0 += RD_BATCH) {
+      float4 t[RD_BATCH], v[RD_BATCH];
+#pragma unroll
+      for (int u = 0; u < RD_BATCH; ++u) {
+        const float* pc = p + min(c0 + u, a.split_k - 1) * stride;
+        t[u] = *(const float4*)pc, v[u] = *(const float4*)(pc + 64);
+      }
+#pragma unroll
+      for (int u = 0; u < RD_BATCH; ++u)
+        if (c0 + u < a.split_k) {
+          lo4.x += t[u].x, lo4.y += t[u].y, lo4.z += t[u].z, lo4.w += t[u].w;
+          hi4.x += v[u].x, hi4.y += v[u].y, hi4.z += v[u].z, hi4.w += v[u].w;
+        }
     }
     float lo[4] = {lo4.x, lo4.y, lo4.z, lo4.w}, hi[4] = {hi4.x, hi4.y, hi4.z, hi4.w};
     const bf16_t* bias = (const bf16_t*)a.bias + (size_t)head * 128;
@@ -484,42 +506,59 @@ int gemm_tile_rows(const GemmArgs& a) {
 // Contraction split: launches whose tiles would occupy at most a quarter of the CUs (few tokens against a long k:
 // text chunks and decode steps through the layer, where the weights are streamed once and HBM is the bound) deal the
 // k-steps to chunks, about one workgroup per CU in all, at least 4 steps per chunk, as many chunks as the scratch holds.
+//
+// With 256-wide tiles a matrix of few outputs needs many chunks for that, and every chunk writes and re-reads an f32
+// copy of the output: the 7B down projection at 64 tokens moved 34 MB of partials beside 136 MB of weights, and each
+// workgroup had 16 steps to hide its start behind. Where more than NARROW_ABOVE chunks would be wanted, tiles of 64
+// outputs are taken instead, in the largest power of two of chunks that keeps them about resident (tiles x chunks <=
+// 2 per CU; 3, 6, 7 and 9 chunks measured up to a third slower on the down projection than 4 and 8), at most
+// NARROW_ABOVE. us at 7B sizes, 64 tokens: QKV 25.1 -> 16.3, o_proj 21.9 -> 12.8, down 62.8 -> 35.3; 128 tokens
+// 32.5 -> 26.0, 29.1 -> 17.2, 77.2 -> 46.4; 200 tokens 37.2 -> 28.9, 31.6 -> 20.5, 73.2 -> 62.4; 3 tokens 19.8 -> 13.2,
+// 17.0 -> 11.6, 53.9 -> 29.0. At 72B sizes (8 chunks or fewer) the wide tiles are as fast or faster and stay: o_proj at
+// 64 tokens 34.7 against 35.3-39.3, down 97.9 against 101-120. So does SwiGLU, which is not split.
+constexpr int NARROW_ABOVE = 8;
 GemmSplit gemm_plan_split(const GemmArgs& a, int mode, size_t scratch_bytes) {
-  GemmSplit p{1, a.k / GM_BK, 0};
+  GemmSplit p{1, a.k / GM_BK, 0, 0};
   if (mode == GEMM_SWIGLU || scratch_bytes == 0 || gemm_uses_gemv(a)) return p;
   const int rows = gemm_tile_rows(a), cus = device_cu_count();
-  const long tiles = (long)((a.m + rows - 1) / rows) * ((a.n + GM_BN - 1) / GM_BN);
+  const long tiles_m = (a.m + rows - 1) / rows, tiles = tiles_m * ((a.n + GM_BN - 1) / GM_BN);
   const int steps = a.k / GM_BK;
   if (tiles * 4 > cus || steps < 8) return p;
   long want = (cus + tiles - 1) / tiles;
   if (want > steps / 4) want = steps / 4;
   const size_t per_chunk = (size_t)a.m * a.n * sizeof(float);
+  if (want > NARROW_ABOVE && rows == 128 && g_forced_tile_rows.load(std::memory_order_relaxed) == 0) {
+    const long narrow = tiles_m * ((a.n + Narrow64::BN - 1) / Narrow64::BN);
+    want = NARROW_ABOVE;
+    while (want > 1 && narrow * want > 2 * cus + cus / 4) want /= 2;  // a quarter of a chip above: 72 tiles x 8 measured better than x 4
+    p.narrow = 1;
+  }
   if ((size_t)want * per_chunk > scratch_bytes) want = (long)(scratch_bytes / per_chunk);
-  if (want < 2) return p;
+  if (want < 2) return GemmSplit{1, steps, 0, 0};
   p.steps_per_split = (int)((steps + want - 1) / want);
   p.split_k = (steps + p.steps_per_split - 1) / p.steps_per_split;  // every chunk non-empty
   p.scratch_bytes = (size_t)p.split_k * per_chunk;
   return p;
 }
 
-template <int MODE, int BM, int BK>
+template <int MODE, typename T>
 static hipError_t launch_tile(GemmArgs a, hipStream_t s) {
   static bool attr_done[QP_MAX_DEVICES] = {};
   const int dev = current_device();
   if (dev < 0) return hipErrorInvalidDevice;
-  const int lds = Tile<BM, BK>::STAGES * Tile<BM, BK>::STAGE;
+  const int lds = T::STAGES * T::STAGE;
   if (!attr_done[dev]) {
-    hipError_t e = hipFuncSetAttribute((const void*)gemm_bf16_kernel<MODE, BM, BK>, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+    hipError_t e = hipFuncSetAttribute((const void*)gemm_bf16_kernel<MODE, T>, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
     if (e != hipSuccess) return e;
     attr_done[dev] = true;
   }
-  a.tiles_m = (a.m + BM - 1) / BM;
-  a.tiles_n = (a.n + GM_BN - 1) / GM_BN;
+  a.tiles_m = (a.m + T::BM - 1) / T::BM;
+  a.tiles_n = (a.n + T::BN - 1) / T::BN;
   a.m_block = a.tiles_m < 8 ? a.tiles_m : 8;
   a.n_quads = ((a.tiles_n + 7) / 8 + 3) / 4;  // weight tiles per XCD, in fours
   const int m_chunks = (a.tiles_m + a.m_block - 1) / a.m_block;
-  hipLaunchKernelGGL((gemm_bf16_kernel<MODE, BM, BK>), dim3(8 * m_chunks * a.m_block * a.n_quads * 4, a.split_k),
-                     dim3(GM_NW * 64), lds, s, a);
+  hipLaunchKernelGGL((gemm_bf16_kernel<MODE, T>), dim3(8 * m_chunks * a.m_block * a.n_quads * 4, a.split_k),
+                     dim3(T::NW * 64), lds, s, a);
   return hipSuccess;
 }
 
@@ -527,7 +566,9 @@ template <int MODE>
 static hipError_t launch_mode(GemmArgs a, void* scratch, size_t scratch_bytes, hipStream_t s) {
   const GemmSplit sp = gemm_plan_split(a, MODE, scratch != nullptr ? scratch_bytes : 0);
   a.split_k = sp.split_k, a.steps_per_split = sp.steps_per_split, a.partial = (float*)scratch;
-  hipError_t e = gemm_tile_rows(a) == 128 ? launch_tile<MODE, 128, GM_BK>(a, s) : launch_tile<MODE, 256, GM_BK>(a, s);
+  hipError_t e;
+  if (MODE != GEMM_SWIGLU && sp.narrow) e = a.m <= 64 ? launch_tile<MODE, Narrow64>(a, s) : launch_tile<MODE, Narrow128>(a, s);
+  else e = gemm_tile_rows(a) == 128 ? launch_tile<MODE, Tile128>(a, s) : launch_tile<MODE, Tile256>(a, s);
   if (e != hipSuccess || a.split_k == 1) return e;
   const long threads = (long)a.m * (MODE == GEMM_QKV_ROPE ? a.n / 8 : a.n / 4);
   hipLaunchKernelGGL(gemm_reduce_kernel<MODE>, dim3((unsigned)((threads + 255) / 256)), dim3(256), 0, s, a);

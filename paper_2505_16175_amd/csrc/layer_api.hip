@@ -146,7 +146,8 @@ qp_status qp_linear_plan(int32_t m, int32_t n, int32_t k, size_t workspace_bytes
     return QP_OK;
   }
   const int rows = qp::gemm_tile_rows(a);
-  const int tiles_m = (m + rows - 1) / rows, tiles_n = (n + 255) / 256;
+  const int cols = sp.narrow ? 64 : 256;
+  const int tiles_m = (m + rows - 1) / rows, tiles_n = (n + cols - 1) / cols;
   const int m_block = tiles_m < 8 ? tiles_m : 8;
   out->token_rows_per_tile = rows;
   out->workgroups = 8 * ((tiles_m + m_block - 1) / m_block) * m_block * (((tiles_n + 7) / 8 + 3) / 4) * 4;

@@ -237,6 +237,7 @@ hipError_t launch_gemm_bf16(const GemmArgs& a, int mode, void* scratch, size_t s
 struct GemmSplit {
   int split_k, steps_per_split;
   size_t scratch_bytes;
+  int narrow;  // 1: tiles of 64 outputs (and of 64 token rows for at most 64 tokens) instead of 256
 };
 GemmSplit gemm_plan_split(const GemmArgs& a, int mode, size_t scratch_bytes);  // host arithmetic only
 // Calls of at most 2 tokens stream the weights once through a kernel of their own (one launch, no partial sums).
