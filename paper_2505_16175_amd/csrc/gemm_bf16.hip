@@ -8,9 +8,10 @@
 //            (Appendix D.1 of the paper: SwiGLU(x) = W_down(SiLU(W_gate x) * W_up x))
 //
 // Tiling. A workgroup of 8 wavefronts owns a 256 x 256 output tile and walks K in steps of 64. Both operand
-// tiles (256 rows x 128 bytes each) go global -> LDS with global_load_lds_dwordx4 into a ring of buffers, the
-// next step's tiles in flight while this step's are multiplied; one barrier per step, placed before the step's last
-// quarter of products so that the matrix pipe stays busy across it. Rows are unpadded; the
+// tiles (256 rows x 128 bytes each) go global -> LDS with global_load_lds_dwordx4 into rings of buffers (two for
+// activations, three for weights), the next steps' tiles in flight while this step's are multiplied; one barrier per
+// step, placed before the step's last quarter of products so that the matrix pipe stays busy across it. Rows are
+// unpadded; the
 // 16-byte chunk c of row r sits at position c ^ ((r >> 1) & 7), which makes both the 1 KB stores of the loads
 // and the fragment reads (32 rows x 16 bytes per half wavefront) conflict-free.
 // Wavefront (wm, wn) of the 2 x 4 arrangement computes 128 tokens x 64 outputs as 4 x 2 blocks of
@@ -36,9 +37,9 @@ typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int GM_BK = 64;   // k per ring slot
 constexpr int GM_BN = 256;  // weight rows per tile of the wide tilings
-// BM token rows x BN weight rows per workgroup, dealt to wavefronts of 32 MI tokens x 64 outputs. STG: depth of the ring
-// of LDS slots, all of whose free slots are in flight.
-template <int BM_, int BN_, int MI_, int STG>
+// BM token rows x BN weight rows per workgroup, dealt to wavefronts of 32 MI tokens x 64 outputs. XS, WS: depth of the
+// rings of LDS slots that hold activation and weight tiles, all of whose free slots are in flight: equal, or 2 and 3.
+template <int BM_, int BN_, int MI_, int XS_, int WS_ = XS_>
 struct Tile {
   static constexpr int BM = BM_, BN = BN_, MI = MI_;        // MI: 32-token blocks per wavefront
   static constexpr int WN = BN / 64, WM = BM / (32 * MI);   // wavefronts across the outputs / the tokens
@@ -50,17 +51,18 @@ struct Tile {
   static constexpr int RPL = 256 / ROWB;                    // rows per 256 bytes of LDS (one sweep of the banks)
   static constexpr int KS = BK / 16;                        // k-steps of the MFMA per slot
   static constexpr int XT = BM * ROWB;                      // bytes of the activation tile
-  static constexpr int STAGE = (BM + BN) * ROWB;            // one ring slot: activation tile + weight tile
-  static constexpr int STAGES = STG;
+  static constexpr int WT = BN * ROWB;                      // ... of the weight tile
+  static constexpr int XS = XS_, WS = WS_;
+  static constexpr int LDS = XS * XT + WS * WT;             // activation ring, then weight ring
   static constexpr int XQ = BM / NW / RPI;                  // activation load instructions per wavefront and slot
   static constexpr int WQ = BN / NW / RPI;                  // weight load instructions per wavefront and slot
   static constexpr int PER_WAVE = XQ + WQ;
-  static_assert(XQ * NW * RPI == BM && WQ * NW * RPI == BN && STAGE * STG <= 160 * 1024, "tile shape");
+  static_assert(XQ * NW * RPI == BM && WQ * NW * RPI == BN && LDS <= 160 * 1024 && (XS == WS || (XS == 2 && WS == 3)), "tile shape");
   // chunk c of row r sits at position c ^ swizzle(r): 16 consecutive rows' reads of one chunk index, and the 1 KB
   // written by one load instruction, then touch every bank group once
   __device__ static constexpr int swizzle(int r) { return (r / RPL) & (CPR - 1); }
 };
-typedef Tile<256, 256, 4, 2> Tile256;     // 8 wavefronts, one workgroup per CU
+typedef Tile<256, 256, 4, 2, 3> Tile256;    // 8 wavefronts, one workgroup per CU
 typedef Tile<128, 256, 2, 3> Tile128;
 typedef Tile<128, 64, 2, 3> Narrow128;    // 2 wavefronts, two workgroups per CU
 typedef Tile<64, 64, 1, 3> Narrow64;      // ... three
@@ -143,24 +145,18 @@ __global__ __launch_bounds__(T::NW * 64) void gemm_bf16_kernel(GemmArgs a) {
   const unsigned char* x_base = xg + (size_t)m0 * row_b + (size_t)step_begin * ROWB;
   const unsigned char* w_base = wg + (size_t)wb * row_b + (size_t)step_begin * ROWB;
   const unsigned smem_lds = (unsigned)(size_t)(__attribute__((address_space(3))) unsigned char*)smem;
-  const unsigned x_lds = smem_lds + wave * (BM / T::NW) * ROWB, w_lds = smem_lds + T::XT + wave * (BN / T::NW) * ROWB;
+  const unsigned x_lds = smem_lds + wave * (BM / T::NW) * ROWB, w_lds = smem_lds + T::XS * T::XT + wave * (BN / T::NW) * ROWB;
 
-  // load instruction p_ of a step (activation loads first, then weight loads) into ring slot slot_
-#define GM_ISSUE_ONE(p_, step_, slot_)                                                                          \
-  {                                                                                                             \
-    const unsigned koff_ = (unsigned)(step_) * ROWB;                                                         \
-    if ((p_) < T::XQ) gm_dma16(x_base, x_off[(p_) < T::XQ ? (p_) : 0] + koff_, x_lds + (slot_)*T::STAGE + 1024 * (p_)); \
-    else gm_dma16(w_base, w_off[(p_) - T::XQ] + koff_, w_lds + (slot_)*T::STAGE + 1024 * ((p_) - T::XQ));       \
-  }
-#define GM_ISSUE(step_, slot_) \
-  { _Pragma("unroll") for (int p_ = 0; p_ < T::PER_WAVE; ++p_) GM_ISSUE_ONE(p_, step_, slot_) }
+  // activation / weight load instruction p_ of a step into slot slot_ of its ring
+#define GM_ISSUE_X(p_, step_, slot_) gm_dma16(x_base, x_off[p_] + (unsigned)(step_) * ROWB, x_lds + (slot_)*T::XT + 1024 * (p_));
+#define GM_ISSUE_W(p_, step_, slot_) gm_dma16(w_base, w_off[p_] + (unsigned)(step_) * ROWB, w_lds + (slot_)*T::WT + 1024 * (p_));
 
   // fragment addresses inside a slot: row (l32 + 32 block), chunk 2 s + g of k-step s
   int f_off[T::KS];
 #pragma unroll
   for (int s = 0; s < T::KS; ++s) f_off[s] = l32 * ROWB + (((2 * s + g) ^ T::swizzle(l32)) << 4);
   const int x_frag = wm * (32 * T::MI) * ROWB;
-  const int w_frag = T::XT + wn * 64 * ROWB;
+  const int w_frag = T::XS * T::XT + wn * 64 * ROWB;
 
   f32x16 acc[2][T::MI];
 #pragma unroll
@@ -170,31 +166,38 @@ __global__ __launch_bounds__(T::NW * 64) void gemm_bf16_kernel(GemmArgs a) {
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[j][i][r] = 0.f;
 
-  // Ring schedule. All slots are free at the start, so the first STAGES steps are requested at once. Inside the
+  // Ring schedule. All slots are free at the start, so the first steps are requested at once. Inside the
   // loop the barrier sits before the LAST k-step's products of a step: by then every wavefront has read all its
-  // fragments of the step (its slot can be refilled), the next step's tiles have landed, and the wait at the
-  // barrier, the refill requests and the latency of the next step's first fragment reads all run under those
-  // products instead of leaving the matrix pipe idle between steps.
+  // fragments of the step (its slots can be refilled), the next step's tiles have landed, and the wait at the
+  // barrier and the latency of the next step's first fragment reads run under those products.
+  // With equal rings all refill requests are issued there too. At 256 x 256 that is 64 of them per step within a quarter
+  // of its products: the address path takes 16 cycles for each, falls behind, and holds up the products behind the
+  // requests. So that tiling (rings of 2 and 3) spreads them: a step t issues, two per k-step and wavefront, the second
+  // half of X(t + 1), then W(t + 2) into the slot that step t - 1 left, then, behind the barrier, the first half of
+  // X(t + 2). PFLOP/s at 4096 x 59136 x 8192 / 4096 x 8192 x 29568 / 2048 x 37888 x 3584: 1.25 / 1.23 / 1.17 all behind
+  // the barrier (with or without the third weight slot), 1.35 / 1.31 / 1.25 spread.
+  // Requests complete in order: when step t + 1 is awaited at the end of step t, what may stay in flight is, with equal
+  // rings, the XS - 2 steps after it, and with rings of 2 and 3 the weights of step t + 2.
   const int n_steps = min(a.steps_per_split, a.k / BK - step_begin);
-  constexpr int S = T::STAGES, PW = T::PER_WAVE;
+  constexpr int XS = T::XS, WS = T::WS, PW = T::PER_WAVE;
 #pragma unroll
-  for (int p = 0; p < S; ++p)
-    if (p < n_steps) GM_ISSUE(p, p)
-  // the first slot's tiles have landed: all but the min(S, n_steps) - 1 later requests are complete
-  switch (n_steps < S ? n_steps : S) {
-    case 1: gm_wait_vmcnt<0>(); break;
-    case 2: gm_wait_vmcnt<PW>(); break;
-    case 3: gm_wait_vmcnt<2 * PW>(); break;
-    case 4: gm_wait_vmcnt<3 * PW>(); break;
-    case 5: gm_wait_vmcnt<4 * PW>(); break;
-    default: gm_wait_vmcnt<5 * PW>(); break;
-  }
+  for (int p = 0; p < XS; ++p)
+    if (p < n_steps) {
+#pragma unroll
+      for (int q = 0; q < T::XQ; ++q) GM_ISSUE_X(q, p, p)
+#pragma unroll
+      for (int q = 0; q < T::WQ; ++q) GM_ISSUE_W(q, p, p)
+    }
+  // the first step's tiles have landed: all but the later requests are complete
+  if (XS >= 3 && n_steps >= 3) gm_wait_vmcnt<2 * PW>();
+  else if (n_steps >= 2) gm_wait_vmcnt<PW>();
+  else gm_wait_vmcnt<0>();
   __syncthreads();
   u32x4 wf[2][2], xf[2][T::MI];  // fragments of k-step s+1 are read while the products of k-step s run (two sets)
-#define GM_READ(st_, s_, b_)                                                                                   \
+#define GM_READ(xst_, wst_, s_, b_)                                                                            \
   {                                                                                                            \
-    _Pragma("unroll") for (int j = 0; j < 2; ++j) wf[b_][j] = *(const u32x4*)((st_) + w_frag + j * 32 * ROWB + f_off[s_]); \
-    _Pragma("unroll") for (int i = 0; i < T::MI; ++i) xf[b_][i] = *(const u32x4*)((st_) + x_frag + i * 32 * ROWB + f_off[s_]); \
+    _Pragma("unroll") for (int j = 0; j < 2; ++j) wf[b_][j] = *(const u32x4*)((wst_) + w_frag + j * 32 * ROWB + f_off[s_]); \
+    _Pragma("unroll") for (int i = 0; i < T::MI; ++i) xf[b_][i] = *(const u32x4*)((xst_) + x_frag + i * 32 * ROWB + f_off[s_]); \
   }
 #define GM_MFMA(b_)                                                                                            \
   _Pragma("unroll") for (int i = 0; i < T::MI; ++i) _Pragma("unroll") for (int j = 0; j < 2; ++j) acc[j][i] =  \
@@ -203,40 +206,50 @@ __global__ __launch_bounds__(T::NW * 64) void gemm_bf16_kernel(GemmArgs a) {
 #define GM_MFMA_ONE(b_, mf_)                                                                                   \
   acc[(mf_) & 1][(mf_) >> 1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(                                        \
       __builtin_bit_cast(bf16x8, wf[b_][(mf_) & 1]), __builtin_bit_cast(bf16x8, xf[b_][(mf_) >> 1]), acc[(mf_) & 1][(mf_) >> 1], 0, 0, 0);
-#define GM_READ_ONE(st_, r_)                                                                                   \
+#define GM_READ_ONE(xst_, wst_, r_)                                                                            \
   {                                                                                                            \
-    if ((r_) < 2) wf[0][(r_) < 2 ? (r_) : 0] = *(const u32x4*)((st_) + w_frag + (r_) * 32 * ROWB + f_off[0]);   \
-    else xf[0][(r_) >= 2 ? (r_) - 2 : 0] = *(const u32x4*)((st_) + x_frag + ((r_) - 2) * 32 * ROWB + f_off[0]); \
+    if ((r_) < 2) wf[0][(r_) < 2 ? (r_) : 0] = *(const u32x4*)((wst_) + w_frag + (r_) * 32 * ROWB + f_off[0]);  \
+    else xf[0][(r_) >= 2 ? (r_) - 2 : 0] = *(const u32x4*)((xst_) + x_frag + ((r_) - 2) * 32 * ROWB + f_off[0]); \
   }
   constexpr int NM = 2 * T::MI;                       // products per k-step
   constexpr int PIECES = PW + 2 + T::MI;              // refill requests + first fragment reads of the next step
   constexpr int PER = (PIECES + NM - 1) / NM;         // of them behind each product
-  GM_READ(smem, 0, 0)
-  int slot = 0;
-  for (int step = 0; step + 1 < n_steps; ++step) {
-    const unsigned char* st = smem + slot * T::STAGE;
+  GM_READ(smem, smem, 0, 0)
+  int xslot = 0, wslot = 0;
+  static_assert(XS == WS || (T::XQ == 4 && T::WQ == 4 && T::MI == 4 && T::KS == 4), "spread of the requests");
+  // One step that has a successor; refill_x / refill_w: there is a step left to request into the freed slots, refill_x0:
+  // the second half of the next step's activations is still to be requested (rings of 2 and 3).
+  auto step_and_next = [&](int step, bool refill_x0, bool refill_x, bool refill_w, auto wait) {
+    const unsigned char *xst = smem + xslot * T::XT, *wst = smem + wslot * T::WT;
 #pragma unroll
     for (int s = 0; s < T::KS - 1; ++s) {
-      GM_READ(st, s + 1, (s + 1) & 1)
+      GM_READ(xst, wst, s + 1, (s + 1) & 1)
       __builtin_amdgcn_sched_barrier(0);
-      GM_MFMA(s & 1)
-      __builtin_amdgcn_sched_barrier(0);
-    }
-    const int next = slot == S - 1 ? 0 : slot + 1;
-    // this wavefront's part of the next step's tiles has landed (later steps' may still be in flight) ...
-    {
-      const int behind = n_steps - 2 - step < S - 2 ? n_steps - 2 - step : S - 2;  // requests that may stay in flight
-      switch (behind) {
-        case 0: gm_wait_vmcnt<0>(); break;
-        case 1: gm_wait_vmcnt<PW>(); break;
-        case 2: gm_wait_vmcnt<2 * PW>(); break;
-        case 3: gm_wait_vmcnt<3 * PW>(); break;
-        default: gm_wait_vmcnt<4 * PW>(); break;
+      if (XS != WS) {
+        const int wfree = wslot == 0 ? WS - 1 : wslot - 1;  // the slot that the step before left
+#pragma unroll
+        for (int mf = 0; mf < NM; ++mf) {
+          GM_MFMA_ONE(s & 1, mf)
+          __builtin_amdgcn_sched_barrier(0);
+          if ((mf & 3) == 1) {  // NM = 8: two requests per k-step
+            const int q = 2 * s + (mf >> 2);
+            if (q < T::XQ / 2) {
+              if (refill_x0) GM_ISSUE_X(T::XQ / 2 + q, step + 1, xslot ^ 1)
+            } else if (refill_w) {
+              GM_ISSUE_W(q - T::XQ / 2, step + 2, wfree)
+            }
+          }
+          __builtin_amdgcn_sched_barrier(0);
+        }
+      } else {
+        GM_MFMA(s & 1)
       }
+      __builtin_amdgcn_sched_barrier(0);
     }
-    __syncthreads();  // ... everyone's has, and everyone has read its last fragments of this step's slot
-    const bool refill = step + S < n_steps;
-    const unsigned char* st_next = smem + next * T::STAGE;
+    const int xnext = xslot == XS - 1 ? 0 : xslot + 1, wnext = wslot == WS - 1 ? 0 : wslot + 1;
+    wait();           // this wavefront's part of the next step's tiles has landed (later ones may still be in flight) ...
+    __syncthreads();  // ... everyone's has, and everyone has read its last fragments of this step's slots
+    const unsigned char *xst_next = smem + xnext * T::XT, *wst_next = smem + wnext * T::WT;
 #pragma unroll
     for (int mf = 0; mf < NM; ++mf) {
       GM_MFMA_ONE(1, mf)
@@ -244,21 +257,31 @@ __global__ __launch_bounds__(T::NW * 64) void gemm_bf16_kernel(GemmArgs a) {
 #pragma unroll
       for (int u = 0; u < PER; ++u) {
         const int p = mf * PER + u;
-        if (p < PW) {
-          if (refill) GM_ISSUE_ONE(p, step + S, slot)
+        if (p < T::XQ) {
+          if (refill_x && (XS == WS || p < T::XQ / 2)) GM_ISSUE_X(p, step + XS, xslot)
+        } else if (p < PW) {
+          if (refill_w && XS == WS) GM_ISSUE_W(p - T::XQ, step + WS, wslot)
         } else if (p < PIECES) {
-          GM_READ_ONE(st_next, p - PW)
+          GM_READ_ONE(xst_next, wst_next, p - PW)
         }
       }
       __builtin_amdgcn_sched_barrier(0);
     }
-    slot = next;
-  }
+    xslot = xnext, wslot = wnext;
+  };
+  int step = 0;
+  for (; step + XS < n_steps; ++step)
+    step_and_next(step, step > 0, true, true, [] { gm_wait_vmcnt<XS != WS ? T::WQ : (XS - 2) * PW>(); });
+  for (; step + 1 < n_steps; ++step)
+    step_and_next(step, step > 0 && step + 1 < n_steps, false, false, [&] {
+      if (XS == WS && XS >= 3 && step + 2 < n_steps) gm_wait_vmcnt<PW>();
+      else gm_wait_vmcnt<0>();
+    });
   {  // last step: nothing left to request or to wait for
-    const unsigned char* st = smem + slot * T::STAGE;
+    const unsigned char *xst = smem + xslot * T::XT, *wst = smem + wslot * T::WT;
 #pragma unroll
     for (int s = 0; s < T::KS - 1; ++s) {
-      GM_READ(st, s + 1, (s + 1) & 1)
+      GM_READ(xst, wst, s + 1, (s + 1) & 1)
       __builtin_amdgcn_sched_barrier(0);
       GM_MFMA(s & 1)
       __builtin_amdgcn_sched_barrier(0);
@@ -267,10 +290,10 @@ __global__ __launch_bounds__(T::NW * 64) void gemm_bf16_kernel(GemmArgs a) {
   }
 #undef GM_MFMA_ONE
 #undef GM_READ_ONE
-#undef GM_ISSUE_ONE
+#undef GM_ISSUE_X
+#undef GM_ISSUE_W
 #undef GM_READ
 #undef GM_MFMA
-#undef GM_ISSUE
 
   // ---- store: lane owns token m = m0 + (BM/2) wm + 32 i + l32 and, in block j, outputs 8 (r >> 2) + 4 g + (r & 3)
   const int u64 = (n0 >> 6) + wn;  // QKV_ROPE: which run of 64 outputs (half a head's rotary pairs) this wavefront has
@@ -296,38 +319,43 @@ __global__ __launch_bounds__(T::NW * 64) void gemm_bf16_kernel(GemmArgs a) {
       }
     return;
   }
+  // What a store combines is loaded for a whole block before the block's first store: the compiler cannot move the
+  // loads over stores that might alias (the residual may be the output), and one memory latency per 8-byte run had cost
+  // 17 us per 256 x 256 tile (72B o_proj at 4096 tokens, two tiles per CU: 499 -> 464 us).
   if (MODE == GEMM_PLAIN) {
     const bf16_t* bias = (const bf16_t*)a.bias;
     const bf16_t* res = (const bf16_t*)a.residual;
     bf16_t* out = (bf16_t*)a.out;
 #pragma unroll
-    for (int j = 0; j < 2; ++j)
+    for (int j = 0; j < 2; ++j) {
+      uint2 bv[4], rv[4][T::MI];
+#pragma unroll
+      for (int q4 = 0; q4 < 4; ++q4) {
+        const int n = min(n0 + wn * 64 + j * 32 + 8 * q4 + 4 * g, a.n - 4);
+        bv[q4] = bias != nullptr ? *(const uint2*)(bias + n) : make_uint2(0u, 0u);
+#pragma unroll
+        for (int i = 0; i < T::MI; ++i)
+          rv[q4][i] = res != nullptr ? *(const uint2*)(res + (size_t)min(m0 + wm * (32 * T::MI) + i * 32 + l32, a.m - 1) * a.n + n)
+                                     : make_uint2(0u, 0u);
+      }
 #pragma unroll
       for (int q4 = 0; q4 < 4; ++q4) {
         const int n = n0 + wn * 64 + j * 32 + 8 * q4 + 4 * g;
         if (n >= a.n) continue;
-        float b[4] = {0.f, 0.f, 0.f, 0.f};
-        if (bias != nullptr) {
-          const uint2 raw = *(const uint2*)(bias + n);
-          b[0] = bf16lo_to_f32(raw.x), b[1] = bf16hi_to_f32(raw.x), b[2] = bf16lo_to_f32(raw.y), b[3] = bf16hi_to_f32(raw.y);
-        }
+        const float b[4] = {bf16lo_to_f32(bv[q4].x), bf16hi_to_f32(bv[q4].x), bf16lo_to_f32(bv[q4].y), bf16hi_to_f32(bv[q4].y)};
 #pragma unroll
         for (int i = 0; i < T::MI; ++i) {
           const int m = m0 + wm * (32 * T::MI) + i * 32 + l32;
           if (m >= a.m) continue;
-          float y[4];
-#pragma unroll
-          for (int e = 0; e < 4; ++e) y[e] = acc[j][i][4 * q4 + e] + b[e];
-          if (res != nullptr) {
-            const uint2 raw = *(const uint2*)(res + (size_t)m * a.n + n);
-            y[0] += bf16lo_to_f32(raw.x), y[1] += bf16hi_to_f32(raw.x), y[2] += bf16lo_to_f32(raw.y), y[3] += bf16hi_to_f32(raw.y);
-          }
+          const uint2 raw = rv[q4][i];
+          const float r[4] = {bf16lo_to_f32(raw.x), bf16hi_to_f32(raw.x), bf16lo_to_f32(raw.y), bf16hi_to_f32(raw.y)};
           bf16x4 pk;
 #pragma unroll
-          for (int e = 0; e < 4; ++e) pk[e] = (__bf16)y[e];
+          for (int e = 0; e < 4; ++e) pk[e] = (__bf16)((acc[j][i][4 * q4 + e] + b[e]) + r[e]);
           *(uint2*)(out + (size_t)m * a.n + n) = __builtin_bit_cast(uint2, pk);
         }
       }
+    }
   } else if (MODE == GEMM_QKV_ROPE) {
     // head of this wavefront and where its rows go
     const int head = u64 >> 1;
@@ -342,6 +370,14 @@ __global__ __launch_bounds__(T::NW * 64) void gemm_bf16_kernel(GemmArgs a) {
 #pragma unroll
     for (int q4 = 0; q4 < 4; ++q4) {
       const int f = dim0 + 8 * q4 + 4 * g;  // rotary frequency index of the run's first element
+      float4 cs0[T::MI], cs1[T::MI];
+      if (rotate) {
+#pragma unroll
+        for (int i = 0; i < T::MI; ++i) {
+          const float* cs = a.cos_sin + ((size_t)min(m0 + wm * (32 * T::MI) + i * 32 + l32, a.m - 1) * 64 + f) * 2;
+          cs0[i] = *(const float4*)cs, cs1[i] = *(const float4*)(cs + 4);
+        }
+      }
       float b0[4], b1[4];
       {
         const uint2 r0 = *(const uint2*)(bias + f), r1 = *(const uint2*)(bias + 64 + f);
@@ -356,9 +392,7 @@ __global__ __launch_bounds__(T::NW * 64) void gemm_bf16_kernel(GemmArgs a) {
 #pragma unroll
         for (int e = 0; e < 4; ++e) lo[e] = acc[0][i][4 * q4 + e] + b0[e], hi[e] = acc[1][i][4 * q4 + e] + b1[e];
         if (rotate) {
-          const float4 cs0 = *(const float4*)(a.cos_sin + ((size_t)m * 64 + f) * 2);
-          const float4 cs1 = *(const float4*)(a.cos_sin + ((size_t)m * 64 + f + 2) * 2);
-          const float c[4] = {cs0.x, cs0.z, cs1.x, cs1.z}, s[4] = {cs0.y, cs0.w, cs1.y, cs1.w};
+          const float c[4] = {cs0[i].x, cs0[i].z, cs1[i].x, cs1[i].z}, s[4] = {cs0[i].y, cs0[i].w, cs1[i].y, cs1[i].w};
 #pragma unroll
           for (int e = 0; e < 4; ++e) {
             const float x0 = lo[e], x1 = hi[e];
@@ -546,7 +580,7 @@ static hipError_t launch_tile(GemmArgs a, hipStream_t s) {
   static bool attr_done[QP_MAX_DEVICES] = {};
   const int dev = current_device();
   if (dev < 0) return hipErrorInvalidDevice;
-  const int lds = T::STAGES * T::STAGE;
+  const int lds = T::LDS;
   if (!attr_done[dev]) {
     hipError_t e = hipFuncSetAttribute((const void*)gemm_bf16_kernel<MODE, T>, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
     if (e != hipSuccess) return e;
