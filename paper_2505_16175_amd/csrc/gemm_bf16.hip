@@ -64,6 +64,7 @@ struct Tile {
 };
 typedef Tile<256, 256, 4, 2, 3> Tile256;    // 8 wavefronts, one workgroup per CU
 typedef Tile<128, 256, 2, 3> Tile128;
+typedef Tile<128, 128, 1, 3> Mid;
 typedef Tile<128, 64, 2, 3> Narrow128;    // 2 wavefronts, two workgroups per CU
 typedef Tile<64, 64, 1, 3> Narrow64;      // ... three
 
@@ -108,15 +109,22 @@ __global__ __launch_bounds__(T::NW * 64) void gemm_bf16_kernel(GemmArgs a) {
   const int l32 = lane & 31, g = lane >> 5;
   const int wm = wave / T::WN, wn = wave % T::WN;
 
-  // workgroup id -> (weight tile, token tile). Ids go round-robin over the 8 XCDs; the 32 workgroups that an XCD
-  // runs side by side form a block of up to 8 token tiles x 4 weight tiles, so that per k-step the XCD's L2 fetches
-  // 8 + 4 operand tiles for 32 products.
-  const int xcd = blockIdx.x & 7, idx = blockIdx.x >> 3;
-  const int mi = idx % a.m_block, t = idx / a.m_block;
-  const int ni = t & 3, b = t >> 2;
-  const int mc = b / a.n_quads, nq = b - mc * a.n_quads;
-  const int tm = mc * a.m_block + mi, tn = xcd + 8 * (nq * 4 + ni);
-  if (tm >= a.tiles_m || tn >= a.tiles_n) return;  // padding of the mapping (whole workgroup, before any barrier)
+  // workgroup id -> (weight tile, token tile). Ids go round-robin over the 8 XCDs; each XCD takes an equal run of the
+  // tiles in an order of blocks of up to 8 token tiles x 4 weight tiles: of the 32 workgroups that an XCD runs side by
+  // side, its L2 then fetches 8 + 4 operand tiles per k-step for 32 products. (Weight tiles dealt to the XCDs in turn
+  // left them unequal: 18 weight tiles x 12 token tiles put 36 workgroups on two XCDs of 32 CUs, 166 us for QKV of 3000
+  // tokens at 7B sizes, 99 now.)
+  const int per_xcd = gridDim.x >> 3, id = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
+  if (id >= a.tiles_m * a.tiles_n) return;  // padding of the mapping (whole workgroup, before any barrier)
+  // block `quad` of n_quads has the weight tiles quad, quad + n_quads, ...: nw of them, one more in the first n_more blocks
+  const int n_quads = (a.tiles_n + 3) / 4, fewer = a.tiles_n / n_quads, n_more = a.tiles_n - fewer * n_quads;
+  const int in_more = n_more * (fewer + 1) * a.tiles_m;
+  const int nw = id < in_more ? fewer + 1 : fewer, rel = id < in_more ? id : id - in_more;
+  const int q0 = rel / (nw * a.tiles_m), in_quad = rel - q0 * nw * a.tiles_m;
+  const int quad = id < in_more ? q0 : n_more + q0;
+  const int mc = in_quad / (nw * a.m_block), in_blk = in_quad - mc * nw * a.m_block;
+  const int mh = min(a.m_block, a.tiles_m - mc * a.m_block);         // token tiles of this block of m_block
+  const int tm = mc * a.m_block + in_blk % mh, tn = quad + n_quads * (in_blk / mh);
   const int m0 = tm * BM, n0 = tn * BN;
   const int d_ff = a.n >> 1;
 
@@ -525,17 +533,32 @@ bool gemm_supported(const GemmArgs& a, int mode) {
 static std::atomic<int> g_forced_tile_rows{0};  // 0: choose per launch; 128 / 256: tests cover both tilings
 void gemm_force_tile_rows(int rows) { g_forced_tile_rows.store(rows, std::memory_order_relaxed); }
 
-// 256-row tiles unless 128-row tiles finish sooner: a launch lasts ceil(tiles / CUs) rounds of one tile each, and a
-// 128-row tile costs about 0.6 of a 256-row one (half the products, less reuse of the weight fragments).
-int gemm_tile_rows(const GemmArgs& a) {
+// The tiling that finishes soonest: a launch lasts ceil(tiles / CUs) rounds of one tile each. A tile's time by its size,
+// measured per 64-wide k-step with one workgroup per CU: 256 x 256 1.55 us, 128 x 256 0.96, 128 x 128 0.60 (fewer
+// products per fragment read and per request, so small tiles pay only where they fill CUs that the larger leave idle:
+// 7B o_proj at 700 tokens, 84 / 168 tiles, 48 -> 30 us; 72B down at 512, 128 / 256 tiles, 420 -> 289 us).
+struct TileChoice {
+  int rows, cols;
+};
+static TileChoice gemm_tile(const GemmArgs& a) {
   const int forced = g_forced_tile_rows.load(std::memory_order_relaxed);
-  if (forced != 0) return forced;
+  if (forced != 0) return {forced, GM_BN};
+  static const struct {
+    int rows, cols;
+    double cost;
+  } kinds[] = {{256, 256, 1.0}, {128, 256, 0.62}, {128, 128, 0.39}};
   const int cus = device_cu_count();
-  const long tiles_n = (a.n + GM_BN - 1) / GM_BN;
-  const long t256 = (long)((a.m + 255) / 256) * tiles_n, t128 = (long)((a.m + 127) / 128) * tiles_n;
-  const double cost256 = (double)((t256 + cus - 1) / cus), cost128 = 0.6 * (double)((t128 + cus - 1) / cus);
-  return cost128 < cost256 ? 128 : 256;
+  TileChoice best{256, 256};
+  double best_cost = 1e30;
+  for (const auto& t : kinds) {
+    const long tiles = (long)((a.m + t.rows - 1) / t.rows) * ((a.n + t.cols - 1) / t.cols);
+    const double cost = t.cost * (double)((tiles + cus - 1) / cus);
+    if (cost < best_cost) best_cost = cost, best = {t.rows, t.cols};
+  }
+  return best;
 }
+int gemm_tile_rows(const GemmArgs& a) { return gemm_tile(a).rows; }
+int gemm_tile_cols(const GemmArgs& a) { return gemm_tile(a).cols; }
 
 // Contraction split: launches whose tiles would occupy at most a quarter of the CUs (few tokens against a long k:
 // text chunks and decode steps through the layer, where the weights are streamed once and HBM is the bound) deal the
@@ -589,10 +612,8 @@ static hipError_t launch_tile(GemmArgs a, hipStream_t s) {
   a.tiles_m = (a.m + T::BM - 1) / T::BM;
   a.tiles_n = (a.n + T::BN - 1) / T::BN;
   a.m_block = a.tiles_m < 8 ? a.tiles_m : 8;
-  a.n_quads = ((a.tiles_n + 7) / 8 + 3) / 4;  // weight tiles per XCD, in fours
-  const int m_chunks = (a.tiles_m + a.m_block - 1) / a.m_block;
-  hipLaunchKernelGGL((gemm_bf16_kernel<MODE, T>), dim3(8 * m_chunks * a.m_block * a.n_quads * 4, a.split_k),
-                     dim3(T::NW * 64), lds, s, a);
+  const long tiles = (long)a.tiles_m * a.tiles_n;
+  hipLaunchKernelGGL((gemm_bf16_kernel<MODE, T>), dim3((unsigned)((tiles + 7) / 8 * 8), a.split_k), dim3(T::NW * 64), lds, s, a);
   return hipSuccess;
 }
 
@@ -601,8 +622,14 @@ static hipError_t launch_mode(GemmArgs a, void* scratch, size_t scratch_bytes, h
   const GemmSplit sp = gemm_plan_split(a, MODE, scratch != nullptr ? scratch_bytes : 0);
   a.split_k = sp.split_k, a.steps_per_split = sp.steps_per_split, a.partial = (float*)scratch;
   hipError_t e;
-  if (MODE != GEMM_SWIGLU && sp.narrow) e = a.m <= 64 ? launch_tile<MODE, Narrow64>(a, s) : launch_tile<MODE, Narrow128>(a, s);
-  else e = gemm_tile_rows(a) == 128 ? launch_tile<MODE, Tile128>(a, s) : launch_tile<MODE, Tile256>(a, s);
+  if (sp.narrow) {  // never for SWIGLU, which is not split
+    if constexpr (MODE != GEMM_SWIGLU) e = a.m <= 64 ? launch_tile<MODE, Narrow64>(a, s) : launch_tile<MODE, Narrow128>(a, s);
+    else e = hipErrorInvalidValue;
+  } else if (a.split_k == 1 && gemm_tile_cols(a) == 128) {
+    e = launch_tile<MODE, Mid>(a, s);
+  } else {
+    e = gemm_tile_rows(a) == 128 ? launch_tile<MODE, Tile128>(a, s) : launch_tile<MODE, Tile256>(a, s);
+  }
   if (e != hipSuccess || a.split_k == 1) return e;
   const long threads = (long)a.m * (MODE == GEMM_QKV_ROPE ? a.n / 8 : a.n / 4);
   hipLaunchKernelGGL(gemm_reduce_kernel<MODE>, dim3((unsigned)((threads + 255) / 256)), dim3(256), 0, s, a);

@@ -146,11 +146,10 @@ qp_status qp_linear_plan(int32_t m, int32_t n, int32_t k, size_t workspace_bytes
     return QP_OK;
   }
   const int rows = qp::gemm_tile_rows(a);
-  const int cols = sp.narrow ? 64 : 256;
+  const int cols = sp.narrow ? 64 : sp.split_k > 1 ? 256 : qp::gemm_tile_cols(a);
   const int tiles_m = (m + rows - 1) / rows, tiles_n = (n + cols - 1) / cols;
-  const int m_block = tiles_m < 8 ? tiles_m : 8;
   out->token_rows_per_tile = rows;
-  out->workgroups = 8 * ((tiles_m + m_block - 1) / m_block) * m_block * (((tiles_n + 7) / 8 + 3) / 4) * 4;
+  out->workgroups = (tiles_m * tiles_n + 7) / 8 * 8;
   out->k_chunks = sp.split_k;
   out->k_steps_per_chunk = sp.steps_per_split;
   out->scratch_bytes = sp.scratch_bytes;

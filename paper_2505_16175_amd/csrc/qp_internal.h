@@ -227,7 +227,7 @@ struct GemmArgs {
   const float* cos_sin;  // QKV_ROPE: [m][64][2] f32, (cos, sin) of each token's 64 rotation angles
   int m, n, k;
   int h_q, h_kv;
-  int tiles_m, tiles_n, m_block, n_quads;  // filled by the launcher (tile counts and the XCD block mapping)
+  int tiles_m, tiles_n, m_block;           // filled by the launcher (tile counts and the XCD block mapping)
   int split_k, steps_per_split;            // filled by the launcher: k chunks (1 = none) and 64-wide k-steps per chunk
   float* partial;                          // [split_k][m][n] f32 partial sums when split_k > 1
 };
@@ -245,6 +245,7 @@ bool gemv_applies(const GemmArgs& a);
 bool gemm_uses_gemv(const GemmArgs& a);   // gemv_applies and no tiling is forced
 hipError_t launch_gemv_bf16(const GemmArgs& a, int mode, hipStream_t s);
 int gemm_tile_rows(const GemmArgs& a);    // token rows per workgroup tile the launcher would use: 128 or 256
+int gemm_tile_cols(const GemmArgs& a);    // outputs per workgroup tile of an unsplit launch: 128 or 256
 void gemm_force_tile_rows(int rows);      // 0 = choose per launch (default), 128 or 256
 void launch_rms_norm(const void* x, const void* w, void* out, int n_tokens, int d_model, float eps, hipStream_t s);
 void launch_rope_table(const int32_t* pos, long axis_stride, int n_tokens, float theta, int s0, int s1, float* cos_sin,

@@ -240,6 +240,39 @@ def test_linear_split_contraction(m, n, k, bias, res):
     assert_stored_close(to_f64(plain), LO.bf16_round(want), "unsplit linear")
 
 
+@pytest.mark.parametrize("m,n,k", [(130, 1000, 640), (129, 264, 192), (257, 520, 64), (700, 3584, 256), (1500, 4608, 128), (3, 8, 64)])
+def test_linear_is_the_same_in_every_tiling(m, n, k):
+    """An unsplit product walks k in the same order whatever the tile, so the launcher's choice (128 x 128 tiles and
+    the dealing of tiles to XCDs among it) and both pinned tilings agree bit for bit, and with the oracle."""
+    g = torch.Generator().manual_seed(m + n + k)
+    x, w, r = _bf(m, k, gen=g), _bf(n, k, gen=g, scale=k ** -0.5), _bf(m, n, gen=g)
+    outs = []
+    for rows in (0, 128, 256):
+        B.select_linear_tile(rows)
+        try:
+            out = torch.full((m, n), float("nan"), dtype=torch.bfloat16, device=DEV)
+            B.linear(x.to(DEV), w.to(DEV), None, r.to(DEV), out)
+            torch.cuda.synchronize()
+            outs.append(out)
+        finally:
+            B.select_linear_tile(0)
+    assert torch.equal(outs[0], outs[1]) and torch.equal(outs[0], outs[2])
+    assert_stored_close(to_f64(outs[0]), LO.bf16_round(LO.linear(to_f64(x), to_f64(w)) + to_f64(r)), "linear")
+
+
+@pytest.mark.parametrize("m,n,k", [(63, 3584, 1088), (65, 4600, 2048), (200, 3584, 2112), (3, 1000, 4096)])
+def test_narrow_split_tiles(m, n, k):
+    """Few outputs against a long k with scratch: 64-wide tiles, token rows and outputs that end inside a tile."""
+    g = torch.Generator().manual_seed(m + n + k)
+    x, w, b, r = _bf(m, k, gen=g), _bf(n, k, gen=g, scale=k ** -0.5), _bf(n, gen=g), _bf(m, n, gen=g)
+    assert B.linear_plan(m, n, k, 32 << 20)["k_chunks"] > 1
+    scratch = torch.empty(32 << 20, dtype=torch.uint8, device=DEV).fill_(0xff)
+    out = torch.full((m, n), float("nan"), dtype=torch.bfloat16, device=DEV)
+    B.linear(x.to(DEV), w.to(DEV), b.to(DEV), r.to(DEV), out, scratch)
+    torch.cuda.synchronize()
+    assert_stored_close(to_f64(out), LO.bf16_round(LO.linear(to_f64(x), to_f64(w), to_f64(b)) + to_f64(r)), "narrow tiles")
+
+
 @pytest.mark.parametrize("n,d_model,h_q,h_kv", [(1, 3584, 28, 4), (9, 1024, 4, 2), (64, 3584, 28, 4)])
 def test_qkv_rope_split_contraction(n, d_model, h_q, h_kv):
     print(f"case n={n} d_model={d_model} heads={h_q}/{h_kv}", flush=True)
