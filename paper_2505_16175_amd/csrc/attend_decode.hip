@@ -19,8 +19,8 @@
 // F8 (the pruned cache in 8-bit E4M3): a cache block cannot go global -> LDS directly. The wavefront loads it into
 // registers one block ahead with ordinary loads (8 bytes per lane, key and tensor: half the bytes of a bf16 block),
 // widens it exactly to bf16 and writes it to its own LDS buffer in the same swizzled layout, so that the products
-// and the softmax are the same code; the group's own block is bf16 and still loaded directly. The call is bound by
-// the cache's bytes, which this halves.
+// and the softmax are the same code; the group's own block is bf16 and still loaded directly. One LDS buffer per
+// wavefront then suffices, and two workgroups share a CU.
 #include "qp_internal.h"
 
 #include <algorithm>
@@ -40,7 +40,9 @@ constexpr int DC_BK = 32;                  // keys per block
 constexpr int DC_NW = 4;                   // wavefronts per workgroup
 constexpr int DC_TILE = DC_BK * DC_D * 2;  // bytes of one K or V block in LDS
 constexpr int DC_BUF = 2 * DC_TILE;        // K block + V block
-constexpr int DC_WAVE_LDS = 2 * DC_BUF;    // two buffers per wavefront; the first 16 KB are reused for the final merge
+// LDS per wavefront: two buffers, one for 8-bit caches (the block ahead waits in registers); the first 16 KB are reused
+// for the final merge
+constexpr int dc_wave_lds(bool f8) { return f8 ? DC_BUF : 2 * DC_BUF; }
 constexpr int DC_MAX_ROWS = 32;
 constexpr float DC_RESCALE_LOG2 = 8.f;
 
@@ -120,7 +122,7 @@ __device__ __forceinline__ void decode_pv(const unsigned char* vt, const int (&v
 }
 
 template <bool F8>
-__global__ __launch_bounds__(DC_NW * 64) void attend_decode_kernel(AttendArgs a) {
+__global__ __launch_bounds__(DC_NW * 64, F8 ? 2 : 1) void attend_decode_kernel(AttendArgs a) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   __shared__ float sm_m[DC_NW][DC_MAX_ROWS], sm_l[DC_NW][DC_MAX_ROWS];
   const int tid = threadIdx.x, lane = tid & 63;
@@ -145,6 +147,7 @@ __global__ __launch_bounds__(DC_NW * 64) void attend_decode_kernel(AttendArgs a)
   const unsigned gstride_b = (unsigned)a.h_kv * (DC_D * 2);
   const int n_cb = (a.c + DC_BK - 1) / DC_BK;  // cache blocks; block n_cb is the group's own keys
   const int b_end = min(n_cb + 1, (chunk + 1) * a.split_tiles);
+  constexpr int DC_WAVE_LDS = dc_wave_lds(F8);
   unsigned char* vbuf = smem + wave * DC_WAVE_LDS;
 
   // staging: load i of a block moves keys 4i .. 4i+3; this lane fills LDS position (lane & 15) of key 4i + (lane >> 4)
@@ -213,10 +216,9 @@ __global__ __launch_bounds__(DC_NW * 64) void attend_decode_kernel(AttendArgs a)
       return o4;
     };
     int b = chunk * a.split_tiles + wave;
-    int cur = 0;
+    unsigned char* buf = vbuf;  // one buffer: a wavefront's LDS operations stay in order
     if (b < b_end && b < n_cb) load_block(b);
     while (b < b_end) {
-      unsigned char* buf = vbuf + cur * DC_BUF;
       const bool has1 = b + DC_NW < b_end;
       if (b < n_cb) {
         // this block's pieces have arrived (requested a block ago): widen them into the buffer, then request the next
@@ -227,8 +229,9 @@ __global__ __launch_bounds__(DC_NW * 64) void attend_decode_kernel(AttendArgs a)
         }
         if (has1 && b + DC_NW < n_cb) load_block(b + DC_NW);
       } else {
-        QP_DC_REQUEST(b, cur, false)  // the group's own keys and values: bf16, loaded directly
-        QP_DC_REQUEST(b, cur, true)
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // the direct loads are not ordered behind the last block's reads
+        QP_DC_REQUEST(b, 0, false)  // the group's own keys and values: bf16, loaded directly
+        QP_DC_REQUEST(b, 0, true)
         wait_vmcnt<0>();
       }
       bf16x8 pf[2];
@@ -236,7 +239,6 @@ __global__ __launch_bounds__(DC_NW * 64) void attend_decode_kernel(AttendArgs a)
                         m_run, l_run, o, pf);
       decode_pv(buf + DC_TILE, v_addr, pf, o);
       b += DC_NW;
-      cur ^= 1;
     }
   } else {
     // The Q fragments (ordinary loads) must have arrived before the first request: from here on only untracked
@@ -334,7 +336,10 @@ AttendPlan plan_attend_decode(const AttendArgs& a, size_t split_ws_bytes) {
   AttendPlan p;
   const int n_rows = a.n_g * (a.h_q / a.h_kv);
   const int nb = (a.c + DC_BK - 1) / DC_BK + 1;
-  const int per_head = std::max(1, device_cu_count() / a.h_kv);
+  // An 8-bit block is a longer chain for its wavefront (widen, write, read back, two products, softmax: ~2 us alone on a
+  // SIMD) over half the bytes, so two workgroups share a CU there, each with half the LDS: one token of the 72B heads
+  // over 32,768 entries 23.1 -> 20.6 us. (A second block ahead in registers, one workgroup per CU: 23.1.)
+  const int per_head = std::max(1, device_cu_count() * (a.cache_fp8 ? 2 : 1) / a.h_kv);
   int bpw = std::max(DC_NW, (nb + per_head - 1) / per_head);
   int chunks = (nb + bpw - 1) / bpw;
   const size_t per_chunk = (size_t)a.h_kv * n_rows * (DC_D + 1) * sizeof(float);
@@ -358,9 +363,9 @@ void launch_attend_decode(const AttendArgs& a_in, void* split_ws, size_t split_w
   const int dev = current_device();
   if (dev < 0 || !attr_set[dev]) {
     (void)hipFuncSetAttribute((const void*)attend_decode_kernel<false>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                              DC_NW * DC_WAVE_LDS);
+                              DC_NW * dc_wave_lds(false));
     (void)hipFuncSetAttribute((const void*)attend_decode_kernel<true>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                              DC_NW * DC_WAVE_LDS);
+                              DC_NW * dc_wave_lds(true));
     if (dev >= 0) attr_set[dev] = true;
   }
   AttendArgs a = a_in;
@@ -378,9 +383,9 @@ void launch_attend_decode(const AttendArgs& a_in, void* split_ws, size_t split_w
     a.part_lse = a.part_o + (size_t)p.n_split * rows_total * DC_D;
   }
   if (a.cache_fp8)
-    hipLaunchKernelGGL(attend_decode_kernel<true>, dim3(p.n_split, a.h_kv), dim3(DC_NW * 64), DC_NW * DC_WAVE_LDS, s, a);
+    hipLaunchKernelGGL(attend_decode_kernel<true>, dim3(p.n_split, a.h_kv), dim3(DC_NW * 64), DC_NW * dc_wave_lds(true), s, a);
   else
-    hipLaunchKernelGGL(attend_decode_kernel<false>, dim3(p.n_split, a.h_kv), dim3(DC_NW * 64), DC_NW * DC_WAVE_LDS, s, a);
+    hipLaunchKernelGGL(attend_decode_kernel<false>, dim3(p.n_split, a.h_kv), dim3(DC_NW * 64), DC_NW * dc_wave_lds(false), s, a);
   if (p.n_split > 1) launch_attend_merge(a, s);
 }
 
