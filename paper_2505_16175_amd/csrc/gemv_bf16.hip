@@ -11,10 +11,11 @@
 //   * a workgroup of 4 wavefronts owns 4 weight rows, chosen so that the values a store combines belong to the same
 //     workgroup: 4 consecutive outputs (PLAIN), 2 dims of a head and their rotary partners (QKV_ROPE), 2 gate rows and
 //     the up rows of the same outputs (SWIGLU);
-//   * wavefront w walks the w-th quarter of k, 16 bytes per lane and row (a wavefront reads 1 KB runs of each row),
-//     two such steps per loop trip with all of their loads issued before the first product, so that a wavefront has
-//     8 KB of weights in flight and a compute unit (up to 32 wavefronts) well over the ~40 KB that 8 TB/s need at
-//     ~2 us of latency; the activations (a few KB per token) come from L2 alongside;
+//   * the wavefronts walk k side by side, 16 bytes per lane and row (1 KB runs of each row per wavefront, 4 KB per
+//     workgroup), two steps per loop trip, and request the next trip's weights before the products of this one: 16 KB
+//     in flight per wavefront. With a quarter of k per wavefront and a wait for each trip's own loads the weights came
+//     at 4.1-5.6 TB/s; now, at one token, 7B sizes: gate/up 48.8 -> 43.1 us (6.3 TB/s), down 32.9 -> 28.0, all four
+//     101.6 -> 90.2; 72B sizes 344 -> 289. The activations (a few KB per token) come from L2 alongside;
 //   * products are v_dot2_f32_bf16 (two multiply-adds per lane and instruction, f32 accumulation);
 //   * the 64 lanes' sums are added by shuffles, the 4 wavefronts' sums meet in LDS and are added in wavefront order
 //     (deterministic), and one lane per token applies the store.
@@ -54,8 +55,7 @@ __global__ __launch_bounds__(GV_WAVES * 64) void gemv_bf16_kernel(GemmArgs a) {
   } else {
     row[0] = 4 * quad, row[1] = row[0] + 1, row[2] = row[0] + 2, row[3] = row[0] + 3;
   }
-  const int chunks = a.k / 8, per_wave = chunks / GV_WAVES;  // k is a multiple of 64 (checked by the launcher)
-  const int c_end = (wave + 1) * per_wave;
+  const int chunks = a.k / 8;
   const uint4* w[4];
 #pragma unroll
   for (int e = 0; e < 4; ++e) w[e] = (const uint4*)((const bf16_t*)a.w + (size_t)row[e] * a.k);
@@ -68,23 +68,44 @@ __global__ __launch_bounds__(GV_WAVES * 64) void gemv_bf16_kernel(GemmArgs a) {
   for (int e = 0; e < 4; ++e)
 #pragma unroll
     for (int t = 0; t < M; ++t) acc[e][t] = 0.f;
-  const uint4 zero = make_uint4(0u, 0u, 0u, 0u);
-  for (int c = wave * per_wave + lane; c < c_end; c += 128) {
-    const int c1 = c + 64;
-    const bool has1 = c1 < c_end;
-    uint4 w0[4], w1[4], x0[M], x1[M];
+  // U steps per trip, the next trip's loads issued before this trip's products; steps past the end load the last chunk
+  // and are dropped
+  constexpr int U = 2, STEP = GV_WAVES * 64;
+  uint4 wv[U][4], xv[U][M];
+  auto load = [&](int c) {
 #pragma unroll
-    for (int e = 0; e < 4; ++e) w0[e] = w[e][c];
+    for (int u = 0; u < U; ++u) {
+      const int cc = min(c + u * STEP, chunks - 1);
 #pragma unroll
-    for (int t = 0; t < M; ++t) x0[t] = x[t][c];
+      for (int e = 0; e < 4; ++e) wv[u][e] = w[e][cc];
 #pragma unroll
-    for (int e = 0; e < 4; ++e) w1[e] = has1 ? w[e][c1] : zero;
+      for (int t = 0; t < M; ++t) xv[u][t] = x[t][cc];
+    }
+  };
+  const int c_first = wave * 64 + lane;
+  load(c_first);
+  const int trips = (chunks + U * STEP - 1) / (U * STEP);
+  for (int i = 0; i < trips; ++i) {
+    uint4 w0[U][4], x0[U][M];
 #pragma unroll
-    for (int t = 0; t < M; ++t) x1[t] = has1 ? x[t][c1] : zero;
+    for (int u = 0; u < U; ++u) {
 #pragma unroll
-    for (int e = 0; e < 4; ++e)
+      for (int e = 0; e < 4; ++e) w0[u][e] = wv[u][e];
 #pragma unroll
-      for (int t = 0; t < M; ++t) acc[e][t] = dot8(w1[e], x1[t], dot8(w0[e], x0[t], acc[e][t]));
+      for (int t = 0; t < M; ++t) x0[u][t] = xv[u][t];
+    }
+    if (i + 1 < trips) load(c_first + (i + 1) * U * STEP);
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const bool exists = c_first + (i * U + u) * STEP < chunks;
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+#pragma unroll
+        for (int t = 0; t < M; ++t) {
+          const float sum = dot8(w0[u][e], x0[u][t], acc[e][t]);
+          acc[e][t] = exists ? sum : acc[e][t];
+        }
+    }
   }
 #pragma unroll
   for (int e = 0; e < 4; ++e)
@@ -145,8 +166,8 @@ __global__ __launch_bounds__(GV_WAVES * 64) void gemv_bf16_kernel(GemmArgs a) {
   }
 }
 
-// The shapes gemm_supported admits all fit: k is a multiple of 64 (a wavefront's quarter of it a whole number of
-// 16-byte chunks), n a multiple of 8 (PLAIN), of 128 per head (QKV_ROPE) or of 256 (SWIGLU), hence of 4.
+// The shapes gemm_supported admits all fit: k is a multiple of 64 (a whole number of 16-byte chunks), n a multiple of 8
+// (PLAIN), of 128 per head (QKV_ROPE) or of 256 (SWIGLU), hence of 4.
 bool gemv_applies(const GemmArgs& a) { return a.m <= GV_MAX_M; }
 
 template <int MODE>
