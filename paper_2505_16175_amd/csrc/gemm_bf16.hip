@@ -519,6 +519,63 @@ __global__ __launch_bounds__(256) void gemm_reduce_kernel(GemmArgs a) {
   }
 }
 
+// The PLAIN reduction with the RMSNorm of its result behind it (the layer's o_proj before the second norm): a workgroup
+// per token holds the row, rounded as stored, between the sums and the scaling. As two launches the norm of 64 tokens
+// cost 5.9 us, nearly all of it the start of one more dependent launch: 7B layer, 64 tokens 223.8 -> 218.4 us.
+constexpr int RNK_THREADS = 512;
+constexpr int RNK_RUNS = 4;  // runs of 4 outputs per thread: rows of up to 8192
+__global__ __launch_bounds__(RNK_THREADS) void gemm_reduce_norm_kernel(GemmArgs a, const bf16_t* __restrict__ norm_w,
+                                                                       bf16_t* __restrict__ norm_out, float eps) {
+  __shared__ float wave_ss[RNK_THREADS / 64];
+  const int m = blockIdx.x, tid = threadIdx.x, runs = a.n / 4;
+  const size_t stride = (size_t)a.m * a.n;
+  uint2 row[RNK_RUNS], wv[RNK_RUNS];
+  float ss = 0.f;
+#pragma unroll
+  for (int i = 0; i < RNK_RUNS; ++i) {
+    const int r = tid + i * RNK_THREADS;
+    if (r >= runs) continue;
+    const float* p = a.partial + (size_t)m * a.n + 4 * r;
+    wv[i] = *(const uint2*)(norm_w + 4 * r);
+    const uint2 raw = a.residual != nullptr ? *(const uint2*)((const bf16_t*)a.residual + (size_t)m * a.n + 4 * r) : make_uint2(0u, 0u);
+    float4 y = make_float4(0.f, 0.f, 0.f, 0.f);
+    for (int c0 = 0; c0 < a.split_k; c0 += 2 * RD_BATCH) {
+      float4 t[2 * RD_BATCH];
+#pragma unroll
+      for (int u = 0; u < 2 * RD_BATCH; ++u) t[u] = *(const float4*)(p + min(c0 + u, a.split_k - 1) * stride);
+#pragma unroll
+      for (int u = 0; u < 2 * RD_BATCH; ++u)
+        if (c0 + u < a.split_k) y.x += t[u].x, y.y += t[u].y, y.z += t[u].z, y.w += t[u].w;
+    }
+    y.x += bf16lo_to_f32(raw.x), y.y += bf16hi_to_f32(raw.x), y.z += bf16lo_to_f32(raw.y), y.w += bf16hi_to_f32(raw.y);
+    bf16x4 pk;
+    pk[0] = (__bf16)y.x, pk[1] = (__bf16)y.y, pk[2] = (__bf16)y.z, pk[3] = (__bf16)y.w;
+    row[i] = __builtin_bit_cast(uint2, pk);
+    *(uint2*)((bf16_t*)a.out + (size_t)m * a.n + 4 * r) = row[i];
+    const float f[4] = {bf16lo_to_f32(row[i].x), bf16hi_to_f32(row[i].x), bf16lo_to_f32(row[i].y), bf16hi_to_f32(row[i].y)};
+#pragma unroll
+    for (int e = 0; e < 4; ++e) ss = fmaf(f[e], f[e], ss);
+  }
+  ss = wave_sum(ss);
+  if ((tid & 63) == 0) wave_ss[tid >> 6] = ss;
+  __syncthreads();
+  float tot = 0.f;
+#pragma unroll
+  for (int w = 0; w < RNK_THREADS / 64; ++w) tot += wave_ss[w];
+  const float inv = 1.f / sqrtf(tot / (float)a.n + eps);
+#pragma unroll
+  for (int i = 0; i < RNK_RUNS; ++i) {
+    const int r = tid + i * RNK_THREADS;
+    if (r >= runs) continue;
+    uint2 o;
+    o.x = (uint32_t)f32_to_bf16_rne(bf16lo_to_f32(row[i].x) * inv * bf16lo_to_f32(wv[i].x)) |
+          ((uint32_t)f32_to_bf16_rne(bf16hi_to_f32(row[i].x) * inv * bf16hi_to_f32(wv[i].x)) << 16);
+    o.y = (uint32_t)f32_to_bf16_rne(bf16lo_to_f32(row[i].y) * inv * bf16lo_to_f32(wv[i].y)) |
+          ((uint32_t)f32_to_bf16_rne(bf16hi_to_f32(row[i].y) * inv * bf16hi_to_f32(wv[i].y)) << 16);
+    *(uint2*)(norm_out + (size_t)m * a.n + 4 * r) = o;
+  }
+}
+
 bool gemm_supported(const GemmArgs& a, int mode) {
   if (a.m <= 0 || a.n <= 0 || a.k <= 0 || a.k % 64 != 0) return false;
   // byte offsets inside a tile's row range are 32-bit (plus the k offset of the step)
@@ -617,8 +674,9 @@ static hipError_t launch_tile(GemmArgs a, hipStream_t s) {
   return hipSuccess;
 }
 
+// reduce = false leaves a split product's partial sums to the caller (a.split_k says whether there are any)
 template <int MODE>
-static hipError_t launch_mode(GemmArgs a, void* scratch, size_t scratch_bytes, hipStream_t s) {
+static hipError_t launch_mode(GemmArgs& a, void* scratch, size_t scratch_bytes, hipStream_t s, bool reduce = true) {
   const GemmSplit sp = gemm_plan_split(a, MODE, scratch != nullptr ? scratch_bytes : 0);
   a.split_k = sp.split_k, a.steps_per_split = sp.steps_per_split, a.partial = (float*)scratch;
   hipError_t e;
@@ -630,7 +688,7 @@ static hipError_t launch_mode(GemmArgs a, void* scratch, size_t scratch_bytes, h
   } else {
     e = gemm_tile_rows(a) == 128 ? launch_tile<MODE, Tile128>(a, s) : launch_tile<MODE, Tile256>(a, s);
   }
-  if (e != hipSuccess || a.split_k == 1) return e;
+  if (e != hipSuccess || a.split_k == 1 || !reduce) return e;
   const long threads = (long)a.m * (MODE == GEMM_QKV_ROPE ? a.n / 8 : a.n / 4);
   hipLaunchKernelGGL(gemm_reduce_kernel<MODE>, dim3((unsigned)((threads + 255) / 256)), dim3(256), 0, s, a);
   return hipSuccess;
@@ -642,7 +700,24 @@ bool gemm_uses_gemv(const GemmArgs& a) {
   return gemv_applies(a) && g_forced_tile_rows.load(std::memory_order_relaxed) == 0;
 }
 
-hipError_t launch_gemm_bf16(const GemmArgs& a, int mode, void* scratch, size_t scratch_bytes, hipStream_t s) {
+hipError_t launch_gemm_norm(const GemmArgs& a_in, const void* norm_w, void* norm_out, float eps, void* scratch,
+                            size_t scratch_bytes, hipStream_t s) {
+  GemmArgs a = a_in;
+  a.split_k = 1;
+  const bool fits = a.n <= 4 * RNK_RUNS * RNK_THREADS && a.bias == nullptr;
+  const hipError_t e = gemm_uses_gemv(a) ? launch_gemv_bf16(a, GEMM_PLAIN, s)
+                                         : launch_mode<GEMM_PLAIN>(a, scratch, scratch_bytes, s, !fits);
+  if (e != hipSuccess) return e;
+  if (fits && a.split_k > 1)
+    hipLaunchKernelGGL(gemm_reduce_norm_kernel, dim3((unsigned)a.m), dim3(RNK_THREADS), 0, s, a, (const bf16_t*)norm_w,
+                       (bf16_t*)norm_out, eps);
+  else
+    launch_rms_norm(a.out, norm_w, norm_out, a.m, a.n, eps, s);
+  return hipSuccess;
+}
+
+hipError_t launch_gemm_bf16(const GemmArgs& a_in, int mode, void* scratch, size_t scratch_bytes, hipStream_t s) {
+  GemmArgs a = a_in;
   if (gemm_uses_gemv(a)) return launch_gemv_bf16(a, mode, s);
   switch (mode) {
     case GEMM_PLAIN: return launch_mode<GEMM_PLAIN>(a, scratch, scratch_bytes, s);

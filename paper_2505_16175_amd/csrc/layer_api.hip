@@ -250,9 +250,8 @@ qp_status qp_layer_group(const qp_layout* layout, const qp_layer_shape* shape, c
   st = qp_topk_compact(layout, (const float*)(ws + c.scores), ws + c.k, ws + c.v, n_g, keep, group_token_base, cache,
                        kept_idx_or_null, score_ws, score_bytes, fork.stream());
   if (st != QP_OK) return st;
-  st = finish(qp::launch_gemm_bf16(oproj, qp::GEMM_PLAIN, ws + c.gemm, kGemmSplitBytes, s));
+  st = finish(qp::launch_gemm_norm(oproj, weights->ln2_w, ws + c.h, shape->rms_eps, ws + c.gemm, kGemmSplitBytes, s));
   if (st != QP_OK) return st;
-  qp::launch_rms_norm(ws + c.x1, weights->ln2_w, ws + c.h, n_g, dm, shape->rms_eps, s);
   st = finish(qp::launch_gemm_bf16(gate_up, qp::GEMM_SWIGLU, nullptr, 0, s));
   if (st != QP_OK) return st;
   return finish(qp::launch_gemm_bf16(down, qp::GEMM_PLAIN, ws + c.gemm, kGemmSplitBytes, s));

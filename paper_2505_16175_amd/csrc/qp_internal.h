@@ -234,6 +234,9 @@ struct GemmArgs {
 bool gemm_supported(const GemmArgs& a, int mode);
 // scratch: optional (256-byte aligned) room for the partial sums of a split contraction; without it nothing is split
 hipError_t launch_gemm_bf16(const GemmArgs& a, int mode, void* scratch, size_t scratch_bytes, hipStream_t s);
+// PLAIN without bias, then RMSNorm of its rows (weights norm_w) into norm_out: one launch less where the product is split
+hipError_t launch_gemm_norm(const GemmArgs& a, const void* norm_w, void* norm_out, float eps, void* scratch,
+                            size_t scratch_bytes, hipStream_t s);
 struct GemmSplit {
   int split_k, steps_per_split;
   size_t scratch_bytes;
