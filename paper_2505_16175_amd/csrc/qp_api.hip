@@ -604,9 +604,11 @@ qp_status qp_prefill_video(const qp_layout* L, int32_t n_frames, int32_t tokens_
   }
 
   {
-    // Videos whose attention fills the chip at least twice, and every video on the scalar kernel (a launch per row
-    // group, never split), go in runs of groups; shorter ones keep the per-group launches, whose key splits fill the
-    // chip (a group there may be split into more chunks than the video has groups), and so do decode-shaped groups.
+    // Three groups or more whose attention fills the chip at least once, and every video on the scalar kernel (never
+    // split), go in runs of groups. us against the loop at 7B / 72B heads, rho 0.3: 12 groups of 512 tokens 391 -> 131,
+    // 6 of 1024 258 -> 147, 8 of 2048 806 -> 751; 12 of 512 350 -> 298, 8 of 1024 551 -> 493. Two groups gain nothing
+    // (4096 + 512 tokens 171 -> 181): the loop splits the second one's last round. Below one round it keeps the key
+    // splits that fill the chip, and decode-shaped groups their own kernel.
     VideoRun r{};
     r.L = L, r.rule = rule, r.q = (const char*)q, r.k = (const char*)k, r.v = (const char*)v, r.q_win = q_win;
     r.n_window = n_window, r.out = (char*)out, r.n_g = (int32_t)max_group;
@@ -619,7 +621,7 @@ qp_status qp_prefill_video(const qp_layout* L, int32_t n_frames, int32_t tokens_
     const int which = g_attend_kernel.load(std::memory_order_relaxed);
     r.mfma = which != QP_ATTEND_SCALAR && qp::attend_mfma_supported(probe, L->dtype);
     const int64_t wgs = (int64_t)r.n_groups * qp::attend_mfma_row_blocks(r.n_g, L->n_q_heads, L->n_kv_heads) * L->n_kv_heads;
-    const bool runs = r.mfma ? wgs >= 2 * qp::device_cu_count() && wgs < (1 << 28) &&
+    const bool runs = r.mfma ? r.n_groups > 2 && wgs >= qp::device_cu_count() && wgs < (1 << 28) &&
                                    !(which == QP_ATTEND_AUTO && qp::attend_decode_applies(probe, L->dtype))
                              : cache->format == QP_CACHE_SAME;
     if (r.n_groups > 1 && runs) return prefill_in_runs(r, cache, workspace, workspace_bytes, (hipStream_t)hip_stream);

@@ -691,6 +691,7 @@ RUNS = [  # layout (H_q, H_kv, d, dtype), frames, tokens per frame, frames per g
     ((28, 4, 128, "bf16"), 321, 128, 16, 0.1, "window_attn", 1170, False, 0),   # more window scratch than one run holds
     ((28, 4, 128, "bf16"), 65, 65, 65, 0.5, "window_logit", 8, False, 3),       # one group: the per-group loop
     ((12, 3, 128, "bf16"), 250, 64, 1, 0.5, "window_logit", 9, False, 5),       # many small groups, heads that do not divide the XCDs
+    ((28, 4, 128, "bf16"), 21, 129, 6, 0.3, "value_norm", 0, False, 0),         # just over one round of workgroups
     ((4, 2, 64, "f32"), 9, 16, 2, 0.5, "window_attn", 16, False, 0),            # scalar kernel
     ((4, 2, 64, "bf16"), 7, 13, 3, 0.4, "key_norm_small", 0, False, 9),
 ]
@@ -731,6 +732,30 @@ def test_prefill_video_in_runs_equals_the_step_calls(layout, frames, tpf, group,
     assert torch.equal(caches[0].k.float(), caches[1].k.float()) and torch.equal(caches[0].v.float(), caches[1].v.float())
     if frames > group:
         assert torch.equal(outs[0], outs[1])
+
+
+@pytest.mark.parametrize("frames,group", [(60, 16), (40, 4)])   # group 0 beside the scoring, and inside the run
+def test_prefill_video_in_runs_replays_from_a_hip_graph(frames, group):
+    w = scaled(CONFIGS["cfg2_7b_32k"], n_frames=frames, tokens_per_frame=128, group_frames=group)
+    q, k, v, qw = make_layer(w, device=DEV, sharp=True)
+    want, cache = _run_prefill(w, q, k, v, qw, "window_attn")                 # eager: also creates the library's streams
+    want = (want.clone(), cache.k.clone(), cache.v.clone(), cache.pos.clone())
+    layout = B.make_layout(w.n_q_heads, w.n_kv_heads, w.head_dim, w.dtype)
+    ws = B.make_workspace(layout, w.group_tokens, w.n_window)
+    out = torch.empty_like(q)
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        cache.reset()
+        B.prefill_video(layout, w.n_frames, w.tokens_per_frame, w.group_frames, w.retention, "window_attn", q, k, v, qw,
+                        cache, out, ws)
+    for replay in range(3):
+        for t in (out, cache.k, cache.v):
+            t.zero_()
+        cache.pos.fill_(-1)
+        graph.replay()
+        torch.cuda.synchronize()
+        for a, b in zip(want, (out, cache.k, cache.v, cache.pos)):
+            assert torch.equal(a, b), f"replay {replay}"
 
 
 @pytest.mark.parametrize("group_frames", [5, 1])
