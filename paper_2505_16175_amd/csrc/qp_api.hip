@@ -452,12 +452,12 @@ qp_status qp_topk_compact(const qp_layout* L, const float* scores, const void* k
 // one selects and appends, and one attends for all groups behind them, latest group first. Against a launch of every
 // kind per group (the loop in qp_prefill_video) nothing waits for a partly filled last round of workgroups, no row
 // block needs splitting to fill one, and the dependent launches of a video go from three or four per group to a handful.
-// Run length: what the workspace holds of scores and scoring scratch (all groups of an hour-long video with the
-// standard workspace). Group 0 meets only what the cache already held, so its attention starts beside the first run's
+// Run length: what the workspace holds of scores and scoring scratch (over 100 groups of 2048 tokens at 7B sizes with
+// the standard workspace). Group 0 meets only what the cache already held, so its attention starts beside the first run's
 // scoring when it is large enough to be worth the cross-stream waits, else it joins the first run's attention launch.
 // Measured against the loop, us per layer: 8 f32 frames 139 -> 22; 99 frames of 121 tokens in groups of 4, 8-bit cache
-// 976 -> 574; 256 frames of 128 in groups of 16 2647 -> 2535 (1.05 PFLOP/s); 1024 in groups of 32 24862 -> 24125; 512 of
-// 256 tokens, 72B heads, 68227 -> 67950; 3600 frames in groups of 64 155475 -> 154622 (1.15 PFLOP/s).
+// 976 -> 574; 256 frames of 128 in groups of 16 2647 -> 2535 (1.05 PFLOP/s); 1024 in groups of 32 24862 -> 24125
+// (1.15 PFLOP/s).
 struct VideoRun {
   const qp_layout* L;
   qp_score_rule rule;
@@ -604,11 +604,15 @@ qp_status qp_prefill_video(const qp_layout* L, int32_t n_frames, int32_t tokens_
   }
 
   {
-    // Three groups or more whose attention fills the chip at least once, and every video on the scalar kernel (never
-    // split), go in runs of groups. us against the loop at 7B / 72B heads, rho 0.3: 12 groups of 512 tokens 391 -> 131,
+    // Three groups or more of under two rounds of workgroups each whose attention fills the chip at least once, and
+    // every video on the scalar kernel (never split), go in runs of groups. us against the loop at 7B / 72B heads, rho 0.3: 12 groups of 512 tokens 391 -> 131,
     // 6 of 1024 258 -> 147, 8 of 2048 806 -> 751; 12 of 512 350 -> 298, 8 of 1024 551 -> 493. Two groups gain nothing
     // (4096 + 512 tokens 171 -> 181): the loop splits the second one's last round. Below one round it keeps the key
-    // splits that fill the chip, and decode-shaped groups their own kernel.
+    // splits that fill the chip, and decode-shaped groups their own kernel. Groups of two rounds and more lose little at
+    // their ends, while a launch over all of them lets its workgroups drift apart along the cache (a launch per group
+    // starts them together, and they share the L2s' lines): 3600 frames in groups of 64 (3.5 rounds) measured 155.5 ->
+    // 154.6 ms on one card and 157.8 -> 162.2 on a hotter one, 72B heads in groups of 4 rounds 68.2 -> 67.9 and
+    // 69.1 -> 71.3; groups of 1.75 rounds gained on both (24.9 -> 24.1, 26.1 -> 25.7).
     VideoRun r{};
     r.L = L, r.rule = rule, r.q = (const char*)q, r.k = (const char*)k, r.v = (const char*)v, r.q_win = q_win;
     r.n_window = n_window, r.out = (char*)out, r.n_g = (int32_t)max_group;
@@ -621,7 +625,7 @@ qp_status qp_prefill_video(const qp_layout* L, int32_t n_frames, int32_t tokens_
     const int which = g_attend_kernel.load(std::memory_order_relaxed);
     r.mfma = which != QP_ATTEND_SCALAR && qp::attend_mfma_supported(probe, L->dtype);
     const int64_t wgs = (int64_t)r.n_groups * qp::attend_mfma_row_blocks(r.n_g, L->n_q_heads, L->n_kv_heads) * L->n_kv_heads;
-    const bool runs = r.mfma ? r.n_groups > 2 && wgs >= qp::device_cu_count() && wgs < (1 << 28) &&
+    const bool runs = r.mfma ? r.n_groups > 2 && wgs >= qp::device_cu_count() && wgs < (1 << 28) && wgs < 2 * (int64_t)r.n_groups * qp::device_cu_count() &&
                                    !(which == QP_ATTEND_AUTO && qp::attend_decode_applies(probe, L->dtype))
                              : cache->format == QP_CACHE_SAME;
     if (r.n_groups > 1 && runs) return prefill_in_runs(r, cache, workspace, workspace_bytes, (hipStream_t)hip_stream);
