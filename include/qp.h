@@ -229,7 +229,7 @@ qp_status qp_topk_compact(const qp_layout* layout, const float* scores, const vo
  * default priority) for scoring / compaction and for part of the attention. They are forked from hip_stream at entry
  * and joined back into it before the call returns: work the caller enqueues on hip_stream afterwards is ordered after
  * all of this call's work. The call only enqueues (it never waits for the GPU); calls from several host threads
- * are serialised while they enqueue on those streams.
+ * are serialised while they enqueue, so that calls on one stream may share a workspace.
  * Failure after the first launch (QP_ERR_HIP from a launch or a stream call): nothing further is enqueued, the
  * library's streams are still joined back into hip_stream, the groups already enqueued run to completion, and
  * cache->len is restored to its value at entry (rows beyond it, and `out`, then hold unspecified data). */

@@ -487,13 +487,13 @@ static qp_status prefill_in_runs(const VideoRun& r, qp_cache* cache, void* works
   float* scores = (float*)(ws + shared_b);
   void* scratch_ws = base_rule == QP_SCORE_WINDOW_LOGIT ? (void*)ws : (void*)(ws + shared_b + per_run * score_b);
 
+  // Held without side streams too: calls from several threads on one stream may share a workspace, and stay apart in it
+  // only because each enqueues all of its steps before the next one's first.
+  std::lock_guard<std::mutex> lock(g_prefill_mutex);
   SideStreams* side = nullptr;
-  std::unique_lock<std::mutex> lock;
   // half a chip of workgroups: below, group 0's attention is shorter than the waits between streams
-  if (r.mfma && 2 * qp::attend_mfma_row_blocks(r.n_g, L->n_q_heads, L->n_kv_heads) * L->n_kv_heads >= qp::device_cu_count()) {
-    lock = std::unique_lock<std::mutex>(g_prefill_mutex);
+  if (r.mfma && 2 * qp::attend_mfma_row_blocks(r.n_g, L->n_q_heads, L->n_kv_heads) * L->n_kv_heads >= qp::device_cu_count())
     side = side_streams();
-  }
   const int32_t len_at_entry = cache->len;
   hipStream_t score_stream = side ? side->score : main_stream;
   qp_status st = QP_OK;

@@ -758,6 +758,59 @@ def test_prefill_video_in_runs_replays_from_a_hip_graph(frames, group):
             assert torch.equal(a, b), f"replay {replay}"
 
 
+@pytest.mark.parametrize("name,frames,tpf,group,rule", [
+    ("cfg1_tiny_f32", 9, 16, 2, "window_attn"),          # a run of groups without side streams
+    ("cfg2_7b_32k", 40, 128, 4, "window_attn"),          # ... on the MFMA kernel
+    ("cfg2_7b_32k", 24, 64, 4, "key_norm_small"),        # the per-group loop
+])
+def test_threads_share_a_stream_and_a_workspace(name, frames, tpf, group, rule):
+    """Calls are serialised while they enqueue: several threads that prefill their own videos on one stream through one
+    workspace each get what they get alone."""
+    import threading
+    n_threads, rounds = 4, 40
+    w = scaled(CONFIGS[name], n_frames=frames, tokens_per_frame=tpf, group_frames=group)
+    layout = B.make_layout(w.n_q_heads, w.n_kv_heads, w.head_dim, w.dtype)
+    cap = B.cache_capacity(frames, tpf, group, w.retention)
+    ws = B.make_workspace(layout, w.group_tokens, w.n_window)
+    vids = [make_layer(w, layer=i, device=DEV, sharp=True) for i in range(n_threads)]
+    caches = [B.Cache(layout, cap) for _ in vids]
+    outs = [torch.empty_like(v[0]) for v in vids]
+
+    def run(i):
+        q, k, v, qw = vids[i]
+        caches[i].reset()
+        B.prefill_video(layout, frames, tpf, group, w.retention, rule, q, k, v, qw, caches[i], outs[i], ws)
+
+    want = []
+    for i in range(n_threads):
+        run(i)
+        torch.cuda.synchronize()
+        want.append([t.clone() for t in (outs[i], caches[i].k, caches[i].v, caches[i].pos)])
+    failed = []
+
+    def worker(i):
+        try:
+            for _ in range(rounds):
+                run(i)
+        except Exception as e:                                # noqa: BLE001 - reported by the main thread
+            failed.append(e)
+
+    for _ in range(3):
+        for i in range(n_threads):
+            outs[i].zero_(), caches[i].k.zero_(), caches[i].v.zero_(), caches[i].pos.fill_(-1)
+        torch.cuda.synchronize()
+        threads = [threading.Thread(target=worker, args=(i,)) for i in range(n_threads)]
+        for t in threads:
+            t.start()
+        for t in threads:
+            t.join()
+        torch.cuda.synchronize()
+        assert not failed, failed
+        for i in range(n_threads):
+            for a, b in zip(want[i], (outs[i], caches[i].k, caches[i].v, caches[i].pos)):
+                assert torch.equal(a, b), f"thread {i}"
+
+
 @pytest.mark.parametrize("group_frames", [5, 1])
 def test_prefill_video_replays_from_a_hip_graph(group_frames):
     """A caller may capture qp_prefill_video (its forked library streams included) into a HIP graph: every replay,
