@@ -600,6 +600,7 @@ qp_status qp_prefill_video(const qp_layout* L, int32_t n_frames, int32_t tokens_
     probe.h_kv = L->n_kv_heads;
     probe.d = L->head_dim;
     probe.n_g = (int)max_group;
+    probe.cap = cache->capacity;
     if (!qp::attend_mfma_supported(probe, L->dtype)) return QP_ERR_UNSUPPORTED;
   }
 

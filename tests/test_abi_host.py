@@ -54,6 +54,22 @@ def test_prefill_video_reports_a_failed_launch_and_leaves_the_cache_length():
     assert st == B.QP_ERR_HIP and c.len == 5 and B.last_hip_error() != 0
 
 
+@pytest.mark.parametrize("frames", [2, 8])                                    # one group, and four
+def test_forced_mfma_kernel_refuses_a_cache_beyond_its_offsets(frames):
+    """A cache of 2^23 entries (256 bytes each) is past the kernel's 32-bit offsets: a pinned kernel is not replaced by
+    another one, the call is refused before its first launch."""
+    L = B.make_layout(8, 2, 128, "bf16")
+    fake = 1 << 20
+    B.select_attend_kernel(B.QP_ATTEND_MFMA)
+    try:
+        c = B.qp_cache(fake, fake, fake, 1 << 23, 5)
+        st = B.lib().qp_prefill_video(ctypes.byref(L), frames, 16, 2, 0.5, 0, fake, fake, fake, None, 0, ctypes.byref(c),
+                                      fake, fake, B.workspace_bytes(L, 32, 0), None)
+        assert st == B.QP_ERR_UNSUPPORTED and c.len == 5
+    finally:
+        B.select_attend_kernel(B.QP_ATTEND_AUTO)
+
+
 def test_debug_fail_after_arguments():
     assert B.lib().qp_debug_fail_after(-1) == B.QP_ERR_INVALID_ARG
     assert B.lib().qp_debug_fail_after(0) == B.QP_OK
