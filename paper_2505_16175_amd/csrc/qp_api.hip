@@ -466,23 +466,69 @@ struct VideoRun {
   int32_t n_window, n_g, n_last, n_groups, keep, keep_last;
   char* out;
   bool mfma;
+  // workspace: [rule's shared scratch][scores of a run][window scratch of a run] ... [key-split scratch of group 0]
+  size_t score_b, win_b, shared_b, split_at;
+  int32_t per_run;  // groups per run
 };
 
-static qp_status prefill_in_runs(const VideoRun& r, qp_cache* cache, void* workspace, size_t workspace_bytes, hipStream_t main_stream) {
+static void lay_out_runs(VideoRun& r, size_t workspace_bytes) {
+  const qp_layout* L = r.L;
+  const int base_rule = (int)r.rule & ~QP_SCORE_SHARED_HEADS;
+  r.score_b = scores_bytes(L, r.n_g);
+  r.win_b = r.keep < r.n_g && base_rule == QP_SCORE_WINDOW_ATTN
+                ? qp::window_workspace_bytes(L->n_q_heads, L->n_kv_heads, r.n_g, r.n_window) : 0;
+  r.shared_b = base_rule == QP_SCORE_WINDOW_LOGIT ? qp::window_logit_workspace_bytes(L->n_kv_heads, L->head_dim) : 0;
+  r.split_at = (workspace_bytes - kAttendSplitBytes) / 256 * 256;
+  size_t fit = (r.split_at - r.shared_b) / (r.score_b + r.win_b);
+  if (fit > (size_t)qp::QP_MAX_RUN_GROUPS) fit = qp::QP_MAX_RUN_GROUPS;
+  r.per_run = r.n_groups < (int32_t)fit ? r.n_groups : (int32_t)fit;
+}
+
+// Whether a video on the MFMA kernel is served in runs of groups: from three groups on, where a run's workgroups fill the
+// chip at least once (below, the loop has the key splits that fill it), each group is under two rounds, and the loop is
+// not faster. us against the loop at 7B / 72B heads, rho 0.3: 12 groups of 512 tokens 391 -> 131, 6 of 1024 258 -> 147,
+// 8 of 2048 806 -> 751; 12 of 512 350 -> 298, 8 of 1024 551 -> 493. Two groups gain nothing (4096 + 512 tokens 171 ->
+// 181): the loop splits the second one's last round. Groups of two rounds and more lose little at their ends, while a
+// launch over all of them lets its workgroups drift apart along the cache (a launch per group starts them together, and
+// they share the L2s' lines): 3600 frames in groups of 64 (3.5 rounds) 155.5 -> 154.6 ms on one card and 157.8 -> 162.2
+// on a hotter one, 72B heads in groups of 4 rounds 68.2 -> 67.9 and 69.1 -> 71.3; groups of 1.75 rounds gained on both
+// (24.9 -> 24.1, 26.1 -> 25.7).
+// A run is not split, so its partly filled last round takes as long as its row blocks do, and entries from before the
+// call make all of them long: 5 groups of 512 tokens are 1.09 rounds, and over 80,000 entries two took 4707 us against
+// the loop's 2985, over 20,000 1134 against 798, over 4,000 264 against 248, over none 55 against 172. So both sides are
+// estimated, in keys that a row block walks (28 us per 1000, 256 rows): the run as its work spread over the chip plus
+// what the last round leaves idle for as long as the shortest row blocks last, plus 25 us; the loop as its groups' key
+// splits (or whole rounds), plus 20 us per group for its launches. Within 5 % the loop stays. Of 40 measured combinations
+// of 3..8 groups of under a round and 0..80,000 entries this picks the faster side in 35; in four of the others the sides
+// differ by 0-9 %, and 3 groups of 1100 tokens over 4,000 entries stay with the loop (356 us, 290 as a run).
+// From one round per group on the loop's groups fill their last rounds by splits and by the next group's start: runs gain
+// 1-8 % from six groups on, as much as they lose over three (3 groups of 3000 tokens 364 -> 375, 3 of 2400 over 1,500
+// entries 408 -> 436), and what a last round may leave idle is held to 10 us per group.
+static bool runs_pay(const VideoRun& r, int32_t cache_len) {
+  const qp_layout* L = r.L;
+  const double cus = qp::device_cu_count();
+  const double group_wgs = (double)qp::attend_mfma_row_blocks(r.n_g, L->n_q_heads, L->n_kv_heads) * L->n_kv_heads;
+  const double wgs = (r.n_groups - 1) * group_wgs + (double)qp::attend_mfma_row_blocks(r.n_last, L->n_q_heads, L->n_kv_heads) * L->n_kv_heads;
+  if (r.n_groups < 3 || r.per_run * group_wgs < cus || group_wgs >= 2 * cus || wgs >= (1 << 28)) return false;
+  const double idle_keys = (ceil(wgs / cus) - wgs / cus) * (cache_len + 0.5 * r.n_g);
+  if (group_wgs >= cus) return r.n_groups >= 6 && idle_keys <= 350. * r.n_groups;
+  qp::AttendArgs mid{};  // a group in the middle of the video
+  mid.n_g = r.n_g, mid.h_q = L->n_q_heads, mid.h_kv = L->n_kv_heads, mid.d = L->head_dim;
+  mid.c = mid.cap = cache_len + (int)((int64_t)(r.n_groups - 1) * r.keep / 2);
+  const qp::AttendPlan p = qp::plan_attend_mfma(mid, kAttendSplitBytes);
+  const double keys = mid.c + 0.5 * r.n_g, rounds = p.n_split > 1 ? 1. / p.n_split : 1.;
+  const double run = r.n_groups * keys * group_wgs / cus + idle_keys + 900., loop = r.n_groups * (keys * rounds + 700.);
+  return 1.05 * run < loop;
+}
+
+static qp_status prefill_in_runs(const VideoRun& r, qp_cache* cache, void* workspace, hipStream_t main_stream) {
   const qp_layout* L = r.L;
   const size_t esz = L->dtype == QP_F32 ? 4 : 2;
   const size_t q_tok = (size_t)L->n_q_heads * L->head_dim * esz, kv_tok = (size_t)L->n_kv_heads * L->head_dim * esz;
   const int base_rule = (int)r.rule & ~QP_SCORE_SHARED_HEADS;
   const bool scored = r.keep < r.n_g;  // else every group keeps everything, the shorter last one included
-  const size_t score_b = scores_bytes(L, r.n_g);
-  const size_t win_b = scored && base_rule == QP_SCORE_WINDOW_ATTN
-                           ? qp::window_workspace_bytes(L->n_q_heads, L->n_kv_heads, r.n_g, r.n_window) : 0;
-  const size_t shared_b = base_rule == QP_SCORE_WINDOW_LOGIT ? qp::window_logit_workspace_bytes(L->n_kv_heads, L->head_dim) : 0;
-  // workspace: [rule's shared scratch][scores of a run][window scratch of a run] ... [key-split scratch of group 0]
-  const size_t split_at = (workspace_bytes - kAttendSplitBytes) / 256 * 256;
-  size_t fit = (split_at - shared_b) / (score_b + win_b);
-  if (fit > (size_t)qp::QP_MAX_RUN_GROUPS) fit = qp::QP_MAX_RUN_GROUPS;
-  const int32_t per_run = r.n_groups < (int32_t)fit ? r.n_groups : (int32_t)fit;
+  const size_t score_b = r.score_b, win_b = r.win_b, shared_b = r.shared_b, split_at = r.split_at;
+  const int32_t per_run = r.per_run;
   char* ws = (char*)workspace;
   float* scores = (float*)(ws + shared_b);
   void* scratch_ws = base_rule == QP_SCORE_WINDOW_LOGIT ? (void*)ws : (void*)(ws + shared_b + per_run * score_b);
@@ -605,15 +651,8 @@ qp_status qp_prefill_video(const qp_layout* L, int32_t n_frames, int32_t tokens_
   }
 
   {
-    // Three groups or more of under two rounds of workgroups each whose attention fills the chip at least once, and
-    // every video on the scalar kernel (never split), go in runs of groups. us against the loop at 7B / 72B heads, rho 0.3: 12 groups of 512 tokens 391 -> 131,
-    // 6 of 1024 258 -> 147, 8 of 2048 806 -> 751; 12 of 512 350 -> 298, 8 of 1024 551 -> 493. Two groups gain nothing
-    // (4096 + 512 tokens 171 -> 181): the loop splits the second one's last round. Below one round it keeps the key
-    // splits that fill the chip, and decode-shaped groups their own kernel. Groups of two rounds and more lose little at
-    // their ends, while a launch over all of them lets its workgroups drift apart along the cache (a launch per group
-    // starts them together, and they share the L2s' lines): 3600 frames in groups of 64 (3.5 rounds) measured 155.5 ->
-    // 154.6 ms on one card and 157.8 -> 162.2 on a hotter one, 72B heads in groups of 4 rounds 68.2 -> 67.9 and
-    // 69.1 -> 71.3; groups of 1.75 rounds gained on both (24.9 -> 24.1, 26.1 -> 25.7).
+    // Videos of two groups or more on the scalar kernel (never split) go in runs of groups, and where it is faster those
+    // on the MFMA kernel; decode-shaped groups keep their own kernel.
     VideoRun r{};
     r.L = L, r.rule = rule, r.q = (const char*)q, r.k = (const char*)k, r.v = (const char*)v, r.q_win = q_win;
     r.n_window = n_window, r.out = (char*)out, r.n_g = (int32_t)max_group;
@@ -625,11 +664,10 @@ qp_status qp_prefill_video(const qp_layout* L, int32_t n_frames, int32_t tokens_
     probe.c = probe.cap = cache->capacity;
     const int which = g_attend_kernel.load(std::memory_order_relaxed);
     r.mfma = which != QP_ATTEND_SCALAR && qp::attend_mfma_supported(probe, L->dtype);
-    const int64_t wgs = (int64_t)r.n_groups * qp::attend_mfma_row_blocks(r.n_g, L->n_q_heads, L->n_kv_heads) * L->n_kv_heads;
-    const bool runs = r.mfma ? r.n_groups > 2 && wgs >= qp::device_cu_count() && wgs < (1 << 28) && wgs < 2 * (int64_t)r.n_groups * qp::device_cu_count() &&
-                                   !(which == QP_ATTEND_AUTO && qp::attend_decode_applies(probe, L->dtype))
+    lay_out_runs(r, workspace_bytes);
+    const bool runs = r.mfma ? !(which == QP_ATTEND_AUTO && qp::attend_decode_applies(probe, L->dtype)) && runs_pay(r, cache->len)
                              : cache->format == QP_CACHE_SAME;
-    if (r.n_groups > 1 && runs) return prefill_in_runs(r, cache, workspace, workspace_bytes, (hipStream_t)hip_stream);
+    if (r.n_groups > 1 && runs) return prefill_in_runs(r, cache, workspace, (hipStream_t)hip_stream);
   }
 
   const size_t esz = L->dtype == QP_F32 ? 4 : 2;

@@ -734,6 +734,41 @@ def test_prefill_video_in_runs_equals_the_step_calls(layout, frames, tpf, group,
         assert torch.equal(outs[0], outs[1])
 
 
+@pytest.mark.parametrize("h_q,h_kv,groups,n_g,before", [
+    (28, 4, 5, 512, 20000), (64, 8, 5, 256, 20000),       # 1.09 and 1.25 rounds of workgroups, nearly all equally long
+    (28, 4, 3, 1100, 20000), (28, 4, 3, 2400, 20000),     # 1.45 rounds, and 1.03 per group
+])
+def test_prefill_video_over_a_long_cache_keeps_the_key_splits(h_q, h_kv, groups, n_g, before):
+    """A short video over many entries from before the call: one launch for all groups would spend a round of workgroups
+    on what exceeds the last whole round (up to 1.6 times the time), so the groups take the split launches of
+    qp_group_attend and equal them bit for bit."""
+    gen = torch.Generator(device=DEV).manual_seed(12)
+    mk = lambda *s: torch.randn(*s, generator=gen, device=DEV).to(torch.bfloat16)
+    n, rho = groups * n_g, 0.3
+    q, k, v = mk(n, h_q, 128), mk(n, h_kv, 128), mk(n, h_kv, 128)
+    L = B.make_layout(h_q, h_kv, 128, "bf16")
+    ws = B.make_workspace(L, n_g, 0)
+    split = torch.empty(128 << 20, dtype=torch.uint8, device=DEV)
+    caches = [B.Cache(L, before + B.cache_capacity(groups, n_g, 1, rho)) for _ in range(2)]
+    old = mk(h_kv, before, 128), mk(h_kv, before, 128)
+    for c in caches:
+        c.k[:, :before].copy_(old[0])
+        c.v[:, :before].copy_(old[1])
+        c.c.len = before
+    outs = [torch.full_like(q, float("nan")) for _ in range(2)]
+    B.prefill_video(L, groups, n_g, 1, rho, "key_norm_small", q, k, v, None, caches[0], outs[0], ws)
+    for i in range(groups):
+        sl = slice(i * n_g, (i + 1) * n_g)
+        scores = torch.empty(h_kv, n_g, device=DEV)
+        assert B.attend_plan(L, n_g, caches[1].len, 128 << 20)["key_chunks"] > 1
+        B.group_attend(L, q[sl], k[sl], v[sl], caches[1], outs[1][sl], None, split)
+        B.score_kv(L, "key_norm_small", k[sl], v[sl], None, scores, ws)
+        B.topk_compact(L, scores, k[sl], v[sl], B.keep_count(n_g, rho), i * n_g, caches[1], None, ws)
+    torch.cuda.synchronize()
+    assert torch.equal(outs[0], outs[1])
+    assert torch.equal(caches[0].pos, caches[1].pos) and torch.equal(caches[0].k, caches[1].k)
+
+
 @pytest.mark.parametrize("frames,group", [(60, 16), (40, 4)])   # group 0 beside the scoring, and inside the run
 def test_prefill_video_in_runs_replays_from_a_hip_graph(frames, group):
     w = scaled(CONFIGS["cfg2_7b_32k"], n_frames=frames, tokens_per_frame=128, group_frames=group)
