@@ -250,8 +250,7 @@ qp_status qp_prefill_video(const qp_layout* layout, int32_t n_frames, int32_t to
  * rounds, so that their chunks fill the compute units evenly), whether rows are dealt to workgroups as
  * mirrored early/late half blocks (launches of at most one workgroup per compute unit) or consecutively,
  * and how much of the offered workspace the split would use.
- * For the scalar kernel only `kernel` and key_chunks = 1 are meaningful. The decode kernel takes up to twice the
- * chunks reported here over an 8-bit cache. */
+ * For the scalar kernel only `kernel` and key_chunks = 1 are meaningful. */
 typedef struct {
   int32_t kernel;          /* QP_ATTEND_SCALAR, QP_ATTEND_MFMA or QP_ATTEND_MFMA_DECODE */
   int32_t workgroups;      /* of the first launch, all chunks and idle padding workgroups included */

@@ -4,7 +4,8 @@
 //
 // The cache's K and V are read exactly once and nothing is reused, so the kernel is shaped for HBM, not for the
 // matrix pipe: no workgroup-shared tiles and no barrier in the loop. Keys are cut into blocks of 32; a workgroup
-// takes a run of blocks and deals them to its 4 wavefronts, each of which works alone on its own 32 KB of LDS:
+// takes a run of blocks and deals them to its wavefronts (4; 8 over an 8-bit cache), each of which works alone on its
+// own 32 KB of LDS:
 //   K, V block  global -> LDS with direct loads (XOR-swizzled 16-byte chunks, as in the large kernel), two buffers
 //               each, refilled half by half: K two blocks ahead as soon as the QK product has its fragments, V two
 //               blocks ahead after the PV product. All loads of the loop are
@@ -20,7 +21,12 @@
 // registers one block ahead with ordinary loads (8 bytes per lane, key and tensor: half the bytes of a bf16 block),
 // widens it exactly to bf16 and writes it to its own LDS buffer in the same swizzled layout, so that the products
 // and the softmax are the same code; the group's own block is bf16 and still loaded directly. One LDS buffer per
-// wavefront then suffices, and two workgroups share a CU.
+// wavefront then suffices, which leaves room for 8 wavefronts: an 8-bit block is a longer chain for its wavefront (widen,
+// write, read back, two products, softmax: ~2 us alone on a SIMD) over half the bytes, so two of them share a SIMD. us
+// with 4 wavefronts per CU / two workgroups of 4 and twice the chunks / one of 8, 72B heads, one token over 32,768
+// entries again and again (67 MB stay in the last-level cache) 23.1 / 20.6 / 19.3; caches in turn, more than that cache
+// holds: over 46,125 entries 30.9 / 25.2 / 25.1, over 120,000 56.5 / 44.6 / 43.7; 7B heads, 4 tokens over 20,000
+// 17.9 / 21.3 / 17.5 (twice the chunks there cost more in partial sums and their merge than they gained).
 #include "qp_internal.h"
 
 #include <algorithm>
@@ -37,12 +43,14 @@ typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int DC_D = 128;
 constexpr int DC_BK = 32;                  // keys per block
-constexpr int DC_NW = 4;                   // wavefronts per workgroup
+constexpr int DC_NW = 4;                   // wavefronts per workgroup; the least blocks of a chunk
+constexpr int dc_waves(bool f8) { return f8 ? 2 * DC_NW : DC_NW; }
 constexpr int DC_TILE = DC_BK * DC_D * 2;  // bytes of one K or V block in LDS
 constexpr int DC_BUF = 2 * DC_TILE;        // K block + V block
 // LDS per wavefront: two buffers, one for 8-bit caches (the block ahead waits in registers); the first 16 KB are reused
 // for the final merge
 constexpr int dc_wave_lds(bool f8) { return f8 ? DC_BUF : 2 * DC_BUF; }
+constexpr int dc_lds(bool f8) { return dc_waves(f8) * dc_wave_lds(f8); }  // 128 KB either way
 constexpr int DC_MAX_ROWS = 32;
 constexpr float DC_RESCALE_LOG2 = 8.f;
 
@@ -122,9 +130,10 @@ __device__ __forceinline__ void decode_pv(const unsigned char* vt, const int (&v
 }
 
 template <bool F8>
-__global__ __launch_bounds__(DC_NW * 64, F8 ? 2 : 1) void attend_decode_kernel(AttendArgs a) {
+__global__ __launch_bounds__(dc_waves(F8) * 64) void attend_decode_kernel(AttendArgs a) {
+  constexpr int NW = dc_waves(F8);
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-  __shared__ float sm_m[DC_NW][DC_MAX_ROWS], sm_l[DC_NW][DC_MAX_ROWS];
+  __shared__ float sm_m[NW][DC_MAX_ROWS], sm_l[NW][DC_MAX_ROWS];
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // wave-uniform for the compiler too: block choice, pointers
   const int l32 = lane & 31, g = lane >> 5;
@@ -219,7 +228,7 @@ __global__ __launch_bounds__(DC_NW * 64, F8 ? 2 : 1) void attend_decode_kernel(A
     unsigned char* buf = vbuf;  // one buffer: a wavefront's LDS operations stay in order
     if (b < b_end && b < n_cb) load_block(b);
     while (b < b_end) {
-      const bool has1 = b + DC_NW < b_end;
+      const bool has1 = b + NW < b_end;
       if (b < n_cb) {
         // this block's pieces have arrived (requested a block ago): widen them into the buffer, then request the next
 #pragma unroll
@@ -227,7 +236,7 @@ __global__ __launch_bounds__(DC_NW * 64, F8 ? 2 : 1) void attend_decode_kernel(A
           *(u32x4*)(buf + i * 1024 + lane * 16) = widen8(rk[i]);
           *(u32x4*)(buf + DC_TILE + i * 1024 + lane * 16) = widen8(rv[i]);
         }
-        if (has1 && b + DC_NW < n_cb) load_block(b + DC_NW);
+        if (has1 && b + NW < n_cb) load_block(b + NW);
       } else {
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // the direct loads are not ordered behind the last block's reads
         QP_DC_REQUEST(b, 0, false)  // the group's own keys and values: bf16, loaded directly
@@ -238,7 +247,7 @@ __global__ __launch_bounds__(DC_NW * 64, F8 ? 2 : 1) void attend_decode_kernel(A
       decode_qk_softmax(buf, k_addr, qf, b == n_cb, b == n_cb ? a.n_g : min(DC_BK, a.c - b * DC_BK), t_lane, g, c2, lazy,
                         m_run, l_run, o, pf);
       decode_pv(buf + DC_TILE, v_addr, pf, o);
-      b += DC_NW;
+      b += NW;
     }
   } else {
     // The Q fragments (ordinary loads) must have arrived before the first request: from here on only untracked
@@ -252,13 +261,13 @@ __global__ __launch_bounds__(DC_NW * 64, F8 ? 2 : 1) void attend_decode_kernel(A
     if (b < b_end) {
       QP_DC_REQUEST(b, 0, false)
       QP_DC_REQUEST(b, 0, true)
-      if (b + DC_NW < b_end) {
-        QP_DC_REQUEST(b + DC_NW, 1, false)
-        QP_DC_REQUEST(b + DC_NW, 1, true)
+      if (b + NW < b_end) {
+        QP_DC_REQUEST(b + NW, 1, false)
+        QP_DC_REQUEST(b + NW, 1, true)
       }
     }
     while (b < b_end) {
-      const bool has1 = b + DC_NW < b_end, has2 = b + 2 * DC_NW < b_end;
+      const bool has1 = b + NW < b_end, has2 = b + 2 * NW < b_end;
       unsigned char* buf = vbuf + cur * DC_BUF;
       // K(i) has landed: V(i) and block i+1 (16 requests) may still be in flight
       if (has1) wait_vmcnt<24>();
@@ -266,14 +275,14 @@ __global__ __launch_bounds__(DC_NW * 64, F8 ? 2 : 1) void attend_decode_kernel(A
       bf16x8 pf[2];
       decode_qk_softmax(buf, k_addr, qf, b == n_cb, b == n_cb ? a.n_g : min(DC_BK, a.c - b * DC_BK), t_lane, g, c2, lazy,
                         m_run, l_run, o, pf);
-      if (has2) QP_DC_REQUEST(b + 2 * DC_NW, cur, false)  // the K fragments of block i are in registers
+      if (has2) QP_DC_REQUEST(b + 2 * NW, cur, false)  // the K fragments of block i are in registers
       // V(i) has landed: block i+1 and K(i+2) may still be in flight
       if (has2) wait_vmcnt<24>();
       else if (has1) wait_vmcnt<16>();
       else wait_vmcnt<0>();
       decode_pv(buf + DC_TILE, v_addr, pf, o);
-      if (has2) QP_DC_REQUEST(b + 2 * DC_NW, cur, true)
-      b += DC_NW;
+      if (has2) QP_DC_REQUEST(b + 2 * NW, cur, true)
+      b += NW;
       cur ^= 1;
     }
   }
@@ -299,16 +308,16 @@ __global__ __launch_bounds__(DC_NW * 64, F8 ? 2 : 1) void attend_decode_kernel(A
   __syncthreads();
   const int d = tid & (DC_D - 1);
   const size_t total = (size_t)a.h_kv * n_rows;
-  for (int row = tid >> 7; row < n_rows; row += (DC_NW * 64) >> 7) {
-    float mw[DC_NW], big = -INFINITY;
+  for (int row = tid >> 7; row < n_rows; row += (NW * 64) >> 7) {
+    float mw[NW], big = -INFINITY;
 #pragma unroll
-    for (int w = 0; w < DC_NW; ++w) {
+    for (int w = 0; w < NW; ++w) {
       mw[w] = sm_m[w][row];
       big = fmaxf(big, mw[w]);
     }
     float den = 0.f, acc = 0.f;  // at least one wavefront had a block, so big is finite
 #pragma unroll
-    for (int w = 0; w < DC_NW; ++w) {
+    for (int w = 0; w < NW; ++w) {
       const float wgt = __builtin_amdgcn_exp2f(mw[w] - big);
       den = fmaf(wgt, sm_l[w][row], den);
       acc = fmaf(wgt, ((const float*)(smem + w * DC_WAVE_LDS))[row * DC_D + d], acc);
@@ -336,10 +345,7 @@ AttendPlan plan_attend_decode(const AttendArgs& a, size_t split_ws_bytes) {
   AttendPlan p;
   const int n_rows = a.n_g * (a.h_q / a.h_kv);
   const int nb = (a.c + DC_BK - 1) / DC_BK + 1;
-  // An 8-bit block is a longer chain for its wavefront (widen, write, read back, two products, softmax: ~2 us alone on a
-  // SIMD) over half the bytes, so two workgroups share a CU there, each with half the LDS: one token of the 72B heads
-  // over 32,768 entries 23.1 -> 20.6 us. (A second block ahead in registers, one workgroup per CU: 23.1.)
-  const int per_head = std::max(1, device_cu_count() * (a.cache_fp8 ? 2 : 1) / a.h_kv);
+  const int per_head = std::max(1, device_cu_count() / a.h_kv);
   int bpw = std::max(DC_NW, (nb + per_head - 1) / per_head);
   int chunks = (nb + bpw - 1) / bpw;
   const size_t per_chunk = (size_t)a.h_kv * n_rows * (DC_D + 1) * sizeof(float);
@@ -363,9 +369,9 @@ void launch_attend_decode(const AttendArgs& a_in, void* split_ws, size_t split_w
   const int dev = current_device();
   if (dev < 0 || !attr_set[dev]) {
     (void)hipFuncSetAttribute((const void*)attend_decode_kernel<false>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                              DC_NW * dc_wave_lds(false));
+                              dc_lds(false));
     (void)hipFuncSetAttribute((const void*)attend_decode_kernel<true>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                              DC_NW * dc_wave_lds(true));
+                              dc_lds(true));
     if (dev >= 0) attr_set[dev] = true;
   }
   AttendArgs a = a_in;
@@ -382,10 +388,9 @@ void launch_attend_decode(const AttendArgs& a_in, void* split_ws, size_t split_w
     a.part_o = (float*)split_ws;
     a.part_lse = a.part_o + (size_t)p.n_split * rows_total * DC_D;
   }
-  if (a.cache_fp8)
-    hipLaunchKernelGGL(attend_decode_kernel<true>, dim3(p.n_split, a.h_kv), dim3(DC_NW * 64), DC_NW * dc_wave_lds(true), s, a);
-  else
-    hipLaunchKernelGGL(attend_decode_kernel<false>, dim3(p.n_split, a.h_kv), dim3(DC_NW * 64), DC_NW * dc_wave_lds(false), s, a);
+  const dim3 grid(p.n_split, a.h_kv), block(dc_waves(a.cache_fp8) * 64);
+  if (a.cache_fp8) hipLaunchKernelGGL(attend_decode_kernel<true>, grid, block, dc_lds(true), s, a);
+  else hipLaunchKernelGGL(attend_decode_kernel<false>, grid, block, dc_lds(false), s, a);
   if (p.n_split > 1) launch_attend_merge(a, s);
 }
 

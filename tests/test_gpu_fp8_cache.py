@@ -52,6 +52,35 @@ def test_compaction_stores_the_oracles_roundings(keep):
     assert cache.nbytes() * 2 == 2 * h_kv * cache.len * 128 * 2  # half the bytes of a bf16 cache of the same length
 
 
+@pytest.mark.parametrize("fmt", [B.QP_CACHE_SAME, FP8])
+@pytest.mark.parametrize("n_g,h_q,h_kv,c", [(1, 64, 8, 32768), (4, 28, 4, 9840), (1, 28, 4, 700), (1, 6, 3, 50000), (77, 28, 4, 9840)])
+def test_attend_writes_the_scratch_that_the_plan_reports(n_g, h_q, h_kv, c, fmt):
+    """qp_attend_plan describes the launch over either cache format: the call writes every byte of scratch_bytes and none
+    behind them, with scratch to spare and with exactly that much."""
+    g = torch.Generator(device=DEV).manual_seed(c)
+    bf = lambda *s: torch.randn(*s, generator=g, device=DEV).to(torch.bfloat16)
+    q, k, v = bf(n_g, h_q, 128), bf(n_g, h_kv, 128), bf(n_g, h_kv, 128)
+    layout = B.make_layout(h_q, h_kv, 128, "bf16")
+    cache = B.Cache(layout, c, fmt=fmt)
+    cache.k.copy_(bf(h_kv, c, 128))
+    cache.v.copy_(bf(h_kv, c, 128))
+    cache.c.len = c
+    out = torch.empty_like(q)
+    offered = 64 << 20
+    scratch = B.attend_plan(layout, n_g, c, offered)["scratch_bytes"]
+    assert 0 < scratch < offered
+    for size in (offered, scratch):
+        assert B.attend_plan(layout, n_g, c, size)["scratch_bytes"] == scratch
+        seen = []
+        for fill in (0x00, 0xff):                               # a byte that shows both fills was not written
+            ws = torch.full((offered,), fill, dtype=torch.uint8, device=DEV)
+            B.group_attend(layout, q, k, v, cache, out, None, ws[:size])
+            torch.cuda.synchronize()
+            seen.append(ws)
+        untouched = (seen[0] == 0x00) & (seen[1] == 0xff)
+        assert not untouched[:scratch].any() and untouched[scratch:].all()
+
+
 @pytest.mark.parametrize("n_g,h_q,h_kv,c", [(300, 28, 4, 1000), (64, 28, 4, 5000), (1, 28, 4, 9840), (7, 8, 8, 77),
                                             (2048, 28, 4, 4920), (130, 64, 8, 0), (1, 64, 8, 40000), (4, 28, 4, 31),
                                             (3, 28, 4, 32), (1, 28, 4, 129), (2, 28, 4, 0), (4, 64, 8, 2051)])
