@@ -240,6 +240,22 @@ def test_linear_split_contraction(m, n, k, bias, res):
     assert_stored_close(to_f64(plain), LO.bf16_round(want), "unsplit linear")
 
 
+@pytest.mark.parametrize("d_model", [4104, 5120, 8192, 8200])
+def test_rms_norm_rows_do_not_depend_on_the_token_count(d_model):
+    """From 12 tokens per compute unit on rows of over 4096 elements take a variant of fewer registers: every row's bits
+    are the same on both sides of that count, and the last rows equal the oracle."""
+    per_cu = torch.cuda.get_device_properties(0).multi_processor_count * 12
+    g = torch.Generator(device=DEV).manual_seed(d_model)
+    x = torch.randn(per_cu + 5, d_model, generator=g, device=DEV).to(torch.bfloat16)
+    w = torch.randn(d_model, generator=g, device=DEV).to(torch.bfloat16)
+    few, many = torch.empty_like(x[:per_cu]), torch.empty_like(x)
+    B.rms_norm(x[:per_cu], w, few, 1e-6)
+    B.rms_norm(x, w, many, 1e-6)
+    torch.cuda.synchronize()
+    assert torch.equal(few, many[:per_cu])
+    assert_stored_close(to_f64(many[-7:]), LO.bf16_round(LO.rms_norm(to_f64(x[-7:]), to_f64(w), 1e-6)), "rms norm")
+
+
 @pytest.mark.parametrize("m,n,k", [(130, 1000, 640), (129, 264, 192), (257, 520, 64), (700, 3584, 256), (1500, 4608, 128), (3, 8, 64)])
 def test_linear_is_the_same_in_every_tiling(m, n, k):
     """An unsplit product walks k in the same order whatever the tile, so the launcher's choice (128 x 128 tiles and
