@@ -276,6 +276,24 @@ def test_linear_is_the_same_in_every_tiling(m, n, k):
     assert_stored_close(to_f64(outs[0]), LO.bf16_round(LO.linear(to_f64(x), to_f64(w)) + to_f64(r)), "linear")
 
 
+@pytest.mark.parametrize("bias", [False, True])
+@pytest.mark.parametrize("m,n,k", [(130, 1000, 640), (257, 520, 64), (700, 3584, 256)])
+def test_linear_without_a_residual_in_every_tiling(m, n, k, bias):
+    """The store without a residual is code of its own: rows and outputs that end inside a tile, all three unsplit tilings."""
+    g = torch.Generator().manual_seed(m + n + k)
+    x, w, b = _bf(m, k, gen=g), _bf(n, k, gen=g, scale=k ** -0.5), _bf(n, gen=g)
+    want = LO.bf16_round(LO.linear(to_f64(x), to_f64(w), to_f64(b) if bias else None))
+    for rows in (0, 128, 256):
+        B.select_linear_tile(rows)
+        try:
+            out = torch.full((m, n), float("nan"), dtype=torch.bfloat16, device=DEV)
+            B.linear(x.to(DEV), w.to(DEV), b.to(DEV) if bias else None, None, out)
+            torch.cuda.synchronize()
+        finally:
+            B.select_linear_tile(0)
+        assert_stored_close(to_f64(out), want, f"linear, {rows} rows")
+
+
 @pytest.mark.parametrize("m,n,k", [(63, 3584, 1088), (65, 4600, 2048), (200, 3584, 2112), (3, 1000, 4096)])
 def test_narrow_split_tiles(m, n, k):
     """Few outputs against a long k with scratch: 64-wide tiles, token rows and outputs that end inside a tile."""
