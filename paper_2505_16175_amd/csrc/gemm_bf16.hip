@@ -645,7 +645,9 @@ int gemm_tile_cols(const GemmArgs& a) { return gemm_tile(a).cols; }
 
 // Contraction split: launches whose tiles would occupy at most a quarter of the CUs (few tokens against a long k:
 // text chunks and decode steps through the layer, where the weights are streamed once and HBM is the bound) deal the
-// k-steps to chunks, about one workgroup per CU in all, at least 4 steps per chunk, as many chunks as the scratch holds.
+// k-steps to chunks, at most one workgroup per CU in all, at least 4 steps per chunk, as many chunks as the scratch holds.
+// One chunk more, rounded up, starts its last workgroups only when others end: 72B QKV at 64 tokens, 40 tiles, 7 chunks
+// (280 workgroups) 54.0 us, 6 chunks 41.4; 100 x 14336 x 4096 5 chunks of 56 tiles 49.5, 4 chunks 34.7.
 //
 // With 256-wide tiles a matrix of few outputs needs many chunks for that, and every chunk writes and re-reads an f32
 // copy of the output: the 7B down projection at 64 tokens moved 34 MB of partials beside 136 MB of weights, and each
@@ -666,8 +668,10 @@ GemmSplit gemm_plan_split(const GemmArgs& a, int mode, size_t scratch_bytes) {
   if (tiles * 4 > cus || steps < 8) return p;
   long want = (cus + tiles - 1) / tiles;
   if (want > steps / 4) want = steps / 4;
+  const bool few_outputs = want > NARROW_ABOVE;
+  if (want > cus / tiles) want = cus / tiles;
   const size_t per_chunk = (size_t)a.m * a.n * sizeof(float);
-  if (want > NARROW_ABOVE && rows == 128 && g_forced_tile_rows.load(std::memory_order_relaxed) == 0) {
+  if (few_outputs && rows == 128 && g_forced_tile_rows.load(std::memory_order_relaxed) == 0) {
     const long narrow = tiles_m * ((a.n + Narrow64::BN - 1) / Narrow64::BN);
     want = NARROW_ABOVE;
     while (want > 1 && narrow * want > 2 * cus + cus / 4) want /= 2;  // a quarter of a chip above: 72 tiles x 8 measured better than x 4

@@ -111,6 +111,15 @@ def test_linear_plan_chunks_cover_the_contraction():
         B.linear_plan(4, 8, 72)                                   # k not a multiple of 64
 
 
+@pytest.mark.parametrize("m,n,k", [(64, 10240, 8192), (100, 14336, 4096), (200, 5120, 4096), (3, 9216, 4096), (128, 8192, 29568)])
+def test_linear_plan_splits_into_one_round_of_workgroups(m, n, k):
+    """A split product on 256-wide tiles takes as many chunks as run at once on 256 compute units, no more: one workgroup
+    per unit, so that the rest of one more chunk would start only when others end."""
+    p = B.linear_plan(m, n, k, 256 << 20)
+    tiles = -(-m // p["token_rows_per_tile"]) * -(-n // 256)
+    assert p["k_chunks"] == 256 // tiles
+
+
 def test_layer_workspace_and_shape_errors():
     L = B.make_layout(28, 4, 128, "bf16")
     S = B.make_layer_shape(3584, 18944)
