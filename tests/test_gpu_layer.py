@@ -294,12 +294,15 @@ def test_linear_without_a_residual_in_every_tiling(m, n, k, bias):
         assert_stored_close(to_f64(out), want, f"linear, {rows} rows")
 
 
-@pytest.mark.parametrize("m,n,k", [(63, 3584, 1088), (65, 4600, 2048), (200, 3584, 2112), (3, 1000, 4096)])
+@pytest.mark.parametrize("m,n,k", [(63, 3584, 3584), (64, 3592, 4096), (3, 1000, 4096),      # 64 token rows per tile
+                                   (65, 3592, 4096), (129, 1000, 4096), (200, 3584, 3584)])  # 128
 def test_narrow_split_tiles(m, n, k):
     """Few outputs against a long k with scratch: 64-wide tiles, token rows and outputs that end inside a tile."""
     g = torch.Generator().manual_seed(m + n + k)
     x, w, b, r = _bf(m, k, gen=g), _bf(n, k, gen=g, scale=k ** -0.5), _bf(n, gen=g), _bf(m, n, gen=g)
-    assert B.linear_plan(m, n, k, 32 << 20)["k_chunks"] > 1
+    p = B.linear_plan(m, n, k, 32 << 20)
+    tiles = -(-m // 128) * -(-n // 64)
+    assert p["k_chunks"] > 1 and p["workgroups"] == (tiles + 7) // 8 * 8      # tiles of 64 outputs, not of 256
     scratch = torch.empty(32 << 20, dtype=torch.uint8, device=DEV).fill_(0xff)
     out = torch.full((m, n), float("nan"), dtype=torch.bfloat16, device=DEV)
     B.linear(x.to(DEV), w.to(DEV), b.to(DEV), r.to(DEV), out, scratch)
@@ -307,7 +310,23 @@ def test_narrow_split_tiles(m, n, k):
     assert_stored_close(to_f64(out), LO.bf16_round(LO.linear(to_f64(x), to_f64(w), to_f64(b)) + to_f64(r)), "narrow tiles")
 
 
-@pytest.mark.parametrize("n,d_model,h_q,h_kv", [(1, 3584, 28, 4), (9, 1024, 4, 2), (64, 3584, 28, 4)])
+@pytest.mark.parametrize("m,n,k", [(63, 3584, 1088), (65, 4600, 2048), (200, 3584, 2112), (100, 10240, 1024)])
+def test_wide_split_tiles(m, n, k):
+    """The split of 256-wide tiles at the same kind of edges: too short a k for the 64-wide ones, or many outputs."""
+    g = torch.Generator().manual_seed(m + n + k)
+    x, w, b, r = _bf(m, k, gen=g), _bf(n, k, gen=g, scale=k ** -0.5), _bf(n, gen=g), _bf(m, n, gen=g)
+    p = B.linear_plan(m, n, k, 32 << 20)
+    tiles = -(-m // 128) * -(-n // 256)
+    assert p["k_chunks"] > 1 and p["workgroups"] == (tiles + 7) // 8 * 8
+    scratch = torch.empty(32 << 20, dtype=torch.uint8, device=DEV).fill_(0xff)
+    out = torch.full((m, n), float("nan"), dtype=torch.bfloat16, device=DEV)
+    B.linear(x.to(DEV), w.to(DEV), b.to(DEV), r.to(DEV), out, scratch)
+    torch.cuda.synchronize()
+    assert_stored_close(to_f64(out), LO.bf16_round(LO.linear(to_f64(x), to_f64(w), to_f64(b)) + to_f64(r)), "wide split tiles")
+
+
+@pytest.mark.parametrize("n,d_model,h_q,h_kv", [(1, 3584, 28, 4), (9, 1024, 4, 2), (64, 3584, 28, 4),
+                                                  (65, 3584, 28, 4), (128, 3584, 28, 4), (37, 2048, 64, 8)])
 def test_qkv_rope_split_contraction(n, d_model, h_q, h_kv):
     print(f"case n={n} d_model={d_model} heads={h_q}/{h_kv}", flush=True)
     g = torch.Generator().manual_seed(7 * n + d_model + h_q)
@@ -635,6 +654,46 @@ def test_decode_step_equals_its_parts_bit_for_bit(dims, n_t):
         assert torch.equal(caches[0].k[h_, :c0], caches[1].k[h_, :c0])
     np.testing.assert_array_equal(kept.cpu().numpy(), np.tile(np.arange(n_t), (dims.n_kv_heads, 1)))
     np.testing.assert_array_equal(caches[0].pos.cpu().numpy()[:, c0:c0 + n_t], 5000 + np.tile(np.arange(n_t), (dims.n_kv_heads, 1)))
+
+
+@pytest.mark.parametrize("n_t,dims", [(7, SMALL), (3, W.LayerDims(2112, 256, 4, 2)), (64, W.LayerDims(8192, 256, 8, 2)),
+                                      (5, W.LayerDims(8256, 256, 8, 2))], ids=["256", "2112", "8192", "8256"])
+def test_text_chunk_equals_its_parts(n_t, dims):
+    """A few tokens through the layer, whose split o_proj hands its rows to the second norm in the reduction's launch
+    (rows of up to 8192 outputs, 2048 per pass of its threads; beyond, two launches): against the separate calls. The norm
+    there sums a row's squares in another order, so its f32 factor may differ in the last bit and, once in about 2^15
+    values, the stored h by a bf16 step. The bound for a row with such a value: a step of up to 2^-5 (|h| <= 4) moves the
+    gates by up to 3 d_model^-0.5 2^-5 = 1e-3, which carries about a quarter of the 256 activations over a rounding
+    boundary, 2^-8 of 0.6 each, and all of them by 1e-3: 1.2e-3 and 1e-3 after down (weights of d_ff^-0.5), 1.6e-3
+    together, four sigma 6.4e-3 of an output of RMS 1.2, plus the output's own rounding. A wrong factor is wrong for a
+    whole row: the normalised error of the output stays at 1e-3."""
+    layout = B.make_layout(dims.n_q_heads, dims.n_kv_heads, 128, "bf16")
+    shape = B.make_layer_shape(dims.d_model, dims.d_ff, dims.rms_eps, dims.rope_theta, dims.mrope_section)
+    wt = {k_: v_.to(DEV) for k_, v_ in W.make_decoder_layer(dims, 0, seed=3).items()}
+    x = W.make_hidden(1, n_t, dims.d_model, seed=8).to(DEV)
+    pos = W.text_positions(n_t, 900).to(DEV)
+    cache = B.Cache(layout, n_t)
+    out = torch.full_like(x, float("nan"))
+    B.layer_group(layout, shape, B.LayerWeights(**wt), x, pos, 0, 0, None, "key_norm_small", n_t, cache, out, None,
+                  B.make_layer_workspace(layout, shape, n_t, 0))
+    assert B.linear_plan(n_t, dims.d_model, dims.n_q_heads * 128, 32 << 20)["k_chunks"] > 1
+    split = torch.empty(32 << 20, dtype=torch.uint8, device=DEV)
+    h, x1, x2 = torch.empty_like(x), torch.empty_like(x), torch.empty_like(x)
+    cs = torch.empty(n_t, 64, 2, dtype=torch.float32, device=DEV)
+    q = torch.empty(n_t, dims.n_q_heads, 128, dtype=torch.bfloat16, device=DEV)
+    k = torch.empty(n_t, dims.n_kv_heads, 128, dtype=torch.bfloat16, device=DEV)
+    v, attn, act = torch.empty_like(k), torch.empty_like(q), torch.empty(n_t, dims.d_ff, dtype=torch.bfloat16, device=DEV)
+    B.rms_norm(x, wt["ln1_w"], h, dims.rms_eps)
+    B.rope_table(pos, 0, n_t, dims.rope_theta, dims.mrope_section, cs)
+    B.qkv_rope(layout, h, wt["w_qkv"], wt["b_qkv"], cs, q, k, v, split)
+    B.group_attend(layout, q, k, v, None, attn, None, None)
+    B.linear(attn.view(n_t, -1), wt["w_o"], None, x, x1, split)
+    B.rms_norm(x1, wt["ln2_w"], h, dims.rms_eps)
+    B.swiglu_gate_up(h, wt["w_gate_up"], act)
+    B.linear(act, wt["w_down"], None, x1, x2, split)
+    torch.cuda.synchronize()
+    assert torch.equal(cache.k.transpose(0, 1), k) and torch.equal(cache.v.transpose(0, 1), v)
+    assert_stored_close(to_f64(out), to_f64(x2), "layer against its parts", floor=6e-3, nrm=1e-3)
 
 
 def test_layer_stack_replays_from_a_hip_graph():

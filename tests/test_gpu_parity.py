@@ -689,6 +689,11 @@ RUNS = [  # layout (H_q, H_kv, d, dtype), frames, tokens per frame, frames per g
     ((28, 4, 128, "bf16"), 67, 121, 4, 0.5, "value_norm", 0, True, 0),          # 8-bit cache, none of it for group 0
     ((28, 4, 128, "bf16"), 41, 128, 2, 1.0, "key_norm_small", 0, True, 77),     # everything kept, entries from before
     ((28, 4, 128, "bf16"), 321, 128, 16, 0.1, "window_attn", 1170, False, 0),   # more window scratch than one run holds
+    ((28, 4, 128, "bf16"), 515, 128, 16, 0.1, "window_attn", 1170, False, 0),   # three runs, the last of one short group
+    ((4, 2, 64, "f32"), 2073, 4, 1024, 0.02, "window_attn", 65535, False, 0),   # scratch for one group: a run each
+    ((28, 4, 128, "bf16"), 67, 121, 4, 0.3, "window_attn+shared", 64, False, 0),  # summed over heads, short last group
+    ((12, 3, 128, "bf16"), 250, 64, 3, 0.5, "value_norm+shared", 0, False, 0),
+    ((4, 2, 64, "f32"), 9, 16, 2, 0.5, "window_logit+shared", 16, False, 0),
     ((28, 4, 128, "bf16"), 65, 65, 65, 0.5, "window_logit", 8, False, 3),       # one group: the per-group loop
     ((12, 3, 128, "bf16"), 250, 64, 1, 0.5, "window_logit", 9, False, 5),       # many small groups, heads that do not divide the XCDs
     ((28, 4, 128, "bf16"), 21, 129, 6, 0.3, "value_norm", 0, False, 0),         # just over one round of workgroups
@@ -986,3 +991,50 @@ def test_prefill_video_failure_mid_loop_joins_streams_and_restores_the_cache_len
         assert cache.len == final_len
         for a, b in zip(want, (out, cache.k, cache.v, cache.pos)):
             assert torch.equal(a, b), f"after a failure at check {nth}"
+
+
+@pytest.mark.parametrize("frames,group,rule,window,checks", [
+    (291, 16, "window_attn", 1170, (1, 2, 3, 4, 5, 6, 7)),      # group 0 beside the first of two runs, side streams
+    (67, 4, "key_norm_small+shared", 0, (1, 2, 3)),             # one run on the caller's stream
+])
+def test_prefill_video_in_runs_failure_joins_streams_and_restores_the_cache_length(frames, group, rule, window, checks):
+    """As above for a video in runs of groups: the check after group 0's attention (with side streams), then after the
+    scores, the selection and the attention of every run; one check later the call succeeds."""
+    h_q, h_kv, tpf, rho, before = 28, 4, 128, 0.1, 3
+    gen = torch.Generator(device=DEV).manual_seed(13)
+    mk = lambda *s: torch.randn(*s, generator=gen, device=DEV).to(torch.bfloat16)
+    n = frames * tpf
+    q, k, v, qw = mk(n, h_q, 128), mk(n, h_kv, 128), mk(n, h_kv, 128), mk(window, h_q, 128) if window else None
+    layout = B.make_layout(h_q, h_kv, 128, "bf16")
+    ws = B.make_workspace(layout, group * tpf, window)
+    cache = B.Cache(layout, before + B.cache_capacity(frames, tpf, group, rho))
+    cache.k.normal_(), cache.v.normal_()
+    out = torch.empty_like(q)
+
+    def run():
+        cache.c.len = before
+        B.prefill_video(layout, frames, tpf, group, rho, rule, q, k, v, qw, cache, out, ws)
+
+    run()
+    torch.cuda.synchronize()
+    want = (out.clone(), cache.k.clone(), cache.v.clone(), cache.pos.clone())
+    final_len = cache.len
+    for nth in checks:
+        assert B.lib().qp_debug_fail_after(nth) == B.QP_OK
+        try:
+            with pytest.raises(B.QPError) as e:
+                run()
+        finally:
+            B.lib().qp_debug_fail_after(0)
+        assert e.value.status == B.QP_ERR_HIP
+        assert cache.len == before
+        run()                                                 # no synchronisation in between: ordered by the join
+        torch.cuda.synchronize()
+        assert cache.len == final_len
+        for a, b in zip(want, (out, cache.k, cache.v, cache.pos)):
+            assert torch.equal(a, b), f"after a failure at check {nth}"
+    assert B.lib().qp_debug_fail_after(checks[-1] + 1) == B.QP_OK
+    try:
+        run()                                                 # the call makes no further check
+    finally:
+        B.lib().qp_debug_fail_after(0)
