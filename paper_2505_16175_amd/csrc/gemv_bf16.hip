@@ -12,10 +12,14 @@
 //     workgroup: 4 consecutive outputs (PLAIN), 2 dims of a head and their rotary partners (QKV_ROPE), 2 gate rows and
 //     the up rows of the same outputs (SWIGLU);
 //   * the wavefronts walk k side by side, 16 bytes per lane and row (1 KB runs of each row per wavefront, 4 KB per
-//     workgroup), two steps per loop trip, and request the next trip's weights before the products of this one: 16 KB
-//     in flight per wavefront. With a quarter of k per wavefront and a wait for each trip's own loads the weights came
-//     at 4.1-5.6 TB/s; now, at one token, 7B sizes: gate/up 48.8 -> 43.1 us (6.3 TB/s), down 32.9 -> 28.0, all four
-//     101.6 -> 90.2; 72B sizes 344 -> 289. The activations (a few KB per token) come from L2 alongside;
+//     workgroup), two steps per loop trip, all loads of a trip issued before its first product: 8 KB of weights in
+//     flight per wavefront, and a compute unit (up to 32 wavefronts) well over the ~40 KB that 8 TB/s need at ~2 us of
+//     latency. A step past the end loads the first one again and is dropped: as a conditional load it was a branch that
+//     waited for the loads before it, and the weights came at 4.1-5.6 TB/s. us at one token, conditional / not, 7B sizes:
+//     gate/up 48.9 / 43.4 (6.3 TB/s), down 32.8 / 26.4, all four 102 / 89; 72B sizes 343 / 287, of which 9 by the
+//     wavefronts' places (a quarter of k each: 296). Requesting the next trip's weights before the products of this one
+//     gained nothing on top (89 and 291; at k <= 4096 there is one trip). The activations (a few KB per token) come from
+//     L2 alongside;
 //   * products are v_dot2_f32_bf16 (two multiply-adds per lane and instruction, f32 accumulation);
 //   * the 64 lanes' sums are added by shuffles, the 4 wavefronts' sums meet in LDS and are added in wavefront order
 //     (deterministic), and one lane per token applies the store.
@@ -68,44 +72,26 @@ __global__ __launch_bounds__(GV_WAVES * 64) void gemv_bf16_kernel(GemmArgs a) {
   for (int e = 0; e < 4; ++e)
 #pragma unroll
     for (int t = 0; t < M; ++t) acc[e][t] = 0.f;
-  // U steps per trip, the next trip's loads issued before this trip's products; steps past the end load the last chunk
-  // and are dropped
-  constexpr int U = 2, STEP = GV_WAVES * 64;
-  uint4 wv[U][4], xv[U][M];
-  auto load = [&](int c) {
+  constexpr int STEP = GV_WAVES * 64;
+  for (int c = wave * 64 + lane; c < chunks; c += 2 * STEP) {
+    const bool has1 = c + STEP < chunks;
+    const int c1 = has1 ? c + STEP : c;
+    uint4 w0[4], w1[4], x0[M], x1[M];
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const int cc = min(c + u * STEP, chunks - 1);
+    for (int e = 0; e < 4; ++e) w0[e] = w[e][c];
 #pragma unroll
-      for (int e = 0; e < 4; ++e) wv[u][e] = w[e][cc];
+    for (int t = 0; t < M; ++t) x0[t] = x[t][c];
 #pragma unroll
-      for (int t = 0; t < M; ++t) xv[u][t] = x[t][cc];
-    }
-  };
-  const int c_first = wave * 64 + lane;
-  load(c_first);
-  const int trips = (chunks + U * STEP - 1) / (U * STEP);
-  for (int i = 0; i < trips; ++i) {
-    uint4 w0[U][4], x0[U][M];
+    for (int e = 0; e < 4; ++e) w1[e] = w[e][c1];
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
+    for (int t = 0; t < M; ++t) x1[t] = x[t][c1];
 #pragma unroll
-      for (int e = 0; e < 4; ++e) w0[u][e] = wv[u][e];
+    for (int e = 0; e < 4; ++e)
 #pragma unroll
-      for (int t = 0; t < M; ++t) x0[u][t] = xv[u][t];
-    }
-    if (i + 1 < trips) load(c_first + (i + 1) * U * STEP);
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const bool exists = c_first + (i * U + u) * STEP < chunks;
-#pragma unroll
-      for (int e = 0; e < 4; ++e)
-#pragma unroll
-        for (int t = 0; t < M; ++t) {
-          const float sum = dot8(w0[u][e], x0[u][t], acc[e][t]);
-          acc[e][t] = exists ? sum : acc[e][t];
-        }
-    }
+      for (int t = 0; t < M; ++t) {
+        const float s0 = dot8(w0[e], x0[t], acc[e][t]), s1 = dot8(w1[e], x1[t], s0);
+        acc[e][t] = has1 ? s1 : s0;
+      }
   }
 #pragma unroll
   for (int e = 0; e < 4; ++e)
