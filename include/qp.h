@@ -225,8 +225,8 @@ qp_status qp_topk_compact(const qp_layout* layout, const float* scores, const vo
  * faster: one launch per step scores, selects and attends for a whole run. Videos on the scalar kernel are so from two
  * groups on. Others (among them short ones over many entries from before the call, whose last round of workgroups a run
  * would leave partly empty) and groups of at most 32 stacked rows per KV head take the steps group by group, with the key
- * splits of qp_group_attend; a row's
- * result may differ between the two in the last bits (a split adds a merge of partial sums), kept entries never do.
+ * splits of qp_group_attend; a row's result may differ between the two in the last bits (a split adds a merge of partial
+ * sums), kept entries never do.
  * Where it pays, the call uses two library-owned streams per device (created on first use on the current device,
  * default priority) for scoring / compaction and for part of the attention. They are forked from hip_stream at entry
  * and joined back into it before the call returns: work the caller enqueues on hip_stream afterwards is ordered after
@@ -269,8 +269,8 @@ qp_status qp_attend_plan(const qp_layout* layout, int32_t n_group_tokens, int32_
 qp_status qp_select_attend_kernel(int32_t which);
 
 /* Test seam for the error paths: the n_checks-th launch check from now on (every entry point of this header checks
- * once after it has enqueued its launches; qp_prefill_video checks three times per group or run of groups) reports QP_ERR_HIP with
- * hipErrorLaunchFailure although the GPU work was enqueued and runs normally. 0 switches it off. Process-wide. */
+ * once after it has enqueued its launches; qp_prefill_video checks up to three times per group or run of groups, and once
+ * more for a group 0 that runs beside the first run) reports QP_ERR_HIP with hipErrorLaunchFailure although the GPU work was enqueued and runs normally. 0 switches it off. Process-wide. */
 qp_status qp_debug_fail_after(int32_t n_checks);
 
 const char* qp_status_string(qp_status s); /* static string, never NULL */

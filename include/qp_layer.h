@@ -81,9 +81,10 @@ qp_status qp_qkv_rope(const qp_layout* layout, const void* h, const void* w_qkv,
 qp_status qp_swiglu_gate_up(const void* h, const void* w_gate_up, void* act, int32_t n_tokens, int32_t d_model,
                             int32_t d_ff, void* hip_stream);
 
-/* The projections run 256 x 256 output tiles per workgroup, or 128 (tokens) x 256 when the larger tile would leave
- * compute units idle; the launcher chooses per call. This pins the choice for later calls of this process (tests
- * cover both): 0 = choose per call, 128 or 256. INVALID_ARG for any other value. */
+/* The projections run 256 x 256 output tiles per workgroup, or 128 (tokens) x 256 or 128 x 128 when the larger tiles
+ * would leave compute units idle; a split call of few outputs runs 64-wide tiles of 128 or, up to 64 tokens, 64 rows. The
+ * launcher chooses per call. This pins 256-wide tiles of so many token rows for later calls of this process (tests cover
+ * both; the 128- and 64-wide tiles cannot be pinned): 0 = choose per call, 128 or 256. INVALID_ARG for any other value. */
 qp_status qp_select_linear_tile(int32_t token_rows);
 
 /* How qp_linear would lay out a call (host arithmetic only, nothing is launched): token rows per workgroup tile,
@@ -94,7 +95,7 @@ qp_status qp_select_linear_tile(int32_t token_rows);
  * qp_select_linear_tile keeps such calls on the tiled kernel. */
 typedef struct {
   int32_t token_rows_per_tile; /* 128 or 256; 1 or 2 for the weight-streaming kernel. A split call of at most 64 tokens
-                                  may leave out the upper 64 rows of its one tile */
+                                  on 64-wide tiles leaves out the upper 64 rows of its one tile */
   int32_t workgroups;
   int32_t k_chunks;
   int32_t k_steps_per_chunk;   /* the last chunk may have fewer */

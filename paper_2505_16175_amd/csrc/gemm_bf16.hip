@@ -651,13 +651,17 @@ int gemm_tile_cols(const GemmArgs& a) { return gemm_tile(a).cols; }
 //
 // With 256-wide tiles a matrix of few outputs needs many chunks for that, and every chunk writes and re-reads an f32
 // copy of the output: the 7B down projection at 64 tokens moved 34 MB of partials beside 136 MB of weights, and each
-// workgroup had 16 steps to hide its start behind. Where more than NARROW_ABOVE chunks would be wanted, tiles of 64
-// outputs are taken instead, in the largest power of two of chunks that keeps them about resident (tiles x chunks <=
-// 2 per CU; 3, 6, 7 and 9 chunks measured up to a third slower on the down projection than 4 and 8), at most
-// NARROW_ABOVE. us at 7B sizes, 64 tokens: QKV 25.1 -> 16.3, o_proj 21.9 -> 12.8, down 62.8 -> 35.3; 128 tokens
-// 32.5 -> 26.0, 29.1 -> 17.2, 77.2 -> 46.4; 200 tokens 37.2 -> 28.9, 31.6 -> 20.5, 73.2 -> 62.4; 3 tokens 19.8 -> 13.2,
-// 17.0 -> 11.6, 53.9 -> 29.0. At 72B sizes (8 chunks or fewer) the wide tiles are as fast or faster and stay: o_proj at
-// 64 tokens 34.7 against 35.3-39.3, down 97.9 against 101-120. So does SwiGLU, which is not split.
+// workgroup had 16 steps to hide its start behind. Where more than NARROW_ABOVE chunks would be wanted (fewer than 32
+// wide tiles: 7B o_proj and down up to 256 tokens, 7B QKV up to 128), tiles of 64 outputs are taken instead, in the
+// largest power of two of chunks that keeps tiles x chunks at 2.25 per CU (3, 6, 7 and 9 chunks measured up to a third
+// slower on the down projection than 4 and 8), at most NARROW_ABOVE. us at 7B sizes, wide tiles / 64 outputs, 64 tokens:
+// QKV 25.7 / 18.1, o_proj 22.4 / 13.7, down 63.3 / 36.8; 128 tokens 33.2 / 24.7, 29.9 / 17.8, 78.3 / 47.5; 200 tokens
+// o_proj 31.5 / 20.6, down 73.8 / 63.1; 3 tokens 19.8 / 13.2, 17.0 / 11.6, 53.9 / 29.0. At 72B sizes (8 chunks or fewer)
+// the wide tiles are as fast or faster and stay: o_proj at 64 tokens 34.7 against 35.3-39.3, down 97.9 against 101-120.
+// So does SwiGLU, which is not split. The 2.25: with 72 tiles (576 workgroups in 8 chunks) 8 chunks against 4 take 23.8 /
+// 26.5 us at 40 tokens and k = 8192, 31.8 / 35.3 at 100 tokens, but 13.4 / 13.3 and 19.9 / 17.8 at k = 3584; with 80
+// tiles, which take 4, 24.5 / 27.2 and 34.0 / 36.1, but 14.1 / 13.4 and 20.1 / 18.0: the line lies where long and short
+// contractions lose about as much.
 constexpr int NARROW_ABOVE = 8;
 GemmSplit gemm_plan_split(const GemmArgs& a, int mode, size_t scratch_bytes) {
   GemmSplit p{1, a.k / GM_BK, 0, 0};

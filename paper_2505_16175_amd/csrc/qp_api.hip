@@ -508,7 +508,8 @@ static bool runs_pay(const VideoRun& r, int32_t cache_len) {
   const qp_layout* L = r.L;
   const double cus = qp::device_cu_count();
   const double group_wgs = (double)qp::attend_mfma_row_blocks(r.n_g, L->n_q_heads, L->n_kv_heads) * L->n_kv_heads;
-  const double wgs = (r.n_groups - 1) * group_wgs + (double)qp::attend_mfma_row_blocks(r.n_last, L->n_q_heads, L->n_kv_heads) * L->n_kv_heads;
+  const double wgs = (r.n_groups - 1) * group_wgs +
+                     (double)qp::attend_mfma_row_blocks(r.n_last, L->n_q_heads, L->n_kv_heads) * L->n_kv_heads;
   if (r.n_groups < 3 || r.per_run * group_wgs < cus || group_wgs >= 2 * cus || wgs >= (1 << 28)) return false;
   const double idle_keys = (ceil(wgs / cus) - wgs / cus) * (cache_len + 0.5 * r.n_g);
   if (group_wgs >= cus) return r.n_groups >= 6 && idle_keys <= 350. * r.n_groups;

@@ -1,6 +1,6 @@
 // TopK of Eq. 2 (Sec. 3.2) per KV head, and compaction K~ = K_g[I], V~ = V_g[I] into the cache, in ONE launch.
 //
-// topk_compact_kernel: grid (slices, KV heads). Every workgroup of a head finds the head's selection threshold
+// topk_compact_kernel: grid (slices, KV heads, groups of a run). Every workgroup of a head finds the head's selection threshold
 // itself, on order-preserving 32-bit keys held in LDS (the head's scores are a few tens of KB and come from L2, so
 // repeating the search costs less than a second launch or a wait between workgroups), and then handles only its own
 // slice of the group's tokens: it ranks the slice's survivors, writes their indices and cache positions, and copies
@@ -74,7 +74,7 @@ __device__ __forceinline__ void run_group(TopkArgs& a, size_t token_bytes) {
 
 // keep == n_g (retention 1, and the single tokens and text chunks that follow the video, Sec. 2.1): every token
 // survives whatever its score, so the selection is the identity and the compaction a plain append. One lane per 16
-// bytes of a row; grid (row runs, KV heads).
+// bytes of a row; grid (row runs, KV heads, groups of a run).
 constexpr int APPEND_THREADS = 256;
 template <typename T, int D>
 __global__ __launch_bounds__(APPEND_THREADS) void append_all_kernel(TopkArgs a, int32_t* __restrict__ kept_out) {
