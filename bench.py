@@ -6,7 +6,9 @@
 One step = one pass of the whole path (group attention + scoring + top-k/compaction for every group of every layer)
 over the named synthetic workload, through qp_prefill_video of the C ABI, inputs already resident in HBM. Without
 --config the headline is the largest config, cfg5_7b_hour_stack (28 layers, every layer's inputs and pruned cache
-resident), and the line also carries a `configs` array with all five configs. Prints ONE JSON line:
+resident), and all five configs are measured. Prints ONE JSON line on stdout, short enough to be kept whole by whatever
+keeps the end of a program's output, with the headline and, per config, its time, rate and attention fraction
+(`configs`); everything below goes to stderr before it, one line per section, "[bench] detail <section> <JSON>":
   value         video tokens prefilled per second per layer over the K timed steps
   roofline      the group-attention kernel (dominant): useful flops of a launch / its average duration (HIP events
                 around every qp_group_attend launch of a serial replay of layer 0, on the stream the kernels run on)
@@ -821,7 +823,34 @@ def main():
                 "tokens_per_s_per_layer": r8["value"], "attend_frac_of_mfma_peak": r8["roofline"]["frac"],
                 "resident_cache_bytes": r8["config"]["resident_cache_bytes"],
                 "after_prefill": characterise_after_prefill(torch, B, w2, k8["layout"], k8["cache"], k8["ws"])}
-    print(json.dumps(result))
+    emit(result)
+
+
+BRIEF = ("metric", "value", "unit", "n_gpus", "steps", "warmup", "ms_per_step", "ms_per_step_median", "ms_per_step_min",
+         "higher_is_better", "scaling", "vs_baseline", "dtype", "data", "launch", "config")
+
+
+def emit(result):
+    """The full record to stderr, section by section, then the one line on stdout."""
+    for section, value in result.items():
+        if isinstance(value, list):
+            for i, entry in enumerate(value):
+                print(f"[bench] detail {section}[{i}] {json.dumps(entry)}", file=sys.stderr)
+        elif isinstance(value, dict):
+            print(f"[bench] detail {section} {json.dumps(value)}", file=sys.stderr)
+    sys.stderr.flush()
+    line = {key: result[key] for key in BRIEF}
+    rf = result["roofline"]
+    line["roofline"] = {key: rf.get(key) for key in ("bound", "achieved", "peak", "frac", "whole_step_frac", "avg_launch_us")}
+    if result.get("near_tie"):
+        line["near_tie"] = {key: v for key, v in result["near_tie"].items() if isinstance(v, int)}
+    if result.get("cpu_baseline"):
+        line["cpu_baseline"] = {key: v for key, v in result["cpu_baseline"].items() if key != "sample"}
+    if "configs" in result:
+        line["configs"] = [{"name": c["name"], "rule": c["rule"], "ms_per_step": c["ms_per_step"],
+                            "tokens_per_s_per_layer": c["tokens_per_s_per_layer"], "attend_frac": c["attend"]["frac"]}
+                           for c in result["configs"]]
+    print(json.dumps(line))
 
 
 def _config_entry(name, rule, res):
