@@ -103,9 +103,9 @@ def main():
                     f"{rf['avg_launch_us']:.1f}  achieved {rf['achieved']:.1f} TFLOP/s  frac {rf['frac']:.3f}  "
                     f"whole_step_frac {rf['whole_step_frac']:.3f}",
                     "  (roofline.avg_launch_us is taken with HIP events around the qp_group_attend calls of a serial replay. Where the",
-                    "   timed steps alternate consecutive groups' attention launches over two streams (groups of under two rounds of",
-                    "   workgroups: configs 2 and 3) the overlap stretches each launch's begin-to-end time in this trace and the --stats",
-                    "   average below mixes both kinds of launches; where they run on one stream (configs 4 and 5) the two agree)"]
+                    "   timed steps serve runs of groups (configs 2 and 3) one launch attends for all groups behind the first, and the",
+                    "   averages below mix those launches with the replay's; where every group has launches of its own on one stream",
+                    "   (configs 4 and 5) the two agree)"]
         out += ["", "kernel | calls | total ms | average us | min us | max us | % of GPU time"]
         for k, v in sorted(stats.items(), key=lambda kv: -sum(kv[1]))[:14]:
             out.append(f"{_short(k)} | {len(v)} | {sum(v) / 1e3:.3f} | {sum(v) / len(v):.2f} | {min(v):.2f} | {max(v):.2f} | "
