@@ -223,10 +223,10 @@ qp_status qp_topk_compact(const qp_layout* layout, const float* scores, const vo
  * Videos of three groups or more, each under two rounds of attention workgroups, whose attention fills the GPU at least
  * once are therefore served in runs of groups (as many as the workspace holds scores for) where that is estimated to be
  * faster: one launch per step scores, selects and attends for a whole run. Videos on the scalar kernel are so from two
- * groups on. Others (among them short ones over many entries from before the call, whose last round of workgroups a run
- * would leave partly empty) and groups of at most 32 stacked rows per KV head take the steps group by group, with the key
- * splits of qp_group_attend; a row's result may differ between the two in the last bits (a split adds a merge of partial
- * sums), kept entries never do.
+ * groups on, of under 448 tokens each. Others (among them short ones over many entries from before the call, whose last
+ * round of workgroups a run would leave partly empty) and groups of at most 32 stacked rows per KV head take the steps
+ * group by group, with the key splits of qp_group_attend; a row's result may differ between the two in the last bits (a
+ * split adds a merge of partial sums), kept entries never do.
  * Where it pays, the call uses two library-owned streams per device (created on first use on the current device,
  * default priority) for scoring / compaction and for part of the attention. They are forked from hip_stream at entry
  * and joined back into it before the call returns: work the caller enqueues on hip_stream afterwards is ordered after

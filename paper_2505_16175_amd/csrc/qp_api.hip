@@ -522,6 +522,14 @@ static bool runs_pay(const VideoRun& r, int32_t cache_len) {
   return 1.05 * run < loop;
 }
 
+// On the scalar kernel runs pay by the launches that they save, most of all those of the window rule, whose workgroups of
+// one short group fill a fraction of the chip: us group by group / as a run, 64 window rows, f32 8 heads and bf16 d = 64 28
+// heads: 24 groups of 64 tokens 5457 / 1025 and 5013 / 610, 12 of 256 3102 / 2493 and 3076 / 1837. With longer groups
+// the loop's overlap of scoring and attention is worth more: 3 of 500 960 / 1168 and 784 / 757, 3 of 1024 2773 / 3224 and
+// 2139 / 2448 (f32, 3 of 500, 16 rows 792 / 799, 128 rows 1489 / 1604; norm rules the same either way): SCALAR_LOOP tokens
+// and more keep it. Between, group 0 attends beside the scoring: 4 of 300 tokens, 16 / 64 rows, f32, 604 -> 560 / 868 -> 824.
+constexpr int SCALAR_BESIDE = 256, SCALAR_LOOP = 448;
+
 static qp_status prefill_in_runs(const VideoRun& r, qp_cache* cache, void* workspace, hipStream_t main_stream) {
   const qp_layout* L = r.L;
   const size_t esz = L->dtype == QP_F32 ? 4 : 2;
@@ -538,8 +546,9 @@ static qp_status prefill_in_runs(const VideoRun& r, qp_cache* cache, void* works
   // only because each enqueues all of its steps before the next one's first.
   std::lock_guard<std::mutex> lock(g_prefill_mutex);
   SideStreams* side = nullptr;
-  // half a chip of workgroups: below, group 0's attention is shorter than the waits between streams
-  if (r.mfma && 2 * qp::attend_mfma_row_blocks(r.n_g, L->n_q_heads, L->n_kv_heads) * L->n_kv_heads >= qp::device_cu_count())
+  // half a chip of workgroups: below, group 0's attention is shorter than the waits between streams (scalar kernel: tokens)
+  if (r.mfma ? 2 * qp::attend_mfma_row_blocks(r.n_g, L->n_q_heads, L->n_kv_heads) * L->n_kv_heads >= qp::device_cu_count()
+             : r.n_g > SCALAR_BESIDE)
     side = side_streams();
   const int32_t len_at_entry = cache->len;
   hipStream_t score_stream = side ? side->score : main_stream;
@@ -667,7 +676,7 @@ qp_status qp_prefill_video(const qp_layout* L, int32_t n_frames, int32_t tokens_
     r.mfma = which != QP_ATTEND_SCALAR && qp::attend_mfma_supported(probe, L->dtype);
     lay_out_runs(r, workspace_bytes);
     const bool runs = r.mfma ? !(which == QP_ATTEND_AUTO && qp::attend_decode_applies(probe, L->dtype)) && runs_pay(r, cache->len)
-                             : cache->format == QP_CACHE_SAME;
+                             : cache->format == QP_CACHE_SAME && r.n_g < SCALAR_LOOP;
     if (r.n_groups > 1 && runs) return prefill_in_runs(r, cache, workspace, (hipStream_t)hip_stream);
   }
 

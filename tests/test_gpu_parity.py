@@ -690,7 +690,7 @@ RUNS = [  # layout (H_q, H_kv, d, dtype), frames, tokens per frame, frames per g
     ((28, 4, 128, "bf16"), 41, 128, 2, 1.0, "key_norm_small", 0, True, 77),     # everything kept, entries from before
     ((28, 4, 128, "bf16"), 321, 128, 16, 0.1, "window_attn", 1170, False, 0),   # more window scratch than one run holds
     ((28, 4, 128, "bf16"), 515, 128, 16, 0.1, "window_attn", 1170, False, 0),   # three runs, the last of one short group
-    ((4, 2, 64, "f32"), 2073, 4, 1024, 0.02, "window_attn", 65535, False, 0),   # scratch for one group: a run each
+    ((64, 64, 64, "bf16"), 203, 4, 100, 0.1, "window_attn", 37600, False, 0),   # scratch for one group: a run each
     ((28, 4, 128, "bf16"), 67, 121, 4, 0.3, "window_attn+shared", 64, False, 0),  # summed over heads, short last group
     ((12, 3, 128, "bf16"), 250, 64, 3, 0.5, "value_norm+shared", 0, False, 0),
     ((4, 2, 64, "f32"), 9, 16, 2, 0.5, "window_logit+shared", 16, False, 0),
@@ -699,6 +699,8 @@ RUNS = [  # layout (H_q, H_kv, d, dtype), frames, tokens per frame, frames per g
     ((28, 4, 128, "bf16"), 21, 129, 6, 0.3, "value_norm", 0, False, 0),         # just over one round of workgroups
     ((4, 2, 64, "f32"), 9, 16, 2, 0.5, "window_attn", 16, False, 0),            # scalar kernel
     ((4, 2, 64, "bf16"), 7, 13, 3, 0.4, "key_norm_small", 0, False, 9),
+    ((8, 2, 128, "f32"), 34, 64, 6, 0.3, "window_attn", 16, False, 5),          # ... with group 0 beside the scoring
+    ((8, 2, 128, "f32"), 17, 64, 7, 0.3, "window_attn", 16, False, 5),          # ... and groups of its per-group loop
 ]
 
 
