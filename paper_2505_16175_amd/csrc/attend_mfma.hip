@@ -21,42 +21,43 @@
 // long cache (so that the launch covers the chip), and, in launches of several rounds of workgroups, only the row
 // blocks of a partly filled last round (so that their chunks fill the compute units evenly); see plan_attend_mfma.
 //
-// Per wavefront (32 rows), per tile of 64 keys, with v_mfma_f32_32x32x16_bf16:
-//   S^T[key][row] = K_tile . Q^T      (A = K from LDS, 16-byte reads; B = Q held in registers)
-//     -> a lane holds ONE row (column of S^T) and 16 keys per 32-key block, so the softmax row
-//        max / sum are in-register reductions plus one exchange between lane l and l+32.
+// Per wavefront (32 rows), per block of 32 keys, with v_mfma_f32_32x32x16_bf16:
+//   S^T[key][row] = K_block . Q^T     (A = K from LDS, 16-byte reads; B = Q held in registers)
+//     -> a lane holds ONE row (column of S^T) and 16 of the block's keys, lane l + 32 the other 16.
 //   P^T = exp2(c*S^T - c*m) rounded to bf16, fed straight back as the B operand of
 //   O^T[d][row] += V^T . P^T         (A = V^T read from the row-major V tile in LDS with the
 //                                      transposing ds_read_tr16_b64, 4 keys x 16 d per 16 lanes)
-//     -> O^T keeps the lane <-> row association, so the online-softmax rescale is a per-lane
-//        scalar multiply.
+//     -> O^T keeps the lane <-> row association, so a rescale is a per-lane scalar multiply.
 // The contraction index of the second product is permuted (keys 4g..4g+3 and 8+4g..8+4g+3 of
 // each 16-key step go to lane half g) so that the accumulator layout of S^T is already the
 // operand layout of P^T; V^T is read with the same permutation.
 //
-// Choices aimed at the vector/LDS work that competes with the matrix pipe:
+// Schedule. What bounds the loop is the matrix pipe (64 products of 32 cycles per SIMD and tile) and, at full occupancy, the
+// power that the products and their operands cost: the chip lowers its clock. The loop is software-pipelined over three
+// consecutive blocks: one step issues S^T of block j+1, the numerators of block j and O^T += V^T P^T of block j-1, none
+// of which waits for another, in a fixed order of 16 products with two vector operations and an exponential or so behind
+// each, and fragments read three products ahead. For that the numerators must not wait for the block's max:
+//   * The reference m of a row is not the running max. It moves only when a block's numerators outgrow it (a lane's sum of
+//     16 beyond 2^12, infinity included), checked after they are formed and before they are used; the block's numerators are
+//     then formed again around the new max. bf16 and f32 numerators lose nothing by a reference below the max. The first
+//     block always sets it.
+//   * The row sum of the bf16-rounded numerators is taken with shifts and adds (pack_pair).
+// 8192 tokens of the 7B heads over 24,576 entries, random (all-zero, which leaves the clock alone) inputs: 2945 us (2000);
+// one tile after the other with max, numerators and v_dot2 sum between the two products 3240 (2590); this pipeline with the
+// v_dot2 sum and all requests behind the barrier 3220 (2500). Products in fours per kind: alternating one by one costs 1 %.
 //   * K/V tiles go global -> LDS with global_load_lds_dwordx4 (no staging registers, no ds_write):
 //     one instruction moves 64 lanes x 16 bytes into 1 KB of LDS, lane L landing at base + 16 L.
 //     Rows are 256 bytes, unpadded; bank conflicts are avoided by an XOR swizzle of the 16-byte
 //     chunk index: K chunk c of key k sits at position c ^ (k & 15), V chunk c at position
 //     c ^ ((k & 7) << 1); each lane fetches the global chunk that belongs at its LDS position.
-//   * Tiles sit in a ring of LDS buffers and are requested two tiles ahead.
+//   * Tiles of 64 keys sit in rings of four LDS slots and are requested more than two tiles ahead, one barrier per tile, the
+//     wavefront's four requests spread over a step (issued together behind the barrier they cost 10 %, all-zero 15 %).
 //   * Workgroup ids are mapped so that the workgroups of one KV head run on the same XCDs (ids are
 //     dealt round-robin over the 8 XCDs, each with its own L2): with 4 KV heads, XCDs 2h and 2h+1
 //     serve head h, so every L2 streams one head's K/V instead of all of them.
-//   * The reference max only moves when some row's max grew by more than 2^8 (the softmax
-//     numerators stay below 2^8, harmless in f32/bf16), so O^T is rescaled a few times per row
-//     instead of once per tile on slowly growing maxima.
-//   * The row sum is taken over the bf16-rounded numerators with v_dot2c_f32_bf16.
-// Schedule: every wavefront runs QK -> softmax -> PV on the same tile, one barrier per tile. Schedules that
-// keep the two wavefronts of a SIMD half a tile apart (one in its matrix phase while the other is in its
-// softmax phase: with a barrier per phase, or with opposite phase order between two barriers), software
-// pipelining inside a wavefront, and raising the wavefront's priority (s_setprio) around the matrix phases
-// or around the softmax were all measured and were all slower than this plain loop (1-19 %); two tiles per
-// barrier (a ring of four slots, so that the two wavefronts of a SIMD drift apart between barriers) measured the
-// same within 2 %. At full occupancy the chip lowers its clock under this kernel: time per tile is then set by
-// the energy a tile costs, not by how well the phases overlap.
 #include "qp_internal.h"
+
+#include <float.h>
 
 #include <algorithm>
 
@@ -70,6 +71,7 @@ typedef __attribute__((__vector_size__(4 * sizeof(short)))) short s16x4;
 typedef __attribute__((__vector_size__(8 * sizeof(short)))) short s16x8;
 typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+typedef __attribute__((address_space(3))) u32x4 lds_u32x4;
 
 constexpr int MF_D = 128;               // head_dim
 constexpr int MF_BN = 64;               // keys per tile
@@ -77,104 +79,57 @@ constexpr int MF_NW = 8;                // wavefronts per workgroup
 constexpr int MF_NT = MF_NW * 64;
 constexpr int MF_HB = MF_NW / 2 * 32;   // rows per half block (4 wavefronts); a workgroup owns two half blocks
 constexpr int MF_TILE = MF_BN * 256;    // bytes of one K or V tile (unpadded, swizzled)
-constexpr int MF_SLOT = 2 * MF_TILE;    // K tile + V tile
-constexpr int MF_STAGES = 3;            // ring of K+V tile slots
-constexpr float MF_RESCALE_LOG2 = 8.f;  // move the reference max only when it grows by more than 2^8
+constexpr int MF_STAGES = 4;            // ring slots of K and of V tiles
+constexpr int MF_V0 = MF_STAGES * MF_TILE;  // LDS offset of the V ring
+constexpr int MF_LDS = 2 * MF_STAGES * MF_TILE;
+constexpr float MF_RESCALE = 4096.f;    // move the reference when a lane's 16 numerators of a block sum to more
 constexpr int MF_VMCNT0 = 0x0f70;       // s_waitcnt vmcnt(0), other counters untouched
 constexpr int MF_VMCNT4 = 0x0f74;       // s_waitcnt vmcnt(4)
+constexpr int MF_LGKM0 = 0xc07f;        // s_waitcnt lgkmcnt(0)
 constexpr int MF_SPLIT_BELOW = 128;     // launches of fewer workgroups split the cache over chunks
 constexpr int MF_MAX_SPLIT = 128;       // chunks at most
 constexpr size_t MF_SPLIT_ALL_BYTES = (size_t)32 << 20;  // scratch that a split of every row block takes at most
 constexpr int MF_TAIL_SPLIT_MAX = 8;    // chunks per row block when only the last round's row blocks are split
 constexpr int MF_TAIL_MIN_TILES = 16;   // ... whose chunks hold at least this many cache tiles
 
-// S^T (64 keys x 32 rows, two 32-key blocks) = K tile . Q^T. All 16 K fragments are read before the
-// first MFMA (a scheduling barrier keeps the compiler from sinking each read next to its use,
-// which would serialise on LDS latency).
-__device__ __forceinline__ void qk_tile(const unsigned char* kt, const int (&k_addr)[8], const bf16x8 (&qf)[8],
-                                        f32x16 (&st)[2]) {
-  u32x4 kf[2][8];
+// Masks S^T of one 32-key block: this lane's keys beyond `lim` (block-local, minus 4 g) become -inf.
+__device__ __forceinline__ void mask_block(f32x16& st, int lim) {
 #pragma unroll
-  for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-    for (int s = 0; s < 8; ++s) kf[kb][s] = *(const u32x4*)(kt + kb * 32 * 256 + k_addr[s]);
-  __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-  for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-    for (int r = 0; r < 16; ++r) st[kb][r] = 0.f;
-#pragma unroll
-  for (int s = 0; s < 8; ++s)
-#pragma unroll
-    for (int kb = 0; kb < 2; ++kb)
-      st[kb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, kf[kb][s]), qf[s], st[kb], 0, 0, 0);
-  __builtin_amdgcn_sched_barrier(0);
+  for (int r = 0; r < 16; ++r) st[r] = 8 * (r >> 2) + (r & 3) > lim ? -INFINITY : st[r];
 }
 
-// Online softmax of one tile for this lane's row (32 of the tile's 64 keys; lane ^ 32 has the others):
-// masks keys with key_local > lim_local (only when need_mask), updates the reference max / the lane's
-// share of the denominator, rescales O^T when the reference moved, leaves P^T (bf16) in pf.
-__device__ __forceinline__ void softmax_tile(f32x16 (&st)[2], bool need_mask, int lim_local, int g, float c2,
-                                             float lazy, float& m_run, float& l_run, f32x16 (&o)[4],
-                                             bf16x8 (&pf)[4]) {
-  if (need_mask) {
-#pragma unroll
-    for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-      for (int r = 0; r < 16; ++r)
-        if (kb * 32 + 8 * (r >> 2) + 4 * g + (r & 3) > lim_local) st[kb][r] = -INFINITY;
-  }
-  float mx = st[0][0];
-#pragma unroll
-  for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-    for (int r = 0; r < 16; ++r) mx = fmaxf(mx, st[kb][r]);
-  mx = max_halves(mx);
-  // first tile: m_run = -inf, so the max is adopted; key 0 is visible to every row, so it is finite
-  const float m_new = (mx > m_run + lazy) ? mx : m_run;
-  const float mc = m_new * c2;
-  bf16x2 ones;
-  ones[0] = (__bf16)1.0f;
-  ones[1] = (__bf16)1.0f;
-  float psum = 0.f;
-#pragma unroll
-  for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-    for (int r = 0; r < 16; r += 2) {
-      bf16x2 pr;
-      pr[0] = (__bf16)__builtin_amdgcn_exp2f(fmaf(st[kb][r], c2, -mc));
-      pr[1] = (__bf16)__builtin_amdgcn_exp2f(fmaf(st[kb][r + 1], c2, -mc));
-      psum = __builtin_amdgcn_fdot2_f32_bf16(pr, ones, psum, false);
-      pf[kb * 2 + (r >> 3)][r & 7] = pr[0];
-      pf[kb * 2 + (r >> 3)][(r & 7) + 1] = pr[1];
-    }
-  if (__any(m_new != m_run)) {
-    const float alpha = __builtin_amdgcn_exp2f((m_run - m_new) * c2);
-    l_run *= alpha;
-#pragma unroll
-    for (int n = 0; n < 4; ++n)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) o[n][r] *= alpha;
-    m_run = m_new;
-  }
-  l_run += psum;
+// Two numerators, rounded to bf16, as elements i and i + 1 of a P^T operand; their rounded values are added to s0 and s1.
+// The sum is taken with shifts and adds: v_dot2_f32_bf16 would do it in one instruction, but that runs on the matrix pipe
+// and holds it for 16 cycles.
+__device__ __forceinline__ void pack_pair(float e0, float e1, bf16x8& p, int i, float& s0, float& s1) {
+  bf16x2 pr;
+  pr[0] = (__bf16)e0;
+  pr[1] = (__bf16)e1;
+  unsigned u = __builtin_bit_cast(unsigned, pr);
+  asm("" : "+v"(u));  // one conversion for the operand and the sum
+  pr = __builtin_bit_cast(bf16x2, u);
+  p[i] = pr[0];
+  p[i + 1] = pr[1];
+  const float lo = __uint_as_float(u << 16), hi = __uint_as_float(u & 0xffff0000u);
+  s0 += lo;
+  s1 += hi;
 }
 
-// O^T (128 d x 32 rows) += V^T . P^T over the tile's 64 keys: 4 key steps of 16 x 4 d-blocks of 32.
-__device__ __forceinline__ void pv_tile(const unsigned char* vt, const int (&v_addr)[4], const bf16x8 (&pf)[4],
-                                        f32x16 (&o)[4]) {
-#pragma unroll
-  for (int ks = 0; ks < 4; ++ks) {
-#pragma unroll
-    for (int n = 0; n < 4; ++n) {
-      const unsigned char* p0 = vt + ks * 16 * 256 + v_addr[n];
-      const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(p0));
-      const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(p0 + 8 * 256));
-      const s16x8 cat = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
-      o[n] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, cat), pf[ks], o[n], 0, 0, 0);
-    }
-  }
+struct Pieces {
+  uint2 p[4];
+};
+// 8 E4M3 bytes -> 8 bf16 (exact)
+__device__ __forceinline__ u32x4 widen8(uint2 p) {
+  u32x4 o;
+  o.x = __builtin_bit_cast(unsigned, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(p.x, 1.f, false));
+  o.y = __builtin_bit_cast(unsigned, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(p.x, 1.f, true));
+  o.z = __builtin_bit_cast(unsigned, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(p.y, 1.f, false));
+  o.w = __builtin_bit_cast(unsigned, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(p.y, 1.f, true));
+  return o;
 }
+
+struct true_type { static constexpr bool value = true; };
+struct false_type { static constexpr bool value = false; };
 
 // F8: the cache's K~ and V~ hold one E4M3 byte per element (the pruned cache's 8-bit format). Their tiles cannot go
 // global -> LDS directly: every wavefront loads its share of a tile into registers one tile ahead (8 bytes per lane
@@ -182,7 +137,6 @@ __device__ __forceinline__ void pv_tile(const unsigned char* vt, const int (&v_a
 // after the staging is the same code. The group's own tiles are bf16 and staged as usual.
 template <bool F8>
 __global__ __launch_bounds__(MF_NT, 2) void attend_mfma_kernel(AttendArgs a) {
-  constexpr int STAGES = MF_STAGES;
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // wave-uniform for the compiler too: scalar address and branch work
@@ -281,143 +235,326 @@ __global__ __launch_bounds__(MF_NT, 2) void attend_mfma_kernel(AttendArgs a) {
   const unsigned st_kc0 = (unsigned)((st_pos ^ (st_key0 & 15)) * 16), st_kc1 = (unsigned)((st_pos ^ (st_key1 & 15)) * 16);
   const unsigned st_vc0 = (unsigned)((st_pos ^ ((st_key0 & 7) << 1)) * 16),
                  st_vc1 = (unsigned)((st_pos ^ ((st_key1 & 7) << 1)) * 16);
-  const int st_lds = wave * 2048;  // LDS offset of this wavefront's 2 x 1 KB inside a tile
+  const unsigned st_lds = lds_address(smem) + wave * 2048;  // this wavefront's 2 x 1 KB inside a tile
 
-  // request tile `tile_` into ring slot `slot_` (4 loads per wavefront)
-#define QP_ISSUE(tile_, slot_)                                                                                 \
-  {                                                                                                            \
-    const bool in_cache_ = (tile_) < n_ct;                                                                     \
-    const int base_ = in_cache_ ? (tile_)*MF_BN : ((tile_)-n_ct) * MF_BN;                                      \
-    const int last_ = in_cache_ ? a.c - 1 : a.n_g - 1; /* rows past the end are clamped: masked, never used */ \
-    const unsigned stride_ = in_cache_ ? (unsigned)(MF_D * 2) : gstride_b;                                     \
-    const unsigned char* ksrc_ = in_cache_ ? ck : gk;                                                          \
-    const unsigned char* vsrc_ = in_cache_ ? cv : gv;                                                          \
-    const unsigned r0_ = __umul24((unsigned)min(base_ + st_key0, last_), stride_);                             \
-    const unsigned r1_ = __umul24((unsigned)min(base_ + st_key1, last_), stride_);                             \
-    unsigned char* kdst_ = smem + (slot_)*MF_SLOT + st_lds;                                                    \
-    unsigned char* vdst_ = kdst_ + MF_TILE;                                                                    \
-    lds_dma16(ksrc_, r0_ + st_kc0, kdst_);                                                                     \
-    lds_dma16(ksrc_, r1_ + st_kc1, kdst_ + 1024);                                                              \
-    lds_dma16(vsrc_, r0_ + st_vc0, vdst_);                                                                     \
-    lds_dma16(vsrc_, r1_ + st_vc1, vdst_ + 1024);                                                              \
-  }
-
-  // 8-bit cache tiles: this lane's 8-byte pieces of the pending tile (same keys and LDS positions as above; global
-  // chunk c of a row is 8 bytes at c * 8), and their widened form written to a ring slot
-  uint2 f8k0 = make_uint2(0, 0), f8k1 = f8k0, f8v0 = f8k0, f8v1 = f8k0;
-  auto f8_load = [&](int tile_) {
-    const int base_ = tile_ * MF_BN, last_ = a.c - 1;
-    const unsigned r0_ = (unsigned)min(base_ + st_key0, last_) * (unsigned)MF_D;
-    const unsigned r1_ = (unsigned)min(base_ + st_key1, last_) * (unsigned)MF_D;
-    f8k0 = *(const uint2*)(ck + r0_ + (st_kc0 >> 1));
-    f8k1 = *(const uint2*)(ck + r1_ + (st_kc1 >> 1));
-    f8v0 = *(const uint2*)(cv + r0_ + (st_vc0 >> 1));
-    f8v1 = *(const uint2*)(cv + r1_ + (st_vc1 >> 1));
+  // One tensor's tile requests, in order: the next tile, its address, and this lane's byte offsets of its two rows in it.
+  // The offsets change only where a segment starts or a tile is cut off by its segment's end (rows past the end are
+  // clamped: masked, never used); `event` is the next such tile.
+  struct Stream {
+    const unsigned char* src;
+    unsigned o0, o1, step;
+    int tile, event;
   };
-  auto widen8 = [](uint2 p) -> u32x4 {  // 8 E4M3 bytes -> 8 bf16 (the f32 values are exact; their high halves are the bf16)
-    const auto a0 = __builtin_amdgcn_cvt_pk_f32_fp8((int)p.x, false), a1 = __builtin_amdgcn_cvt_pk_f32_fp8((int)p.x, true);
-    const auto b0 = __builtin_amdgcn_cvt_pk_f32_fp8((int)p.y, false), b1 = __builtin_amdgcn_cvt_pk_f32_fp8((int)p.y, true);
-    u32x4 o;
-    o.x = (__float_as_uint(a0[0]) >> 16) | (__float_as_uint(a0[1]) & 0xffff0000u);
-    o.y = (__float_as_uint(a1[0]) >> 16) | (__float_as_uint(a1[1]) & 0xffff0000u);
-    o.z = (__float_as_uint(b0[0]) >> 16) | (__float_as_uint(b0[1]) & 0xffff0000u);
-    o.w = (__float_as_uint(b1[0]) >> 16) | (__float_as_uint(b1[1]) & 0xffff0000u);
-    return o;
+  const int cache_tail = a.c % MF_BN != 0 ? n_ct - 1 : -1;
+  const int group_tail = a.n_g % MF_BN != 0 ? n_ct + a.n_g / MF_BN : -1;
+  auto settle = [&](Stream& s, const unsigned char* cache, const unsigned char* group, unsigned c0, unsigned c1) {
+    const bool in_cache = s.tile < n_ct;
+    const int first = (in_cache ? s.tile : s.tile - n_ct) * MF_BN;
+    const int left = (in_cache ? a.c : a.n_g) - first - 1;  // last valid row of the tile
+    const unsigned stride = in_cache ? (unsigned)CROW : gstride_b;
+    const int sh = F8 && in_cache ? 1 : 0;  // 8 bytes of an 8-bit row where a bf16 row has 16
+    s.src = (in_cache ? cache : group) + (size_t)first * stride;
+    s.step = MF_BN * stride;
+    s.o0 = __umul24((unsigned)min(st_key0, left), stride) + (c0 >> sh);
+    s.o1 = __umul24((unsigned)min(st_key1, left), stride) + (c1 >> sh);
+    const int tail = in_cache ? cache_tail : group_tail;
+    s.event = s.tile < tail ? tail : in_cache ? n_ct : 0x7fffffff;
   };
-  auto f8_store = [&](int slot_) {
-    unsigned char* kdst_ = smem + slot_ * MF_SLOT + st_lds + lane * 16;
-    unsigned char* vdst_ = kdst_ + MF_TILE;
-    *(u32x4*)(kdst_) = widen8(f8k0);
-    *(u32x4*)(kdst_ + 1024) = widen8(f8k1);
-    *(u32x4*)(vdst_) = widen8(f8v0);
-    *(u32x4*)(vdst_ + 1024) = widen8(f8v1);
+  auto advance = [&](Stream& s, const unsigned char* cache, const unsigned char* group, unsigned c0, unsigned c1) {
+    s.src += s.step;
+    if (++s.tile >= s.event && s.tile < t_end) settle(s, cache, group, c0, c1);
   };
-  // stage tile `tile_` for slot `slot_`: cache tiles of an 8-bit cache go through registers (f8_store follows later)
-#define QP_STAGE(tile_, slot_)                    \
-  {                                               \
-    if (F8 && (tile_) < n_ct) f8_load(tile_);     \
-    else QP_ISSUE(tile_, slot_)                   \
-  }
+  Stream sk, sv;
+  sk.tile = sv.tile = t_begin;
+  settle(sk, ck, gk, st_kc0, st_kc1);
+  settle(sv, cv, gv, st_vc0, st_vc1);
+  // A pair's four requests: halves of its K tile (0, 1) and of its V tile (2, 3). Tiles of an 8-bit cache cannot go to LDS
+  // directly: this lane's 8 bytes of each half are pending in registers until they are stored, widened.
+  Pieces pend;
+  auto load_piece = [&](int i) {
+    const Stream& s = i < 2 ? sk : sv;
+    return *(const uint2*)(s.src + ((i & 1) ? s.o1 : s.o0));
+  };
+  auto request_half = [&](int i, unsigned dst) {  // dst: LDS address of the slot's K tile
+    const Stream& s = i < 2 ? sk : sv;
+    lds_dma16_to(s.src, (i & 1) ? s.o1 : s.o0, dst + (i < 2 ? 0 : MF_V0) + (i & 1) * 1024);
+  };
+  auto store_piece = [&](int i, uint2 p, int slot) {
+    *(u32x4*)(smem + slot * MF_TILE + (i < 2 ? 0 : MF_V0) + (i & 1) * 1024 + wave * 2048 + lane * 16) = widen8(p);
+  };
+  auto request_k = [&](int slot) {
+    if (F8 && sk.tile < n_ct) pend.p[0] = load_piece(0), pend.p[1] = load_piece(1);
+    else request_half(0, st_lds + slot * MF_TILE), request_half(1, st_lds + slot * MF_TILE);
+  };
+  auto request_v = [&](int slot) {
+    if (F8 && sv.tile < n_ct) pend.p[2] = load_piece(2), pend.p[3] = load_piece(3);
+    else request_half(2, st_lds + slot * MF_TILE), request_half(3, st_lds + slot * MF_TILE);
+  };
+  auto store_k = [&](int tile, const Pieces& p, int slot) {  // if `tile` is a tile of an 8-bit cache
+    if (F8 && tile < n_ct) store_piece(0, p.p[0], slot), store_piece(1, p.p[1], slot);
+  };
+  auto store_v = [&](int tile, const Pieces& p, int slot) {
+    if (F8 && tile < n_ct) store_piece(2, p.p[2], slot), store_piece(3, p.p[3], slot);
+  };
 
   // fragment read addresses (bytes inside a tile)
-  int k_addr[8];  // K fragment of d-step s: key l32 (+32 per block), chunk 2s+g at position (2s+g) ^ (l32 & 15)
+  const unsigned lds0 = lds_address(smem);
+  unsigned k_addr[8];  // K fragment of d-step s: key l32 (+32 per block), chunk 2s+g at position (2s+g) ^ (l32 & 15)
 #pragma unroll
-  for (int s = 0; s < 8; ++s) k_addr[s] = l32 * 256 + (((2 * s + g) ^ (l32 & 15)) << 4);
+  for (int s = 0; s < 8; ++s) {
+    k_addr[s] = lds0 + l32 * 256 + (((2 * s + g) ^ (l32 & 15)) << 4);
+    asm("" : "+v"(k_addr[s]));  // opaque: ring offsets stay immediates of the reads instead of more address registers
+  }
   const int l16 = lane & 15, grp = lane >> 4;
   const int v_key = 4 * (grp >> 1) + (l16 >> 2);  // key inside a 16-key step (second read: + 8)
-  int v_addr[4];  // V^T fragment of d-block n: chunk 4n + 2(grp&1) + ((l16&3)>>1), half (l16&1)
+  unsigned v_addr[4];  // V^T fragment of d-block n: chunk 4n + 2(grp&1) + ((l16&3)>>1), half (l16&1)
 #pragma unroll
-  for (int n = 0; n < 4; ++n)
-    v_addr[n] = v_key * 256 + (((4 * n + 2 * (grp & 1) + ((l16 & 3) >> 1)) ^ ((v_key & 7) << 1)) << 4) + (l16 & 1) * 8;
+  for (int n = 0; n < 4; ++n) {
+    v_addr[n] = lds0 + MF_V0 + v_key * 256 + (((4 * n + 2 * (grp & 1) + ((l16 & 3) >> 1)) ^ ((v_key & 7) << 1)) << 4) +
+                (l16 & 1) * 8;
+    asm("" : "+v"(v_addr[n]));
+  }
+  // fragment s of the 32-key K block / (ks, n) = (s >> 2, s & 3) of the 32-key V block at LDS offset `off`
+  auto read_k = [&](int off, int s) { return __builtin_bit_cast(bf16x8, *(const lds_u32x4*)(k_addr[s] + off)); };
+  auto read_v = [&](int off, int s) {
+    const unsigned p0 = v_addr[s & 3] + (off + (s >> 2) * (16 * 256));
+    const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(p0));
+    const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(p0 + 8 * 256));
+    return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+  };
 
   f32x16 o[4];
 #pragma unroll
   for (int n = 0; n < 4; ++n)
 #pragma unroll
     for (int r = 0; r < 16; ++r) o[n][r] = 0.f;
-  float m_run = -INFINITY;  // reference max of the raw logits (lags the true running max by < 2^8 after scaling)
+  float m_run = -INFINITY;  // reference of the row's numerators: the max of the raw logits when it was last moved
   float l_run = 0.f;        // this lane's share of the row's denominator
   const float c2 = a.scale_log2;
-  const float lazy = MF_RESCALE_LOG2 / c2;
+  float nmc = 0.f;  // -m_run * c2
 
-  // visibility of tile `tile_` for this wavefront / lane
-#define QP_TILE_VIEW(tile_)                                                                             \
-  const bool in_cache = (tile_) < n_ct;                                                                 \
-  const int gt0 = ((tile_)-n_ct) * MF_BN; /* first group token of a group tile */                       \
-  const bool live = wave_live && (in_cache || gt0 <= t_w_max);                                          \
-  const int lim_local = in_cache ? a.c - 1 - (tile_)*MF_BN : t_lane - gt0; /* key_local <= lim_local */ \
-  const bool need_mask = in_cache ? (a.c - (tile_)*MF_BN < MF_BN) : (gt0 + MF_BN - 1 > t_w_min);
+  // Moves the reference to the rows' max including this block, rescales what was summed so far and forms the block's
+  // numerators (first block of a row, and blocks whose numerators outgrew the reference).
+  auto move_reference = [&](const f32x16& st, bf16x8 (&pf)[2], float& psum) {
+    float mx = st[0];
+#pragma unroll
+    for (int r = 1; r < 16; ++r) mx = fmaxf(mx, st[r]);
+    // finite also where every logit so far is -inf: the numerators are 0 then, and the next finite logit moves it again
+    mx = fmaxf(fmaxf(m_run, max_halves(mx)), -FLT_MAX);
+    const float alpha = __builtin_amdgcn_exp2f((m_run - mx) * c2);
+    m_run = mx;
+    nmc = -mx * c2;
+    l_run *= alpha;
+#pragma unroll
+    for (int n = 0; n < 4; ++n)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) o[n][r] *= alpha;
+    float ps0 = 0.f, ps1 = 0.f;
+#pragma unroll
+    for (int r = 0; r < 16; r += 2) {
+      pack_pair(__builtin_amdgcn_exp2f(fmaf(st[r], c2, nmc)), __builtin_amdgcn_exp2f(fmaf(st[r + 1], c2, nmc)), pf[r >> 3],
+                r & 7, ps0, ps1);
+    }
+    psum = ps0 + ps1;
+  };
 
-  // each wavefront has 4 loads in flight per requested tile: vmcnt(4) = all but the newest tile have landed
-  QP_STAGE(t_begin, 0)
-  if (F8 && t_begin < n_ct) f8_store(0);
-  if (t_begin + 1 < t_end) {
-    QP_STAGE(t_begin + 1, 1)
-    if (F8 && t_begin + 1 < n_ct) f8_store(1);
-  }
-  // Q^T operand: 8 k-steps of 16 d; this lane holds d = 16 s + 8 g .. + 7 of its row. Requested behind the first
-  // tiles so that the two latencies overlap (short key chunks are mostly prologue).
+  bf16x8 kf[4], vf[4];  // fragments under way: three ahead of the products
   bf16x8 qf[8];
+  // One step of the pipeline on three consecutive 32-key blocks: S^T of the next one (QK), numerators of the current one,
+  // O^T += V^T P^T of the previous one. QK: the step has a next block. K_CUR / K_NEXT: LDS offsets of the K block being
+  // read and of the one after it (likewise V); SECOND: the step works on a tile's second blocks and its last reads belong
+  // to the next ring slot. `extra(s)` runs between the products.
+  auto step = [&](auto qk, auto second, f32x16& s_next, const f32x16& s_cur, const bf16x8 (&p_prev)[2], bf16x8 (&p_cur)[2],
+                  unsigned turn_mask, auto extra) {
+    constexpr bool QK = decltype(qk)::value, SECOND = decltype(second)::value;
+    constexpr int CUR = SECOND ? 32 * 256 : 0, NEXT = SECOND ? 0 : 32 * 256;
+    float ps0 = 0.f, ps1 = 0.f, e0 = 0.f, e1 = 0.f;
+    f32x16 sn;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) sn[r] = 0.f;
+    float t0 = fmaf(s_cur[0], c2, nmc), t1 = fmaf(s_cur[1], c2, nmc);
+    auto pack = [&](int s) {
+      pack_pair(e0, e1, p_cur[s >> 2], 2 * (s & 3), ps0, ps1);
+    };
+    auto do_qk = [&](int s) {
+      if (QK) {
+        sn = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[s & 3], qf[s], sn, 0, 0, 0);
+        if (SECOND && s >= 5) k_addr[s - 5] ^= turn_mask;
+        kf[(s + 3) & 3] = s + 3 < 8 ? read_k(CUR, s + 3) : read_k(NEXT, s - 5);
+      }
+    };
+    auto do_pv = [&](int s) {
+      o[s & 3] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[s & 3], p_prev[s >> 2], o[s & 3], 0, 0, 0);
+      if (SECOND && s >= 5) v_addr[s - 5] ^= turn_mask;
+      vf[(s + 3) & 3] = s + 3 < 8 ? read_v(CUR, s + 3) : read_v(NEXT, s - 5);
+    };
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      const int s = i >> 1, f = (i >> 3) * 4 + (i & 3);  // products in fours: QK 0..3, PV 0..3, QK 4..7, PV 4..7
+      if (i & 4) do_pv(f);
+      else do_qk(f);
+      if (i & 1) {
+        e1 = __builtin_amdgcn_exp2f(t1);
+        if (s < 7) t1 = fmaf(s_cur[2 * s + 3], c2, nmc);
+        extra(s);
+      } else {
+        if (s > 0) pack(s - 1);
+        e0 = __builtin_amdgcn_exp2f(t0);
+        if (s < 7) t0 = fmaf(s_cur[2 * s + 2], c2, nmc);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    if (SECOND) {
+#pragma unroll
+      for (int s = 3; s < 8; ++s) k_addr[s] ^= turn_mask;
+      v_addr[3] ^= turn_mask;
+    }
+    pack(7);
+    if (QK) s_next = sn;
+    float psum = ps0 + ps1;
+    if (__any(psum > MF_RESCALE)) move_reference(s_cur, p_cur, psum);
+    l_run += psum;
+  };
+
+  // Tiles of this workgroup: n of them from t_begin. Pair p = (V of tile p, K of tile p + 1), counted from t_begin, sits in
+  // ring slot p & 3; the K of tile 0 in slot 3.
+  const int n = t_end - t_begin;
+  // Between the two steps of iteration `it`: pair it + 1 becomes visible to all wavefronts, and with it the slot of pair
+  // it - 1, which every wavefront has left, is free. Each pair is 4 requests per wavefront (the last one 2).
+  auto turn = [&](int it) {
+    if (it + 1 >= n) return;
+    if (it + 3 < n) __builtin_amdgcn_s_waitcnt(MF_VMCNT4);
+    else __builtin_amdgcn_s_waitcnt(MF_VMCNT0);
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+  };
+  // Widened pieces of pair p go to its slot: the slot's last readers passed the barrier before last. They are visible two
+  // barriers later; this wavefront's LDS operations complete in order, so its writes are done when fragments that it
+  // requested after them have arrived.
+  auto store_pending = [&](int p) {
+    if (F8 && p + 1 < n) store_k(t_begin + p + 1, pend, p & 3);
+    if (F8 && p < n) store_v(t_begin + p, pend, p & 3);
+  };
+  auto advance_both = [&]() {
+    advance(sk, ck, gk, st_kc0, st_kc1);
+    advance(sv, cv, gv, st_vc0, st_vc1);
+  };
+  // All requests of pair p, as far as its tiles exist.
+  auto request = [&](int p) {
+    if (p + 1 < n) request_k(p & 3);
+    if (p < n) request_v(p & 3);
+    advance_both();
+  };
+
+  // Masked tiles: the cache's last one if cut off, and the group's from this wavefront's diagonal on.
+  const int diag_tile = n_ct + (t_w_min + 1) / MF_BN;  // first with keys beyond t_w_min
+  auto masked = [&](int tile) { return tile == cache_tail || tile >= diag_tile; };
+  auto mask = [&](f32x16& st, int tile, int kb) {
+    const int lim = tile < n_ct ? a.c - 1 - tile * MF_BN : t_lane - (tile - n_ct) * MF_BN;
+    mask_block(st, lim - 32 * kb - 4 * g);
+  };
+  // this wavefront's last tile (relative; -1: no rows)
+  const int last = wave_live ? min(n, n_ct + t_w_max / MF_BN + 1 - t_begin) - 1 : -1;
+
 #pragma unroll
   for (int s = 0; s < 8; ++s) qf[s] = __builtin_bit_cast(bf16x8, *(const u32x4*)(qrow + 16 * s + 8 * g));
-  // The Q fragments must have arrived before the loop: from there on the only vector-memory operations in flight
-  // are the tile requests, which the compiler does not see (it would otherwise re-wait for "pending" Q loads
-  // inside the loop and drain the tile requests with them).
+  request_k(3);
+  advance(sk, ck, gk, st_kc0, st_kc1);
+  if (F8) {
+    // tiles go through registers one after the other; pair 2 stays pending
+    const Pieces first = pend;
+    request(0);
+    const Pieces p0 = pend;
+    request(1);
+    const Pieces p1 = pend;
+    request(2);
+    store_k(t_begin, first, 3);
+    if (n > 1) store_k(t_begin + 1, p0, 0);
+    store_v(t_begin, p0, 0);
+    if (n > 2) store_k(t_begin + 2, p1, 1);
+    if (n > 1) store_v(t_begin + 1, p1, 1);
+  } else {
+    request(0);
+    request(1);
+    request(2);
+  }
+  // Everything requested so far has to be here: from now on the only vector-memory operations in flight are the tile
+  // requests, which the compiler does not see.
   __builtin_amdgcn_s_waitcnt(MF_VMCNT0);
   __syncthreads();
 
-  {
-    int slot = 0, slot2 = 2;  // ring positions of tile and tile + 2
-    for (int tile = t_begin; tile < t_end; ++tile) {
-      // slot of tile+2 = slot of tile-1: every wavefront finished reading it before the last barrier
-      if (tile + 2 < t_end) QP_STAGE(tile + 2, slot2)
-      QP_TILE_VIEW(tile)
-      if (live) {
-        const unsigned char* kt = smem + slot * MF_SLOT;
-        f32x16 st[2];
-        bf16x8 pf[4];
-        qk_tile(kt, k_addr, qf, st);
-        softmax_tile(st, need_mask, lim_local, g, c2, lazy, m_run, l_run, o, pf);
-        pv_tile(kt + MF_TILE, v_addr, pf, o);
-      }
-      if (F8) {
-        // the pending 8-bit tile was requested a whole tile ago: widen it into its slot (last read before the
-        // previous barrier); every request, direct ones included, is awaited here
-        if (tile + 2 < t_end && tile + 2 < n_ct) f8_store(slot2);
-        __builtin_amdgcn_s_waitcnt(MF_VMCNT0);
-      } else {
-        // this wavefront's part of the next tile has landed in LDS (the tile after it may still be in flight)
-        if (tile + 2 < t_end) __builtin_amdgcn_s_waitcnt(MF_VMCNT4);
-        else __builtin_amdgcn_s_waitcnt(MF_VMCNT0);
-      }
-      __syncthreads();
-      slot = slot == STAGES - 1 ? 0 : slot + 1;
-      slot2 = slot2 == STAGES - 1 ? 0 : slot2 + 1;
+  int it = 0;
+  if (last >= 0) {
+    f32x16 sa, sb;  // S^T of the tile's two blocks
+    bf16x8 pa[2], pb[2];
+#pragma unroll
+    for (int r = 0; r < 16; ++r) sa[r] = sb[r] = 0.f;
+#pragma unroll
+    for (int s = 0; s < 8; ++s) {
+      sa = __builtin_amdgcn_mfma_f32_32x32x16_bf16(read_k(3 * MF_TILE, s), qf[s], sa, 0, 0, 0);
+      sb = __builtin_amdgcn_mfma_f32_32x32x16_bf16(read_k(3 * MF_TILE + 32 * 256, s), qf[s], sb, 0, 0, 0);
+    }
+#pragma unroll
+    for (int s = 0; s < 3; ++s) {
+      kf[s] = read_k(0, s);
+      vf[s] = read_v(0, s);
+    }
+    if (masked(t_begin)) {
+      mask(sa, t_begin, 0);
+      mask(sb, t_begin, 1);
+    }
+    {
+      float psum;
+      move_reference(sa, pa, psum);
+      l_run += psum;
+    }
+    // While the pairs to be stored and requested are whole (and, over an 8-bit cache, cache tiles), that work is spread
+    // over a step: issued together, the requests hold the wavefront up until the address path has taken those of all
+    // wavefronts.
+    const int whole = min(last, (F8 ? min(n, n_ct - t_begin) : n) - 4);
+    while (it < whole) {
+      const unsigned turn_mask = (it & 1) ? 3 * MF_TILE : MF_TILE;  // slot it & 3 -> slot (it + 1) & 3
+      step(true_type(), false_type(), sa, sb, pa, pb, 0u, [&](int s) {
+        if (F8 && (s & 1)) {
+          store_piece(s >> 1, pend.p[s >> 1], (it + 2) & 3);
+          pend.p[s >> 1] = load_piece(s >> 1);
+        }
+      });
+      turn(it);
+      const unsigned dst = st_lds + ((it + 3) & 3) * MF_TILE;
+      ++it;
+      if (masked(t_begin + it)) mask(sa, t_begin + it, 0);
+      step(true_type(), true_type(), sb, sa, pb, pa, turn_mask, [&](int s) {
+        if (!F8 && (s & 1)) request_half(s >> 1, dst);
+      });
+      advance_both();
+      if (masked(t_begin + it)) mask(sb, t_begin + it, 1);
+    }
+    while (it < last) {
+      const unsigned turn_mask = (it & 1) ? 3 * MF_TILE : MF_TILE;
+      step(true_type(), false_type(), sa, sb, pa, pb, 0u, [](int) {});
+      store_pending(it + 2);
+      turn(it);
+      request(it + 3);
+      ++it;
+      if (masked(t_begin + it)) mask(sa, t_begin + it, 0);
+      step(true_type(), true_type(), sb, sa, pb, pa, turn_mask, [](int) {});
+      if (masked(t_begin + it)) mask(sb, t_begin + it, 1);
+    }
+    step(false_type(), false_type(), sa, sb, pa, pb, 0u, [](int) {});
+#pragma unroll
+    for (int s = 0; s < 8; ++s) {
+      if (s > 0 && s + 2 < 8) vf[(s + 2) & 3] = read_v(32 * 256, s + 2);
+      o[s & 3] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[s & 3], pb[s >> 2], o[s & 3], 0, 0, 0);
     }
   }
-#undef QP_STAGE
-#undef QP_ISSUE
-#undef QP_TILE_VIEW
+  for (; it + 1 < n; ++it) {
+    store_pending(it + 2);
+    if (F8) __builtin_amdgcn_s_waitcnt(MF_LGKM0);
+    turn(it);
+    request(it + 3);
+  }
 
   if (!wave_live) return;
   const float l_tot = sum_halves(l_run);
@@ -659,9 +796,9 @@ static void set_lds_limit() {
   const int dev = current_device();
   if (dev >= 0 && attr_set[dev]) return;
   (void)hipFuncSetAttribute((const void*)attend_mfma_kernel<false>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                            MF_STAGES * MF_SLOT);
+                            MF_LDS);
   (void)hipFuncSetAttribute((const void*)attend_mfma_kernel<true>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                            MF_STAGES * MF_SLOT);
+                            MF_LDS);
   if (dev >= 0) attr_set[dev] = true;
 }
 
@@ -682,9 +819,9 @@ void launch_attend_mfma_run(const AttendArgs& a_in, hipStream_t s) {
     wgs = (items + per - 1) / per * 8;
   }
   if (a.cache_fp8)
-    hipLaunchKernelGGL(attend_mfma_kernel<true>, dim3((unsigned)wgs), dim3(MF_NT), MF_STAGES * MF_SLOT, s, a);
+    hipLaunchKernelGGL(attend_mfma_kernel<true>, dim3((unsigned)wgs), dim3(MF_NT), MF_LDS, s, a);
   else
-    hipLaunchKernelGGL(attend_mfma_kernel<false>, dim3((unsigned)wgs), dim3(MF_NT), MF_STAGES * MF_SLOT, s, a);
+    hipLaunchKernelGGL(attend_mfma_kernel<false>, dim3((unsigned)wgs), dim3(MF_NT), MF_LDS, s, a);
 }
 
 void launch_attend_mfma(const AttendArgs& a_in, void* split_ws, size_t split_ws_bytes, hipStream_t s) {
@@ -703,9 +840,9 @@ void launch_attend_mfma(const AttendArgs& a_in, void* split_ws, size_t split_ws_
     a.part_lse = a.part_o + (size_t)p.n_split * a.h_kv * a.part_rows * MF_D;
   }
   if (a.cache_fp8)
-    hipLaunchKernelGGL(attend_mfma_kernel<true>, dim3(p.workgroups), dim3(MF_NT), MF_STAGES * MF_SLOT, s, a);
+    hipLaunchKernelGGL(attend_mfma_kernel<true>, dim3(p.workgroups), dim3(MF_NT), MF_LDS, s, a);
   else
-    hipLaunchKernelGGL(attend_mfma_kernel<false>, dim3(p.workgroups), dim3(MF_NT), MF_STAGES * MF_SLOT, s, a);
+    hipLaunchKernelGGL(attend_mfma_kernel<false>, dim3(p.workgroups), dim3(MF_NT), MF_LDS, s, a);
   if (p.n_split > 1) launch_attend_merge(a, s);
 }
 

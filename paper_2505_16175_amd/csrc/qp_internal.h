@@ -103,7 +103,20 @@ __device__ __forceinline__ void lds_dma16(const unsigned char* base, unsigned by
       : "v"(byte_off), "s"(base), "s"(lds_addr)
       : "memory", "m0");
 }
+// The same for a caller that keeps LDS byte addresses itself (wave-uniform).
+__device__ __forceinline__ void lds_dma16_to(const unsigned char* base, unsigned byte_off, unsigned lds_addr) {
+  asm volatile(
+      "s_mov_b32 m0, %2\n\t"
+      "s_nop 0\n\t"
+      "global_load_lds_dwordx4 %0, %1"
+      :
+      : "v"(byte_off), "s"(base), "s"(lds_addr)
+      : "memory", "m0");
+}
 #pragma clang diagnostic pop
+__device__ __forceinline__ unsigned lds_address(unsigned char* p) {
+  return (unsigned)(size_t)(__attribute__((address_space(3))) unsigned char*)p;
+}
 
 // Arguments common to the attention kernels. All pointers are device pointers.
 struct AttendArgs {

@@ -153,6 +153,39 @@ def test_group_attend_last_round_split(h_q, h_kv, n_g, c, fp8):
 
 
 @pytest.mark.gpu
+@pytest.mark.parametrize("profile", ["up", "jump", "down"])
+@pytest.mark.parametrize("c,fp8", [(0, False), (1, False), (32, False), (65, False), (192, False), (256, False), (257, False),
+                                   (333, False), (33, True), (256, True), (257, True), (384, True), (450, True)])
+def test_group_attend_moving_reference(profile, c, fp8):
+    """Logits that climb by 195 powers of two along the keys (slowly, so that the reference of a row's numerators moves
+    again and again, or in one jump that overflows them) or fall by as much; one tile up to several turns of the tile ring,
+    caches that end inside and at the end of a 32-key block."""
+    h_q, h_kv, d, n_g = 14, 2, 128, 70
+    g = torch.Generator().manual_seed(c + len(profile))
+    mk = lambda *s: torch.randn(*s, generator=g)
+    x = torch.arange(c + n_g) / (c + n_g - 1)
+    amp = {"up": 12 * x, "down": 12 - 12 * x, "jump": 12.0 * (x > 0.6)}[profile]     # logit: about amp * 11.3
+    keys = amp[None, :, None] + 0.1 * mk(h_kv, c + n_g, d)
+    q = (1 + 0.05 * mk(n_g, h_q, d)).bfloat16()
+    k = keys[:, c:].transpose(0, 1).contiguous().bfloat16()
+    v, ck, cv = mk(n_g, h_kv, d).bfloat16(), keys[:, :c].bfloat16(), mk(h_kv, c, d).bfloat16()
+    layout = B.make_layout(h_q, h_kv, d, "bf16")
+    cache = B.Cache(layout, c + 3, fmt=B.QP_CACHE_FP8_E4M3 if fp8 else B.QP_CACHE_SAME)
+    if fp8:
+        ck, cv = ck.to(torch.float8_e4m3fn), cv.to(torch.float8_e4m3fn)
+    cache.k[:, :c].copy_(ck)
+    cache.v[:, :c].copy_(cv)
+    cache.c.len = c
+    want, want_lse = O.attend_group(_f64(q), _f64(k), _f64(v), _f64(ck.float()), _f64(cv.float()), return_lse=True)
+    out = torch.full((n_g, h_q, d), float("nan"), dtype=torch.bfloat16, device=DEV)
+    lse = torch.full((h_q, n_g), float("nan"), dtype=torch.float32, device=DEV)
+    B.group_attend(layout, q.to(DEV), k.to(DEV), v.to(DEV), cache if c > 0 else None, out, lse)
+    torch.cuda.synchronize()
+    assert_attn_close(_f64(out), want, "bf16", profile)
+    np.testing.assert_allclose(_f64(lse), want_lse, rtol=2e-5, atol=2e-3)
+
+
+@pytest.mark.gpu
 def test_group_attend_key_split_at_the_chunk_limit():
     """One workgroup's worth of rows against 24566 cache entries: the large kernel splits into its maximum of 128
     chunks, and the merge kernel takes two batches per wavefront."""
