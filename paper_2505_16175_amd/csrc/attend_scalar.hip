@@ -1,26 +1,50 @@
-// Scalar (non-MFMA) group attention: f32 and bf16 inputs, f32 arithmetic.
+// Group attention without the matrix pipe: f32 and bf16 inputs, f32 arithmetic. It serves f32 (the tiny clips) and the
+// layouts that the MFMA kernel does not take.
 //
-// One wavefront owns one query row (token i of query head qh). Its 64 lanes take the
-// visible keys round-robin (lane l: keys l, l+64, ...), each lane running its own online
-// softmax (running max m, denominator l, d accumulators); the 64 partial states are
-// merged once at the end. The visible keys of a row are the C cache entries of its KV head
-// followed by group tokens 0..i (Sec. 3.2: pruned cache + own group, causal).
+// A wavefront, or with few rows over a long cache the workgroup's four (SPLIT), batch by batch in turn, own one query row
+// (token i of query head qh). The visible keys of a row are the C cache entries of its
+// KV head followed by group tokens 0..i (Sec. 3.2: pruned cache + own group, causal). A key row is spread over LPR lanes of
+// 16 bytes each, so that a load instruction reads 64 / LPR whole rows; each of these lane groups runs its own online
+// softmax (running max m, denominator l, this lane's slice of the weighted sum), and the groups are merged once at the end.
 //
-// This kernel is the f32 path (tiny config) and the fallback for layouts the MFMA kernel
-// does not take; it is not tuned.
+// Such calls are small: what they cost is latency, one memory round trip per batch of keys. A batch is UNROLL keys per
+// lane group (32 keys), its K and V are requested together and one batch ahead. With one key per lane (every load
+// instruction touching 64 rows, both tensors of a key one after the other, and the merge of 64 states by shuffles) the
+// video of eight f32 frames of 16 tokens, 4 heads of 64, took 21.8 us, now 15.3; 48 frames of 32 in groups of 8, 217 and 96;
+// 2048 tokens of 28 heads over 10,000 entries 34.3 and 13.4 ms; 512 bf16 ones over 4,000 1762 and 896 us.
 #include "qp_internal.h"
 
 namespace qp {
 
-template <typename T, int D>
-__global__ __launch_bounds__(256) void attend_scalar_kernel(AttendArgs a) {
-  constexpr int WAVES = 4;
-  constexpr int PER = Elem<T>::kPer16B;   // elements per 16-byte chunk
-  constexpr int CHUNKS = D / PER;
-  __shared__ float q_lds[WAVES][D];
+template <int CTRL>
+__device__ __forceinline__ float dpp_add(float x) {  // x + the value of the lane that CTRL names
+  return x + __uint_as_float((unsigned)__builtin_amdgcn_update_dpp(0, (int)__float_as_uint(x), CTRL, 0xf, 0xf, true));
+}
+// Sum over aligned groups of LANES lanes, in every lane. The mirrors pair equal partial sums of the halves.
+template <int LANES>
+__device__ __forceinline__ float group_sum(float x) {
+  static_assert(LANES == 8 || LANES == 16 || LANES == 32, "lanes per row");
+  x = dpp_add<0xB1>(x);                    // quad_perm 1,0,3,2
+  x = dpp_add<0x4E>(x);                    // quad_perm 2,3,0,1
+  x = dpp_add<0x141>(x);                   // row_half_mirror
+  if (LANES >= 16) x = dpp_add<0x140>(x);  // row_mirror
+  if (LANES >= 32) x += __shfl_xor(x, 16, 64);
+  return x;
+}
+
+constexpr int WAVES = 4;
+
+template <typename T, int D, bool SPLIT>
+__global__ __launch_bounds__(WAVES * 64) void attend_scalar_kernel(AttendArgs a) {
+  constexpr int PER = Elem<T>::kPer16B;  // elements per 16-byte chunk
+  constexpr int LPR = D / PER;           // lanes per key row
+  constexpr int GROUPS = 64 / LPR;       // keys per load instruction
+  constexpr int UNROLL = 32 / PER;       // keys per lane group and batch
+  constexpr int BATCH = GROUPS * UNROLL;
+  constexpr int STRIDE = SPLIT ? WAVES * BATCH : BATCH;
 
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int i = blockIdx.x * WAVES + wave;  // group token (query row)
+  const int sub = lane % LPR, lg = lane / LPR;
   const int qh = blockIdx.y;
   const int r = a.h_q / a.h_kv;
   const int h = qh / r;
@@ -33,102 +57,156 @@ __global__ __launch_bounds__(256) void attend_scalar_kernel(AttendArgs a) {
     a.c += blockIdx.z * a.keep;
     if ((int)blockIdx.z == a.groups - 1) a.n_g = a.n_last;
   }
-  const bool active = i < a.n_g;            // whole wave agrees
-
-  if (active) {
-    const T* qrow = (const T*)a.q + ((size_t)i * a.h_q + qh) * D;
-    for (int c = lane; c < CHUNKS; c += 64) {
-      uint4 raw = *(const uint4*)(qrow + c * PER);
-      float tmp[PER];
-      widen16<T>(raw, tmp);
-#pragma unroll
-      for (int e = 0; e < PER; ++e) q_lds[wave][c * PER + e] = tmp[e];
-    }
-  }
-  __syncthreads();
-  if (!active) return;
-
-  float m = -INFINITY, l = 0.f;
-  float acc[D];
-#pragma unroll
-  for (int c = 0; c < D; ++c) acc[c] = 0.f;
+  const int part = SPLIT ? wave : 0;                            // this wavefront's share of the row's batches
+  const int i = SPLIT ? blockIdx.x : blockIdx.x * WAVES + wave;  // group token (query row)
+  if (i >= a.n_g) return;  // whole wavefront; the whole workgroup if SPLIT
 
   const int n_keys = a.c + i + 1;
-  const T* ck = (const T*)a.ck + (size_t)h * a.cap * D;
-  const T* cv = (const T*)a.cv + (size_t)h * a.cap * D;
-  const T* gk = (const T*)a.k + (size_t)h * D;
-  const T* gv = (const T*)a.v + (size_t)h * D;
+  const T* ck = (const T*)a.ck + (size_t)h * a.cap * D + sub * PER;
+  const T* cv = (const T*)a.cv + (size_t)h * a.cap * D + sub * PER;
+  const T* gk = (const T*)a.k + (size_t)h * D + sub * PER;
+  const T* gv = (const T*)a.v + (size_t)h * D + sub * PER;
   const size_t gstride = (size_t)a.h_kv * D;
 
-  for (int j = lane; j < n_keys; j += 64) {
-    const T* krow;
-    const T* vrow;
-    if (j < a.c) {
-      krow = ck + (size_t)j * D;
-      vrow = cv + (size_t)j * D;
-    } else {
-      krow = gk + (size_t)(j - a.c) * gstride;
-      vrow = gv + (size_t)(j - a.c) * gstride;
+  uint4 kr[UNROLL], vr[UNROLL];
+  auto request = [&](int j0) {  // this lane's chunks of the batch of keys from j0; keys past the end: the last one again
+#pragma unroll
+    for (int u = 0; u < UNROLL; ++u) {
+      const int j = min(j0 + u * GROUPS + lg, n_keys - 1);
+      const bool cached = j < a.c;
+      kr[u] = *(const uint4*)(cached ? ck + (size_t)j * D : gk + (size_t)(j - a.c) * gstride);
+      vr[u] = *(const uint4*)(cached ? cv + (size_t)j * D : gv + (size_t)(j - a.c) * gstride);
     }
-    float s = 0.f;
+  };
+  request(part * BATCH);
+  float q[PER];
+  widen16<T>(*(const uint4*)((const T*)a.q + ((size_t)i * a.h_q + qh) * D + sub * PER), q);
+
+  float m = -INFINITY, l = 0.f;
+  float acc[PER];
 #pragma unroll
-    for (int c = 0; c < CHUNKS; ++c) {
-      uint4 raw = *(const uint4*)(krow + c * PER);
-      float kv[PER];
-      widen16<T>(raw, kv);
+  for (int e = 0; e < PER; ++e) acc[e] = 0.f;
+
+  for (int j0 = part * BATCH; j0 < n_keys; j0 += STRIDE) {
+    uint4 vc[UNROLL];
+    float s[UNROLL], mb = -INFINITY;
 #pragma unroll
-      for (int e = 0; e < PER; ++e) s = fmaf(q_lds[wave][c * PER + e], kv[e], s);
+    for (int u = 0; u < UNROLL; ++u) {
+      float kv[PER], dot = 0.f;
+      widen16<T>(kr[u], kv);
+#pragma unroll
+      for (int e = 0; e < PER; ++e) dot = fmaf(q[e], kv[e], dot);
+      s[u] = dot;
+      vc[u] = vr[u];
     }
-    s *= a.scale_log2;
-    if (s > m) {
-      const float alpha = exp2f(m - s);    // exp2(-inf) = 0 on the first key
-      l *= alpha;
+    if (j0 + STRIDE < n_keys) request(j0 + STRIDE);
 #pragma unroll
-      for (int c = 0; c < D; ++c) acc[c] *= alpha;
-      m = s;
+    for (int u = 0; u < UNROLL; ++u) {
+      s[u] = group_sum<LPR>(s[u]);
+      mb = fmaxf(mb, s[u] * a.scale_log2);  // a key past the end is the last one again: its logit may set the reference
     }
-    const float p = exp2f(s - m);
-    l += p;
+    const float m_new = fmaxf(m, mb);
+    const float ref = m_new == -INFINITY ? 0.f : m_new;  // a lane group without a key so far: all its weights are 0
+    const float alpha = exp2f(m - ref);                  // exp2(-inf) = 0 on the first keys
+    m = m_new;
+    // the batch is summed by itself, in pairs, so that the running sums take one addition per batch and their rounding
+    // stays what it was with a key per lane
+    float p[UNROLL], t[UNROLL][PER];
 #pragma unroll
-    for (int c = 0; c < CHUNKS; ++c) {
-      uint4 raw = *(const uint4*)(vrow + c * PER);
-      float vv[PER];
-      widen16<T>(raw, vv);
-#pragma unroll
-      for (int e = 0; e < PER; ++e) acc[c * PER + e] = fmaf(p, vv[e], acc[c * PER + e]);
+    for (int u = 0; u < UNROLL; ++u) {
+      // the scaled logit is not rounded before the reference is taken off
+      p[u] = exp2f(fmaf(s[u], a.scale_log2, -ref));
+      widen16<T>(vc[u], t[u]);
     }
+    if (j0 + BATCH > n_keys) {  // the row's last batch: keys past the end weigh nothing, whatever the last one holds
+#pragma unroll
+      for (int u = 0; u < UNROLL; ++u)
+        if (j0 + u * GROUPS + lg >= n_keys) {
+          p[u] = 0.f;
+#pragma unroll
+          for (int e = 0; e < PER; ++e) t[u][e] = 0.f;
+        }
+    }
+#pragma unroll
+    for (int u = 0; u < UNROLL; u += 2)
+#pragma unroll
+      for (int e = 0; e < PER; ++e) t[u][e] = fmaf(p[u + 1], t[u + 1][e], p[u] * t[u][e]);
+#pragma unroll
+    for (int w = 1; w < UNROLL; w *= 2)
+#pragma unroll
+      for (int u = 0; u < UNROLL; u += 2 * w) {
+        p[u] += p[u + w];
+        if (w > 1)
+#pragma unroll
+          for (int e = 0; e < PER; ++e) t[u][e] += t[u + w][e];
+      }
+    l = fmaf(l, alpha, p[0]);
+#pragma unroll
+    for (int e = 0; e < PER; ++e) acc[e] = fmaf(acc[e], alpha, t[0][e]);
   }
 
-  // merge the 64 lane states
-  const float mw = wave_max(m);             // finite: every row sees at least itself
-  const float f = exp2f(m - mw);            // lanes without keys: exp2(-inf) = 0
-  const float lw = wave_sum(l * f);
-  const float inv = 1.f / lw;
-  constexpr int OUT_PER_LANE = (D + 63) / 64;
-  float o[OUT_PER_LANE];
+  // merge the lane groups' states
+  float mw = m;
 #pragma unroll
-  for (int c = 0; c < D; ++c) {
-    const float t = wave_sum(acc[c] * f);
-    if (lane == (c & 63)) o[c >> 6] = t * inv;
+  for (int o = LPR; o < 64; o <<= 1) mw = fmaxf(mw, __shfl_xor(mw, o, 64));
+  const float ref = mw == -INFINITY ? 0.f : mw;  // a wavefront without keys (only beside others of its row)
+  const float f = exp2f(m - ref);                // lane groups without keys: exp2(-inf) = 0
+  l *= f;
+#pragma unroll
+  for (int e = 0; e < PER; ++e) acc[e] *= f;
+#pragma unroll
+  for (int o = LPR; o < 64; o <<= 1) {
+    l += __shfl_xor(l, o, 64);
+#pragma unroll
+    for (int e = 0; e < PER; ++e) acc[e] += __shfl_xor(acc[e], o, 64);
   }
   T* orow = (T*)a.out + ((size_t)i * a.h_q + qh) * D;
+  if constexpr (!SPLIT) {
+    if (lg == 0)
 #pragma unroll
-  for (int e = 0; e < OUT_PER_LANE; ++e) {
-    const int c = e * 64 + lane;
-    if (c < D) store_elem<T>(orow + c, o[e]);
+      for (int e = 0; e < PER; ++e) store_elem<T>(orow + sub * PER + e, acc[e] / l);
+  } else {  // and those of the row's wavefronts
+    __shared__ float part_acc[WAVES][D], part_m[WAVES], part_l[WAVES];
+    if (lg == 0)
+#pragma unroll
+      for (int e = 0; e < PER; ++e) part_acc[wave][sub * PER + e] = acc[e];
+    if (lane == 0) part_m[wave] = mw, part_l[wave] = l;
+    __syncthreads();
+    mw = part_m[0];  // finite: the first batch has a key
+#pragma unroll
+    for (int w = 1; w < WAVES; ++w) mw = fmaxf(mw, part_m[w]);
+    float o = 0.f;
+    l = 0.f;
+#pragma unroll
+    for (int w = 0; w < WAVES; ++w) {
+      const float wgt = exp2f(part_m[w] - mw);  // 0 for a wavefront without keys
+      l = fmaf(wgt, part_l[w], l);
+      o = fmaf(wgt, part_acc[w][threadIdx.x % D], o);
+    }
+    if (threadIdx.x < D) store_elem<T>(orow + threadIdx.x, o / l);
   }
-  if (a.lse != nullptr && lane == 0) a.lse[(size_t)qh * a.n_g + i] = (mw + log2f(lw)) * 0.6931471805599453f;
+  if (a.lse != nullptr && lane == 0 && part == 0) a.lse[(size_t)qh * a.n_g + i] = (mw + log2f(l)) * 0.6931471805599453f;
+}
+
+// Rows that would leave SIMDs idle are split over a workgroup, for caches of several batches: us unsplit / split, f32 d=64,
+// 4 rows over 300 entries 14.7 / 7.6, 256 over 1000 47 / 13, 800 over 1000 54 / 39, 1600 over 1000 70 / 68; with rows
+// enough the wavefronts of a workgroup are better off reading the same keys: 57,344 over 10,000 12.7 / 17.4 ms.
+// Groups of a run never are, so that a row's arithmetic does not depend on how many groups share the launch.
+constexpr int SPLIT_FROM = 256;
+
+template <typename T, int D>
+static void launch_scalar(const AttendArgs& a, hipStream_t s) {
+  const unsigned groups = a.groups > 1 ? a.groups : 1;
+  if (groups == 1 && a.c >= SPLIT_FROM && (long)a.n_g * a.h_q <= 4 * device_cu_count())
+    hipLaunchKernelGGL((attend_scalar_kernel<T, D, true>), dim3(a.n_g, a.h_q), dim3(WAVES * 64), 0, s, a);
+  else
+    hipLaunchKernelGGL((attend_scalar_kernel<T, D, false>), dim3((a.n_g + WAVES - 1) / WAVES, a.h_q, groups), dim3(WAVES * 64), 0,
+                       s, a);
 }
 
 void launch_attend_scalar(const AttendArgs& a, int dtype, hipStream_t s) {
-  dim3 grid((a.n_g + 3) / 4, a.h_q, a.groups > 1 ? a.groups : 1), block(256);
-  if (dtype == QP_F32) {
-    if (a.d == 64) hipLaunchKernelGGL((attend_scalar_kernel<float, 64>), grid, block, 0, s, a);
-    else hipLaunchKernelGGL((attend_scalar_kernel<float, 128>), grid, block, 0, s, a);
-  } else {
-    if (a.d == 64) hipLaunchKernelGGL((attend_scalar_kernel<bf16_t, 64>), grid, block, 0, s, a);
-    else hipLaunchKernelGGL((attend_scalar_kernel<bf16_t, 128>), grid, block, 0, s, a);
-  }
+  if (dtype == QP_F32) a.d == 64 ? launch_scalar<float, 64>(a, s) : launch_scalar<float, 128>(a, s);
+  else a.d == 64 ? launch_scalar<bf16_t, 64>(a, s) : launch_scalar<bf16_t, 128>(a, s);
 }
 
 }  // namespace qp

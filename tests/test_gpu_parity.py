@@ -153,6 +153,34 @@ def test_group_attend_last_round_split(h_q, h_kv, n_g, c, fp8):
 
 
 @pytest.mark.gpu
+@pytest.mark.parametrize("dtype,d", [("f32", 64), ("f32", 128), ("bf16", 64), ("bf16", 128)])
+@pytest.mark.parametrize("n_g,c", [(1, 255), (1, 256), (1, 257), (31, 290), (3, 381), (5, 1023), (256, 256), (257, 256)])
+def test_group_attend_rows_shared_by_a_workgroup(dtype, d, n_g, c):
+    """The scalar kernel's rows over four wavefronts: batches of 32 keys that end inside, at and behind a wavefront's turn,
+    both sides of the rule (256 entries, 1024 rows), sharp and flat rows."""
+    h_q, h_kv = 4, 2
+    g = torch.Generator().manual_seed(n_g * 5000 + c)
+    tdt = torch.float32 if dtype == "f32" else torch.bfloat16
+    mk = lambda *s: torch.randn(*s, generator=g)
+    q = (mk(n_g, h_q, d) * torch.tensor([0.1, 1.0, 3.0, 6.0])[:, None]).to(tdt)
+    k, v, ck, cv = (mk(*s).to(tdt) for s in ((n_g, h_kv, d), (n_g, h_kv, d), (h_kv, c, d), (h_kv, c, d)))
+    want, want_lse = O.attend_group(_f64(q), _f64(k), _f64(v), _f64(ck), _f64(cv), return_lse=True)
+    layout = B.make_layout(h_q, h_kv, d, dtype)
+    cache = B.Cache(layout, c + 3)
+    cache.k[:, :c].copy_(ck)
+    cache.v[:, :c].copy_(cv)
+    cache.c.len = c
+    B.select_attend_kernel(B.QP_ATTEND_SCALAR)
+    out = torch.full((n_g, h_q, d), float("nan"), dtype=tdt, device=DEV)
+    lse = torch.full((h_q, n_g), float("nan"), dtype=torch.float32, device=DEV)
+    B.group_attend(layout, q.to(DEV), k.to(DEV), v.to(DEV), cache, out, lse)
+    torch.cuda.synchronize()
+    assert_attn_close(_f64(out), want, dtype)
+    # logits of up to ~60, f32 dot products of 128 terms: |error| <= 128 * 2^-24 * sum |q k| / sqrt(d) < 3e-4, 1e-5 relative
+    np.testing.assert_allclose(_f64(lse), want_lse, rtol=2e-5, atol=2e-5)
+
+
+@pytest.mark.gpu
 @pytest.mark.parametrize("profile", ["up", "jump", "down"])
 @pytest.mark.parametrize("c,fp8", [(0, False), (1, False), (32, False), (65, False), (192, False), (256, False), (257, False),
                                    (333, False), (33, True), (256, True), (257, True), (384, True), (450, True)])
