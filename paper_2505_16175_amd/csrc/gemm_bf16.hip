@@ -16,8 +16,8 @@
 // and the fragment reads (32 rows x 16 bytes per half wavefront) conflict-free.
 // Wavefront (wm, wn) of the 2 x 4 arrangement computes 128 tokens x 64 outputs as 4 x 2 blocks of
 // v_mfma_f32_32x32x16_bf16 with the WEIGHT rows as the A operand and the token rows as B, so that a lane ends
-// up with one token (m = lane & 31) and, per block, 16 outputs in runs of 4: stores are 8-byte runs of a token's
-// row, and the fused steps below only ever combine values of the same lane:
+// up with one token (m = lane & 31) and, per block, 16 outputs in runs of 4: the fused steps below
+// only ever combine values of the same lane:
 //   * QKV_ROPE: the 256 tile columns are two heads; wavefront wn serves head wn >> 1 and, of its 128 dims, the
 //     32 dims [32 (wn & 1), +32) in block 0 and their rotary partners (+64) in block 1. The weight rows are
 //     fetched into LDS in that order (a permutation inside the tile, contiguous in runs of 32 rows).
@@ -327,122 +327,7 @@ __global__ __launch_bounds__(T::NW * 64) void gemm_bf16_kernel(GemmArgs a) {
       }
     return;
   }
-  // A residual (and the rotary angles below) is loaded for a whole block before the block's first store: the compiler
-  // cannot move the loads over stores that might alias (the residual may be the output), and one memory latency per
-  // 8-byte run had cost 17 us per 256 x 256 tile (72B o_proj at 4096 tokens, two tiles per CU: 499 -> 455 us). Without a
-  // residual nothing is awaited between the stores. As one code, with zeros for the missing residual, the registers were
-  // a merge of loads and zeros, for which the compiler waits until all loads and stores before are complete: 4096 x 3584 x
-  // 256 34 -> 22 us, 3000 x 4608 x 3584 96 -> 87 (with a residual 36 -> 33 and 99 -> 97).
-  if (MODE == GEMM_PLAIN) {
-    const bf16_t* bias = (const bf16_t*)a.bias;
-    const bf16_t* res = (const bf16_t*)a.residual;
-    bf16_t* out = (bf16_t*)a.out;
-    if (res == nullptr) {
-#pragma unroll
-      for (int j = 0; j < 2; ++j)
-#pragma unroll
-        for (int q4 = 0; q4 < 4; ++q4) {
-          const int n = n0 + wn * 64 + j * 32 + 8 * q4 + 4 * g;
-          if (n >= a.n) continue;
-          float b[4] = {0.f, 0.f, 0.f, 0.f};
-          if (bias != nullptr) {  // widened in the branch, for the same reason
-            const uint2 raw = *(const uint2*)(bias + n);
-            b[0] = bf16lo_to_f32(raw.x), b[1] = bf16hi_to_f32(raw.x), b[2] = bf16lo_to_f32(raw.y), b[3] = bf16hi_to_f32(raw.y);
-          }
-#pragma unroll
-          for (int i = 0; i < T::MI; ++i) {
-            const int m = m0 + wm * (32 * T::MI) + i * 32 + l32;
-            if (m >= a.m) continue;
-            bf16x4 pk;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) pk[e] = (__bf16)((acc[j][i][4 * q4 + e] + b[e]) + 0.f);
-            *(uint2*)(out + (size_t)m * a.n + n) = __builtin_bit_cast(uint2, pk);
-          }
-        }
-      return;
-    }
-#pragma unroll
-    for (int j = 0; j < 2; ++j) {
-      uint2 bv[4], rv[4][T::MI];
-#pragma unroll
-      for (int q4 = 0; q4 < 4; ++q4) {
-        const int n = min(n0 + wn * 64 + j * 32 + 8 * q4 + 4 * g, a.n - 4);
-        bv[q4] = bias != nullptr ? *(const uint2*)(bias + n) : make_uint2(0u, 0u);
-#pragma unroll
-        for (int i = 0; i < T::MI; ++i)
-          rv[q4][i] = *(const uint2*)(res + (size_t)min(m0 + wm * (32 * T::MI) + i * 32 + l32, a.m - 1) * a.n + n);
-      }
-#pragma unroll
-      for (int q4 = 0; q4 < 4; ++q4) {
-        const int n = n0 + wn * 64 + j * 32 + 8 * q4 + 4 * g;
-        if (n >= a.n) continue;
-        const float b[4] = {bf16lo_to_f32(bv[q4].x), bf16hi_to_f32(bv[q4].x), bf16lo_to_f32(bv[q4].y), bf16hi_to_f32(bv[q4].y)};
-#pragma unroll
-        for (int i = 0; i < T::MI; ++i) {
-          const int m = m0 + wm * (32 * T::MI) + i * 32 + l32;
-          if (m >= a.m) continue;
-          const uint2 raw = rv[q4][i];
-          const float r[4] = {bf16lo_to_f32(raw.x), bf16hi_to_f32(raw.x), bf16lo_to_f32(raw.y), bf16hi_to_f32(raw.y)};
-          bf16x4 pk;
-#pragma unroll
-          for (int e = 0; e < 4; ++e) pk[e] = (__bf16)((acc[j][i][4 * q4 + e] + b[e]) + r[e]);
-          *(uint2*)(out + (size_t)m * a.n + n) = __builtin_bit_cast(uint2, pk);
-        }
-      }
-    }
-  } else if (MODE == GEMM_QKV_ROPE) {
-    // head of this wavefront and where its rows go
-    const int head = u64 >> 1;
-    const int dim0 = (u64 & 1) * 32;  // block 0: dims dim0 + ..., block 1: dim0 + 64 + ...
-    const bf16_t* bias = (const bf16_t*)a.bias + (size_t)head * 128;
-    bf16_t* dst;
-    int heads_dst, head_dst;
-    bool rotate = true;
-    if (head < a.h_q) dst = (bf16_t*)a.q, heads_dst = a.h_q, head_dst = head;
-    else if (head < a.h_q + a.h_kv) dst = (bf16_t*)a.k_out, heads_dst = a.h_kv, head_dst = head - a.h_q;
-    else dst = (bf16_t*)a.v_out, heads_dst = a.h_kv, head_dst = head - a.h_q - a.h_kv, rotate = false;
-#pragma unroll
-    for (int q4 = 0; q4 < 4; ++q4) {
-      const int f = dim0 + 8 * q4 + 4 * g;  // rotary frequency index of the run's first element
-      float4 cs0[T::MI], cs1[T::MI];
-      if (rotate) {
-#pragma unroll
-        for (int i = 0; i < T::MI; ++i) {
-          const float* cs = a.cos_sin + ((size_t)min(m0 + wm * (32 * T::MI) + i * 32 + l32, a.m - 1) * 64 + f) * 2;
-          cs0[i] = *(const float4*)cs, cs1[i] = *(const float4*)(cs + 4);
-        }
-      }
-      float b0[4], b1[4];
-      {
-        const uint2 r0 = *(const uint2*)(bias + f), r1 = *(const uint2*)(bias + 64 + f);
-        b0[0] = bf16lo_to_f32(r0.x), b0[1] = bf16hi_to_f32(r0.x), b0[2] = bf16lo_to_f32(r0.y), b0[3] = bf16hi_to_f32(r0.y);
-        b1[0] = bf16lo_to_f32(r1.x), b1[1] = bf16hi_to_f32(r1.x), b1[2] = bf16lo_to_f32(r1.y), b1[3] = bf16hi_to_f32(r1.y);
-      }
-#pragma unroll
-      for (int i = 0; i < T::MI; ++i) {
-        const int m = m0 + wm * (32 * T::MI) + i * 32 + l32;
-        if (m >= a.m) continue;
-        float lo[4], hi[4];
-#pragma unroll
-        for (int e = 0; e < 4; ++e) lo[e] = acc[0][i][4 * q4 + e] + b0[e], hi[e] = acc[1][i][4 * q4 + e] + b1[e];
-        if (rotate) {
-          const float c[4] = {cs0[i].x, cs0[i].z, cs1[i].x, cs1[i].z}, s[4] = {cs0[i].y, cs0[i].w, cs1[i].y, cs1[i].w};
-#pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            const float x0 = lo[e], x1 = hi[e];
-            lo[e] = x0 * c[e] - x1 * s[e];
-            hi[e] = x1 * c[e] + x0 * s[e];
-          }
-        }
-        bf16x4 p0, p1;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) p0[e] = (__bf16)lo[e], p1[e] = (__bf16)hi[e];
-        bf16_t* row = dst + ((size_t)m * heads_dst + head_dst) * 128;
-        *(uint2*)(row + f) = __builtin_bit_cast(uint2, p0);
-        *(uint2*)(row + 64 + f) = __builtin_bit_cast(uint2, p1);
-      }
-    }
-  } else {  // GEMM_SWIGLU
+  if (MODE == GEMM_SWIGLU) {  // half as many outputs: 64-byte runs of rows staged as below gained nothing (7.5 us per tile)
     bf16_t* out = (bf16_t*)a.out;
 #pragma unroll
     for (int q4 = 0; q4 < 4; ++q4) {
@@ -460,6 +345,141 @@ __global__ __launch_bounds__(T::NW * 64) void gemm_bf16_kernel(GemmArgs a) {
         *(uint2*)(out + (size_t)m * d_ff + n) = __builtin_bit_cast(uint2, pk);
       }
     }
+    return;
+  }
+  // Results go through LDS, bf16, so that a store instruction writes whole runs of rows: 8 rows x 128 bytes (PLAIN) or 16
+  // rows x 64 (QKV_ROPE: half of a half head), 16 bytes per lane; a residual is read the same way. Stored from the
+  // accumulator layout an instruction touched 32 rows in pieces of 16 bytes, and a short contraction was bound by that:
+  // 8192 x 8192 x 512, four tiles per CU, 154 us (with a residual 169), now 102 (109; the library's plain product 81);
+  // x 3584 437 (457), now 376 (400); 4096 x 4096 x 512 31 (47), now 26 (30).
+  // Each wavefront stages its own tokens x outputs, so one barrier (the ring's last readers) is all it takes. Row r's
+  // 16-byte chunk c sits at c ^ (r & 7) (128-byte rows) or c ^ ((r >> 2) & 3) (64-byte rows): no bank conflicts.
+  __syncthreads();
+  constexpr int SROW = MODE == GEMM_PLAIN ? 128 : 64;  // bytes of a staged row
+  constexpr int SC = SROW / 16;                         // its chunks
+  constexpr int SBLK = 32 * SROW;                       // bytes of 32 staged tokens
+  constexpr int SREG = (MODE == GEMM_QKV_ROPE ? 2 : 1) * T::MI * SBLK;  // this wavefront's region
+  static_assert(T::NW * SREG <= T::LDS, "staging fits the rings");
+  unsigned char* const stage = smem + wave * SREG;
+  auto swizzled = [](int r, int c) { return c ^ (SC == 8 ? r & 7 : (r >> 2) & 3); };
+  // this lane's run of 4 outputs at chunk c (half g) of its token in block `blk`
+  auto staged = [&](int blk, int c) { return (uint2*)(stage + blk * SBLK + l32 * SROW + swizzled(l32, c) * 16 + g * 8); };
+  auto settle = [] { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); };  // the wavefront's writes before its reads
+  const int s_row = lane / SC, s_chunk = lane % SC;  // where this lane reads and stores
+  auto chunk_of = [&](int blk, int r) { return *(const u32x4*)(stage + blk * SBLK + r * SROW + swizzled(r, s_chunk) * 16); };
+  const int mw = m0 + wm * (32 * T::MI);  // this wavefront's first token
+  if (MODE == GEMM_PLAIN) {
+    const bf16_t* bias = (const bf16_t*)a.bias;
+    bf16_t* out = (bf16_t*)a.out;
+    const int nw0 = n0 + wn * 64, n_lane = nw0 + 8 * s_chunk;
+    const bool has_res = a.residual != nullptr;
+    if (has_res) {  // into the staging region, to be replaced by the results in place (it may be the output itself)
+      u32x4 rv[T::MI][32 * SC / 64];
+#pragma unroll
+      for (int i = 0; i < T::MI; ++i)
+#pragma unroll
+        for (int u = 0; u < 32 * SC / 64; ++u)  // past the end: not used
+          rv[i][u] = *(const u32x4*)((const bf16_t*)a.residual + (size_t)min(mw + 32 * i + u * (64 / SC) + s_row, a.m - 1) * a.n + min(n_lane, a.n - 8));
+#pragma unroll
+      for (int i = 0; i < T::MI; ++i)
+#pragma unroll
+        for (int u = 0; u < 32 * SC / 64; ++u) {
+          const int r = u * (64 / SC) + s_row;
+          *(u32x4*)(stage + i * SBLK + r * SROW + swizzled(r, s_chunk) * 16) = rv[i][u];
+        }
+      settle();
+    }
+#pragma unroll
+    for (int i = 0; i < T::MI; ++i)
+#pragma unroll
+      for (int j = 0; j < 2; ++j)
+#pragma unroll
+        for (int q4 = 0; q4 < 4; ++q4) {
+          float b[4] = {0.f, 0.f, 0.f, 0.f}, r[4] = {0.f, 0.f, 0.f, 0.f};
+          if (bias != nullptr) {
+            const uint2 raw = *(const uint2*)(bias + min(nw0 + j * 32 + 8 * q4 + 4 * g, a.n - 4));
+            b[0] = bf16lo_to_f32(raw.x), b[1] = bf16hi_to_f32(raw.x), b[2] = bf16lo_to_f32(raw.y), b[3] = bf16hi_to_f32(raw.y);
+          }
+          uint2* const at = staged(i, 4 * j + q4);
+          if (has_res) {
+            const uint2 raw = *at;
+            r[0] = bf16lo_to_f32(raw.x), r[1] = bf16hi_to_f32(raw.x), r[2] = bf16lo_to_f32(raw.y), r[3] = bf16hi_to_f32(raw.y);
+          }
+          bf16x4 pk;
+#pragma unroll
+          for (int e = 0; e < 4; ++e) pk[e] = (__bf16)((acc[j][i][4 * q4 + e] + b[e]) + r[e]);
+          *at = __builtin_bit_cast(uint2, pk);
+        }
+    settle();
+#pragma unroll
+    for (int i = 0; i < T::MI; ++i)
+#pragma unroll
+      for (int u = 0; u < 32 * SC / 64; ++u) {
+        const int r = u * (64 / SC) + s_row, m = mw + 32 * i + r;
+        if (m < a.m && n_lane < a.n) *(u32x4*)(out + (size_t)m * a.n + n_lane) = chunk_of(i, r);
+      }
+  } else {  // GEMM_QKV_ROPE
+    // head of this wavefront and where its rows go
+    const int head = u64 >> 1;
+    const int dim0 = (u64 & 1) * 32;  // block 0: dims dim0 + ..., block 1: dim0 + 64 + ...
+    const bf16_t* bias = (const bf16_t*)a.bias + (size_t)head * 128;
+    bf16_t* dst;
+    int heads_dst, head_dst;
+    bool rotate = true;
+    if (head < a.h_q) dst = (bf16_t*)a.q, heads_dst = a.h_q, head_dst = head;
+    else if (head < a.h_q + a.h_kv) dst = (bf16_t*)a.k_out, heads_dst = a.h_kv, head_dst = head - a.h_q;
+    else dst = (bf16_t*)a.v_out, heads_dst = a.h_kv, head_dst = head - a.h_q - a.h_kv, rotate = false;
+#pragma unroll
+    for (int q4 = 0; q4 < 4; ++q4) {
+      const int f = dim0 + 8 * q4 + 4 * g;  // rotary frequency index of the run's first element
+      float4 cs0[T::MI], cs1[T::MI];
+      if (rotate) {
+#pragma unroll
+        for (int i = 0; i < T::MI; ++i) {
+          const float* cs = a.cos_sin + ((size_t)min(mw + i * 32 + l32, a.m - 1) * 64 + f) * 2;
+          cs0[i] = *(const float4*)cs, cs1[i] = *(const float4*)(cs + 4);
+        }
+      }
+      float b0[4], b1[4];
+      {
+        const uint2 r0 = *(const uint2*)(bias + f), r1 = *(const uint2*)(bias + 64 + f);
+        b0[0] = bf16lo_to_f32(r0.x), b0[1] = bf16hi_to_f32(r0.x), b0[2] = bf16lo_to_f32(r0.y), b0[3] = bf16hi_to_f32(r0.y);
+        b1[0] = bf16lo_to_f32(r1.x), b1[1] = bf16hi_to_f32(r1.x), b1[2] = bf16lo_to_f32(r1.y), b1[3] = bf16hi_to_f32(r1.y);
+      }
+#pragma unroll
+      for (int i = 0; i < T::MI; ++i) {
+        float lo[4], hi[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) lo[e] = acc[0][i][4 * q4 + e] + b0[e], hi[e] = acc[1][i][4 * q4 + e] + b1[e];
+        if (rotate) {
+          const float c[4] = {cs0[i].x, cs0[i].z, cs1[i].x, cs1[i].z}, s[4] = {cs0[i].y, cs0[i].w, cs1[i].y, cs1[i].w};
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            const float x0 = lo[e], x1 = hi[e];
+            lo[e] = x0 * c[e] - x1 * s[e];
+            hi[e] = x1 * c[e] + x0 * s[e];
+          }
+        }
+        bf16x4 p0, p1;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) p0[e] = (__bf16)lo[e], p1[e] = (__bf16)hi[e];
+        *staged(2 * i, q4) = __builtin_bit_cast(uint2, p0);
+        *staged(2 * i + 1, q4) = __builtin_bit_cast(uint2, p1);
+      }
+    }
+    settle();
+    bf16_t* const col = dst + (size_t)head_dst * 128 + dim0 + 8 * s_chunk;
+#pragma unroll
+    for (int i = 0; i < T::MI; ++i)
+#pragma unroll
+      for (int u = 0; u < 32 * SC / 64; ++u) {
+        const int r = u * (64 / SC) + s_row, m = mw + 32 * i + r;
+        if (m < a.m) {
+          bf16_t* const at = col + (size_t)m * heads_dst * 128;
+          *(u32x4*)at = chunk_of(2 * i, r);
+          *(u32x4*)(at + 64) = chunk_of(2 * i + 1, r);
+        }
+      }
   }
 }
 
