@@ -536,6 +536,9 @@ static qp_status prefill_in_runs(const VideoRun& r, qp_cache* cache, void* works
   const size_t q_tok = (size_t)L->n_q_heads * L->head_dim * esz, kv_tok = (size_t)L->n_kv_heads * L->head_dim * esz;
   const int base_rule = (int)r.rule & ~QP_SCORE_SHARED_HEADS;
   const bool scored = r.keep < r.n_g;  // else every group keeps everything, the shorter last one included
+  // small groups under a norm rule, each head selecting for itself: the selection takes the norms, without a scoring launch
+  const int norm = !scored || !qp::topk_takes_norms(r.n_g) ? 0
+                   : (int)r.rule == QP_SCORE_KEY_NORM_SMALL ? -1 : (int)r.rule == QP_SCORE_VALUE_NORM ? 1 : 0;
   const size_t score_b = r.score_b, win_b = r.win_b, shared_b = r.shared_b, split_at = r.split_at;
   const int32_t per_run = r.per_run;
   char* ws = (char*)workspace;
@@ -569,7 +572,7 @@ static qp_status prefill_in_runs(const VideoRun& r, qp_cache* cache, void* works
     const char* kf = r.k + (size_t)first * r.n_g * kv_tok;
     const char* vf = r.v + (size_t)first * r.n_g * kv_tok;
     const qp::GroupRun run{count, has_last ? r.n_last : r.n_g, score_b / sizeof(float)};
-    if (scored) {
+    if (scored && norm == 0) {
       st = score_run(L, r.rule, kf, vf, r.n_g, r.q_win, r.n_window, scores, scratch_ws, win_b, run, score_stream);
       if (st != QP_OK) break;
     }
@@ -582,6 +585,7 @@ static qp_status prefill_in_runs(const VideoRun& r, qp_cache* cache, void* works
     t.cache_fp8 = cache->format == QP_CACHE_FP8_E4M3;
     t.keep_last = has_last ? r.keep_last : r.keep;
     t.run = run;
+    t.norm = norm;
     st = finish(qp::launch_topk_compact(t, L->dtype, nullptr, score_stream));
     if (st != QP_OK) break;
     // attention of every group whose cache rows are all enqueued by now: through the group after this run

@@ -222,7 +222,9 @@ struct TopkArgs {
   int cache_fp8;        // 1: ck / cv take one E4M3 byte per element (bf16 inputs only)
   int keep_last;        // keep of the run's last group; group i appends at len + i * keep, its tokens start at base + i * n_g
   GroupRun run;
+  int norm = 0;         // -1: the scores are -||K_g||, +1: +||V_g||, taken by the selection itself; 0: given in `scores`
 };
+bool topk_takes_norms(int n_g);  // groups whose selection can take them
 size_t topk_workspace_bytes(int h_kv, int keep);
 hipError_t launch_topk_compact(const TopkArgs& a, int dtype, int32_t* kept_ws, hipStream_t s);
 

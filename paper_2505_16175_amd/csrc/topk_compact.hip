@@ -6,7 +6,8 @@
 // slice of the group's tokens: it ranks the slice's survivors, writes their indices and cache positions, and copies
 // their K and V rows (16-byte vector loads/stores, d*sizeof/16 lanes per row, all loads of a batch in flight before
 // the first store). Copies of early workgroups overlap the searches of later ones.
-// When every token is kept (k = N_g) there is nothing to select: append_all_kernel copies the rows in order.
+// When every token is kept (k = N_g) there is nothing to select: append_all_kernel copies the rows in order. Small groups are
+// ranked directly by topk_rank_kernel.
 //
 // Selection = find the k-th largest key T and how many keys equal to T survive (`need`), then emit.
 //   * While loading, the workgroup takes the minimum and maximum key. A round spreads the current key
@@ -361,6 +362,107 @@ __global__ __launch_bounds__(TOPK_THREADS) void topk_compact_kernel(TopkArgs a, 
   }
 }
 
+// The same selection and copy for groups of up to RANK_MAX tokens (tiny clips, last groups): a token's rank is the number of
+// keys above its own, and of equal ones before it, counted directly; no threshold, no slices. Such a call is a chain of
+// latencies, so eight lanes share a token's count, and all rows of the group are requested beside the scores, before it is
+// known which survive. With the norm rules a caller that scores only to select (qp_prefill_video's runs) leaves the scoring
+// to it too, from the rows that it holds. us per launch, half of the tokens kept, by threshold / by rank: 2 f32 heads of 64,
+// 4 tokens 6.0 / 2.9, 32 6.1 / 3.0, 128 6.7 / 4.1; 112 bf16 heads of 128, 32 tokens 6.6 / 3.4, 128 7.3 / 4.8. The line: with
+// four lanes per token and twice the rows held, up to 256 tokens, 128 took 5.2, 192 6.4 and 256 8.1, by threshold 6.7, 6.9
+// and 7.2. The video of eight f32 frames of 16 tokens, now two launches for three: 15.2 -> 11.1 us.
+constexpr int RANK_MAX = 128;
+template <typename T, int D>
+__global__ __launch_bounds__(TOPK_THREADS) void topk_rank_kernel(TopkArgs a, int32_t* __restrict__ kept_out) {
+  constexpr int PER = Elem<T>::kPer16B;
+  constexpr int LPR = D / PER;  // lanes per row
+  constexpr int ROWS = TOPK_THREADS / LPR;
+  constexpr int BATCHES = RANK_MAX / ROWS;
+  static_assert(TOPK_THREADS == 8 * RANK_MAX, "eight lanes per token");
+  __shared__ __attribute__((aligned(16))) uint32_t keys[RANK_MAX];
+  __shared__ int32_t slots[RANK_MAX];  // cache slot of a survivor, -1 for the others
+  __shared__ uint32_t wave_n[TOPK_WAVES];
+
+  run_group(a, (size_t)a.h_kv * D * sizeof(T));
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int h = blockIdx.y, n = a.n_g;
+  const float score = a.norm == 0 && tid < n ? a.scores[(size_t)h * n + tid] : 0.f;
+  const int sub = tid % LPR, row0 = tid / LPR;
+  u32x4 kk[BATCHES], vv[BATCHES];
+#pragma unroll
+  for (int u = 0; u < BATCHES; ++u) {
+    const int r = row0 + u * ROWS;
+    kk[u] = vv[u] = u32x4{0u, 0u, 0u, 0u};
+    if (r < n) {
+      const size_t src = ((size_t)r * a.h_kv + h) * D + sub * PER;
+      kk[u] = *(const u32x4*)((const T*)a.k + src);
+      vv[u] = *(const u32x4*)((const T*)a.v + src);
+    }
+  }
+  // keys past the end: above no key, before none
+  if (a.norm == 0) {
+    if (tid < RANK_MAX) keys[tid] = tid < n ? order_key(score) : 0u;
+  } else {  // score_norm_kernel's sums, in its order
+    const float sign = (float)a.norm;
+#pragma unroll
+    for (int u = 0; u < BATCHES; ++u) {
+      const int r = row0 + u * ROWS;
+      const u32x4 raw = a.norm < 0 ? kk[u] : vv[u];
+      float f[PER], ss = 0.f;
+      widen16<T>(make_uint4(raw.x, raw.y, raw.z, raw.w), f);
+#pragma unroll
+      for (int e = 0; e < PER; ++e) ss = fmaf(f[e], f[e], ss);
+#pragma unroll
+      for (int o = LPR / 2; o > 0; o >>= 1) ss += __shfl_xor(ss, o, 64);
+      if (sub == 0) keys[r] = r < n ? order_key(sign * sqrtf(ss) + 0.f) : 0u;
+    }
+  }
+  __syncthreads();
+  const int token = tid >> 3;
+  const uint32_t x = keys[token];
+  uint32_t rank = 0;
+#pragma unroll
+  for (int j0 = 0; j0 < RANK_MAX; j0 += 32) {
+    if (j0 >= n) break;
+    const int j = j0 + 4 * (tid & 7);
+    const u32x4 y = *(const u32x4*)&keys[j];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) rank += y[e] > x || (y[e] == x && j + e < token);
+  }
+#pragma unroll
+  for (int o = 1; o < 8; o <<= 1) rank += (uint32_t)__shfl_xor((int)rank, o, 64);
+  const bool kept = token < n && rank < (uint32_t)a.keep;  // ranks are a permutation: exactly a.keep survive
+  const bool first = (tid & 7) == 0;
+  const unsigned long long survivors = __ballot(kept && first);
+  if (lane == 0) wave_n[wave] = (uint32_t)__popcll(survivors);
+  __syncthreads();
+  uint32_t slot = (uint32_t)__popcll(survivors & ((1ull << lane) - 1ull));
+#pragma unroll
+  for (int w = 0; w < TOPK_WAVES; ++w) slot += w < wave ? wave_n[w] : 0u;
+  if (first) {
+    slots[token] = kept ? (int)slot : -1;
+    if (kept) {
+      a.pos[(size_t)h * a.cap + a.len + slot] = a.base + token;
+      if (kept_out != nullptr) kept_out[(size_t)h * a.keep + slot] = token;
+    }
+  }
+  __syncthreads();
+#pragma unroll
+  for (int u = 0; u < BATCHES; ++u) {
+    const int r = row0 + u * ROWS;
+    if (r >= n || slots[r] < 0) continue;
+    const size_t dst = ((size_t)h * a.cap + a.len + slots[r]) * D + sub * PER;
+    if (sizeof(T) == 2 && a.cache_fp8) {  // 8-bit cache rows: one byte per element, 8 bytes per lane
+      *(uint2*)((unsigned char*)a.ck + dst) = pack8_e4m3(kk[u]);
+      *(uint2*)((unsigned char*)a.cv + dst) = pack8_e4m3(vv[u]);
+    } else {
+      *(u32x4*)((T*)a.ck + dst) = kk[u];
+      *(u32x4*)((T*)a.cv + dst) = vv[u];
+    }
+  }
+}
+
+bool topk_takes_norms(int n_g) { return n_g <= RANK_MAX; }
+
 size_t topk_workspace_bytes(int h_kv, int keep) { return ((size_t)h_kv * keep * sizeof(int32_t) + 255) / 256 * 256; }
 
 // Tokens per slice: about SLICE_WANT_KEEP survivors each, at most SLICES_MAX slices and about one workgroup per
@@ -384,6 +486,10 @@ static hipError_t launch_fused(const TopkArgs& a, int32_t* kept_out, hipStream_t
     constexpr int LPR = D / Elem<T>::kPer16B;
     hipLaunchKernelGGL((append_all_kernel<T, D>), dim3((a.n_g * LPR + APPEND_THREADS - 1) / APPEND_THREADS, a.h_kv, a.run.count),
                        dim3(APPEND_THREADS), 0, s, a, kept_out);
+    return hipSuccess;
+  }
+  if (a.n_g <= RANK_MAX) {
+    hipLaunchKernelGGL((topk_rank_kernel<T, D>), dim3(1, a.h_kv, a.run.count), dim3(TOPK_THREADS), 0, s, a, kept_out);
     return hipSuccess;
   }
   const int slice_tokens = slice_tokens_for(a.n_g, a.keep, a.h_kv * a.run.count);

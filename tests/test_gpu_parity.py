@@ -427,6 +427,69 @@ def test_topk_compact_many_heads(h_kv, n_g, keep):
         assert (ck[h, :2] == 0).all()
 
 
+@pytest.mark.parametrize("dtype,d,fp8", [("f32", 64, False), ("f32", 128, False), ("bf16", 64, False), ("bf16", 128, False),
+                                         ("bf16", 128, True)])
+@pytest.mark.parametrize("n_g,keep", [(2, 1), (31, 30), (32, 1), (33, 17), (64, 32), (100, 7), (127, 126), (128, 64), (129, 64)])
+def test_topk_small_groups_by_rank(dtype, d, fp8, n_g, keep):
+    """Groups around the size up to which ranks are counted directly: index sets, positions and rows bit-exact, ties and
+    infinities among the scores, nothing written beside the appended rows."""
+    print(f"case dtype={dtype} d={d} fp8={fp8} n_g={n_g} keep={keep}", flush=True)
+    g = torch.Generator().manual_seed(n_g * 131 + keep)
+    h_kv, pre, base = 3, 2, 500
+    s = torch.round(torch.randn(h_kv, n_g, generator=g) * 4) / 4
+    s[0] = -0.0
+    s[0, ::2] = 0.0                                             # all equal
+    s[1, 0], s[1, -1] = float("-inf"), float("inf")
+    tdt = torch.float32 if dtype == "f32" else torch.bfloat16
+    k, v = (torch.randn(n_g, h_kv, d, generator=g).to(tdt) for _ in range(2))
+    layout = B.make_layout(h_kv, h_kv, d, dtype)
+    cache = B.Cache(layout, pre + keep + 3, fmt=B.QP_CACHE_FP8_E4M3 if fp8 else B.QP_CACHE_SAME)
+    cache.c.len = pre
+    kept = torch.full((h_kv, keep), -1, dtype=torch.int32, device=DEV)
+    B.topk_compact(layout, s.to(DEV), k.to(DEV), v.to(DEV), keep, base, cache, kept)
+    torch.cuda.synchronize()
+    want = O.topk_select(s.double().numpy(), keep)
+    np.testing.assert_array_equal(kept.cpu().numpy(), want)
+    pos = cache.pos.cpu().numpy()
+    np.testing.assert_array_equal(pos[:, pre:pre + keep], base + want)
+    assert (pos[:, :pre] == -1).all() and (pos[:, pre + keep:] == -1).all()
+    for t, src in ((cache.k.cpu(), k), (cache.v.cpu(), v)):
+        for h in range(h_kv):
+            rows = src[torch.from_numpy(want[h]), h]
+            if fp8:                                             # unit-scale rows: far below the format's limit
+                rows = rows.float().to(torch.float8_e4m3fn)
+            assert torch.equal(t[h, pre:pre + keep].float(), rows.float())
+            assert (t[h, :pre].float() == 0).all() and (t[h, pre + keep:].float() == 0).all()
+
+
+@pytest.mark.parametrize("dtype,d", [("f32", 64), ("f32", 128), ("bf16", 64)])
+@pytest.mark.parametrize("frames,tpf,group,rho", [(9, 8, 1, 0.5), (7, 16, 2, 0.3), (11, 32, 4, 0.9), (10, 33, 4, 0.5)])
+@pytest.mark.parametrize("rule", ["key_norm_small", "value_norm"])
+def test_prefill_video_selects_small_groups_by_their_own_norms(dtype, d, frames, tpf, group, rho, rule):
+    """Groups of up to 128 tokens (and one of 132): the call scores and selects in one launch and keeps exactly what the
+    step calls keep, ragged last groups included."""
+    print(f"case dtype={dtype} d={d} frames={frames} tpf={tpf} group={group} rho={rho} {rule}", flush=True)
+    g = torch.Generator(device=DEV).manual_seed(frames * tpf)
+    tdt = torch.float32 if dtype == "f32" else torch.bfloat16
+    n, h_q, h_kv = frames * tpf, 4, 2
+    q, k, v = (torch.randn(n, h, d, generator=g, device=DEV).to(tdt) for h in (h_q, h_kv, h_kv))
+    layout = B.make_layout(h_q, h_kv, d, dtype)
+    capacity = B.cache_capacity(frames, tpf, group, rho)
+    whole, steps = B.Cache(layout, capacity), B.Cache(layout, capacity)
+    ws = B.make_workspace(layout, group * tpf, 0)
+    B.prefill_video(layout, frames, tpf, group, rho, rule, q, k, v, None, whole, torch.empty_like(q), ws)
+    scores = torch.empty(h_kv * group * tpf, device=DEV)
+    for f in range(0, frames, group):
+        n_g, t0 = min(group, frames - f) * tpf, f * tpf
+        sc = scores[:h_kv * n_g].view(h_kv, n_g)
+        B.score_kv(layout, rule, k[t0:t0 + n_g], v[t0:t0 + n_g], None, sc, ws)
+        B.topk_compact(layout, sc, k[t0:t0 + n_g], v[t0:t0 + n_g], B.keep_count(n_g, rho), t0, steps, None, ws)
+    torch.cuda.synchronize()
+    assert whole.len == steps.len == capacity
+    for a, b in ((whole.k, steps.k), (whole.v, steps.v), (whole.pos, steps.pos)):
+        assert torch.equal(a, b)
+
+
 def _score_families(n_g, g):
     """Score vectors that drive the selection through each of its routes (one KV head per family)."""
     base = torch.rand(n_g, generator=g)
