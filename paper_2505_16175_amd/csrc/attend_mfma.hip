@@ -39,8 +39,8 @@
 // each, and fragments read three products ahead. For that the numerators must not wait for the block's max:
 //   * The reference m of a row is not the running max. It moves only when a block's numerators outgrow it (a lane's sum of
 //     16 beyond 2^12, infinity included), checked after they are formed and before they are used; the block's numerators are
-//     then formed again around the new max. bf16 and f32 numerators lose nothing by a reference below the max. The first
-//     block always sets it.
+//     then formed again around the new max. bf16 and f32 numerators lose nothing by a reference below the max. The row's
+//     first tile sets it, from both of its blocks.
 //   * The row sum of the bf16-rounded numerators is taken with shifts and adds (pack_pair).
 // 8192 tokens of the 7B heads over 24,576 entries, random (all-zero, which leaves the clock alone) inputs: 2945 us (2000);
 // one tile after the other with max, numerators and v_dot2 sum between the two products 3240 (2590); this pipeline with the
