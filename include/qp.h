@@ -159,7 +159,10 @@ size_t qp_workspace_bytes(const qp_layout* layout, int32_t max_group_tokens, int
  *     own blocks of keys; larger ones split the tiles of the large kernel (at most 128 chunks).
  *     Launches of several rounds of workgroups use the scratch too: the row blocks of a partly
  *     filled last round (the group's earliest tokens) are split over up to 8 key chunks, so that
- *     their chunks fill the compute units evenly (partials for those rows only).
+ *     their chunks fill the compute units evenly (partials for those rows only). The scalar kernel deals
+ *     the keys of a row to the four wavefronts of a workgroup when at most four rows per compute unit
+ *     (n_group_tokens * H_q) meet 256 cache entries or more; that is one launch, and it writes nothing to
+ *     the scratch, but it merges partial results like the others and is taken only where scratch is given.
  *     Without scratch nothing is split. Calls that may overlap on different streams need distinct
  *     scratch. qp_attend_plan reports the choice.
  * Errors: INVALID_ARG (NULL/misaligned pointers, n_group_tokens <= 0, bad layout),
@@ -226,7 +229,8 @@ qp_status qp_topk_compact(const qp_layout* layout, const float* scores, const vo
  * groups on, of under 448 tokens each. Others (among them short ones over many entries from before the call, whose last
  * round of workgroups a run would leave partly empty) and groups of at most 32 stacked rows per KV head take the steps
  * group by group, with the key splits of qp_group_attend; a row's result may differ between the two in the last bits (a
- * split adds a merge of partial sums), kept entries never do.
+ * split adds a merge of partial sums), kept entries never do. Runs on the scalar kernel split nothing: their rows are
+ * those of qp_group_attend without scratch, whatever the number of groups in the video or in a launch.
  * Where it pays, the call uses two library-owned streams per device (created on first use on the current device,
  * default priority) for scoring / compaction and for part of the attention. They are forked from hip_stream at entry
  * and joined back into it before the call returns: work the caller enqueues on hip_stream afterwards is ordered after
@@ -250,7 +254,8 @@ qp_status qp_prefill_video(const qp_layout* layout, int32_t n_frames, int32_t to
  * rounds, so that their chunks fill the compute units evenly), whether rows are dealt to workgroups as
  * mirrored early/late half blocks (launches of at most one workgroup per compute unit) or consecutively,
  * and how much of the offered workspace the split would use.
- * For the scalar kernel only `kernel` and key_chunks = 1 are meaningful. */
+ * For the scalar kernel only `kernel` and key_chunks are meaningful: 4 where the wavefronts of a workgroup share a row
+ * (one launch, no scratch used), else 1. */
 typedef struct {
   int32_t kernel;          /* QP_ATTEND_SCALAR, QP_ATTEND_MFMA or QP_ATTEND_MFMA_DECODE */
   int32_t workgroups;      /* of the first launch, all chunks and idle padding workgroups included */

@@ -1,8 +1,8 @@
 // Group attention without the matrix pipe: f32 and bf16 inputs, f32 arithmetic. It serves f32 (the tiny clips) and the
 // layouts that the MFMA kernel does not take.
 //
-// A wavefront, or with few rows over a long cache the workgroup's four (SPLIT), batch by batch in turn, own one query row
-// (token i of query head qh). The visible keys of a row are the C cache entries of its
+// A wavefront, or with few rows over a long cache the workgroup's four (SPLIT, attend_scalar_chunks), batch by batch in turn,
+// own one query row (token i of query head qh). The visible keys of a row are the C cache entries of its
 // KV head followed by group tokens 0..i (Sec. 3.2: pruned cache + own group, causal). A key row is spread over LPR lanes of
 // 16 bytes each, so that a load instruction reads 64 / LPR whole rows; each of these lane groups runs its own online
 // softmax (running max m, denominator l, this lane's slice of the weighted sum), and the groups are merged once at the end.
@@ -191,22 +191,28 @@ __global__ __launch_bounds__(WAVES * 64) void attend_scalar_kernel(AttendArgs a)
 // Rows that would leave SIMDs idle are split over a workgroup, for caches of several batches: us unsplit / split, f32 d=64,
 // 4 rows over 300 entries 14.7 / 7.6, 256 over 1000 47 / 13, 800 over 1000 54 / 39, 1600 over 1000 70 / 68; with rows
 // enough the wavefronts of a workgroup are better off reading the same keys: 57,344 over 10,000 12.7 / 17.4 ms.
-// Groups of a run never are, so that a row's arithmetic does not depend on how many groups share the launch.
+// The split needs no scratch, but its merge changes a row's last bits, so it keeps to the rule of every key split: a call
+// without scratch is not split, and a launch of qp_prefill_video's runs never is, even of one group, because there the
+// groups that share a launch follow from the workspace and from the length of the video.
 constexpr int SPLIT_FROM = 256;
 
+int attend_scalar_chunks(const AttendArgs& a, size_t scratch_bytes) {
+  return scratch_bytes > 0 && a.c >= SPLIT_FROM && (long)a.n_g * a.h_q <= 4 * device_cu_count() ? WAVES : 1;
+}
+
 template <typename T, int D>
-static void launch_scalar(const AttendArgs& a, hipStream_t s) {
+static void launch_scalar(const AttendArgs& a, int chunks, hipStream_t s) {
   const unsigned groups = a.groups > 1 ? a.groups : 1;
-  if (groups == 1 && a.c >= SPLIT_FROM && (long)a.n_g * a.h_q <= 4 * device_cu_count())
+  if (chunks > 1)
     hipLaunchKernelGGL((attend_scalar_kernel<T, D, true>), dim3(a.n_g, a.h_q), dim3(WAVES * 64), 0, s, a);
   else
     hipLaunchKernelGGL((attend_scalar_kernel<T, D, false>), dim3((a.n_g + WAVES - 1) / WAVES, a.h_q, groups), dim3(WAVES * 64), 0,
                        s, a);
 }
 
-void launch_attend_scalar(const AttendArgs& a, int dtype, hipStream_t s) {
-  if (dtype == QP_F32) a.d == 64 ? launch_scalar<float, 64>(a, s) : launch_scalar<float, 128>(a, s);
-  else a.d == 64 ? launch_scalar<bf16_t, 64>(a, s) : launch_scalar<bf16_t, 128>(a, s);
+void launch_attend_scalar(const AttendArgs& a, int dtype, int chunks, hipStream_t s) {
+  if (dtype == QP_F32) a.d == 64 ? launch_scalar<float, 64>(a, chunks, s) : launch_scalar<float, 128>(a, chunks, s);
+  else a.d == 64 ? launch_scalar<bf16_t, 64>(a, chunks, s) : launch_scalar<bf16_t, 128>(a, chunks, s);
 }
 
 }  // namespace qp

@@ -310,7 +310,7 @@ qp_status qp_attend_plan(const qp_layout* L, int32_t n_g, int32_t cache_len, siz
     out->split_row_blocks = p.split_rb;
   } else {
     out->kernel = QP_ATTEND_SCALAR;
-    out->key_chunks = 1;
+    out->key_chunks = qp::attend_scalar_chunks(a, workspace_bytes);
   }
   return QP_OK;
 }
@@ -370,7 +370,7 @@ qp_status qp_group_attend(const qp_layout* L, const void* q_g, const void* k_g, 
   if (mfma_ok && which == QP_ATTEND_AUTO && qp::attend_decode_applies(a, L->dtype))
     qp::launch_attend_decode(a, workspace, ws_bytes, s);
   else if (mfma_ok && which != QP_ATTEND_SCALAR) qp::launch_attend_mfma(a, workspace, ws_bytes, s);
-  else qp::launch_attend_scalar(a, L->dtype, s);
+  else qp::launch_attend_scalar(a, L->dtype, qp::attend_scalar_chunks(a, ws_bytes), s);
   return finish(hipSuccess);
 }
 
@@ -562,8 +562,9 @@ static qp_status prefill_in_runs(const VideoRun& r, qp_cache* cache, void* works
     QP_HIP_OK(hipEventRecord(side->fork, main_stream));
     QP_HIP_OK(hipStreamWaitEvent(side->score, side->fork, 0));
     QP_HIP_OK(hipStreamWaitEvent(side->attend[1], side->fork, 0));
-    if (st == QP_OK)
-      st = qp_group_attend(L, r.q, r.k, r.v, r.n_g, cache, r.out, nullptr, ws + split_at, kAttendSplitBytes, main_stream);
+    if (st == QP_OK)  // on the scalar kernel without scratch: no launch of a run splits its rows there
+      st = qp_group_attend(L, r.q, r.k, r.v, r.n_g, cache, r.out, nullptr, r.mfma ? ws + split_at : nullptr, kAttendSplitBytes,
+                           main_stream);
   }
   int32_t attended = side ? 1 : 0;  // groups whose attention is enqueued
   for (int32_t first = 0, i = 0; first < r.n_groups && st == QP_OK; first += per_run, ++i) {
@@ -608,7 +609,7 @@ static qp_status prefill_in_runs(const VideoRun& r, qp_cache* cache, void* works
     a.groups = end - attended, a.n_last = end == r.n_groups ? r.n_last : r.n_g, a.keep = r.keep;
     if (a.groups == 1) a.n_g = a.n_last;
     if (r.mfma) qp::launch_attend_mfma_run(a, att);
-    else qp::launch_attend_scalar(a, L->dtype, att);
+    else qp::launch_attend_scalar(a, L->dtype, 1, att);
     st = finish(hipSuccess);
     attended = end;
   }
@@ -665,8 +666,8 @@ qp_status qp_prefill_video(const qp_layout* L, int32_t n_frames, int32_t tokens_
   }
 
   {
-    // Videos of two groups or more on the scalar kernel (never split) go in runs of groups, and where it is faster those
-    // on the MFMA kernel; decode-shaped groups keep their own kernel.
+    // Videos of two groups or more on the scalar kernel go in runs of groups if the groups are short (SCALAR_LOOP), and
+    // where it is faster those on the MFMA kernel; decode-shaped groups keep their own kernel.
     VideoRun r{};
     r.L = L, r.rule = rule, r.q = (const char*)q, r.k = (const char*)k, r.v = (const char*)v, r.q_win = q_win;
     r.n_window = n_window, r.out = (char*)out, r.n_g = (int32_t)max_group;

@@ -147,7 +147,9 @@ struct AttendArgs {
 };
 
 // Launchers (defined next to their kernels). They only enqueue; hipGetLastError is checked by the caller.
-void launch_attend_scalar(const AttendArgs& a, int dtype, hipStream_t s);  // a run of groups if a.groups > 1
+// chunks: wavefronts that share a row, 1 or attend_scalar_chunks'; a run of groups, which is never split, if a.groups > 1
+void launch_attend_scalar(const AttendArgs& a, int dtype, int chunks, hipStream_t s);
+int attend_scalar_chunks(const AttendArgs& a, size_t scratch_bytes);
 void launch_attend_mfma_run(const AttendArgs& a, hipStream_t s);            // a run of groups, never split
 long attend_mfma_row_blocks(int n_g, int h_q, int h_kv);                    // workgroups per KV head of an unsplit group
 bool attend_mfma_supported(const AttendArgs& a, int dtype);

@@ -266,6 +266,18 @@ def test_attend_plan_chunks_cover_the_cache_exactly():
         B.attend_plan(L, 16, -1, 0)
 
 
+def test_attend_plan_reports_shared_rows_of_the_scalar_kernel():
+    """Few rows over 256 cache entries and more are dealt to four wavefronts each, within one launch and only where scratch
+    is offered; plan and header call them key chunks like the large kernel's."""
+    for dtype, d in (("f32", 64), ("f32", 128), ("bf16", 64)):
+        L = B.make_layout(4, 2, d, dtype)
+        for n_g, c, chunks in ((1, 255, 1), (1, 256, 4), (256, 5000, 4), (257, 5000, 1), (1, 0, 1)):
+            p = B.attend_plan(L, n_g, c, 1 << 20)
+            assert (p["kernel"], p["key_chunks"]) == (B.QP_ATTEND_SCALAR, chunks), (dtype, d, n_g, c)
+            assert p["scratch_bytes"] == p["tiles_per_chunk"] == p["split_row_blocks"] == 0
+            assert B.attend_plan(L, n_g, c, 0)["key_chunks"] == 1
+
+
 def test_argument_errors_are_caught_on_the_host():
     lib = B.lib()
     L = B.make_layout(28, 4, 128, "bf16")

@@ -154,10 +154,11 @@ def test_group_attend_last_round_split(h_q, h_kv, n_g, c, fp8):
 
 @pytest.mark.gpu
 @pytest.mark.parametrize("dtype,d", [("f32", 64), ("f32", 128), ("bf16", 64), ("bf16", 128)])
-@pytest.mark.parametrize("n_g,c", [(1, 255), (1, 256), (1, 257), (31, 290), (3, 381), (5, 1023), (256, 256), (257, 256)])
+@pytest.mark.parametrize("n_g,c", [(1, 255), (1, 256), (1, 257), (34, 270), (31, 290), (3, 381), (5, 1023), (256, 256), (257, 256)])
 def test_group_attend_rows_shared_by_a_workgroup(dtype, d, n_g, c):
-    """The scalar kernel's rows over four wavefronts: batches of 32 keys that end inside, at and behind a wavefront's turn,
-    both sides of the rule (256 entries, 1024 rows), sharp and flat rows."""
+    """The scalar kernel's rows over four wavefronts, which a call with scratch takes: batches of 32 keys (16 at d = 128)
+    that end inside, at and behind a wavefront's turn, both sides of the rule (256 entries, 1024 rows), sharp and flat
+    rows. Without scratch a row is one wavefront's: its bits do not depend on the rows beside it."""
     h_q, h_kv = 4, 2
     g = torch.Generator().manual_seed(n_g * 5000 + c)
     tdt = torch.float32 if dtype == "f32" else torch.bfloat16
@@ -171,13 +172,25 @@ def test_group_attend_rows_shared_by_a_workgroup(dtype, d, n_g, c):
     cache.v[:, :c].copy_(cv)
     cache.c.len = c
     B.select_attend_kernel(B.QP_ATTEND_SCALAR)
-    out = torch.full((n_g, h_q, d), float("nan"), dtype=tdt, device=DEV)
-    lse = torch.full((h_q, n_g), float("nan"), dtype=torch.float32, device=DEV)
-    B.group_attend(layout, q.to(DEV), k.to(DEV), v.to(DEV), cache, out, lse)
+    q, k, v = q.to(DEV), k.to(DEV), v.to(DEV)
+    scratch = torch.empty(1 << 20, dtype=torch.uint8, device=DEV)
+    shared = c >= 256 and n_g * h_q <= 1024
+    assert B.attend_plan(layout, n_g, c, scratch.numel())["key_chunks"] == (4 if shared else 1)
+    assert B.attend_plan(layout, n_g, c, 0)["key_chunks"] == 1
+    for ws in (scratch, None):
+        out = torch.full((n_g, h_q, d), float("nan"), dtype=tdt, device=DEV)
+        lse = torch.full((h_q, n_g), float("nan"), dtype=torch.float32, device=DEV)
+        B.group_attend(layout, q, k, v, cache, out, lse, ws)
+        torch.cuda.synchronize()
+        assert_attn_close(_f64(out), want, dtype)
+        # logits of up to ~60, f32 dot products of 128 terms: |error| <= 128 * 2^-24 * sum |q k| / sqrt(d) < 3e-4, 1e-5 relative
+        np.testing.assert_allclose(_f64(lse), want_lse, rtol=2e-5, atol=2e-5)
+    # rows enough that no call of this size is shared: the same first rows, behind which others follow
+    many = lambda t: torch.cat([t, t[:1].expand(257, *t.shape[1:])])
+    wide, wide_lse = torch.empty(n_g + 257, h_q, d, dtype=tdt, device=DEV), torch.empty(h_q, n_g + 257, device=DEV)
+    B.group_attend(layout, many(q), many(k), many(v), cache, wide, wide_lse)
     torch.cuda.synchronize()
-    assert_attn_close(_f64(out), want, dtype)
-    # logits of up to ~60, f32 dot products of 128 terms: |error| <= 128 * 2^-24 * sum |q k| / sqrt(d) < 3e-4, 1e-5 relative
-    np.testing.assert_allclose(_f64(lse), want_lse, rtol=2e-5, atol=2e-5)
+    assert torch.equal(wide[:n_g], out) and torch.equal(wide_lse[:, :n_g], lse)
 
 
 @pytest.mark.gpu
@@ -825,6 +838,10 @@ RUNS = [  # layout (H_q, H_kv, d, dtype), frames, tokens per frame, frames per g
     ((4, 2, 64, "bf16"), 7, 13, 3, 0.4, "key_norm_small", 0, False, 9),
     ((8, 2, 128, "f32"), 34, 64, 6, 0.3, "window_attn", 16, False, 5),          # ... with group 0 beside the scoring
     ((8, 2, 128, "f32"), 17, 64, 7, 0.3, "window_attn", 16, False, 5),          # ... and groups of its per-group loop
+    # few rows over 256 entries and more on the scalar kernel:
+    ((2, 2, 64, "f32"), 6, 100, 3, 0.9, "key_norm_small", 0, False, 0),         # group 1 alone behind group 0
+    ((2, 2, 64, "f32"), 8, 100, 3, 0.9, "value_norm", 0, False, 300),           # groups 1 and 2 in one launch, group 0 beside the scoring
+    ((64, 64, 64, "bf16"), 28, 4, 4, 0.5, "window_attn", 60000, False, 300),    # runs of five groups: six attend at once, the last one alone
 ]
 
 
