@@ -201,6 +201,20 @@ def test_group_attend_moving_reference(profile, c, fp8):
     """Logits that climb by 195 powers of two along the keys (slowly, so that the reference of a row's numerators moves
     again and again, or in one jump that overflows them) or fall by as much; one tile up to several turns of the tile ring,
     caches that end inside and at the end of a 32-key block."""
+    _check_moving_reference(profile, c, fp8, split=False)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("profile", ["up", "jump", "down"])
+@pytest.mark.parametrize("c", [257, 1000, 2624])
+@pytest.mark.parametrize("fp8", [False, True])
+def test_group_attend_moving_reference_in_key_chunks(profile, c, fp8):
+    """The same logits dealt to key chunks: every chunk starts at a tile of its own with a reference of its own, and the
+    merge meets partial sums that lie more than 128 powers of two apart."""
+    _check_moving_reference(profile, c, fp8, split=True)
+
+
+def _check_moving_reference(profile, c, fp8, split):
     h_q, h_kv, d, n_g = 14, 2, 128, 70
     g = torch.Generator().manual_seed(c + len(profile))
     mk = lambda *s: torch.randn(*s, generator=g)
@@ -220,7 +234,9 @@ def test_group_attend_moving_reference(profile, c, fp8):
     want, want_lse = O.attend_group(_f64(q), _f64(k), _f64(v), _f64(ck.float()), _f64(cv.float()), return_lse=True)
     out = torch.full((n_g, h_q, d), float("nan"), dtype=torch.bfloat16, device=DEV)
     lse = torch.full((h_q, n_g), float("nan"), dtype=torch.float32, device=DEV)
-    B.group_attend(layout, q.to(DEV), k.to(DEV), v.to(DEV), cache if c > 0 else None, out, lse)
+    scratch = torch.empty(32 << 20, dtype=torch.uint8, device=DEV) if split else None
+    assert (B.attend_plan(layout, n_g, c, 32 << 20 if split else 0)["key_chunks"] > 1) == split
+    B.group_attend(layout, q.to(DEV), k.to(DEV), v.to(DEV), cache if c > 0 else None, out, lse, scratch)
     torch.cuda.synchronize()
     assert_attn_close(_f64(out), want, "bf16", profile)
     np.testing.assert_allclose(_f64(lse), want_lse, rtol=2e-5, atol=2e-3)
