@@ -8,8 +8,8 @@
 // softmax (running max m, denominator l, this lane's slice of the weighted sum), and the groups are merged once at the end.
 //
 // Such calls are small: what they cost is latency, one memory round trip per batch of keys. A batch is UNROLL keys per
-// lane group (32 keys), its K and V are requested together and one batch ahead. With one key per lane (every load
-// instruction touching 64 rows, both tensors of a key one after the other, and the merge of 64 states by shuffles) the
+// lane group (32 keys at d = 64, 16 at d = 128), its K and V are requested together and one batch ahead. With one key per lane
+// (every load instruction touching 64 rows, both tensors of a key one after the other, and the merge of 64 states by shuffles) the
 // video of eight f32 frames of 16 tokens, 4 heads of 64, took 21.8 us, 15.3 with this kernel; 48 frames of 32 in groups of 8, 217 and 96;
 // 2048 tokens of 28 heads over 10,000 entries 34.3 and 13.4 ms; 512 bf16 ones over 4,000 1762 and 896 us.
 #include "qp_internal.h"
