@@ -38,9 +38,10 @@
 // of which waits for another, in a fixed order of 16 products with two vector operations and an exponential or so behind
 // each, and fragments read three products ahead. For that the numerators must not wait for the block's max:
 //   * The reference m of a row is not the running max. It moves only when a block's numerators outgrow it (a lane's sum of
-//     16 beyond 2^12, infinity included), checked after they are formed and before they are used; the block's numerators are
-//     then formed again around the new max. bf16 and f32 numerators lose nothing by a reference below the max. The row's
-//     first tile sets it, from both of its blocks.
+//     16 beyond 2^6, infinity included), checked after they are formed and before they are used; the block's numerators are
+//     then formed again around the new max, of both blocks of a tile if it is the first. The row's first tile sets it. The
+//     range of bf16 and f32 would allow a reference far below the max, but the max itself is then rounded to bf16, where
+//     around itself it is an exact 1, and of a sharp row it is most of the sum: see MF_RESCALE.
 //   * The row sum of the bf16-rounded numerators is taken with shifts and adds (pack_pair).
 // 8192 tokens of the 7B heads over 24,576 entries, random (all-zero, which leaves the clock alone) inputs: 2945 us (2000);
 // one tile after the other with max, numerators and v_dot2 sum between the two products 3240 (2590); this pipeline with the
@@ -81,7 +82,12 @@ constexpr int MF_TILE = MF_BN * 256;    // bytes of one K or V tile (unpadded, s
 constexpr int MF_STAGES = 4;            // ring slots of K and of V tiles
 constexpr int MF_V0 = MF_STAGES * MF_TILE;  // LDS offset of the V ring
 constexpr int MF_LDS = 2 * MF_STAGES * MF_TILE;
-constexpr float MF_RESCALE = 4096.f;    // move the reference when a lane's 16 numerators of a block sum to more
+// Move the reference when a lane's 16 numerators of a block sum to more. Relative error against 64 bits (512 tokens of the
+// 7B heads over 8192 entries, unit-normal keys, queries scaled by 1 / 2 / 4 / 8), by the limit: 2^12 2.34e-3 / 2.26 / 1.91 /
+// 1.73, 2^8 2.34 / 2.23 / 1.85 / 1.70, 2^6 2.34 / 2.16 / 1.81 / 1.69; a max per tile that moves it by 2^8 and more 2.34 /
+// 2.23 / 1.82 / 1.71. What it costs: 4096 tokens over 24,576 entries 1293 / 1328 / 1384 / 1420 us, with 2^12 1294 / 1316 /
+// 1348 / 1388; 77 tokens over 9840 29.0 / 30.2 / 32.3 / 33.0 and 29.1 / 28.9 / 30.2 / 32.9.
+constexpr float MF_RESCALE = 64.f;
 constexpr int MF_VMCNT0 = 0x0f70;       // s_waitcnt vmcnt(0), other counters untouched
 constexpr int MF_VMCNT4 = 0x0f74;       // s_waitcnt vmcnt(4)
 constexpr int MF_LGKM0 = 0xc07f;        // s_waitcnt lgkmcnt(0)
@@ -333,11 +339,17 @@ __global__ __launch_bounds__(MF_NT, 2) void attend_mfma_kernel(AttendArgs a) {
   float nmc = 0.f;  // -m_run * c2
 
   // Moves the reference to the rows' max including this block, rescales what was summed so far and forms the block's
-  // numerators (first block of a row, and blocks whose numerators outgrew the reference).
-  auto move_reference = [&](const f32x16& st, bf16x8 (&pf)[2], float& psum) {
+  // numerators (first block of a row, and blocks whose numerators outgrew the reference). look: the max of the tile's other
+  // block is taken too, so that it does not move the reference once more (64 tokens over 46,125 entries, queries scaled by
+  // 16: 69.9 -> 64.9 us).
+  auto move_reference = [&](const f32x16& st, const f32x16& other, bool look, bf16x8 (&pf)[2], float& psum) {
     float mx = st[0];
 #pragma unroll
     for (int r = 1; r < 16; ++r) mx = fmaxf(mx, st[r]);
+    if (look) {
+#pragma unroll
+      for (int r = 0; r < 16; ++r) mx = fmaxf(mx, other[r]);
+    }
     // finite also where every logit so far is -inf: the numerators are 0 then, and the next finite logit moves it again
     mx = fmaxf(fmaxf(m_run, max_halves(mx)), -FLT_MAX);
     const float alpha = __builtin_amdgcn_exp2f((m_run - mx) * c2);
@@ -361,10 +373,11 @@ __global__ __launch_bounds__(MF_NT, 2) void attend_mfma_kernel(AttendArgs a) {
   bf16x8 qf[8];
   // One step of the pipeline on three consecutive 32-key blocks: S^T of the next one (QK), numerators of the current one,
   // O^T += V^T P^T of the previous one. QK: the step has a next block. K_CUR / K_NEXT: LDS offsets of the K block being
-  // read and of the one after it (likewise V); SECOND: the step works on a tile's second blocks and its last reads belong
-  // to the next ring slot. `extra(s)` runs between the products.
+  // read and of the one after it (likewise V); SECOND: the step works on a tile's second blocks (QK) and its last reads
+  // belong to the next ring slot. `cut`: the next block will be masked, so a moving reference does not look at it (SECOND
+  // only: in the other steps that block belongs to the next tile). `extra(s)` runs between the products.
   auto step = [&](auto qk, auto second, f32x16& s_next, const f32x16& s_cur, const bf16x8 (&p_prev)[2], bf16x8 (&p_cur)[2],
-                  unsigned turn_mask, auto extra) {
+                  unsigned turn_mask, bool cut, auto extra) {
     constexpr bool QK = decltype(qk)::value, SECOND = decltype(second)::value;
     constexpr int CUR = SECOND ? 32 * 256 : 0, NEXT = SECOND ? 0 : 32 * 256;
     float ps0 = 0.f, ps1 = 0.f, e0 = 0.f, e1 = 0.f;
@@ -411,7 +424,7 @@ __global__ __launch_bounds__(MF_NT, 2) void attend_mfma_kernel(AttendArgs a) {
     pack(7);
     if (QK) s_next = sn;
     float psum = ps0 + ps1;
-    if (__any(psum > MF_RESCALE)) move_reference(s_cur, p_cur, psum);
+    if (__any(psum > MF_RESCALE)) move_reference(s_cur, sn, QK && SECOND && !cut, p_cur, psum);
     l_run += psum;
   };
 
@@ -507,12 +520,8 @@ __global__ __launch_bounds__(MF_NT, 2) void attend_mfma_kernel(AttendArgs a) {
       // The first reference is the max of the tile's both blocks: a numerator just above 1 is rounded twice as coarsely as
       // one just below, and of nearly equal logits 1 in 64 lies above this reference instead of 1 in 32 (row error over
       // 26,000 such keys 1.6e-3 with the first block's max, 1.5e-3).
-      float mx = sb[0];
-#pragma unroll
-      for (int r = 1; r < 16; ++r) mx = fmaxf(mx, sb[r]);
-      m_run = max_halves(mx);  // -inf where the second block is masked
       float psum;
-      move_reference(sa, pa, psum);
+      move_reference(sa, sb, true, pa, psum);
       l_run += psum;
     }
     // While the pairs to be stored and requested are whole (and, over an 8-bit cache, cache tiles), that work is spread
@@ -521,7 +530,7 @@ __global__ __launch_bounds__(MF_NT, 2) void attend_mfma_kernel(AttendArgs a) {
     const int whole = min(last, (F8 ? min(n, n_ct - t_begin) : n) - 4);
     while (it < whole) {
       const unsigned turn_mask = (it & 1) ? 3 * MF_TILE : MF_TILE;  // slot it & 3 -> slot (it + 1) & 3
-      step(true_type(), false_type(), sa, sb, pa, pb, 0u, [&](int s) {
+      step(true_type(), false_type(), sa, sb, pa, pb, 0u, false, [&](int s) {
         if (F8 && (s & 1)) {
           store_piece(s >> 1, pend.p[s >> 1], (it + 2) & 3);
           pend.p[s >> 1] = load_piece(s >> 1);
@@ -531,7 +540,7 @@ __global__ __launch_bounds__(MF_NT, 2) void attend_mfma_kernel(AttendArgs a) {
       const unsigned dst = st_lds + ((it + 3) & 3) * MF_TILE;
       ++it;
       if (masked(t_begin + it)) mask(sa, t_begin + it, 0);
-      step(true_type(), true_type(), sb, sa, pb, pa, turn_mask, [&](int s) {
+      step(true_type(), true_type(), sb, sa, pb, pa, turn_mask, masked(t_begin + it), [&](int s) {
         if (!F8 && (s & 1)) request_half(s >> 1, dst);
       });
       advance_both();
@@ -539,16 +548,16 @@ __global__ __launch_bounds__(MF_NT, 2) void attend_mfma_kernel(AttendArgs a) {
     }
     while (it < last) {
       const unsigned turn_mask = (it & 1) ? 3 * MF_TILE : MF_TILE;
-      step(true_type(), false_type(), sa, sb, pa, pb, 0u, [](int) {});
+      step(true_type(), false_type(), sa, sb, pa, pb, 0u, false, [](int) {});
       store_pending(it + 2);
       turn(it);
       request(it + 3);
       ++it;
       if (masked(t_begin + it)) mask(sa, t_begin + it, 0);
-      step(true_type(), true_type(), sb, sa, pb, pa, turn_mask, [](int) {});
+      step(true_type(), true_type(), sb, sa, pb, pa, turn_mask, masked(t_begin + it), [](int) {});
       if (masked(t_begin + it)) mask(sb, t_begin + it, 1);
     }
-    step(false_type(), false_type(), sa, sb, pa, pb, 0u, [](int) {});
+    step(false_type(), false_type(), sa, sb, pa, pb, 0u, false, [](int) {});
 #pragma unroll
     for (int s = 0; s < 8; ++s) {
       if (s > 0 && s + 2 < 8) vf[(s + 2) & 3] = read_v(32 * 256, s + 2);

@@ -243,6 +243,36 @@ def _check_moving_reference(profile, c, fp8, split):
 
 
 @pytest.mark.gpu
+@pytest.mark.parametrize("fp8", [False, True])
+@pytest.mark.parametrize("at", [64, 95, 130, 200, 319])
+def test_group_attend_large_key_is_its_own_reference(fp8, at):
+    """Behind a first tile whose largest logit is 0, one key lies 8.1 to 11.2 powers of two above it and makes up the row
+    (the others are 30 and more below). Its numerator has to be taken around itself, an exact 1: against a reference that
+    far below, its rounding to bf16 puts the log-sum-exp off by up to 2^-8 = 4e-3."""
+    h_q, h_kv, d, n_g, c = 7, 1, 128, 40, 320
+    ck, k, q = torch.zeros(h_kv, c, d), torch.zeros(n_g, h_kv, d), torch.zeros(n_g, h_q, d)
+    ck[..., 0], k[..., 0] = -352.0, -352.0                           # exact in both formats, as are 0 and 88
+    ck[0, 3, 0], ck[0, at, 0] = 0.0, 88.0                            # 88 / sqrt(128) = 11.2 ln 2
+    q[..., 0] = torch.linspace(8.1 / 11.2, 1.0, n_g * h_q).view(n_g, h_q)
+    q, ck = q.bfloat16(), ck.to(torch.float8_e4m3fn if fp8 else torch.bfloat16)
+    g = torch.Generator().manual_seed(at)
+    v, cv = torch.randn(n_g, h_kv, d, generator=g).bfloat16(), torch.randn(h_kv, c, d, generator=g).to(ck.dtype)
+    k = k.bfloat16()
+    want, want_lse = O.attend_group(_f64(q), _f64(k), _f64(v), _f64(ck.float()), _f64(cv.float()), return_lse=True)
+    layout = B.make_layout(h_q, h_kv, d, "bf16")
+    cache = B.Cache(layout, c, fmt=B.QP_CACHE_FP8_E4M3 if fp8 else B.QP_CACHE_SAME)
+    cache.k.copy_(ck)
+    cache.v.copy_(cv)
+    cache.c.len = c
+    out, lse = torch.empty(n_g, h_q, d, dtype=torch.bfloat16, device=DEV), torch.empty(h_q, n_g, device=DEV)
+    B.group_attend(layout, q.to(DEV), k.to(DEV), v.to(DEV), cache, out, lse)
+    torch.cuda.synchronize()
+    assert_attn_close(_f64(out), want, "bf16")
+    # the key at 0 weighs 2^-8 at most and is rounded by 2^-8 of that; f32 logits of 8 and their sums: 2^-19
+    np.testing.assert_allclose(_f64(lse), want_lse, rtol=0, atol=2.0 ** -16 + 2.0 ** -19)
+
+
+@pytest.mark.gpu
 def test_group_attend_key_split_at_the_chunk_limit():
     """One workgroup's worth of rows against 24566 cache entries: the large kernel splits into its maximum of 128
     chunks, and the merge kernel takes two batches per wavefront."""
