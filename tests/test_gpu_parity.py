@@ -194,6 +194,29 @@ def test_group_attend_rows_shared_by_a_workgroup(dtype, d, n_g, c):
 
 
 @pytest.mark.gpu
+@pytest.mark.parametrize("d", [64, 128])
+def test_group_attend_long_rows_keep_their_accuracy(d):
+    """32-bit rows over 32,000 entries of nearly equal weight, a wavefront each. Equal terms summed in one chain of n are
+    off by about 2^-24 sqrt(n / 12) of the result; a key per lane meant chains of 500, and short rows are 1.6e-7 off."""
+    h_q, h_kv, n_g, c = 4, 2, 32, 32000
+    g = torch.Generator().manual_seed(d)
+    q, k, v, ck, cv = (torch.randn(*s, generator=g) for s in
+                       ((n_g, h_q, d), (n_g, h_kv, d), (n_g, h_kv, d), (h_kv, c, d), (h_kv, c, d)))
+    want = O.attend_group(_f64(q), _f64(k), _f64(v), _f64(ck), _f64(cv))
+    layout = B.make_layout(h_q, h_kv, d, "f32")
+    cache = B.Cache(layout, c)
+    cache.k.copy_(ck)
+    cache.v.copy_(cv)
+    cache.c.len = c
+    out = torch.empty(n_g, h_q, d, device=DEV)
+    B.group_attend(layout, q.to(DEV), k.to(DEV), v.to(DEV), cache, out)
+    torch.cuda.synchronize()
+    off = np.linalg.norm(_f64(out) - want) / np.linalg.norm(want)
+    print(f"relative error {off:.3e}")
+    assert off < np.hypot(1.6e-7, 2.0 ** -24 * np.sqrt(500 / 12))     # 4.2e-7
+
+
+@pytest.mark.gpu
 @pytest.mark.parametrize("profile", ["up", "jump", "down"])
 @pytest.mark.parametrize("c,fp8", [(0, False), (1, False), (32, False), (65, False), (192, False), (256, False), (257, False),
                                    (333, False), (33, True), (256, True), (257, True), (384, True), (450, True)])
