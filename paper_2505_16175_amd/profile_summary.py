@@ -27,11 +27,13 @@ import os
 import re
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+RUN_OF_GROUPS = "attend_mfma launches of a run of groups (not in the table of launches per group)"
 CAL_KIB = 262144.0     # the calibration copy reads and writes 256 MiB
 TABLE = os.path.join(ROOT, "profiles", "attend_hbm_traffic.txt")
 TABLE_HEADER = """# HBM-side bytes per launch of the group-attention kernel (attend_mfma_kernel), per config: rocprofv3 --pmc
 # FETCH_SIZE and WRITE_SIZE (KiB per dispatch, one counter per run), averaged over the kernel's launches of the bench
-# command and each scaled by the same counter's reading for a plain 256 MiB device-to-device copy. bench.py reads this
+# command that attend for one group (the serial replay's; where the timed steps serve runs of groups, their launches are
+# left out) and each scaled by the same counter's reading for a plain 256 MiB device-to-device copy. bench.py reads this
 # table for roofline.traffic; rows are rewritten by `python -m paper_2505_16175_amd.profile_summary`.
 # config | bytes per launch | read MB | written MB | launches | bench.py arguments of the counter runs
 """
@@ -55,11 +57,17 @@ def kernel_times(directory):
     return stats
 
 
-def counter(directory, name):
+def counter(directory, name, group_workgroups=None):
+    """Readings per kernel. group_workgroups: attention launches of more workgroups are those of a run of groups, which
+    come under a name of their own."""
     per_kernel = collections.OrderedDict()
     for r in csv.DictReader(open(_one(os.path.join(directory, "**", "*counter_collection.csv")))):
         if r["Counter_Name"] == name:
-            per_kernel.setdefault(r["Kernel_Name"], []).append(float(r["Counter_Value"]))
+            kernel = r["Kernel_Name"]
+            if group_workgroups and "attend_mfma_kernel" in kernel and \
+                    int(r["Grid_Size"]) > group_workgroups * int(r["Workgroup_Size"]):
+                kernel = RUN_OF_GROUPS
+            per_kernel.setdefault(kernel, []).append(float(r["Counter_Value"]))
     return per_kernel
 
 
@@ -85,6 +93,8 @@ def main():
     ap.add_argument("--write")
     ap.add_argument("--bench-json", help="the JSON line bench.py printed in the kernel-trace run")
     ap.add_argument("--command", default="", help="bench.py arguments of the runs")
+    ap.add_argument("--group-workgroups", type=int, help="configs whose timed steps serve runs of groups: the workgroups that "
+                    "one group's attention launch has at most, so that the row counts launches per group only")
     args = ap.parse_args()
     os.makedirs(os.path.join(ROOT, "profiles"), exist_ok=True)
 
@@ -119,7 +129,7 @@ def main():
         print("wrote", path)
 
     if args.fetch and args.write:
-        f, w = counter(args.fetch, "FETCH_SIZE"), counter(args.write, "WRITE_SIZE")
+        f, w = (counter(d, n, args.group_workgroups) for d, n in ((args.fetch, "FETCH_SIZE"), (args.write, "WRITE_SIZE")))
         cf, cw = calibration(f, w)
         sf, sw = CAL_KIB / cf, CAL_KIB / cw
         out = [f"rocprofv3 HBM-side counters per dispatch (KiB), workload {args.name}, MI355X",
