@@ -23,7 +23,18 @@
 //   * products are v_dot2_f32_bf16 (two multiply-adds per lane and instruction, f32 accumulation);
 //   * the 64 lanes' sums are added by shuffles, the 4 wavefronts' sums meet in LDS and are added in wavefront order
 //     (deterministic), and one lane per token applies the store.
+//
+// Inside a layer (launch_gemv_fused) the QKV and gate/up launches also take the RMSNorm of their rows, the rotary angles
+// and the append to the cache, which as launches of their own were latency and nothing else (norm + angles 6.1 us, second
+// norm 4.5, append 1.8 with a side stream forked and joined around it; 7B layer, one token over 46,125 entries 132.3 ->
+// 118.6 us). Every workgroup repeats the norm: wavefront t takes token t's sum of squares, over its row's chunks and
+// lanes in the order of rms_norm_kernel, so that the factor's bits are the same, while the first weights are on
+// their way; every wavefront scales and rounds the chunks that it multiplies. Another wavefront takes the workgroup's
+// four angles (two frequencies per token) in double precision.
+#include "fp8_e4m3.h"
 #include "qp_internal.h"
+
+#include <type_traits>
 
 namespace qp {
 
@@ -32,6 +43,7 @@ typedef __attribute__((__vector_size__(2 * sizeof(__bf16)))) __bf16 bf16x2;
 constexpr int GV_WAVES = 4;
 constexpr int GV_MAX_M = 2;  // tokens this kernel takes: every workgroup re-reads the activations, m / 4 of its weight bytes,
                              // and from 4 tokens on the tiled kernel with its split contraction is as fast or faster
+constexpr int GV_NORM = 8;   // 16-byte chunks per lane of a row being normed that are in flight together
 
 __device__ __forceinline__ float dot8(const uint4& w, const uint4& x, float acc) {
   acc = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, w.x), __builtin_bit_cast(bf16x2, x.x), acc, false);
@@ -41,10 +53,49 @@ __device__ __forceinline__ float dot8(const uint4& w, const uint4& x, float acc)
   return acc;
 }
 
-// M: tokens computed (1 or 2)
-template <int MODE, int M>
-__global__ __launch_bounds__(GV_WAVES * 64) void gemv_bf16_kernel(GemmArgs a) {
+// 1 / rms of row t of x, as one wavefront of rms_norm_kernel takes it: the same sums in the same order
+template <typename First>
+__device__ __forceinline__ float gemv_inv_rms(const uint4* x, int chunks, int k, float eps, int lane, const First& first) {
+  float ss = 0.f;
+  auto add = [&](const uint4& raw) {
+    float f[8];
+    widen16<bf16_t>(raw, f);
+#pragma unroll
+    for (int e = 0; e < 8; ++e) ss = fmaf(f[e], f[e], ss);
+  };
+#pragma unroll
+  for (int i = 0; i < GV_NORM; ++i)
+    if (lane + 64 * i < chunks) add(first[i]);
+  for (int c0 = lane + 64 * GV_NORM; c0 < chunks; c0 += 64 * GV_NORM) {
+    uint4 raw[GV_NORM];
+#pragma unroll
+    for (int i = 0; i < GV_NORM; ++i) raw[i] = x[min(c0 + 64 * i, chunks - 1)];
+#pragma unroll
+    for (int i = 0; i < GV_NORM; ++i)
+      if (c0 + 64 * i < chunks) add(raw[i]);
+  }
+  return 1.f / sqrtf(wave_sum(ss) / (float)k + eps);
+}
+__device__ __forceinline__ uint4 scale8(const uint4& raw, const uint4& w, float inv) {  // as rms_norm_kernel stores it
+  float f[8], g[8];
+  widen16<bf16_t>(raw, f);
+  widen16<bf16_t>(w, g);
+  uint32_t p[4];
+#pragma unroll
+  for (int e = 0; e < 4; ++e)
+    p[e] = (uint32_t)f32_to_bf16_rne(f[2 * e] * inv * g[2 * e]) | ((uint32_t)f32_to_bf16_rne(f[2 * e + 1] * inv * g[2 * e + 1]) << 16);
+  return make_uint4(p[0], p[1], p[2], p[3]);
+}
+
+struct NoFusion {};
+
+// M: tokens computed (1 or 2). F: GemvFusion or NoFusion
+template <int MODE, int M, typename F>
+__global__ __launch_bounds__(GV_WAVES * 64) void gemv_bf16_kernel(GemmArgs a, F fuse) {
+  constexpr bool FUSED = std::is_same<F, GemvFusion>::value;
   __shared__ float part[GV_WAVES][4][M];
+  __shared__ float inv_rms[M];
+  __shared__ float2 angles[M][2];  // QKV_ROPE: (cos, sin) of this workgroup's two frequencies
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int quad = blockIdx.x;  // < n / 4
@@ -73,10 +124,18 @@ __global__ __launch_bounds__(GV_WAVES * 64) void gemv_bf16_kernel(GemmArgs a) {
 #pragma unroll
     for (int t = 0; t < M; ++t) acc[e][t] = 0.f;
   constexpr int STEP = GV_WAVES * 64;
-  for (int c = wave * 64 + lane; c < chunks; c += 2 * STEP) {
-    const bool has1 = c + STEP < chunks;
-    const int c1 = has1 ? c + STEP : c;
-    uint4 w0[4], w1[4], x0[M], x1[M];
+  uint4 ahead[GV_NORM];  // FUSED: wavefront t < M takes token t's norm; its row is requested before anything else
+  if constexpr (FUSED) {
+    if (wave < M) {
+      const uint4* xr = x[0];
+      if (M > 1 && wave > 0) xr = x[M - 1];
+#pragma unroll
+      for (int i = 0; i < GV_NORM; ++i) ahead[i] = xr[min(lane + 64 * i, chunks - 1)];
+    }
+  }
+  uint4 w0[4], w1[4], x0[M], x1[M], n0, n1;
+  auto request = [&](int c) {
+    const int c1 = c + STEP < chunks ? c + STEP : c;
 #pragma unroll
     for (int e = 0; e < 4; ++e) w0[e] = w[e][c];
 #pragma unroll
@@ -85,6 +144,33 @@ __global__ __launch_bounds__(GV_WAVES * 64) void gemv_bf16_kernel(GemmArgs a) {
     for (int e = 0; e < 4; ++e) w1[e] = w[e][c1];
 #pragma unroll
     for (int t = 0; t < M; ++t) x1[t] = x[t][c1];
+    if constexpr (FUSED) n0 = ((const uint4*)fuse.norm_w)[c], n1 = ((const uint4*)fuse.norm_w)[c1];
+  };
+  int c = wave * 64 + lane;
+  request(min(c, chunks - 1));
+  float inv[M];
+  if constexpr (FUSED) {
+    if (wave < M) {
+      const float v = gemv_inv_rms(wave == 0 ? x[0] : x[M - 1], chunks, a.k, fuse.eps, lane, ahead);
+      if (lane == 0) inv_rms[wave] = v;
+    } else if (MODE == GEMM_QKV_ROPE && wave == M + quad % (GV_WAVES - M)) {
+      // the double-precision chain goes to another SIMD from workgroup to workgroup
+      const int f0 = 2 * (quad & 31);
+      const float2 cs = rope_cos_sin(fuse.rope, min(lane >> 1, a.m - 1), f0 + (lane & 1));
+      if (lane < 2 * M) angles[lane >> 1][lane & 1] = cs;
+    }
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // not for the weights under way
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+#pragma unroll
+    for (int t = 0; t < M; ++t) inv[t] = inv_rms[t];
+  }
+  for (; c < chunks; c += 2 * STEP) {
+    const bool has1 = c + STEP < chunks;
+    if constexpr (FUSED) {
+#pragma unroll
+      for (int t = 0; t < M; ++t) x0[t] = scale8(x0[t], n0, inv[t]), x1[t] = scale8(x1[t], n1, inv[t]);
+    }
 #pragma unroll
     for (int e = 0; e < 4; ++e)
 #pragma unroll
@@ -92,6 +178,7 @@ __global__ __launch_bounds__(GV_WAVES * 64) void gemv_bf16_kernel(GemmArgs a) {
         const float s0 = dot8(w0[e], x0[t], acc[e][t]), s1 = dot8(w1[e], x1[t], s0);
         acc[e][t] = has1 ? s1 : s0;
       }
+    if (c + 2 * STEP < chunks) request(c + 2 * STEP);
   }
 #pragma unroll
   for (int e = 0; e < 4; ++e)
@@ -133,7 +220,9 @@ __global__ __launch_bounds__(GV_WAVES * 64) void gemv_bf16_kernel(GemmArgs a) {
     else if (head < a.h_q + a.h_kv) dst = (bf16_t*)a.k_out, heads_dst = a.h_kv, head_dst = head - a.h_q;
     else dst = (bf16_t*)a.v_out, heads_dst = a.h_kv, head_dst = head - a.h_q - a.h_kv;
     if (head < a.h_q + a.h_kv) {
-      const float4 cs = *(const float4*)(a.cos_sin + ((size_t)t * 64 + f0) * 2);  // (cos, sin) of f0 and f0 + 1
+      float4 cs;  // (cos, sin) of f0 and f0 + 1
+      if constexpr (FUSED) cs = make_float4(angles[t][0].x, angles[t][0].y, angles[t][1].x, angles[t][1].y);
+      else cs = *(const float4*)(a.cos_sin + ((size_t)t * 64 + f0) * 2);
       const float c[2] = {cs.x, cs.z}, sn[2] = {cs.y, cs.w};
 #pragma unroll
       for (int e = 0; e < 2; ++e) {
@@ -143,8 +232,27 @@ __global__ __launch_bounds__(GV_WAVES * 64) void gemv_bf16_kernel(GemmArgs a) {
       }
     }
     bf16_t* out_row = dst + ((size_t)t * heads_dst + head_dst) * 128;
-    *(uint32_t*)(out_row + f0) = (uint32_t)f32_to_bf16_rne(lo[0]) | ((uint32_t)f32_to_bf16_rne(lo[1]) << 16);
-    *(uint32_t*)(out_row + 64 + f0) = (uint32_t)f32_to_bf16_rne(hi[0]) | ((uint32_t)f32_to_bf16_rne(hi[1]) << 16);
+    const uint32_t p0 = (uint32_t)f32_to_bf16_rne(lo[0]) | ((uint32_t)f32_to_bf16_rne(lo[1]) << 16);
+    const uint32_t p1 = (uint32_t)f32_to_bf16_rne(hi[0]) | ((uint32_t)f32_to_bf16_rne(hi[1]) << 16);
+    *(uint32_t*)(out_row + f0) = p0;
+    *(uint32_t*)(out_row + 64 + f0) = p1;
+    if constexpr (FUSED) {
+      if (fuse.ck != nullptr && head >= a.h_q) {
+        const size_t row = (size_t)head_dst * fuse.cap + fuse.len + t;
+        unsigned char* const cache = (unsigned char*)(head < a.h_q + a.h_kv ? fuse.ck : fuse.cv);
+        if (fuse.cache_fp8) {
+          *(uint16_t*)(cache + row * 128 + f0) = (uint16_t)(bf16_to_e4m3(p0 & 0xffffu) | (bf16_to_e4m3(p0 >> 16) << 8));
+          *(uint16_t*)(cache + row * 128 + 64 + f0) = (uint16_t)(bf16_to_e4m3(p1 & 0xffffu) | (bf16_to_e4m3(p1 >> 16) << 8));
+        } else {
+          *(uint32_t*)((bf16_t*)cache + row * 128 + f0) = p0;
+          *(uint32_t*)((bf16_t*)cache + row * 128 + 64 + f0) = p1;
+        }
+        if (f0 == 0 && head < a.h_q + a.h_kv) {
+          fuse.pos[row] = fuse.base + t;
+          if (fuse.kept != nullptr) fuse.kept[head_dst * a.m + t] = t;
+        }
+      }
+    }
   } else {  // GEMM_SWIGLU: y[0], y[1] gate and y[2], y[3] up of outputs row[0], row[0] + 1
     const float o0 = y[0] / (1.f + __expf(-y[0])) * y[2], o1 = y[1] / (1.f + __expf(-y[1])) * y[3];
     *(uint32_t*)((bf16_t*)a.out + (size_t)t * d_ff + row[0]) =
@@ -156,20 +264,29 @@ __global__ __launch_bounds__(GV_WAVES * 64) void gemv_bf16_kernel(GemmArgs a) {
 // (PLAIN), of 128 per head (QKV_ROPE) or of 256 (SWIGLU), hence of 4.
 bool gemv_applies(const GemmArgs& a) { return a.m <= GV_MAX_M; }
 
-template <int MODE>
-static hipError_t launch_gemv_mode(const GemmArgs& a, hipStream_t s) {
+template <int MODE, typename F>
+static hipError_t launch_gemv_mode(const GemmArgs& a, const F& f, hipStream_t s) {
   const dim3 grid((unsigned)(a.n / 4)), block(GV_WAVES * 64);
-  if (a.m == 1) hipLaunchKernelGGL((gemv_bf16_kernel<MODE, 1>), grid, block, 0, s, a);
-  else hipLaunchKernelGGL((gemv_bf16_kernel<MODE, 2>), grid, block, 0, s, a);
+  if (a.m == 1) hipLaunchKernelGGL((gemv_bf16_kernel<MODE, 1, F>), grid, block, 0, s, a, f);
+  else hipLaunchKernelGGL((gemv_bf16_kernel<MODE, 2, F>), grid, block, 0, s, a, f);
   return hipSuccess;
 }
 
 hipError_t launch_gemv_bf16(const GemmArgs& a, int mode, hipStream_t s) {
   if (!gemv_applies(a) || !gemm_supported(a, mode)) return hipErrorInvalidValue;
   switch (mode) {
-    case GEMM_PLAIN: return launch_gemv_mode<GEMM_PLAIN>(a, s);
-    case GEMM_QKV_ROPE: return launch_gemv_mode<GEMM_QKV_ROPE>(a, s);
-    case GEMM_SWIGLU: return launch_gemv_mode<GEMM_SWIGLU>(a, s);
+    case GEMM_PLAIN: return launch_gemv_mode<GEMM_PLAIN>(a, NoFusion(), s);
+    case GEMM_QKV_ROPE: return launch_gemv_mode<GEMM_QKV_ROPE>(a, NoFusion(), s);
+    case GEMM_SWIGLU: return launch_gemv_mode<GEMM_SWIGLU>(a, NoFusion(), s);
+  }
+  return hipErrorInvalidValue;
+}
+
+hipError_t launch_gemv_fused(const GemmArgs& a, const GemvFusion& f, int mode, hipStream_t s) {
+  if (!gemv_applies(a) || !gemm_supported(a, mode)) return hipErrorInvalidValue;
+  switch (mode) {
+    case GEMM_QKV_ROPE: return launch_gemv_mode<GEMM_QKV_ROPE>(a, f, s);
+    case GEMM_SWIGLU: return launch_gemv_mode<GEMM_SWIGLU>(a, f, s);
   }
   return hipErrorInvalidValue;
 }

@@ -196,6 +196,8 @@ qp_status qp_layer_group(const qp_layout* layout, const qp_layer_shape* shape, c
   if (cache->capacity < 0 || cache->len < 0 || cache->len > cache->capacity || !aligned16(cache->k) ||
       !aligned16(cache->v) || cache->pos == nullptr)
     return QP_ERR_INVALID_ARG;
+  if ((((uintptr_t)cache->pos) & 3u) || (((uintptr_t)kept_idx_or_null) & 3u)) return QP_ERR_INVALID_ARG;
+  if (cache->format != QP_CACHE_SAME && cache->format != QP_CACHE_FP8_E4M3) return QP_ERR_INVALID_ARG;
   if ((int64_t)cache->len + keep > cache->capacity) return QP_ERR_CAPACITY;
   const int32_t nw = windowed ? n_window : 0;
   const Carve c = carve(layout, shape, n_group_tokens, nw);
@@ -225,21 +227,38 @@ qp_status qp_layer_group(const qp_layout* layout, const qp_layer_shape* shape, c
   void* score_ws = ws + c.path;
   const size_t score_bytes = path_bytes - kSplit;
   void* split_ws = ws + c.path + (path_bytes - kSplit) / 256 * 256;
-  qp::launch_norm_rope(x_g, weights->ln1_w, ws + c.h, n_g, dm, shape->rms_eps, pos, (long)axis_stride, shape->rope_theta,
-                       shape->mrope_section[0], shape->mrope_section[1], (float*)(ws + c.cs), s);
-  st = finish(qp::launch_gemm_bf16(qkv, qp::GEMM_QKV_ROPE, ws + c.gemm, kGemmSplitBytes, s));
+  // A token or two (decoding): the weight-streaming kernel takes the norms, the rotary angles and, where every token is
+  // kept, the append into its own launches.
+  const bool streamed = qp::gemm_uses_gemv(qkv);
+  const bool appended = streamed && keep == n_g;
+  qp::GemvFusion fuse{};
+  if (streamed) {
+    fuse.norm_w = weights->ln1_w, fuse.eps = shape->rms_eps;
+    fuse.rope = qp::RopeArgs{pos, (long)axis_stride, n_g, shape->rope_theta, shape->mrope_section[0], shape->mrope_section[1], nullptr};
+    if (appended) {
+      fuse.ck = cache->k, fuse.cv = cache->v, fuse.pos = cache->pos, fuse.kept = kept_idx_or_null;
+      fuse.cap = cache->capacity, fuse.len = cache->len, fuse.base = group_token_base;
+      fuse.cache_fp8 = cache->format == QP_CACHE_FP8_E4M3;
+    }
+    qkv.x = x_g;
+    st = finish(qp::launch_gemv_fused(qkv, fuse, qp::GEMM_QKV_ROPE, s));
+  } else {
+    qp::launch_norm_rope(x_g, weights->ln1_w, ws + c.h, n_g, dm, shape->rms_eps, pos, (long)axis_stride, shape->rope_theta,
+                         shape->mrope_section[0], shape->mrope_section[1], (float*)(ws + c.cs), s);
+    st = finish(qp::launch_gemm_bf16(qkv, qp::GEMM_QKV_ROPE, ws + c.gemm, kGemmSplitBytes, s));
+  }
   if (st != QP_OK) return st;
   // Scoring, top-k and compaction need the group's K and V only, not its attention: they run on the library's side
   // stream beside the attention and the projections that follow, and are joined back before the call returns.
   // The attention reads cache entries [0, len), the compaction writes [len, len + keep).
   struct Side {
     hipStream_t main, side;
-    explicit Side(hipStream_t m) : main(m), side(qp::side_fork(m)) {}
+    Side(hipStream_t m, bool wanted) : main(m), side(wanted ? qp::side_fork(m) : nullptr) {}
     ~Side() {
       if (side != nullptr) qp::side_join(main);
     }
     hipStream_t stream() const { return side != nullptr ? side : main; }
-  } fork(s);
+  } fork(s, !appended);
   st = qp_group_attend(layout, ws + c.q, ws + c.k, ws + c.v, n_g, cache, ws + c.attn, nullptr, split_ws, kSplit, s);
   if (st != QP_OK) return st;
   if (keep < n_g) {  // with every token kept (the stages after the video) the scores decide nothing
@@ -247,12 +266,24 @@ qp_status qp_layer_group(const qp_layout* layout, const qp_layer_shape* shape, c
                      fork.stream());
     if (st != QP_OK) return st;
   }
-  st = qp_topk_compact(layout, (const float*)(ws + c.scores), ws + c.k, ws + c.v, n_g, keep, group_token_base, cache,
-                       kept_idx_or_null, score_ws, score_bytes, fork.stream());
-  if (st != QP_OK) return st;
-  st = finish(qp::launch_gemm_norm(oproj, weights->ln2_w, ws + c.h, shape->rms_eps, ws + c.gemm, kGemmSplitBytes, s));
-  if (st != QP_OK) return st;
-  st = finish(qp::launch_gemm_bf16(gate_up, qp::GEMM_SWIGLU, nullptr, 0, s));
+  if (appended) {
+    cache->len += keep;
+  } else {
+    st = qp_topk_compact(layout, (const float*)(ws + c.scores), ws + c.k, ws + c.v, n_g, keep, group_token_base, cache,
+                         kept_idx_or_null, score_ws, score_bytes, fork.stream());
+    if (st != QP_OK) return st;
+  }
+  if (streamed) {
+    st = finish(qp::launch_gemv_bf16(oproj, qp::GEMM_PLAIN, s));
+    if (st != QP_OK) return st;
+    fuse.norm_w = weights->ln2_w;
+    gate_up.x = ws + c.x1;
+    st = finish(qp::launch_gemv_fused(gate_up, fuse, qp::GEMM_SWIGLU, s));
+  } else {
+    st = finish(qp::launch_gemm_norm(oproj, weights->ln2_w, ws + c.h, shape->rms_eps, ws + c.gemm, kGemmSplitBytes, s));
+    if (st != QP_OK) return st;
+    st = finish(qp::launch_gemm_bf16(gate_up, qp::GEMM_SWIGLU, nullptr, 0, s));
+  }
   if (st != QP_OK) return st;
   return finish(qp::launch_gemm_bf16(down, qp::GEMM_PLAIN, ws + c.gemm, kGemmSplitBytes, s));
 }

@@ -82,33 +82,16 @@ __device__ __forceinline__ void rms_norm_token(const bf16_t* __restrict__ x, con
   }
 }
 
-// cos_sin[t][i] = (cos, sin)(pos[axis(i)][t] * theta^(-i/64)) for the 64 rotation frequencies of head_dim 128;
-// frequencies [0, s0) use position axis 0, [s0, s0+s1) axis 1, the rest axis 2. The angle (up to ~1e5 rad for long
-// videos) and its sine/cosine are evaluated in f64 and rounded once, so the table is as exact as f32 holds.
-struct RopeArgs {
-  const int32_t* pos;
-  long axis_stride;
-  int n_tokens;
-  float theta;
-  int s0, s1;
-  float2* cos_sin;
-};
-__device__ __forceinline__ void rope_entry(const RopeArgs& a, int id) {
-  if (id >= a.n_tokens * 64) return;
-  const int t = id >> 6, i = id & 63;
-  const int axis = i < a.s0 ? 0 : (i < a.s0 + a.s1 ? 1 : 2);
-  const double ang = (double)a.pos[axis * a.axis_stride + t] * exp2(-(double)i / 64.0 * log2((double)a.theta));
-  double sn, cs;
-  sincos(ang, &sn, &cs);
-  a.cos_sin[id] = make_float2((float)cs, (float)sn);
-}
-
 template <int RN_REG, bool AHEAD>
 __global__ __launch_bounds__(RN_WAVES * 64) void rms_norm_kernel(const bf16_t* __restrict__ x, const bf16_t* __restrict__ w,
                                                                  bf16_t* __restrict__ out, int n_tokens, int d_model,
                                                                  float eps) {
   const int t = blockIdx.x * RN_WAVES + (threadIdx.x >> 6);
   if (t < n_tokens) rms_norm_token<RN_REG, AHEAD>(x, w, out, t, d_model, eps);
+}
+
+__device__ __forceinline__ void rope_entry(const RopeArgs& a, int id) {
+  if (id < a.n_tokens * 64) a.cos_sin[id] = rope_cos_sin(a, id >> 6, id & 63);
 }
 
 __global__ __launch_bounds__(256) void rope_table_kernel(RopeArgs a) { rope_entry(a, blockIdx.x * 256 + threadIdx.x); }

@@ -4,6 +4,7 @@
 #include <stdint.h>
 
 #include "qp.h"
+#include "rope.h"
 
 namespace qp {
 
@@ -264,6 +265,19 @@ GemmSplit gemm_plan_split(const GemmArgs& a, int mode, size_t scratch_bytes);  /
 bool gemv_applies(const GemmArgs& a);
 bool gemm_uses_gemv(const GemmArgs& a);   // gemv_applies and no tiling is forced
 hipError_t launch_gemv_bf16(const GemmArgs& a, int mode, hipStream_t s);
+// Such a call with the layer's steps around it taken into the launch (QKV_ROPE and SWIGLU).
+struct GemvFusion {
+  const void* norm_w;  // x is RMSNormed on the way (weights [k], eps)
+  float eps;
+  RopeArgs rope;       // QKV_ROPE: the angles themselves instead of a table of them
+  // QKV_ROPE, ck != nullptr: the tokens' keys and values are appended to the cache too, all of them (keep = m)
+  void* ck;            // [h_kv][cap][128]
+  void* cv;
+  int32_t* pos;        // [h_kv][cap]
+  int32_t* kept;       // [h_kv][m] or nullptr
+  int cap, len, base, cache_fp8;
+};
+hipError_t launch_gemv_fused(const GemmArgs& a, const GemvFusion& f, int mode, hipStream_t s);
 int gemm_tile_rows(const GemmArgs& a);    // token rows per workgroup tile the launcher would use: 128 or 256
 int gemm_tile_cols(const GemmArgs& a);    // outputs per workgroup tile of an unsplit launch: 128 or 256
 void gemm_force_tile_rows(int rows);      // 0 = choose per launch (default), 128 or 256

@@ -656,6 +656,55 @@ def test_decode_step_equals_its_parts_bit_for_bit(dims, n_t):
     np.testing.assert_array_equal(caches[0].pos.cpu().numpy()[:, c0:c0 + n_t], 5000 + np.tile(np.arange(n_t), (dims.n_kv_heads, 1)))
 
 
+@pytest.mark.parametrize("n_t,keep", [(1, 1), (2, 2), (2, 1)])
+@pytest.mark.parametrize("fp8", [False, True])
+@pytest.mark.parametrize("d_model", [64, 4160, 8192, 8256])
+def test_decode_step_takes_norms_angles_and_append_with_it(d_model, fp8, n_t, keep):
+    """The launches of a token or two norm their rows, take the rotary angles and append to the cache (not where a token is
+    pruned): rows of less than a wavefront's chunks, of several trips, of more than the norm has in flight, over both cache
+    formats. Bit for bit what the separate calls give, the cache rows those of qp_topk_compact."""
+    dims = W.LayerDims(d_model, 256, 6, 2)
+    layout = B.make_layout(6, 2, 128, "bf16")
+    shape = B.make_layer_shape(d_model, 256, dims.rms_eps, dims.rope_theta, dims.mrope_section)
+    wt = {k_: v_.to(DEV) for k_, v_ in W.make_decoder_layer(dims, 0, seed=3).items()}
+    x = W.make_hidden(1, n_t, d_model, seed=8).to(DEV)
+    pos = W.text_positions(n_t, 90000).to(DEV)
+    fmt = B.QP_CACHE_FP8_E4M3 if fp8 else B.QP_CACHE_SAME
+    caches = [B.Cache(layout, 40, fmt=fmt) for _ in range(2)]
+    for cache in caches:
+        for t in (cache.k, cache.v):
+            g = torch.Generator(device=DEV).manual_seed(77)
+            t.copy_(torch.randn(t.shape, generator=g, device=DEV).to(torch.bfloat16))
+        cache.pos.fill_(-1)
+        cache.c.len = 37
+    out = torch.full_like(x, float("nan"))
+    kept = torch.full((2, 2, keep), -1, dtype=torch.int32, device=DEV)
+    B.layer_group(layout, shape, B.LayerWeights(**wt), x, pos, 0, 5000, None, "key_norm_small", keep, caches[0], out,
+                  kept[0], B.make_layer_workspace(layout, shape, n_t, 0))
+    h, x1, x2 = torch.empty_like(x), torch.empty_like(x), torch.empty_like(x)
+    cs = torch.empty(n_t, 64, 2, dtype=torch.float32, device=DEV)
+    q = torch.empty(n_t, 6, 128, dtype=torch.bfloat16, device=DEV)
+    k = torch.empty(n_t, 2, 128, dtype=torch.bfloat16, device=DEV)
+    v, attn, act = torch.empty_like(k), torch.empty_like(q), torch.empty(n_t, 256, dtype=torch.bfloat16, device=DEV)
+    scores = torch.empty(2, n_t, device=DEV)
+    B.rms_norm(x, wt["ln1_w"], h, dims.rms_eps)
+    B.rope_table(pos, 0, n_t, dims.rope_theta, dims.mrope_section, cs)
+    B.qkv_rope(layout, h, wt["w_qkv"], wt["b_qkv"], cs, q, k, v)
+    B.group_attend(layout, q, k, v, caches[1], attn, None, torch.empty(32 << 20, dtype=torch.uint8, device=DEV))
+    B.score_kv(layout, "key_norm_small", k, v, None, scores)
+    B.topk_compact(layout, scores, k, v, keep, 5000, caches[1], kept[1])
+    B.linear(attn.view(n_t, -1), wt["w_o"], None, x, x1)
+    B.rms_norm(x1, wt["ln2_w"], h, dims.rms_eps)
+    B.swiglu_gate_up(h, wt["w_gate_up"], act)
+    B.linear(act, wt["w_down"], None, x1, x2)
+    torch.cuda.synchronize()
+    assert torch.isfinite(out.float()).all() and torch.equal(out, x2)
+    assert caches[0].len == caches[1].len == 37 + keep
+    assert torch.equal(kept[0], kept[1]) and torch.equal(caches[0].pos, caches[1].pos)
+    for a, b in ((caches[0].k, caches[1].k), (caches[0].v, caches[1].v)):
+        assert torch.equal(a.view(torch.uint8), b.view(torch.uint8))
+
+
 @pytest.mark.parametrize("n_t,dims", [(7, SMALL), (3, W.LayerDims(2112, 256, 4, 2)), (64, W.LayerDims(8192, 256, 8, 2)),
                                       (5, W.LayerDims(8256, 256, 8, 2))], ids=["256", "2112", "8192", "8256"])
 def test_text_chunk_equals_its_parts(n_t, dims):
