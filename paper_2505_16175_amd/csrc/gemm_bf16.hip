@@ -178,12 +178,15 @@ __global__ __launch_bounds__(T::NW * 64) void gemm_bf16_kernel(GemmArgs a) {
   // loop the barrier sits before the LAST k-step's products of a step: by then every wavefront has read all its
   // fragments of the step (its slots can be refilled), the next step's tiles have landed, and the wait at the
   // barrier and the latency of the next step's first fragment reads run under those products.
-  // With equal rings all refill requests are issued there too. At 256 x 256 that is 64 of them per step within a quarter
+  // With equal rings of the smaller tilings all refill requests are issued there too. At 256 x 256 that is 64 of them per step within a quarter
   // of its products: the address path takes 16 cycles for each, falls behind, and holds up the products behind the
   // requests. So that tiling (rings of 2 and 3) spreads them: a step t issues, two per k-step and wavefront, the second
   // half of X(t + 1), then W(t + 2) into the slot that step t - 1 left, then, behind the barrier, the first half of
   // X(t + 2). PFLOP/s at 4096 x 59136 x 8192 / 4096 x 8192 x 29568 / 2048 x 37888 x 3584: 1.25 / 1.23 / 1.17 all behind
-  // the barrier (with or without the third weight slot), 1.35 / 1.31 / 1.25 spread.
+  // the barrier (with or without the third weight slot), 1.35 / 1.31 / 1.25 spread. The 128 x 256 tiling (equal rings of 3)
+  // spreads them too: a step t issues step t + 2 into the slot that step t - 1 left, a request behind every other product
+  // before the barrier. us behind the barrier / spread: 2048 x 3584 x 18944 262 / 257, 300 x 37888 x 3584 112 / 105, 257
+  // tokens of it 100 / 96, 300 x 59136 x 8192 365 / 340; 300 x 4608 x 3584 in 4 chunks 27.9 / 28.4.
   // Requests complete in order: when step t + 1 is awaited at the end of step t, what may stay in flight is, with equal
   // rings, the XS - 2 steps after it, and with rings of 2 and 3 the weights of step t + 2.
   const int n_steps = min(a.steps_per_split, a.k / BK - step_begin);
@@ -224,6 +227,8 @@ __global__ __launch_bounds__(T::NW * 64) void gemm_bf16_kernel(GemmArgs a) {
   constexpr int PER = (PIECES + NM - 1) / NM;         // of them behind each product
   GM_READ(smem, smem, 0, 0)
   int xslot = 0, wslot = 0;
+  constexpr bool SPREAD = XS == WS && T::MI == 2 && T::BN == 256;
+  static_assert(!SPREAD || PW <= (T::KS - 1) * NM / 2, "a request behind every other product");
   static_assert(XS == WS || (T::XQ == 4 && T::WQ == 4 && T::MI == 4 && T::KS == 4), "spread of the requests");
   // One step that has a successor; refill_x / refill_w: there is a step left to request into the freed slots, refill_x0:
   // the second half of the next step's activations is still to be requested (rings of 2 and 3).
@@ -249,6 +254,19 @@ __global__ __launch_bounds__(T::NW * 64) void gemm_bf16_kernel(GemmArgs a) {
           }
           __builtin_amdgcn_sched_barrier(0);
         }
+      } else if (SPREAD) {
+        const int free = xslot == 0 ? XS - 1 : xslot - 1;  // the slot that the step before left
+#pragma unroll
+        for (int mf = 0; mf < NM; ++mf) {
+          GM_MFMA_ONE(s & 1, mf)
+          __builtin_amdgcn_sched_barrier(0);
+          const int at = s * NM + mf, q = at / 2;
+          if ((at & 1) && q < PW && refill_w) {
+            if (q < T::XQ) GM_ISSUE_X(q, step + XS - 1, free)
+            else GM_ISSUE_W(q - T::XQ, step + XS - 1, free)
+          }
+          __builtin_amdgcn_sched_barrier(0);
+        }
       } else {
         GM_MFMA(s & 1)
       }
@@ -266,9 +284,9 @@ __global__ __launch_bounds__(T::NW * 64) void gemm_bf16_kernel(GemmArgs a) {
       for (int u = 0; u < PER; ++u) {
         const int p = mf * PER + u;
         if (p < T::XQ) {
-          if (refill_x && (XS == WS || p < T::XQ / 2)) GM_ISSUE_X(p, step + XS, xslot)
+          if (!SPREAD && refill_x && (XS == WS || p < T::XQ / 2)) GM_ISSUE_X(p, step + XS, xslot)
         } else if (p < PW) {
-          if (refill_w && XS == WS) GM_ISSUE_W(p - T::XQ, step + WS, wslot)
+          if (!SPREAD && refill_w && XS == WS) GM_ISSUE_W(p - T::XQ, step + WS, wslot)
         } else if (p < PIECES) {
           GM_READ_ONE(xst_next, wst_next, p - PW)
         }
@@ -279,9 +297,9 @@ __global__ __launch_bounds__(T::NW * 64) void gemm_bf16_kernel(GemmArgs a) {
   };
   int step = 0;
   for (; step + XS < n_steps; ++step)
-    step_and_next(step, step > 0, true, true, [] { gm_wait_vmcnt<XS != WS ? T::WQ : (XS - 2) * PW>(); });
+    step_and_next(step, step > 0, true, !SPREAD || step > 0, [] { gm_wait_vmcnt<XS != WS ? T::WQ : (XS - 2) * PW>(); });
   for (; step + 1 < n_steps; ++step)
-    step_and_next(step, step > 0 && step + 1 < n_steps, false, false, [&] {
+    step_and_next(step, step > 0 && step + 1 < n_steps, false, SPREAD && step > 0 && step + XS - 1 < n_steps, [&] {
       if (XS == WS && XS >= 3 && step + 2 < n_steps) gm_wait_vmcnt<PW>();
       else gm_wait_vmcnt<0>();
     });
