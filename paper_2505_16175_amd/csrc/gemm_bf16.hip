@@ -114,8 +114,17 @@ __global__ __launch_bounds__(T::NW * 64) void gemm_bf16_kernel(GemmArgs a) {
   // side, its L2 then fetches 8 + 4 operand tiles per k-step for 32 products. (Weight tiles dealt to the XCDs in turn
   // left them unequal: 18 weight tiles x 12 token tiles put 36 workgroups on two XCDs of 32 CUs, 166 us for QKV of 3000
   // tokens at 7B sizes, 99 now.)
-  const int per_xcd = gridDim.x >> 3, id = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
-  if (id >= a.tiles_m * a.tiles_n) return;  // padding of the mapping (whole workgroup, before any barrier)
+  // A split contraction has a grid row per k chunk, or (a grid of one row) its items are the chunks of its tiles, tile by
+  // tile, and those are dealt to the XCDs.
+  const bool by_item = gridDim.y < a.split_k;
+  const int per_xcd = gridDim.x >> 3;
+  int id = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3), chunk = blockIdx.y;
+  if (id >= a.tiles_m * a.tiles_n * (by_item ? a.split_k : 1)) return;  // padding of the mapping (whole workgroup, before any barrier)
+  if (by_item) {
+    const int tile = id / a.split_k;
+    chunk = id - tile * a.split_k;
+    id = tile;
+  }
   // block `quad` of n_quads has the weight tiles quad, quad + n_quads, ...: nw of them, one more in the first n_more blocks
   const int n_quads = (a.tiles_n + 3) / 4, fewer = a.tiles_n / n_quads, n_more = a.tiles_n - fewer * n_quads;
   const int in_more = n_more * (fewer + 1) * a.tiles_m;
@@ -148,8 +157,8 @@ __global__ __launch_bounds__(T::NW * 64) void gemm_bf16_kernel(GemmArgs a) {
     const int wr = min(weight_row<MODE>(r, n0, d_ff), a.n - 1);
     w_off[q] = (unsigned)((size_t)(wr - wb) * row_b) + (unsigned)((lane % T::CPR) ^ T::swizzle(r)) * 16;
   }
-  // contraction split (launches of few tiles): grid.y deals the k-steps to chunks, each leaving an f32 partial tile
-  const int step_begin = blockIdx.y * a.steps_per_split;
+  // contraction split (launches of few tiles): the k-steps are dealt to chunks, each leaving an f32 partial tile
+  const int step_begin = chunk * a.steps_per_split;
   const unsigned char* x_base = xg + (size_t)m0 * row_b + (size_t)step_begin * ROWB;
   const unsigned char* w_base = wg + (size_t)wb * row_b + (size_t)step_begin * ROWB;
   const unsigned smem_lds = (unsigned)(size_t)(__attribute__((address_space(3))) unsigned char*)smem;
@@ -326,7 +335,7 @@ __global__ __launch_bounds__(T::NW * 64) void gemm_bf16_kernel(GemmArgs a) {
   if (a.split_k > 1) {
     // partial sums of this k chunk, f32 [chunk][m][n] with n the output's logical column (for QKV: head * 128 + dim);
     // gemm_reduce_kernel adds the chunks in order and applies the mode's store
-    float* part = a.partial + (size_t)blockIdx.y * a.m * a.n;
+    float* part = a.partial + (size_t)chunk * a.m * a.n;
 #pragma unroll
     for (int j = 0; j < 2; ++j)
 #pragma unroll
@@ -745,7 +754,14 @@ static hipError_t launch_tile(GemmArgs a, hipStream_t s) {
   a.tiles_n = (a.n + T::BN - 1) / T::BN;
   a.m_block = a.tiles_m < 8 ? a.tiles_m : 8;
   const long tiles = (long)a.tiles_m * a.tiles_n;
-  hipLaunchKernelGGL((gemm_bf16_kernel<MODE, T>), dim3((unsigned)((tiles + 7) / 8 * 8), a.split_k), dim3(T::NW * 64), lds, s, a);
+  // Tiles of one workgroup per CU that are few and no multiple of 8 leave XCDs short if only they are dealt: 42 tiles x 6
+  // chunks were 36 workgroups on seven XCDs of 32 CUs and none on the last. us dealt by tiles / by items: 3584 x 18944 at
+  // 257 / 300 / 384 tokens 90 / 95 / 106 -> 55 / 59 / 66; 4608 x 3584 at 160 / 256 32 / 38 -> 22 / 26. Narrow tiles, two and
+  // three to a CU, have the room: 4608 x 3584 at 128 tokens 24.0, by items 25.1. Chunk by chunk an XCD would read one range
+  // of k of all rows, and rows 16 KB apart then meet in few memory channels: 8192 x 8192 at 3 tokens 29.5 -> 32.7.
+  const bool by_item = a.split_k > 1 && T::BN == GM_BN && tiles % 8 != 0;
+  const dim3 grid = by_item ? dim3((unsigned)((tiles * a.split_k + 7) / 8 * 8)) : dim3((unsigned)((tiles + 7) / 8 * 8), a.split_k);
+  hipLaunchKernelGGL((gemm_bf16_kernel<MODE, T>), grid, dim3(T::NW * 64), lds, s, a);
   return hipSuccess;
 }
 

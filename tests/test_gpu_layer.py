@@ -792,3 +792,8 @@ def test_layer_stack_replays_from_a_hip_graph():
         torch.cuda.synchronize()
         for a, b in zip([out] + [t for c in caches for t in (c.k, c.v, c.pos)], want):
             assert torch.equal(a, b), f"eager after replay {replay}"
+
+
+def test_qkv_rope_split_in_wide_tiles():
+    """36 tiles of 128 x 256 in 7 chunks, dealt to the XCDs as 252 items."""
+    test_qkv_rope_split_contraction(200, 3584, 28, 4)
