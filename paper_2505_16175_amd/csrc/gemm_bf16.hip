@@ -672,21 +672,22 @@ void gemm_force_tile_rows(int rows) { g_forced_tile_rows.store(rows, std::memory
 // 7B o_proj at 700 tokens, 84 / 168 tiles, 48 -> 30 us; 72B down at 512, 128 / 256 tiles, 420 -> 289 us).
 struct TileChoice {
   int rows, cols;
+  double cost;  // of the launch, in 256 x 256 tiles one after the other
 };
 static TileChoice gemm_tile(const GemmArgs& a) {
   const int forced = g_forced_tile_rows.load(std::memory_order_relaxed);
-  if (forced != 0) return {forced, GM_BN};
+  if (forced != 0) return {forced, GM_BN, 0};
   static const struct {
     int rows, cols;
     double cost;
   } kinds[] = {{256, 256, 1.0}, {128, 256, 0.62}, {128, 128, 0.39}};
   const int cus = device_cu_count();
-  TileChoice best{256, 256};
+  TileChoice best{256, 256, 0};
   double best_cost = 1e30;
   for (const auto& t : kinds) {
     const long tiles = (long)((a.m + t.rows - 1) / t.rows) * ((a.n + t.cols - 1) / t.cols);
     const double cost = t.cost * (double)((tiles + cus - 1) / cus);
-    if (cost < best_cost) best_cost = cost, best = {t.rows, t.cols};
+    if (cost < best_cost) best_cost = cost, best = {t.rows, t.cols, cost};
   }
   return best;
 }
@@ -712,13 +713,35 @@ int gemm_tile_cols(const GemmArgs& a) { return gemm_tile(a).cols; }
 // 26.5 us at 40 tokens and k = 8192, 31.8 / 35.3 at 100 tokens, but 13.4 / 13.3 and 19.9 / 17.8 at k = 3584; with 80
 // tiles, which take 4, 24.5 / 27.2 and 34.0 / 36.1, but 14.1 / 13.4 and 20.1 / 18.0: the line lies where long and short
 // contractions lose about as much.
+//
+// Above a quarter of the CUs a product without fused steps is still split where two or three chunks of its 128 x 256 tiles
+// fill the chip (at least 4/5 of it, one round) and the estimate, with the tile times above and the partial sums at 4.5 TB/s,
+// is a tenth below the unsplit one: long contractions whose tiles leave CUs idle or are small ones. us unsplit / split:
+// 3584 x 18944 at 520 tokens 137 / 91, 640 167 / 105, 768 166 / 110, 900 148 / 130, 1024 170 / 148, 1100 163 / 149; 8192 x
+// 29568 at 400 275 / 221, 512 290 / 253. At k = 3584 (o_proj) there is nothing to gain.
 constexpr int NARROW_ABOVE = 8;
 GemmSplit gemm_plan_split(const GemmArgs& a, int mode, size_t scratch_bytes) {
-  GemmSplit p{1, a.k / GM_BK, 0, 0};
+  GemmSplit p{1, a.k / GM_BK, 0, 0, 0};
   if (mode == GEMM_SWIGLU || scratch_bytes == 0 || gemm_uses_gemv(a)) return p;
   const int rows = gemm_tile_rows(a), cus = device_cu_count();
   const long tiles_m = (a.m + rows - 1) / rows, tiles = tiles_m * ((a.n + GM_BN - 1) / GM_BN);
   const int steps = a.k / GM_BK;
+  if (tiles * 4 > cus && mode == GEMM_PLAIN && g_forced_tile_rows.load(std::memory_order_relaxed) == 0) {
+    const long halves = (long)((a.m + 127) / 128) * ((a.n + GM_BN - 1) / GM_BN);  // tiles of 128 x 256
+    const double us = 1.55 * gemm_tile(a).cost * steps;  // unsplit
+    const size_t per_chunk = (size_t)a.m * a.n * sizeof(float);
+    for (int want = 2; want <= 3; ++want) {
+      const long wgs = halves * want;
+      if (wgs > cus || wgs * 5 < (long)cus * 4 || want * per_chunk > scratch_bytes || steps < 4 * want) continue;
+      const int per = (steps + want - 1) / want;
+      if (0.95 * per + 4 + 2.0 * want * per_chunk / 4.5e6 > 0.9 * us) continue;
+      p.steps_per_split = per;
+      p.split_k = (steps + per - 1) / per;
+      p.scratch_bytes = (size_t)p.split_k * per_chunk;
+      p.halves = 1;
+      return p;
+    }
+  }
   if (tiles * 4 > cus || steps < 8) return p;
   long want = (cus + tiles - 1) / tiles;
   if (want > steps / 4) want = steps / 4;
@@ -732,7 +755,7 @@ GemmSplit gemm_plan_split(const GemmArgs& a, int mode, size_t scratch_bytes) {
     p.narrow = 1;
   }
   if ((size_t)want * per_chunk > scratch_bytes) want = (long)(scratch_bytes / per_chunk);
-  if (want < 2) return GemmSplit{1, steps, 0, 0};
+  if (want < 2) return GemmSplit{1, steps, 0, 0, 0};
   p.steps_per_split = (int)((steps + want - 1) / want);
   p.split_k = (steps + p.steps_per_split - 1) / p.steps_per_split;  // every chunk non-empty
   p.scratch_bytes = (size_t)p.split_k * per_chunk;
@@ -777,7 +800,7 @@ static hipError_t launch_mode(GemmArgs& a, void* scratch, size_t scratch_bytes, 
   } else if (a.split_k == 1 && gemm_tile_cols(a) == 128) {
     e = launch_tile<MODE, Mid>(a, s);
   } else {
-    e = gemm_tile_rows(a) == 128 ? launch_tile<MODE, Tile128>(a, s) : launch_tile<MODE, Tile256>(a, s);
+    e = sp.halves || gemm_tile_rows(a) == 128 ? launch_tile<MODE, Tile128>(a, s) : launch_tile<MODE, Tile256>(a, s);
   }
   if (e != hipSuccess || a.split_k == 1 || !reduce) return e;
   const long threads = (long)a.m * (MODE == GEMM_QKV_ROPE ? a.n / 8 : a.n / 4);

@@ -145,7 +145,7 @@ qp_status qp_linear_plan(int32_t m, int32_t n, int32_t k, size_t workspace_bytes
     out->scratch_bytes = 0;
     return QP_OK;
   }
-  const int rows = qp::gemm_tile_rows(a);
+  const int rows = sp.halves ? 128 : qp::gemm_tile_rows(a);
   const int cols = sp.narrow ? 64 : sp.split_k > 1 ? 256 : qp::gemm_tile_cols(a);
   const int tiles_m = (m + rows - 1) / rows, tiles_n = (n + cols - 1) / cols;
   out->token_rows_per_tile = rows;

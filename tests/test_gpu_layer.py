@@ -325,6 +325,23 @@ def test_wide_split_tiles(m, n, k):
     assert_stored_close(to_f64(out), LO.bf16_round(LO.linear(to_f64(x), to_f64(w), to_f64(b)) + to_f64(r)), "wide split tiles")
 
 
+@pytest.mark.parametrize("m,n,k,chunks", [(513, 3592, 4160, 3), (900, 3584, 18944, 2)])
+def test_split_where_chunks_fill_the_chip(m, n, k, chunks):
+    """A long contraction whose unsplit tiles are small or leave compute units idle: two or three chunks of 128 x 256 tiles,
+    token rows, outputs and the last chunk's steps that end inside them. QKV and SwiGLU keep their layouts."""
+    p = B.linear_plan(m, n, k, 32 << 20)
+    tiles = -(-m // 128) * -(-n // 256)
+    assert p["k_chunks"] == chunks and p["token_rows_per_tile"] == 128 and p["workgroups"] == (tiles + 7) // 8 * 8
+    assert 4 * 256 <= 5 * tiles * chunks <= 5 * 256 and B.linear_plan(m, n, k, chunks * m * n * 4 - 1)["k_chunks"] == 1
+    g = torch.Generator().manual_seed(m + n + k)
+    x, w, b, r = _bf(m, k, gen=g), _bf(n, k, gen=g, scale=k ** -0.5), _bf(n, gen=g), _bf(m, n, gen=g)
+    scratch = torch.empty(32 << 20, dtype=torch.uint8, device=DEV).fill_(0xff)
+    out = torch.full((m, n), float("nan"), dtype=torch.bfloat16, device=DEV)
+    B.linear(x.to(DEV), w.to(DEV), b.to(DEV), r.to(DEV), out, scratch)
+    torch.cuda.synchronize()
+    assert_stored_close(to_f64(out), LO.bf16_round(LO.linear(to_f64(x), to_f64(w), to_f64(b)) + to_f64(r)), "split in halves")
+
+
 @pytest.mark.parametrize("n,d_model,h_q,h_kv", [(1, 3584, 28, 4), (9, 1024, 4, 2), (64, 3584, 28, 4),
                                                   (65, 3584, 28, 4), (128, 3584, 28, 4), (37, 2048, 64, 8)])
 def test_qkv_rope_split_contraction(n, d_model, h_q, h_kv):
