@@ -120,7 +120,7 @@ size_t qp_layer_workspace_bytes(const qp_layout* layout, const qp_layer_shape* s
  * Scoring, top-k and compaction depend on the group's K and V only; they are enqueued on a library-owned side
  * stream (one per device, default priority, the one qp_prefill_video uses) forked from hip_stream after the QKV
  * projection and joined back into it before the call returns, so they run beside the attention and the
- * projections. One or two tokens that are all kept are appended by the QKV projection itself, without that stream.
+ * projections. Tokens that are all kept are appended by the QKV projection itself, without that stream.
  * Calls from several host threads are serialised while they enqueue on it.
  * Errors: INVALID_ARG, UNSUPPORTED (shape), CAPACITY (cache or workspace too small); on any error nothing is
  * launched and the cache is untouched. */

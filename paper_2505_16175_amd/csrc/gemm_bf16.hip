@@ -26,6 +26,7 @@
 // token tiles x weight tiles, which bounds what its L2 has to fetch per k-step.
 #include <atomic>
 
+#include "append.h"
 #include "qp_internal.h"
 
 namespace qp {
@@ -33,7 +34,6 @@ namespace qp {
 typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8;
 typedef __attribute__((__vector_size__(4 * sizeof(__bf16)))) __bf16 bf16x4;
 typedef __attribute__((__vector_size__(16 * sizeof(float)))) float f32x16;
-typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int GM_BK = 64;   // k per ring slot
 constexpr int GM_BN = 256;  // weight rows per tile of the wide tilings
@@ -498,6 +498,7 @@ __global__ __launch_bounds__(T::NW * 64) void gemm_bf16_kernel(GemmArgs a) {
       }
     }
     settle();
+    const bool appends = a.append.k != nullptr && head >= a.h_q;
     bf16_t* const col = dst + (size_t)head_dst * 128 + dim0 + 8 * s_chunk;
 #pragma unroll
     for (int i = 0; i < T::MI; ++i)
@@ -506,8 +507,15 @@ __global__ __launch_bounds__(T::NW * 64) void gemm_bf16_kernel(GemmArgs a) {
         const int r = u * (64 / SC) + s_row, m = mw + 32 * i + r;
         if (m < a.m) {
           bf16_t* const at = col + (size_t)m * heads_dst * 128;
-          *(u32x4*)at = chunk_of(2 * i, r);
-          *(u32x4*)(at + 64) = chunk_of(2 * i + 1, r);
+          const u32x4 lo = chunk_of(2 * i, r), hi = chunk_of(2 * i + 1, r);
+          *(u32x4*)at = lo;
+          *(u32x4*)(at + 64) = hi;
+          if (appends) {
+            const int dim = dim0 + 8 * s_chunk;
+            append_chunk(a.append, !rotate, head_dst, m, dim, lo);
+            append_chunk(a.append, !rotate, head_dst, m, dim + 64, hi);
+            if (rotate && dim == 0) append_index(a.append, head_dst, m, a.m);
+          }
         }
       }
   }
@@ -592,6 +600,12 @@ __global__ __launch_bounds__(256) void gemm_reduce_kernel(GemmArgs a) {
     bf16_t* row = dst + ((size_t)m * heads_dst + head_dst) * 128;
     *(uint2*)(row + f) = __builtin_bit_cast(uint2, p0);
     *(uint2*)(row + 64 + f) = __builtin_bit_cast(uint2, p1);
+    if (a.append.k != nullptr && head >= a.h_q) {
+      const bool is_v = head >= a.h_q + a.h_kv;
+      append_run(a.append, is_v, head_dst, m, f, __builtin_bit_cast(uint2, p0));
+      append_run(a.append, is_v, head_dst, m, f + 64, __builtin_bit_cast(uint2, p1));
+      if (!is_v && f == 0) append_index(a.append, head_dst, m, a.m);
+    }
   }
 }
 

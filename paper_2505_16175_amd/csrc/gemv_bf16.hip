@@ -24,14 +24,14 @@
 //   * the 64 lanes' sums are added by shuffles, the 4 wavefronts' sums meet in LDS and are added in wavefront order
 //     (deterministic), and one lane per token applies the store.
 //
-// Inside a layer (launch_gemv_fused) the QKV and gate/up launches also take the RMSNorm of their rows, the rotary angles
-// and the append to the cache, which as launches of their own were latency and nothing else (norm + angles 6.1 us, second
-// norm 4.5, append 1.8 with a side stream forked and joined around it; 7B layer, one token over 46,125 entries 132.3 ->
-// 118.6 us). Every workgroup repeats the norm: wavefront t takes token t's sum of squares, over its row's chunks and
+// Inside a layer (launch_gemv_fused) the QKV and gate/up launches also take the RMSNorm of their rows and the rotary angles,
+// which as launches of their own were latency and nothing else (norm + angles 6.1 us, second norm 4.5; with the append to
+// the cache, 1.8 us and a side stream forked and joined around it, which QKV_ROPE takes too: 7B layer, one token over
+// 46,125 entries 132.3 -> 118.6 us). Every workgroup repeats the norm: wavefront t takes token t's sum of squares, over its row's chunks and
 // lanes in the order of rms_norm_kernel, so that the factor's bits are the same, while the first weights are on
 // their way; every wavefront scales and rounds the chunks that it multiplies. Another wavefront takes the workgroup's
 // four angles (two frequencies per token) in double precision.
-#include "fp8_e4m3.h"
+#include "append.h"
 #include "qp_internal.h"
 
 #include <type_traits>
@@ -236,22 +236,17 @@ __global__ __launch_bounds__(GV_WAVES * 64) void gemv_bf16_kernel(GemmArgs a, F 
     const uint32_t p1 = (uint32_t)f32_to_bf16_rne(hi[0]) | ((uint32_t)f32_to_bf16_rne(hi[1]) << 16);
     *(uint32_t*)(out_row + f0) = p0;
     *(uint32_t*)(out_row + 64 + f0) = p1;
-    if constexpr (FUSED) {
-      if (fuse.ck != nullptr && head >= a.h_q) {
-        const size_t row = (size_t)head_dst * fuse.cap + fuse.len + t;
-        unsigned char* const cache = (unsigned char*)(head < a.h_q + a.h_kv ? fuse.ck : fuse.cv);
-        if (fuse.cache_fp8) {
-          *(uint16_t*)(cache + row * 128 + f0) = (uint16_t)(bf16_to_e4m3(p0 & 0xffffu) | (bf16_to_e4m3(p0 >> 16) << 8));
-          *(uint16_t*)(cache + row * 128 + 64 + f0) = (uint16_t)(bf16_to_e4m3(p1 & 0xffffu) | (bf16_to_e4m3(p1 >> 16) << 8));
-        } else {
-          *(uint32_t*)((bf16_t*)cache + row * 128 + f0) = p0;
-          *(uint32_t*)((bf16_t*)cache + row * 128 + 64 + f0) = p1;
-        }
-        if (f0 == 0 && head < a.h_q + a.h_kv) {
-          fuse.pos[row] = fuse.base + t;
-          if (fuse.kept != nullptr) fuse.kept[head_dst * a.m + t] = t;
-        }
+    if (a.append.k != nullptr && head >= a.h_q) {
+      const size_t row = append_row(a.append, head_dst, t);
+      unsigned char* const cache = (unsigned char*)(head < a.h_q + a.h_kv ? a.append.k : a.append.v);
+      if (a.append.fp8) {
+        *(uint16_t*)(cache + row * 128 + f0) = (uint16_t)(bf16_to_e4m3(p0 & 0xffffu) | (bf16_to_e4m3(p0 >> 16) << 8));
+        *(uint16_t*)(cache + row * 128 + 64 + f0) = (uint16_t)(bf16_to_e4m3(p1 & 0xffffu) | (bf16_to_e4m3(p1 >> 16) << 8));
+      } else {
+        *(uint32_t*)((bf16_t*)cache + row * 128 + f0) = p0;
+        *(uint32_t*)((bf16_t*)cache + row * 128 + 64 + f0) = p1;
       }
+      if (f0 == 0 && head < a.h_q + a.h_kv) append_index(a.append, head_dst, t, a.m);
     }
   } else {  // GEMM_SWIGLU: y[0], y[1] gate and y[2], y[3] up of outputs row[0], row[0] + 1
     const float o0 = y[0] / (1.f + __expf(-y[0])) * y[2], o1 = y[1] / (1.f + __expf(-y[1])) * y[3];

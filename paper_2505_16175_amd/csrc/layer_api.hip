@@ -227,19 +227,17 @@ qp_status qp_layer_group(const qp_layout* layout, const qp_layer_shape* shape, c
   void* score_ws = ws + c.path;
   const size_t score_bytes = path_bytes - kSplit;
   void* split_ws = ws + c.path + (path_bytes - kSplit) / 256 * 256;
-  // A token or two (decoding): the weight-streaming kernel takes the norms, the rotary angles and, where every token is
-  // kept, the append into its own launches.
-  const bool streamed = qp::gemm_uses_gemv(qkv);
-  const bool appended = streamed && keep == n_g;
+  // Where every token is kept (the stages after the video) the projection appends to the cache itself: the append's launch
+  // is short, but a side stream forked and joined around it held the caller's up (7B layer, 64 tokens over 46,125 entries
+  // 212.5 us, 202.5 without). A token or two (decoding): the weight-streaming kernel takes the norms and the rotary angles into its own launches.
+  const bool appended = keep == n_g, streamed = qp::gemm_uses_gemv(qkv);
+  if (appended)
+    qkv.append = qp::CacheAppend{cache->k, cache->v, cache->pos, kept_idx_or_null, cache->capacity, cache->len,
+                                 group_token_base, cache->format == QP_CACHE_FP8_E4M3};
   qp::GemvFusion fuse{};
   if (streamed) {
     fuse.norm_w = weights->ln1_w, fuse.eps = shape->rms_eps;
     fuse.rope = qp::RopeArgs{pos, (long)axis_stride, n_g, shape->rope_theta, shape->mrope_section[0], shape->mrope_section[1], nullptr};
-    if (appended) {
-      fuse.ck = cache->k, fuse.cv = cache->v, fuse.pos = cache->pos, fuse.kept = kept_idx_or_null;
-      fuse.cap = cache->capacity, fuse.len = cache->len, fuse.base = group_token_base;
-      fuse.cache_fp8 = cache->format == QP_CACHE_FP8_E4M3;
-    }
     qkv.x = x_g;
     st = finish(qp::launch_gemv_fused(qkv, fuse, qp::GEMM_QKV_ROPE, s));
   } else {
@@ -261,14 +259,12 @@ qp_status qp_layer_group(const qp_layout* layout, const qp_layer_shape* shape, c
   } fork(s, !appended);
   st = qp_group_attend(layout, ws + c.q, ws + c.k, ws + c.v, n_g, cache, ws + c.attn, nullptr, split_ws, kSplit, s);
   if (st != QP_OK) return st;
-  if (keep < n_g) {  // with every token kept (the stages after the video) the scores decide nothing
-    st = qp_score_kv(layout, rule, ws + c.k, ws + c.v, n_g, q_win, nw, (float*)(ws + c.scores), score_ws, score_bytes,
-                     fork.stream());
-    if (st != QP_OK) return st;
-  }
   if (appended) {
     cache->len += keep;
   } else {
+    st = qp_score_kv(layout, rule, ws + c.k, ws + c.v, n_g, q_win, nw, (float*)(ws + c.scores), score_ws, score_bytes,
+                     fork.stream());
+    if (st != QP_OK) return st;
     st = qp_topk_compact(layout, (const float*)(ws + c.scores), ws + c.k, ws + c.v, n_g, keep, group_token_base, cache,
                          kept_idx_or_null, score_ws, score_bytes, fork.stream());
     if (st != QP_OK) return st;

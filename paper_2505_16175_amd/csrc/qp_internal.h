@@ -233,6 +233,14 @@ hipError_t launch_topk_compact(const TopkArgs& a, int dtype, int32_t* kept_ws, h
 
 // ---- decoder layer around the path: projections with fused elementwise steps, RMSNorm, rotary table ----
 enum GemmMode { GEMM_PLAIN = 0, GEMM_QKV_ROPE = 1, GEMM_SWIGLU = 2 };
+// Where the QKV projection also appends its tokens' keys and values to the cache, all of them in order (keep = m).
+struct CacheAppend {
+  void* k;         // [h_kv][cap][128], nullptr: nothing is appended
+  void* v;
+  int32_t* pos;    // [h_kv][cap]
+  int32_t* kept;   // [h_kv][m] or nullptr
+  int cap, len, base, fp8;
+};
 struct GemmArgs {
   const void* x;         // [m][k] bf16 activations
   const void* w;         // [n][k] bf16 weights ([out][in]); SWIGLU: n = 2 d_ff, gate rows then up rows
@@ -248,6 +256,7 @@ struct GemmArgs {
   int tiles_m, tiles_n, m_block;           // filled by the launcher (tile counts and the XCD block mapping)
   int split_k, steps_per_split;            // filled by the launcher: k chunks (1 = none) and 64-wide k-steps per chunk
   float* partial;                          // [split_k][m][n] f32 partial sums when split_k > 1
+  CacheAppend append;                      // QKV_ROPE
 };
 bool gemm_supported(const GemmArgs& a, int mode);
 // scratch: optional (256-byte aligned) room for the partial sums of a split contraction; without it nothing is split
@@ -266,17 +275,11 @@ GemmSplit gemm_plan_split(const GemmArgs& a, int mode, size_t scratch_bytes);  /
 bool gemv_applies(const GemmArgs& a);
 bool gemm_uses_gemv(const GemmArgs& a);   // gemv_applies and no tiling is forced
 hipError_t launch_gemv_bf16(const GemmArgs& a, int mode, hipStream_t s);
-// Such a call with the layer's steps around it taken into the launch (QKV_ROPE and SWIGLU).
+// Such a call with the layer's steps before it taken into the launch (QKV_ROPE and SWIGLU).
 struct GemvFusion {
   const void* norm_w;  // x is RMSNormed on the way (weights [k], eps)
   float eps;
   RopeArgs rope;       // QKV_ROPE: the angles themselves instead of a table of them
-  // QKV_ROPE, ck != nullptr: the tokens' keys and values are appended to the cache too, all of them (keep = m)
-  void* ck;            // [h_kv][cap][128]
-  void* cv;
-  int32_t* pos;        // [h_kv][cap]
-  int32_t* kept;       // [h_kv][m] or nullptr
-  int cap, len, base, cache_fp8;
 };
 hipError_t launch_gemv_fused(const GemmArgs& a, const GemvFusion& f, int mode, hipStream_t s);
 int gemm_tile_rows(const GemmArgs& a);    // token rows per workgroup tile the launcher would use: 128 or 256

@@ -26,7 +26,7 @@
 //     (greater, equal) keys before its slice, which fixes where the slice's survivors start; inside the slice
 //     wavefront w owns a contiguous run of tokens and walks it 64 at a time, ballots give every survivor its rank
 //     inside the batch, running counts its slot.
-#include "fp8_e4m3.h"
+#include "append.h"
 #include "qp_internal.h"
 
 namespace qp {
@@ -43,23 +43,12 @@ constexpr int GATHER_UNROLL = 4;       // rows per lane group in flight in the c
 constexpr int SLICE_MAX = 4096;        // tokens per slice at most (their survivors' indices sit in LDS)
 constexpr int SLICE_WANT_KEEP = 128;   // survivors per slice aimed for
 constexpr int SLICES_MAX = 16;
-typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 static_assert(SEL_NB == 2 * TOPK_THREADS, "two buckets per thread");
 
 __device__ __forceinline__ uint32_t order_key(float s) {
   s += 0.f;  // -0.0 -> +0.0 so that the two zeros tie
   const uint32_t u = __float_as_uint(s);
   return (u & 0x80000000u) ? ~u : (u | 0x80000000u);  // ascending in s
-}
-
-// 8 bf16 values (16 bytes) as 8 E4M3 codes (the 8-bit cache's rows)
-__device__ __forceinline__ uint2 pack8_e4m3(const u32x4& b) {
-  uint2 r;
-  r.x = bf16_to_e4m3(b.x & 0xffffu) | (bf16_to_e4m3(b.x >> 16) << 8) | (bf16_to_e4m3(b.y & 0xffffu) << 16) |
-        (bf16_to_e4m3(b.y >> 16) << 24);
-  r.y = bf16_to_e4m3(b.z & 0xffffu) | (bf16_to_e4m3(b.z >> 16) << 8) | (bf16_to_e4m3(b.w & 0xffffu) << 16) |
-        (bf16_to_e4m3(b.w >> 16) << 24);
-  return r;
 }
 
 // Turns the arguments of a run into those of this workgroup's group (grid.z).
