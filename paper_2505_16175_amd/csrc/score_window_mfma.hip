@@ -8,8 +8,8 @@
 // keys before any column sum can be formed.
 //   pass 1   log-sum-exp partials per (row, key chunk)
 //   pass 2   column sums of exp2(c * s - lse[row])
-// Both passes are one kernel template with the same decomposition: a workgroup of 8 wavefronts owns one
-// KV head's chunk of 64..256 keys, stages it ONCE in LDS (direct global -> LDS loads, XOR-swizzled 16-byte
+// Both passes are one kernel template with the same decomposition: a workgroup of 8 wavefronts owns 64..256 keys of one
+// KV head (one key chunk, or several where a run of groups has plenty), stages them ONCE in LDS (direct global -> LDS loads, XOR-swizzled 16-byte
 // chunks as in the attention kernel), and its wavefronts share the head's row blocks of 32 window rows
 // (wavefront w takes blocks w, w+8, ...), whose fragments come straight from global memory into registers:
 // the window tensor is a few hundred KB and lives in L2. So a group's K is read once per pass and the window once
@@ -24,6 +24,8 @@
 //            order.
 // No atomics: results are deterministic.
 #include "qp_internal.h"
+
+#include <algorithm>
 
 namespace qp {
 
@@ -51,10 +53,17 @@ static int win_chunk_keys(int n_g) {
 // PASS 1: partial[h][kc][row] = (m, l): max of the scaled logits (log2 units) over key chunk kc and the sum of
 //         exp2 around it.
 // PASS 2: scores[h][j] for the chunk's keys from the merged partials.
+// A group's key chunks decide which partials there are, and so the bits of its scores; how many of them a workgroup takes
+// does not. A workgroup is a chain of latencies (keys, window rows, in pass 2 the partials of all chunks of its rows), so it
+// takes 2 or 4 chunks, up to 256 keys, as long as that leaves one workgroup per CU. 16 groups of 2048 tokens, 7B heads, 64
+// window rows: pass 1 42.4 -> 25.0 us, pass 2 56.7 -> 27.0; 13 groups of 1152, 72B heads, 128 rows: the whole video 1204 ->
+// 1172, with two workgroups per CU left 1188.
+struct WinChunks {
+  int keys, n, per_wg;  // keys per chunk, chunks of the group, chunks per workgroup
+};
 template <int PASS>
-__global__ __launch_bounds__(WIN_NT) void window_kernel(WindowArgs a, float2* __restrict__ partial, int kc_keys, int n_kc,
-                                                        int kc_last, int n_kc_last) {
-  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];  // [kc_keys x 256 B of K][pass 2: lse, column sums]
+__global__ __launch_bounds__(WIN_NT) void window_kernel(WindowArgs a, float2* __restrict__ partial, WinChunks ch, WinChunks ch_last) {
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];  // [keys x 256 B of K][pass 2: lse, column sums]
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l32 = lane & 31, g = lane >> 5;
@@ -66,45 +75,46 @@ __global__ __launch_bounds__(WIN_NT) void window_kernel(WindowArgs a, float2* __
   a.k = (const bf16_t*)a.k + (size_t)blockIdx.y * a.n_g * a.h_kv * WIN_D;
   a.scores += blockIdx.y * a.run.score_stride;
   partial += blockIdx.y * (a.workspace_stride / sizeof(float2));
-  if ((int)blockIdx.y == a.run.count - 1) a.n_g = a.run.n_last, kc_keys = kc_last, n_kc = n_kc_last;
-  // workgroup id -> (KV head, key chunk), one head's workgroups on the same XCDs
-  int h, kc;
+  if ((int)blockIdx.y == a.run.count - 1) a.n_g = a.run.n_last, ch = ch_last;
+  // workgroup id -> (KV head, run of key chunks), one head's workgroups on the same XCDs
+  int h, wc;
   {
     const int wg = blockIdx.x, xcd = wg & 7, idx = wg >> 3;
     if (8 % a.h_kv == 0) {
       const int per = 8 / a.h_kv;
       h = xcd / per;
-      kc = idx * per + (xcd % per);
+      wc = idx * per + (xcd % per);
     } else if (a.h_kv % 8 == 0) {
       const int hp = a.h_kv / 8;
       h = (idx % hp) * 8 + xcd;
-      kc = idx / hp;
+      wc = idx / hp;
     } else {
       h = wg % a.h_kv;
-      kc = wg / a.h_kv;
+      wc = wg / a.h_kv;
     }
   }
-  if (kc >= n_kc) return;  // padding workgroups of the XCD mapping (whole workgroup, before any barrier)
-  const int k0 = kc * kc_keys;
+  const int n_kc = ch.n, kc0 = wc * ch.per_wg;
+  if (kc0 >= n_kc) return;  // padding workgroups of the XCD mapping (whole workgroup, before any barrier)
+  const int k0 = kc0 * ch.keys, wg_chunks = min(ch.per_wg, n_kc - kc0), wg_keys = wg_chunks * ch.keys;
 
   // stage the chunk's keys: one load instruction moves 4 key rows; chunk c of key k lands at position c ^ (k & 15)
   {
     const unsigned char* gk = (const unsigned char*)a.k + (size_t)h * (WIN_D * 2);
     const unsigned gstride = (unsigned)a.h_kv * (WIN_D * 2);
-    for (int i = wave; i < kc_keys / 4; i += WIN_NW) {
+    for (int i = wave; i < wg_keys / 4; i += WIN_NW) {
       const int kl = 4 * i + (lane >> 4);
       const unsigned row_b = __umul24((unsigned)min(k0 + kl, a.n_g - 1), gstride);  // keys past the end are masked below
       lds_dma16(gk, row_b + (unsigned)((((lane & 15) ^ (kl & 15))) << 4), smem + (size_t)i * 1024);
     }
   }
-  float* lse_w = (float*)(smem + (size_t)kc_keys * 256) + wave * 32;  // pass 2: this wavefront's 32 row normalisers
-  float* red = (float*)(smem + (size_t)kc_keys * 256) + WIN_NW * 32;  // pass 2: [wavefront][key] column sums
+  float* lse_w = (float*)(smem + (size_t)wg_keys * 256) + wave * 32;  // pass 2: this wavefront's 32 row normalisers
+  float* red = (float*)(smem + (size_t)wg_keys * 256) + WIN_NW * 32;  // pass 2: [wavefront][key] column sums
 
   int k_addr[8];  // K fragment of d-step s: key l32 of a 32-key block, chunk 2s+g at position (2s+g) ^ (l32 & 15)
 #pragma unroll
   for (int s = 0; s < 8; ++s) k_addr[s] = l32 * 256 + (((2 * s + g) ^ (l32 & 15)) << 4);
   const float c2 = a.scale_log2;
-  const int n_kb = kc_keys / 32;
+  const int n_kb = wg_keys / 32;
   float colsum[WIN_MAX_KB];
 #pragma unroll
   for (int kb = 0; kb < WIN_MAX_KB; ++kb) colsum[kb] = 0.f;
@@ -152,7 +162,7 @@ __global__ __launch_bounds__(WIN_NT) void window_kernel(WindowArgs a, float2* __
     }
     if (PASS == 1) {
       float m_run = -INFINITY, l_run = 0.f;
-      for (int kb2 = 0; kb2 < n_kb / 2; ++kb2) {
+      for (int kb2 = 0, in_chunk = 0; kb2 < n_kb / 2; ++kb2) {
         const int kbase = k0 + kb2 * 64;
         if (kbase >= a.n_g) break;  // wave-uniform: nothing of this and the later sub-blocks exists
         const unsigned char* kt = smem + (size_t)kb2 * 64 * 256;
@@ -193,8 +203,12 @@ __global__ __launch_bounds__(WIN_NT) void window_kernel(WindowArgs a, float2* __
         const float m_new = fmaxf(m_run, mc);
         l_run = l_run * __builtin_amdgcn_exp2f(m_run - m_new) + psum * __builtin_amdgcn_exp2f(mc - m_new);
         m_run = m_new;
+        in_chunk += 64;
+        if (in_chunk == ch.keys || kbase + 64 >= a.n_g) {  // the chunk ends, or the group's keys do
+          if (g == 0) partial[((size_t)h * n_kc + kc0 + (kb2 * 64) / ch.keys) * n_rows_pad + row] = make_float2(m_run, l_run);
+          m_run = -INFINITY, l_run = 0.f, in_chunk = 0;
+        }
       }
-      if (g == 0) partial[((size_t)h * n_kc + kc) * n_rows_pad + row] = make_float2(m_run, l_run);
     } else {
       // register r of the product holds row 8*(r/4) + 4*g + r%4 of the block for this lane's key
       float4 ls[4];
@@ -234,14 +248,14 @@ __global__ __launch_bounds__(WIN_NT) void window_kernel(WindowArgs a, float2* __
   for (int kb = 0; kb < WIN_MAX_KB; ++kb) {
     if (kb < n_kb) {
       const float c = sum_halves(colsum[kb]);
-      if (g == 0) red[wave * kc_keys + kb * 32 + l32] = c;
+      if (g == 0) red[wave * wg_keys + kb * 32 + l32] = c;
     }
   }
   __syncthreads();
-  if (tid < kc_keys && k0 + tid < a.n_g) {
+  if (tid < wg_keys && k0 + tid < a.n_g) {
     float s = 0.f;
 #pragma unroll
-    for (int w = 0; w < WIN_NW; ++w) s += red[w * kc_keys + tid];
+    for (int w = 0; w < WIN_NW; ++w) s += red[w * wg_keys + tid];
     a.scores[(size_t)h * a.n_g + k0 + tid] = s;
   }
 }
@@ -258,18 +272,23 @@ size_t window_mfma_workspace_bytes(int h_q, int h_kv, int n_g, int w) {
 }
 
 void launch_score_window_mfma(const WindowArgs& a, hipStream_t s) {
-  const int kc_keys = win_chunk_keys(a.n_g);
-  const int n_kc = (a.n_g + kc_keys - 1) / kc_keys;
+  auto chunks = [&](int n_g) {
+    WinChunks c{win_chunk_keys(n_g), 0, 1};
+    c.n = (n_g + c.keys - 1) / c.keys;
+    while (2 * c.per_wg * c.keys <= WIN_KC_MAX && (long)c.n * a.h_kv * a.run.count >= 2l * c.per_wg * device_cu_count()) c.per_wg *= 2;
+    return c;
+  };
+  const WinChunks ch = chunks(a.n_g), ch_last = chunks(a.run.n_last);
   float2* partial = (float2*)a.workspace;
-  const int kc_last = win_chunk_keys(a.run.n_last), n_kc_last = (a.run.n_last + kc_last - 1) / kc_last;
-  const int n_most = n_kc > n_kc_last ? n_kc : n_kc_last;  // a shorter group may be dealt to more, shorter chunks
+  const int n_most = std::max((ch.n + ch.per_wg - 1) / ch.per_wg, (ch_last.n + ch_last.per_wg - 1) / ch_last.per_wg);
+  const size_t keys = std::max(ch.keys * ch.per_wg, ch_last.keys * ch_last.per_wg);
   int wgs = n_most * a.h_kv;
   if (8 % a.h_kv == 0) {
     const int per = 8 / a.h_kv;
     wgs = (n_most + per - 1) / per * 8;
   }
-  const size_t lds1 = (size_t)kc_keys * 256;
-  const size_t lds2 = lds1 + (size_t)WIN_NW * 32 * sizeof(float) + (size_t)WIN_NW * kc_keys * sizeof(float);
+  const size_t lds1 = keys * 256;
+  const size_t lds2 = lds1 + (size_t)WIN_NW * 32 * sizeof(float) + (size_t)WIN_NW * keys * sizeof(float);
   static bool attr_set[QP_MAX_DEVICES] = {};
   const int dev = current_device();
   if (dev < 0 || !attr_set[dev]) {
@@ -278,8 +297,8 @@ void launch_score_window_mfma(const WindowArgs& a, hipStream_t s) {
     (void)hipFuncSetAttribute((const void*)window_kernel<2>, hipFuncAttributeMaxDynamicSharedMemorySize, max2);
     if (dev >= 0) attr_set[dev] = true;
   }
-  hipLaunchKernelGGL(window_kernel<1>, dim3(wgs, a.run.count), dim3(WIN_NT), lds1, s, a, partial, kc_keys, n_kc, kc_last, n_kc_last);
-  hipLaunchKernelGGL(window_kernel<2>, dim3(wgs, a.run.count), dim3(WIN_NT), lds2, s, a, partial, kc_keys, n_kc, kc_last, n_kc_last);
+  hipLaunchKernelGGL(window_kernel<1>, dim3(wgs, a.run.count), dim3(WIN_NT), lds1, s, a, partial, ch, ch_last);
+  hipLaunchKernelGGL(window_kernel<2>, dim3(wgs, a.run.count), dim3(WIN_NT), lds2, s, a, partial, ch, ch_last);
 }
 
 }  // namespace qp
