@@ -150,7 +150,9 @@ def _ptr(t: Optional[torch.Tensor]):
 
 
 def _stream():
-    return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    # the handle alone: torch.cuda.current_stream() builds a Stream object and looks its device up again, 3 of the 11 us
+    # that the host spends on a tiny video
+    return ctypes.c_void_p(torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice()))
 
 
 def _check(status, where):
