@@ -17,16 +17,20 @@
 // (one workgroup per KV head) or a normalised partial + log2-sum-exp per chunk, merged by attend_merge_kernel like
 // the key split of the large kernel. The group's own keys (causal among themselves) form the last block.
 //
-// F8 (the pruned cache in 8-bit E4M3): a cache block cannot go global -> LDS directly. The wavefront loads it into
-// registers one block ahead with ordinary loads (8 bytes per lane, key and tensor: half the bytes of a bf16 block),
-// widens it exactly to bf16 and writes it to its own LDS buffer in the same swizzled layout, so that the products
-// and the softmax are the same code; the group's own block is bf16 and still loaded directly. One LDS buffer per
-// wavefront then suffices, which leaves room for 8 wavefronts: an 8-bit block is a longer chain for its wavefront (widen,
-// write, read back, two products, softmax: ~2 us alone on a SIMD) over half the bytes, so two of them share a SIMD. us
-// with 4 wavefronts per CU / two workgroups of 4 and twice the chunks / one of 8, 72B heads, one token over 32,768
-// entries again and again (67 MB stay in the last-level cache) 23.1 / 20.6 / 19.3; caches in turn, more than that cache
-// holds: over 46,125 entries 30.9 / 25.2 / 25.1, over 120,000 56.5 / 44.6 / 43.7; 7B heads, 4 tokens over 20,000
-// 17.9 / 21.3 / 17.5 (twice the chunks there cost more in partial sums and their merge than they gained).
+// The rows' queries go through LDS too. As ordinary loads waited for in inline assembly, every trip of the loop waited for
+// them once more (the compiler does not count such a wait), and with them for all blocks under way: caches in turn, 7B
+// heads, one token over 46,125 entries 24.2 -> 23.0 us, 72B heads, 4 tokens over 100,000 80.9 -> 79.4. Requested behind the
+// blocks and awaited with all of them, the short chains lose (72B heads, one token over 9,000 14.4 -> 15.0, so 14.2).
+//
+// F8 (the pruned cache in 8-bit E4M3): a block stays bytes in LDS, half the tile, and is widened exactly to bf16 as its
+// fragments are read: 8 bytes of a key for K, the transposing ds_read_tr8_b64 for V (all 8 keys of a fragment at once). So its
+// wavefront has two blocks under way like the bf16 kernel's, and LDS room for 8 wavefronts: an 8-bit block is a longer
+// chain over half the bytes, so two of them share a SIMD. Only the group's own block is bf16; it has 16 KB of its own and is
+// requested first. us, 72B heads, one token over 32,768 entries again and again (67 MB stay in the last-level cache): blocks
+// loaded into registers one ahead, widened and written to LDS in bf16 with 4 wavefronts per CU / two workgroups of 4 and
+// twice the chunks / one of 8 23.1 / 20.6 / 19.1, as bytes 18.3 (the kernel alone, under a profiler, 17.9 -> 15.3). Caches in
+// turn, more than that cache holds, before / now: over 46,125 entries 27.2 / 24.3, over 120,000 52.4 / 49.7; 7B heads, 4
+// tokens over 120,000 36.5 / 33.0.
 #include "qp_internal.h"
 
 #include <algorithm>
@@ -39,6 +43,8 @@ typedef __attribute__((__vector_size__(16 * sizeof(float)))) float f32x16;
 typedef __attribute__((__vector_size__(4 * sizeof(short)))) short s16x4;
 typedef __attribute__((__vector_size__(8 * sizeof(short)))) short s16x8;
 typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
+typedef __attribute__((__vector_size__(2 * sizeof(int)))) int i32x2;
+typedef __attribute__((address_space(3))) i32x2 lds_i32x2;
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int DC_D = 128;
@@ -47,10 +53,11 @@ constexpr int DC_NW = 4;                   // wavefronts per workgroup; the leas
 constexpr int dc_waves(bool f8) { return f8 ? 2 * DC_NW : DC_NW; }
 constexpr int DC_TILE = DC_BK * DC_D * 2;  // bytes of one K or V block in LDS
 constexpr int DC_BUF = 2 * DC_TILE;        // K block + V block
-// LDS per wavefront: two buffers, one for 8-bit caches (the block ahead waits in registers); the first 16 KB are reused
-// for the final merge
+// LDS per wavefront: two buffers; the first 16 KB are reused for the final merge. Over an 8-bit cache 16 KB more for the
+// group's own block, which is bf16
 constexpr int dc_wave_lds(bool f8) { return f8 ? DC_BUF : 2 * DC_BUF; }
-constexpr int dc_lds(bool f8) { return dc_waves(f8) * dc_wave_lds(f8); }  // 128 KB either way
+constexpr int dc_q_at(bool f8) { return dc_waves(f8) * dc_wave_lds(f8) + (f8 ? DC_BUF : 0); }
+constexpr int dc_lds(bool f8) { return dc_q_at(f8) + DC_TILE; }  // and the 32 rows' queries, which the wavefronts share
 constexpr int DC_MAX_ROWS = 32;
 constexpr float DC_RESCALE_LOG2 = 8.f;
 
@@ -62,21 +69,40 @@ __device__ __forceinline__ void wait_vmcnt() {
   asm volatile("s_waitcnt vmcnt(%0)" : : "n"(N) : "memory");
 }
 
+// 8 E4M3 bytes -> 8 bf16 (exact)
+__device__ __forceinline__ bf16x8 widen8(uint2 p) {
+  u32x4 o;
+  o.x = __builtin_bit_cast(unsigned, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(p.x, 1.f, false));
+  o.y = __builtin_bit_cast(unsigned, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(p.x, 1.f, true));
+  o.z = __builtin_bit_cast(unsigned, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(p.y, 1.f, false));
+  o.w = __builtin_bit_cast(unsigned, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(p.y, 1.f, true));
+  return __builtin_bit_cast(bf16x8, o);
+}
+
 // QK^T and online softmax of one 32-key block for this wavefront's rows (a lane holds row lane % 32 and half of the
 // block's keys); leaves P^T (bf16) in pf. is_group: the block is the group's own keys (causal); n_valid: keys that
-// exist in the block. The caller has waited for the block's K.
+// exist in the block. RAW: the block's K is in E4M3 bytes. The caller has waited for the block's K.
+template <bool RAW>
 __device__ __forceinline__ void decode_qk_softmax(const unsigned char* kt, const int (&k_addr)[8], const bf16x8 (&qf)[8],
                                                   bool is_group, int n_valid, int t_lane, int g, float c2, float lazy,
                                                   float& m_run, float& l_run, f32x16 (&o)[4], bf16x8 (&pf)[2]) {
-  u32x4 kf[8];
+  bf16x8 kf[8];
+  if constexpr (RAW) {
+    uint2 raw[8];
 #pragma unroll
-  for (int s = 0; s < 8; ++s) kf[s] = *(const u32x4*)(kt + k_addr[s]);
+    for (int s = 0; s < 8; ++s) raw[s] = *(const uint2*)(kt + k_addr[s]);
+#pragma unroll
+    for (int s = 0; s < 8; ++s) kf[s] = widen8(raw[s]);
+  } else {
+#pragma unroll
+    for (int s = 0; s < 8; ++s) kf[s] = __builtin_bit_cast(bf16x8, *(const u32x4*)(kt + k_addr[s]));
+  }
   f32x16 st;
 #pragma unroll
   for (int r = 0; r < 16; ++r) st[r] = 0.f;
 #pragma unroll
   for (int s = 0; s < 8; ++s)
-    st = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, kf[s]), qf[s], st, 0, 0, 0);
+    st = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[s], qf[s], st, 0, 0, 0);
   if (is_group || n_valid < DC_BK) {
     const int lim = is_group ? min(t_lane, n_valid - 1) : n_valid - 1;  // key_local <= lim is visible
 #pragma unroll
@@ -114,13 +140,20 @@ __device__ __forceinline__ void decode_qk_softmax(const unsigned char* kt, const
   l_run += psum;
 }
 
-// O^T += V^T . P^T for the block whose V sits at vt. The caller has waited for the block's V.
+// O^T += V^T . P^T for the block whose V sits at vt. RAW: in E4M3 bytes, whose transposing read gives a lane all 8 keys of a
+// fragment at once. The caller has waited for the block's V.
+template <bool RAW>
 __device__ __forceinline__ void decode_pv(const unsigned char* vt, const int (&v_addr)[4], const bf16x8 (&pf)[2],
                                           f32x16 (&o)[4]) {
 #pragma unroll
   for (int ks = 0; ks < 2; ++ks)
 #pragma unroll
     for (int n = 0; n < 4; ++n) {
+      if constexpr (RAW) {
+        const i32x2 raw = __builtin_amdgcn_ds_read_tr8_b64_v2i32((lds_i32x2*)(vt + ks * 16 * DC_D + v_addr[n]));
+        o[n] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(widen8(__builtin_bit_cast(uint2, raw)), pf[ks], o[n], 0, 0, 0);
+        continue;
+      }
       const unsigned char* p0 = vt + ks * 16 * 256 + v_addr[n];
       const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(p0));
       const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(p0 + 8 * 256));
@@ -142,11 +175,7 @@ __global__ __launch_bounds__(dc_waves(F8) * 64) void attend_decode_kernel(Attend
   const int n_rows = a.n_g * r_heads;  // <= 32, checked by the launcher
   const bool row_ok = l32 < n_rows;
   const int rowc = row_ok ? l32 : n_rows - 1;
-  const int t_lane = rowc / r_heads, j_lane = rowc - t_lane * r_heads;
-  const bf16_t* qrow = (const bf16_t*)a.q + ((size_t)t_lane * a.h_q + (size_t)h * r_heads + j_lane) * DC_D;
-  bf16x8 qf[8];
-#pragma unroll
-  for (int s = 0; s < 8; ++s) qf[s] = __builtin_bit_cast(bf16x8, *(const u32x4*)(qrow + 16 * s + 8 * g));
+  const int t_lane = rowc / r_heads;
 
   constexpr int CROW = F8 ? DC_D : DC_D * 2;  // bytes of one cached row
   const unsigned char* ck = (const unsigned char*)a.ck + (size_t)h * a.cap * CROW;
@@ -162,10 +191,27 @@ __global__ __launch_bounds__(dc_waves(F8) * 64) void attend_decode_kernel(Attend
   // staging: load i of a block moves keys 4i .. 4i+3; this lane fills LDS position (lane & 15) of key 4i + (lane >> 4)
   // with the chunk that the swizzle puts there
   const int st_sub = lane >> 4, st_pos = lane & 15;
+  // The rows' queries come like a K block, each wavefront a part of them, ahead of its own blocks; the barrier behind the
+  // first block's wait publishes them, and the requests stay under way across it.
+  auto request_q = [&]() {
+#pragma unroll
+    for (int u = 0; u < 8 / NW; ++u) {
+      const int i = wave * (8 / NW) + u, r = 4 * i + st_sub, rc = min(r, n_rows - 1), t = rc / r_heads;
+      const unsigned row = (unsigned)(t * a.h_q + h * r_heads + rc - t * r_heads) * (DC_D * 2);
+      lds_dma16((const unsigned char*)a.q, row + (unsigned)((st_pos ^ (r & 15)) << 4), smem + dc_q_at(F8) + i * 1024);
+    }
+  };
   // K fragment of d-step s: key l32, chunk 2s+g at position (2s+g) ^ (l32 & 15)
   int k_addr[8];
 #pragma unroll
   for (int s = 0; s < 8; ++s) k_addr[s] = l32 * 256 + (((2 * s + g) ^ (l32 & 15)) << 4);
+  bf16x8 qf[8];
+  auto read_q = [&]() {
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+#pragma unroll
+    for (int s = 0; s < 8; ++s) qf[s] = __builtin_bit_cast(bf16x8, *(const u32x4*)(smem + dc_q_at(F8) + k_addr[s]));
+  };
   // V^T fragment addresses inside a block (same layout as the large kernel's tiles)
   const int l16 = lane & 15, grp = lane >> 4;
   const int v_key = 4 * (grp >> 1) + (l16 >> 2);
@@ -183,15 +229,15 @@ __global__ __launch_bounds__(dc_waves(F8) * 64) void attend_decode_kernel(Attend
   const float c2 = a.scale_log2;
   const float lazy = DC_RESCALE_LOG2 / c2;
 
-  // request the K (V) half of block b_ into buffer buf_: 8 direct loads, each moving 4 keys x 256 bytes
-#define QP_DC_REQUEST(b_, buf_, is_v_)                                                                   \
+  // request the K (V) half of block b_ into the buffer at at_: 8 direct loads, each moving 4 keys x 256 bytes
+#define QP_DC_REQUEST(b_, at_, is_v_)                                                                   \
   {                                                                                                      \
     const bool grp_ = (b_) == n_cb;                                                                      \
     const int key0_ = grp_ ? 0 : (b_)*DC_BK;                                                             \
     const int last_ = grp_ ? a.n_g - 1 : a.c - 1; /* keys past the end are clamped: masked below */      \
     const unsigned stride_ = grp_ ? gstride_b : (unsigned)(DC_D * 2);                                    \
     const unsigned char* src_ = (is_v_) ? (grp_ ? gv : cv) : (grp_ ? gk : ck);                           \
-    unsigned char* dst_ = vbuf + (buf_)*DC_BUF + ((is_v_) ? DC_TILE : 0);                                \
+    unsigned char* dst_ = (at_) + ((is_v_) ? DC_TILE : 0);                                               \
     _Pragma("unroll") for (int i = 0; i < 8; ++i) {                                                      \
       const int kl_ = 4 * i + st_sub;                                                                    \
       const unsigned row_ = (unsigned)min(key0_ + kl_, last_) * stride_;                                 \
@@ -201,71 +247,91 @@ __global__ __launch_bounds__(dc_waves(F8) * 64) void attend_decode_kernel(Attend
   }
 
   if constexpr (F8) {
-    // 8-bit cache blocks through registers: 16 pieces of 8 bytes per lane and block (keys 4i + (lane >> 4), the
-    // global chunk that belongs at LDS position lane & 15), requested one block ahead
-    uint2 rk[8], rv[8];
-    auto load_block = [&](int b_) {
-      const int key0 = b_ * DC_BK, last = a.c - 1;
+    // 8-bit blocks stay bytes in LDS: half the tile, four loads of 8 keys x 128 bytes per half. 16-byte chunk c of key k sits
+    // at position c ^ ((k >> 1) & 7): two rows are one sweep of the banks, and both fragment reads (32 keys of a chunk; 16
+    // keys of two) then spread over all of them. The group's own block has its place beside the buffers.
+    constexpr int TILE8 = DC_BK * DC_D, BUF8 = 2 * TILE8;
+    int k_addr8[8], v_addr8[4];
 #pragma unroll
-      for (int i = 0; i < 8; ++i) {
-        const int kl = 4 * i + st_sub;
-        const unsigned row = (unsigned)min(key0 + kl, last) * (unsigned)DC_D;  // keys past the end are clamped: masked below
-        rk[i] = *(const uint2*)(ck + row + ((st_pos ^ (kl & 15)) << 3));
-        rv[i] = *(const uint2*)(cv + row + ((st_pos ^ ((kl & 7) << 1)) << 3));
+    for (int s = 0; s < 8; ++s) k_addr8[s] = l32 * DC_D + ((s ^ ((l32 >> 1) & 7)) << 4) + 8 * g;
+    // V^T fragment: 16 lanes read 8 keys (4g .. 4g+3, 8+4g .. 8+4g+3, as P^T has them) x 16 d, two lanes per key
+    const int v_i = l16 >> 1, v_key8 = (v_i < 4 ? v_i : v_i + 4) + 4 * (grp >> 1);
+#pragma unroll
+    for (int n = 0; n < 4; ++n) v_addr8[n] = v_key8 * DC_D + (((2 * n + (grp & 1)) ^ ((v_key8 >> 1) & 7)) << 4) + 8 * (l16 & 1);
+    auto request8 = [&](int b_, int buf_, bool is_v_) {
+      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // the buffer's last reads are not ordered before direct loads into it
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const int kl = 8 * i + (lane >> 3);
+        const unsigned row = (unsigned)min(b_ * DC_BK + kl, a.c - 1) * (unsigned)DC_D;  // keys past the end are clamped: masked below
+        lds_dma16(is_v_ ? cv : ck, row + (unsigned)(((lane & 7) ^ ((kl >> 1) & 7)) << 4),
+                  vbuf + buf_ * BUF8 + (is_v_ ? TILE8 : 0) + i * 1024);
       }
     };
-    auto widen8 = [](uint2 p) -> u32x4 {  // 8 E4M3 bytes -> 8 bf16 (the f32 values are exact; their high halves are the bf16)
-      const auto a0 = __builtin_amdgcn_cvt_pk_f32_fp8((int)p.x, false), a1 = __builtin_amdgcn_cvt_pk_f32_fp8((int)p.x, true);
-      const auto b0 = __builtin_amdgcn_cvt_pk_f32_fp8((int)p.y, false), b1 = __builtin_amdgcn_cvt_pk_f32_fp8((int)p.y, true);
-      u32x4 o4;
-      o4.x = (__float_as_uint(a0[0]) >> 16) | (__float_as_uint(a0[1]) & 0xffff0000u);
-      o4.y = (__float_as_uint(a1[0]) >> 16) | (__float_as_uint(a1[1]) & 0xffff0000u);
-      o4.z = (__float_as_uint(b0[0]) >> 16) | (__float_as_uint(b0[1]) & 0xffff0000u);
-      o4.w = (__float_as_uint(b1[0]) >> 16) | (__float_as_uint(b1[1]) & 0xffff0000u);
-      return o4;
-    };
-    int b = chunk * a.split_tiles + wave;
-    unsigned char* buf = vbuf;  // one buffer: a wavefront's LDS operations stay in order
-    if (b < b_end && b < n_cb) load_block(b);
-    while (b < b_end) {
-      const bool has1 = b + NW < b_end;
-      if (b < n_cb) {
-        // this block's pieces have arrived (requested a block ago): widen them into the buffer, then request the next
-#pragma unroll
-        for (int i = 0; i < 8; ++i) {
-          *(u32x4*)(buf + i * 1024 + lane * 16) = widen8(rk[i]);
-          *(u32x4*)(buf + DC_TILE + i * 1024 + lane * 16) = widen8(rv[i]);
-        }
-        if (has1 && b + NW < n_cb) load_block(b + NW);
-      } else {
-        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // the direct loads are not ordered behind the last block's reads
-        QP_DC_REQUEST(b, 0, false)  // the group's own keys and values: bf16, loaded directly
-        QP_DC_REQUEST(b, 0, true)
-        wait_vmcnt<0>();
+    const int b0 = chunk * a.split_tiles + wave;
+    const int c_end = min(b_end, n_cb);                                    // cache blocks
+    const bool own = b_end > n_cb && b0 <= n_cb && (n_cb - b0) % NW == 0;  // this wavefront has the group's own block
+    unsigned char* const own_at = smem + NW * DC_WAVE_LDS;
+    request_q();
+    if (own) {
+      QP_DC_REQUEST(n_cb, own_at, false)
+      QP_DC_REQUEST(n_cb, own_at, true)
+    }
+    int b = b0, cur = 0;
+    if (b < c_end) {
+      request8(b, 0, false);
+      request8(b, 0, true);
+      if (b + NW < c_end) {
+        request8(b + NW, 1, false);
+        request8(b + NW, 1, true);
       }
+    }
+    if (b + NW < c_end) wait_vmcnt<12>();
+    else if (b < c_end) wait_vmcnt<4>();
+    else wait_vmcnt<0>();
+    read_q();
+    // as below, with four loads per half
+    while (b < c_end) {
+      const bool has1 = b + NW < c_end, has2 = b + 2 * NW < c_end;
+      unsigned char* const buf = vbuf + cur * BUF8;
+      if (has1) wait_vmcnt<12>();
+      else wait_vmcnt<4>();
       bf16x8 pf[2];
-      decode_qk_softmax(buf, k_addr, qf, b == n_cb, b == n_cb ? a.n_g : min(DC_BK, a.c - b * DC_BK), t_lane, g, c2, lazy,
-                        m_run, l_run, o, pf);
-      decode_pv(buf + DC_TILE, v_addr, pf, o);
+      decode_qk_softmax<true>(buf, k_addr8, qf, false, min(DC_BK, a.c - b * DC_BK), t_lane, g, c2, lazy, m_run, l_run, o, pf);
+      if (has2) request8(b + 2 * NW, cur, false);
+      if (has2) wait_vmcnt<12>();
+      else if (has1) wait_vmcnt<8>();
+      else wait_vmcnt<0>();
+      decode_pv<true>(buf + TILE8, v_addr8, pf, o);
+      if (has2) request8(b + 2 * NW, cur, true);
       b += NW;
+      cur ^= 1;
+    }
+    if (own) {
+      wait_vmcnt<0>();
+      bf16x8 pf[2];
+      decode_qk_softmax<false>(own_at, k_addr, qf, true, a.n_g, t_lane, g, c2, lazy, m_run, l_run, o, pf);
+      decode_pv<false>(own_at + DC_TILE, v_addr, pf, o);
     }
   } else {
-    // The Q fragments (ordinary loads) must have arrived before the first request: from here on only untracked
-    // operations are in flight, and the counts in the waits are exact.
-    wait_vmcnt<0>();
     // Each half of a buffer is refilled as soon as its block has been consumed: K(i+2) right after the QK product of
     // block i, V(i+2) after its PV product, so that up to three halves beyond the current block are in flight.
     // Requests in issue order: K(i) V(i) K(i+1) V(i+1) | K(i+2) after QK(i) | V(i+2) after PV(i) ...
     int b = chunk * a.split_tiles + wave;
     int cur = 0;
+    request_q();
     if (b < b_end) {
-      QP_DC_REQUEST(b, 0, false)
-      QP_DC_REQUEST(b, 0, true)
+      QP_DC_REQUEST(b, vbuf, false)
+      QP_DC_REQUEST(b, vbuf, true)
       if (b + NW < b_end) {
-        QP_DC_REQUEST(b + NW, 1, false)
-        QP_DC_REQUEST(b + NW, 1, true)
+        QP_DC_REQUEST(b + NW, vbuf + DC_BUF, false)
+        QP_DC_REQUEST(b + NW, vbuf + DC_BUF, true)
       }
     }
+    if (b + NW < b_end) wait_vmcnt<24>();
+    else if (b < b_end) wait_vmcnt<8>();
+    else wait_vmcnt<0>();
+    read_q();
     while (b < b_end) {
       const bool has1 = b + NW < b_end, has2 = b + 2 * NW < b_end;
       unsigned char* buf = vbuf + cur * DC_BUF;
@@ -273,15 +339,15 @@ __global__ __launch_bounds__(dc_waves(F8) * 64) void attend_decode_kernel(Attend
       if (has1) wait_vmcnt<24>();
       else wait_vmcnt<8>();
       bf16x8 pf[2];
-      decode_qk_softmax(buf, k_addr, qf, b == n_cb, b == n_cb ? a.n_g : min(DC_BK, a.c - b * DC_BK), t_lane, g, c2, lazy,
+      decode_qk_softmax<false>(buf, k_addr, qf, b == n_cb, b == n_cb ? a.n_g : min(DC_BK, a.c - b * DC_BK), t_lane, g, c2, lazy,
                         m_run, l_run, o, pf);
-      if (has2) QP_DC_REQUEST(b + 2 * NW, cur, false)  // the K fragments of block i are in registers
+      if (has2) QP_DC_REQUEST(b + 2 * NW, buf, false)  // the K fragments of block i are in registers
       // V(i) has landed: block i+1 and K(i+2) may still be in flight
       if (has2) wait_vmcnt<24>();
       else if (has1) wait_vmcnt<16>();
       else wait_vmcnt<0>();
-      decode_pv(buf + DC_TILE, v_addr, pf, o);
-      if (has2) QP_DC_REQUEST(b + 2 * NW, cur, true)
+      decode_pv<false>(buf + DC_TILE, v_addr, pf, o);
+      if (has2) QP_DC_REQUEST(b + 2 * NW, buf, true)
       b += NW;
       cur ^= 1;
     }

@@ -177,3 +177,12 @@ def test_e4m3_cache_is_refused_where_no_kernel_reads_it():
     with pytest.raises(B.QPError) as e:
         B.group_attend(layout, q, kv, kv, bad, torch.empty_like(q))
     assert e.value.status == B.QP_ERR_INVALID_ARG
+
+
+@pytest.mark.parametrize("n_g,h_q,h_kv,c", [(1, 28, 4, 1), (4, 28, 4, 31), (2, 64, 8, 32), (1, 28, 4, 33), (3, 6, 3, 255), (4, 28, 4, 257),
+                                            (1, 28, 4, 2015), (1, 28, 4, 2016), (1, 8, 8, 16384), (4, 28, 4, 32700)])
+def test_decode_over_an_e4m3_cache_at_block_edges(n_g, h_q, h_kv, c):
+    """Cache blocks stay bytes in LDS, two per wavefront under way, the group's own block beside them: caches that end in and
+    at a block, chunks whose last block is the group's own, in the first wavefront and in later ones, and wavefronts of
+    none, one, two and more blocks."""
+    test_group_attend_reads_an_e4m3_cache(n_g, h_q, h_kv, c)
