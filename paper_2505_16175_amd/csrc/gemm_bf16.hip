@@ -99,10 +99,15 @@ __device__ __forceinline__ int weight_row(int j, int n0, int d_ff) {
   return n0 + j;
 }
 
+// A grid of tiles of one kind: block `block` of `blocks` (a multiple of 8) per k chunk, over outputs n_first and up.
+struct TileGrid {
+  int block, blocks;
+  int tiles_m, tiles_n, m_block;
+  int n_first;
+};
 template <int MODE, typename T>
-__global__ __launch_bounds__(T::NW * 64) void gemm_bf16_kernel(GemmArgs a) {
+__device__ __forceinline__ void gemm_tile_product(const GemmArgs& a, const TileGrid& grid, unsigned char* smem) {
   constexpr int ROWB = T::ROWB, BM = T::BM, BN = T::BN, BK = T::BK;
-  extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -117,24 +122,24 @@ __global__ __launch_bounds__(T::NW * 64) void gemm_bf16_kernel(GemmArgs a) {
   // A split contraction has a grid row per k chunk, or (a grid of one row) its items are the chunks of its tiles, tile by
   // tile, and those are dealt to the XCDs.
   const bool by_item = gridDim.y < a.split_k;
-  const int per_xcd = gridDim.x >> 3;
-  int id = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3), chunk = blockIdx.y;
-  if (id >= a.tiles_m * a.tiles_n * (by_item ? a.split_k : 1)) return;  // padding of the mapping (whole workgroup, before any barrier)
+  const int per_xcd = grid.blocks >> 3;
+  int id = (grid.block & 7) * per_xcd + (grid.block >> 3), chunk = blockIdx.y;
+  if (id >= grid.tiles_m * grid.tiles_n * (by_item ? a.split_k : 1)) return;  // padding of the mapping (whole workgroup, before any barrier)
   if (by_item) {
     const int tile = id / a.split_k;
     chunk = id - tile * a.split_k;
     id = tile;
   }
   // block `quad` of n_quads has the weight tiles quad, quad + n_quads, ...: nw of them, one more in the first n_more blocks
-  const int n_quads = (a.tiles_n + 3) / 4, fewer = a.tiles_n / n_quads, n_more = a.tiles_n - fewer * n_quads;
-  const int in_more = n_more * (fewer + 1) * a.tiles_m;
+  const int n_quads = (grid.tiles_n + 3) / 4, fewer = grid.tiles_n / n_quads, n_more = grid.tiles_n - fewer * n_quads;
+  const int in_more = n_more * (fewer + 1) * grid.tiles_m;
   const int nw = id < in_more ? fewer + 1 : fewer, rel = id < in_more ? id : id - in_more;
-  const int q0 = rel / (nw * a.tiles_m), in_quad = rel - q0 * nw * a.tiles_m;
+  const int q0 = rel / (nw * grid.tiles_m), in_quad = rel - q0 * nw * grid.tiles_m;
   const int quad = id < in_more ? q0 : n_more + q0;
-  const int mc = in_quad / (nw * a.m_block), in_blk = in_quad - mc * nw * a.m_block;
-  const int mh = min(a.m_block, a.tiles_m - mc * a.m_block);         // token tiles of this block of m_block
-  const int tm = mc * a.m_block + in_blk % mh, tn = quad + n_quads * (in_blk / mh);
-  const int m0 = tm * BM, n0 = tn * BN;
+  const int mc = in_quad / (nw * grid.m_block), in_blk = in_quad - mc * nw * grid.m_block;
+  const int mh = min(grid.m_block, grid.tiles_m - mc * grid.m_block);         // token tiles of this block of m_block
+  const int tm = mc * grid.m_block + in_blk % mh, tn = quad + n_quads * (in_blk / mh);
+  const int m0 = tm * BM, n0 = grid.n_first + tn * BN;
   const int d_ff = a.n >> 1;
 
   // staging: activation load q of this wavefront covers tile rows (BM/NW) wave + RPI q + lane / CPR, weight load q
@@ -486,8 +491,8 @@ __global__ __launch_bounds__(T::NW * 64) void gemm_bf16_kernel(GemmArgs a) {
 #pragma unroll
           for (int e = 0; e < 4; ++e) {
             const float x0 = lo[e], x1 = hi[e];
-            lo[e] = x0 * c[e] - x1 * s[e];
-            hi[e] = x1 * c[e] + x0 * s[e];
+            lo[e] = fmaf(x0, c[e], -(x1 * s[e]));  // spelled out: every tiling and kind of launch rounds alike
+            hi[e] = fmaf(x1, c[e], x0 * s[e]);
           }
         }
         bf16x4 p0, p1;
@@ -518,6 +523,27 @@ __global__ __launch_bounds__(T::NW * 64) void gemm_bf16_kernel(GemmArgs a) {
           }
         }
       }
+  }
+}
+
+template <int MODE, typename T>
+__global__ __launch_bounds__(T::NW * 64) void gemm_bf16_kernel(GemmArgs a) {
+  extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
+  gemm_tile_product<MODE, T>(a, TileGrid{(int)blockIdx.x, (int)gridDim.x, a.tiles_m, a.tiles_n, a.m_block, 0}, smem);
+}
+
+// Two tilings in one launch: whole rounds of T over the first outputs, U over the rest. Blocks start in order, so the smaller
+// tiles of the last round follow the larger ones onto the CUs as they become free.
+template <int MODE, typename T, typename U>
+__global__ __launch_bounds__(T::NW * 64) void gemm_mixed_kernel(GemmArgs a, TileGrid rest) {
+  static_assert(T::NW == U::NW, "one workgroup size");
+  extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
+  const int first = (int)gridDim.x - rest.blocks;  // blocks of T
+  if ((int)blockIdx.x < first) {
+    gemm_tile_product<MODE, T>(a, TileGrid{(int)blockIdx.x, first, a.tiles_m, a.tiles_n, a.m_block, 0}, smem);
+  } else {
+    rest.block = (int)blockIdx.x - first;
+    gemm_tile_product<MODE, U>(a, rest, smem);
   }
 }
 
@@ -684,29 +710,54 @@ void gemm_force_tile_rows(int rows) { g_forced_tile_rows.store(rows, std::memory
 // measured per 64-wide k-step with one workgroup per CU: 256 x 256 1.55 us, 128 x 256 0.96, 128 x 128 0.60 (fewer
 // products per fragment read and per request, so small tiles pay only where they fill CUs that the larger leave idle:
 // 7B o_proj at 700 tokens, 84 / 168 tiles, 48 -> 30 us; 72B down at 512, 128 / 256 tiles, 420 -> 289 us).
+//
+// Whole rounds of the large tile may be followed by a round of a smaller one instead of one that is mostly empty: the first
+// `wide` weight tiles of 256 outputs then make the whole rounds and the others take the smaller tile, in the same launch.
+// A tile's products walk k in the same order in every tiling, so the results are the same bits. us one tiling / mixed: 512 x
+// 37888 x 3584 (1 round and 160 tiles of 128 x 128) 170 / 138, 1500 360 / 342, 4096 892 / 863; 4096 x 59136 x 8192 (14 and 224 of
+// 128 x 256) 3054 / 2945; 2048 / 4096 x 10240 x 8192 315 / 281 and 574 / 522; 5000 x 3584 x 18944 739 / 605; 4096 x 4608 x 3584
+// 145 / 129. An estimate within 1.5 % keeps one tiling.
 struct TileChoice {
   int rows, cols;
   double cost;  // of the launch, in 256 x 256 tiles one after the other
+  int wide;     // 0, or weight tiles of 256 x 256 before the tiles of rest_cols
+  int rest_cols;
 };
 static TileChoice gemm_tile(const GemmArgs& a) {
   const int forced = g_forced_tile_rows.load(std::memory_order_relaxed);
-  if (forced != 0) return {forced, GM_BN, 0};
+  if (forced != 0) return {forced, GM_BN, 0, 0, 0};
   static const struct {
     int rows, cols;
     double cost;
   } kinds[] = {{256, 256, 1.0}, {128, 256, 0.62}, {128, 128, 0.39}};
   const int cus = device_cu_count();
-  TileChoice best{256, 256, 0};
+  TileChoice best{256, 256, 0, 0, 0};
   double best_cost = 1e30;
   for (const auto& t : kinds) {
     const long tiles = (long)((a.m + t.rows - 1) / t.rows) * ((a.n + t.cols - 1) / t.cols);
     const double cost = t.cost * (double)((tiles + cus - 1) / cus);
-    if (cost < best_cost) best_cost = cost, best = {t.rows, t.cols, cost};
+    if (cost < best_cost) best_cost = cost, best = {t.rows, t.cols, cost, 0, 0};
   }
+  const long tiles_m = (a.m + 255) / 256, tiles_n = (a.n + 255) / 256;
+  const long rounds = tiles_m * tiles_n / cus;
+  const long wide = rounds * cus / tiles_m;
+  if (rounds > 0 && wide > 0 && wide < tiles_n)
+    for (int k = 1; k < 3; ++k) {
+      const auto& t = kinds[k];
+      const long tiles = (long)((a.m + t.rows - 1) / t.rows) * ((a.n - 256 * wide + t.cols - 1) / t.cols);
+      const double cost = (double)rounds + t.cost * (double)((tiles + cus - 1) / cus);
+      if (cost < 0.985 * best_cost) best_cost = cost, best = {256, 256, cost, (int)wide, t.cols};
+    }
   return best;
 }
 int gemm_tile_rows(const GemmArgs& a) { return gemm_tile(a).rows; }
 int gemm_tile_cols(const GemmArgs& a) { return gemm_tile(a).cols; }
+int gemm_tile_blocks(const GemmArgs& a) {
+  const TileChoice t = gemm_tile(a);
+  auto blocks = [&](long m, long n) { return (int)(((a.m + m - 1) / m * n + 7) / 8 * 8); };
+  if (t.wide == 0) return blocks(t.rows, (a.n + t.cols - 1) / t.cols);
+  return blocks(256, t.wide) + blocks(128, (a.n - 256 * t.wide + t.rest_cols - 1) / t.rest_cols);
+}
 
 // Contraction split: launches whose tiles would occupy at most a quarter of the CUs (few tokens against a long k:
 // text chunks and decode steps through the layer, where the weights are streamed once and HBM is the bound) deal the
@@ -802,6 +853,33 @@ static hipError_t launch_tile(GemmArgs a, hipStream_t s) {
   return hipSuccess;
 }
 
+template <int MODE, typename U>
+static hipError_t launch_mixed(GemmArgs a, int wide, hipStream_t s) {
+  typedef Tile256 T;
+  static bool attr_done[QP_MAX_DEVICES] = {};
+  const int dev = current_device();
+  if (dev < 0) return hipErrorInvalidDevice;
+  constexpr int lds = T::LDS > U::LDS ? T::LDS : U::LDS;
+  if (!attr_done[dev]) {
+    hipError_t e = hipFuncSetAttribute((const void*)gemm_mixed_kernel<MODE, T, U>, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+    if (e != hipSuccess) return e;
+    attr_done[dev] = true;
+  }
+  auto blocks = [](long tiles) { return (int)((tiles + 7) / 8 * 8); };
+  a.tiles_m = (a.m + T::BM - 1) / T::BM;
+  a.tiles_n = wide;
+  a.m_block = a.tiles_m < 8 ? a.tiles_m : 8;
+  TileGrid rest{};
+  rest.n_first = wide * T::BN;
+  rest.tiles_m = (a.m + U::BM - 1) / U::BM;
+  rest.tiles_n = (a.n - rest.n_first + U::BN - 1) / U::BN;
+  rest.m_block = rest.tiles_m < 8 ? rest.tiles_m : 8;
+  rest.blocks = blocks((long)rest.tiles_m * rest.tiles_n);
+  hipLaunchKernelGGL((gemm_mixed_kernel<MODE, T, U>), dim3((unsigned)(blocks((long)a.tiles_m * wide) + rest.blocks)), dim3(T::NW * 64),
+                     lds, s, a, rest);
+  return hipSuccess;
+}
+
 // reduce = false leaves a split product's partial sums to the caller (a.split_k says whether there are any)
 template <int MODE>
 static hipError_t launch_mode(GemmArgs& a, void* scratch, size_t scratch_bytes, hipStream_t s, bool reduce = true) {
@@ -811,6 +889,9 @@ static hipError_t launch_mode(GemmArgs& a, void* scratch, size_t scratch_bytes, 
   if (sp.narrow) {  // never for SWIGLU, which is not split
     if constexpr (MODE != GEMM_SWIGLU) e = a.m <= 64 ? launch_tile<MODE, Narrow64>(a, s) : launch_tile<MODE, Narrow128>(a, s);
     else e = hipErrorInvalidValue;
+  } else if (a.split_k == 1 && gemm_tile(a).wide > 0) {
+    const TileChoice t = gemm_tile(a);
+    e = t.rest_cols == 128 ? launch_mixed<MODE, Mid>(a, t.wide, s) : launch_mixed<MODE, Tile128>(a, t.wide, s);
   } else if (a.split_k == 1 && gemm_tile_cols(a) == 128) {
     e = launch_tile<MODE, Mid>(a, s);
   } else {

@@ -284,6 +284,7 @@ struct GemvFusion {
 hipError_t launch_gemv_fused(const GemmArgs& a, const GemvFusion& f, int mode, hipStream_t s);
 int gemm_tile_rows(const GemmArgs& a);    // token rows per workgroup tile the launcher would use: 128 or 256
 int gemm_tile_cols(const GemmArgs& a);    // outputs per workgroup tile of an unsplit launch: 128 or 256
+int gemm_tile_blocks(const GemmArgs& a);  // workgroups of an unsplit launch, padding of the XCD mapping included
 void gemm_force_tile_rows(int rows);      // 0 = choose per launch (default), 128 or 256
 void launch_rms_norm(const void* x, const void* w, void* out, int n_tokens, int d_model, float eps, hipStream_t s);
 void launch_rope_table(const int32_t* pos, long axis_stride, int n_tokens, float theta, int s0, int s1, float* cos_sin,

@@ -848,3 +848,40 @@ def test_layer_stack_replays_from_a_hip_graph():
 def test_qkv_rope_split_in_wide_tiles():
     """36 tiles of 128 x 256 in 7 chunks, dealt to the XCDs as 252 items."""
     test_qkv_rope_split_contraction(200, 3584, 28, 4)
+
+
+@pytest.mark.parametrize("m,n,k", [(1030, 15368, 192), (1030, 15360, 64), (4090, 10240, 128), (512, 37888, 64)])
+def test_mixed_tilings_are_the_same_bits(m, n, k):
+    """Whole rounds of 256 x 256 tiles and a last one of smaller tiles in one launch, for all three kinds of stores: the bits
+    of either pinned tiling, token rows and outputs that end inside the smaller tiles."""
+    tiles = -(-m // 256) * -(-n // 256)
+    assert B.linear_plan(m, n, k, 0)["workgroups"] > (tiles + 7) // 8 * 8 > 256       # more than the large tiles alone
+    g = torch.Generator(device=DEV).manual_seed(m + n + k)
+    rnd = lambda *s: torch.randn(*s, generator=g, device=DEV).to(torch.bfloat16)
+    x, w, b, r = rnd(m, k), rnd(n, k), rnd(n), rnd(m, n)
+    heads = n // 128 - 8
+    fused = n % 256 == 0
+    layout = B.make_layout(heads, 4, 128, "bf16") if fused and heads % 4 == 0 else None
+    cs = torch.randn(m, 64, 2, generator=g, device=DEV)
+    outs = []
+    for rows in (0, 128, 256):
+        B.select_linear_tile(rows)
+        try:
+            o = [torch.full((m, n), float("nan"), dtype=torch.bfloat16, device=DEV)]
+            B.linear(x, w, b, r, o[0])
+            if fused:
+                o.append(torch.full((m, n // 2), float("nan"), dtype=torch.bfloat16, device=DEV))
+                B.swiglu_gate_up(x, w, o[1])
+            if layout is not None:
+                o += [torch.full((m, h, 128), float("nan"), dtype=torch.bfloat16, device=DEV) for h in (heads, 4, 4)]
+                B.qkv_rope(layout, x, w, b, cs, o[-3], o[-2], o[-1])
+            torch.cuda.synchronize()
+            outs.append(o)
+        finally:
+            B.select_linear_tile(0)
+    for other in outs[1:]:
+        for a, c in zip(outs[0], other):
+            assert torch.equal(a, c) and torch.isfinite(a.float()).all()
+    sample = torch.tensor([0, 1, m // 2, m - 1])
+    want = LO.linear(to_f64(x[sample]), to_f64(w), to_f64(b)) + to_f64(r[sample])
+    assert_stored_close(to_f64(outs[0][0][sample]), LO.bf16_round(want), "mixed tilings")
