@@ -914,7 +914,8 @@ hipError_t launch_gemm_norm(const GemmArgs& a_in, const void* norm_w, void* norm
   GemmArgs a = a_in;
   a.split_k = 1;
   const bool fits = a.n <= 4 * RNK_RUNS * RNK_THREADS && a.bias == nullptr;
-  const hipError_t e = launch_mode<GEMM_PLAIN>(a, scratch, scratch_bytes, s, !fits);
+  const hipError_t e = gemm_uses_gemv(a) ? launch_gemv_bf16(a, GEMM_PLAIN, s)
+                                         : launch_mode<GEMM_PLAIN>(a, scratch, scratch_bytes, s, !fits);
   if (e != hipSuccess) return e;
   if (fits && a.split_k > 1)
     hipLaunchKernelGGL(gemm_reduce_norm_kernel, dim3((unsigned)a.m), dim3(RNK_THREADS), 0, s, a, (const bf16_t*)norm_w,

@@ -24,13 +24,14 @@
 //   * the 64 lanes' sums are added by shuffles, the 4 wavefronts' sums meet in LDS and are added in wavefront order
 //     (deterministic), and one lane per token applies the store.
 //
-// Inside a layer (launch_gemv_fused) the QKV and gate/up launches also take the RMSNorm of their rows and the rotary angles,
-// which as launches of their own were latency and nothing else (norm + angles 6.1 us, second norm 4.5; with the append to
-// the cache, 1.8 us and a side stream forked and joined around it, which QKV_ROPE takes too: 7B layer, one token over
-// 46,125 entries 132.3 -> 118.6 us). Every workgroup repeats the norm: wavefront t takes token t's sum of squares, over its row's chunks and
-// lanes in the order of rms_norm_kernel, so that the factor's bits are the same, while the first weights are on
-// their way; every wavefront scales and rounds the chunks that it multiplies. Another wavefront takes the workgroup's
-// four angles (two frequencies per token) in double precision.
+// Inside a layer the QKV launch appends to the cache, and for one token (launch_gemv_fused) it also takes the RMSNorm of the
+// row and the rotary angles, which as a launch of their own are latency and nothing else (6.1 us). Every workgroup repeats
+// the norm: a wavefront takes the row's sum of squares, over its chunks and lanes in the order of rms_norm_kernel, so that the
+// factor's bits are the same, while the first weights are on their way; another takes the workgroup's angles in double
+// precision. It costs registers, and with them wavefronts in flight: for two tokens, and for the large gate/up launch
+// (43.7 -> 52 us), more than the launch it saves. us with norms in both launches / in QKV at one or two tokens / QKV at one
+// / nowhere: 7B layer, one token over 46,125 entries 117.5 / 115.5 / 115.5 / 117.8, two over 9,000 154 / 124 / 113.6 /
+// 113.7; 72B layer, one 311 / 313 / 314 / 320, two 375 / 333 / 322 / 322.
 #include "append.h"
 #include "qp_internal.h"
 
@@ -278,12 +279,9 @@ hipError_t launch_gemv_bf16(const GemmArgs& a, int mode, hipStream_t s) {
 }
 
 hipError_t launch_gemv_fused(const GemmArgs& a, const GemvFusion& f, int mode, hipStream_t s) {
-  if (!gemv_applies(a) || !gemm_supported(a, mode)) return hipErrorInvalidValue;
-  switch (mode) {
-    case GEMM_QKV_ROPE: return launch_gemv_mode<GEMM_QKV_ROPE>(a, f, s);
-    case GEMM_SWIGLU: return launch_gemv_mode<GEMM_SWIGLU>(a, f, s);
-  }
-  return hipErrorInvalidValue;
+  if (a.m != 1 || mode != GEMM_QKV_ROPE || !gemv_applies(a) || !gemm_supported(a, mode)) return hipErrorInvalidValue;
+  hipLaunchKernelGGL((gemv_bf16_kernel<GEMM_QKV_ROPE, 1, GemvFusion>), dim3((unsigned)(a.n / 4)), dim3(GV_WAVES * 64), 0, s, a, f);
+  return hipSuccess;
 }
 
 }  // namespace qp

@@ -230,11 +230,11 @@ qp_status qp_layer_group(const qp_layout* layout, const qp_layer_shape* shape, c
   // Where every token is kept (the stages after the video) the projection appends to the cache itself: the append's launch
   // is short, but a side stream forked and joined around it held the caller's up (7B layer, 64 tokens over 46,125 entries
   // 212.5 us, 202.5 without). A token or two (decoding): the weight-streaming kernel takes the norms and the rotary angles into its own launches.
-  const bool appended = keep == n_g, streamed = qp::gemm_uses_gemv(qkv);
+  const bool appended = keep == n_g, streamed = n_g == 1 && qp::gemm_uses_gemv(qkv);
   if (appended)
     qkv.append = qp::CacheAppend{cache->k, cache->v, cache->pos, kept_idx_or_null, cache->capacity, cache->len,
                                  group_token_base, cache->format == QP_CACHE_FP8_E4M3};
-  qp::GemvFusion fuse{};
+  qp::GemvFusion fuse{};  // one token: the weight-streaming projection takes the norm and the angles
   if (streamed) {
     fuse.norm_w = weights->ln1_w, fuse.eps = shape->rms_eps;
     fuse.rope = qp::RopeArgs{pos, (long)axis_stride, n_g, shape->rope_theta, shape->mrope_section[0], shape->mrope_section[1], nullptr};
@@ -269,17 +269,9 @@ qp_status qp_layer_group(const qp_layout* layout, const qp_layer_shape* shape, c
                          kept_idx_or_null, score_ws, score_bytes, fork.stream());
     if (st != QP_OK) return st;
   }
-  if (streamed) {
-    st = finish(qp::launch_gemv_bf16(oproj, qp::GEMM_PLAIN, s));
-    if (st != QP_OK) return st;
-    fuse.norm_w = weights->ln2_w;
-    gate_up.x = ws + c.x1;
-    st = finish(qp::launch_gemv_fused(gate_up, fuse, qp::GEMM_SWIGLU, s));
-  } else {
-    st = finish(qp::launch_gemm_norm(oproj, weights->ln2_w, ws + c.h, shape->rms_eps, ws + c.gemm, kGemmSplitBytes, s));
-    if (st != QP_OK) return st;
-    st = finish(qp::launch_gemm_bf16(gate_up, qp::GEMM_SWIGLU, nullptr, 0, s));
-  }
+  st = finish(qp::launch_gemm_norm(oproj, weights->ln2_w, ws + c.h, shape->rms_eps, ws + c.gemm, kGemmSplitBytes, s));
+  if (st != QP_OK) return st;
+  st = finish(qp::launch_gemm_bf16(gate_up, qp::GEMM_SWIGLU, nullptr, 0, s));
   if (st != QP_OK) return st;
   return finish(qp::launch_gemm_bf16(down, qp::GEMM_PLAIN, ws + c.gemm, kGemmSplitBytes, s));
 }

@@ -275,7 +275,7 @@ GemmSplit gemm_plan_split(const GemmArgs& a, int mode, size_t scratch_bytes);  /
 bool gemv_applies(const GemmArgs& a);
 bool gemm_uses_gemv(const GemmArgs& a);   // gemv_applies and no tiling is forced
 hipError_t launch_gemv_bf16(const GemmArgs& a, int mode, hipStream_t s);
-// Such a call with the layer's steps before it taken into the launch (QKV_ROPE and SWIGLU).
+// Such a call of one token with the layer's steps before it taken into the launch (QKV_ROPE).
 struct GemvFusion {
   const void* norm_w;  // x is RMSNormed on the way (weights [k], eps)
   float eps;
