@@ -202,6 +202,10 @@ qp_status qp_layer_group(const qp_layout* layout, const qp_layer_shape* shape, c
   const int32_t nw = windowed ? n_window : 0;
   const Carve c = carve(layout, shape, n_group_tokens, nw);
   if (workspace_bytes < c.total) return QP_ERR_CAPACITY;
+  // What the attention and the scoring would refuse is refused before the first launch: the QKV projection may append to
+  // the cache, so theirs would come too late.
+  if ((st = qp::check_group_attend(layout, n_group_tokens, cache)) != QP_OK) return st;
+  if (windowed && keep < n_group_tokens && n_window > 65535) return QP_ERR_UNSUPPORTED;
 
   // every projection's shape is checked before the first launch
   const int n_g = n_group_tokens, dm = shape->d_model, hq = layout->n_q_heads, hkv = layout->n_kv_heads;

@@ -52,6 +52,26 @@ float scale_log2_of(const qp_layout* L) {
   return scale * 1.4426950408889634f;
 }
 
+// What qp_group_attend knows of a call without its tensors, and whether the selected kernel serves it.
+qp::AttendArgs attend_sizes(const qp_layout* L, int32_t n_g, const qp_cache* cache) {
+  qp::AttendArgs a{};
+  a.c = cache ? cache->len : 0;
+  a.cap = cache ? cache->capacity : 0;
+  a.n_g = n_g;
+  a.h_q = L->n_q_heads;
+  a.h_kv = L->n_kv_heads;
+  a.d = L->head_dim;
+  a.scale_log2 = scale_log2_of(L);
+  a.cache_fp8 = cache != nullptr && cache->format == QP_CACHE_FP8_E4M3 && a.c > 0;
+  return a;
+}
+qp_status check_attend_kernel(const qp::AttendArgs& a, int dtype, int which, bool* mfma_ok) {
+  *mfma_ok = qp::attend_mfma_supported(a, dtype);
+  if (which == QP_ATTEND_MFMA && !*mfma_ok) return QP_ERR_UNSUPPORTED;
+  if (a.cache_fp8 && (!*mfma_ok || which == QP_ATTEND_SCALAR)) return QP_ERR_UNSUPPORTED;  // only the MFMA kernels read it
+  return QP_OK;
+}
+
 // Fault injection for the tests of the error paths (qp_debug_fail_after): the n-th status check from now reports a
 // launch failure although nothing failed on the GPU. 0 = off.
 std::atomic<int> g_fail_countdown{0};
@@ -202,6 +222,15 @@ void side_join(hipStream_t main) {
   g_prefill_mutex.unlock();
 }
 
+qp_status check_group_attend(const qp_layout* L, int32_t n_g, const qp_cache* cache) {
+  qp_status st = check_layout(L);
+  if (st == QP_OK) st = check_group(n_g);
+  if (st == QP_OK) st = check_cache(L, cache, false);
+  bool mfma_ok = false;
+  return st != QP_OK ? st : check_attend_kernel(attend_sizes(L, n_g, cache), L->dtype,
+                                                g_attend_kernel.load(std::memory_order_relaxed), &mfma_ok);
+}
+
 int current_device() {
   int dev = -1;
   if (hipGetDevice(&dev) != hipSuccess) {
@@ -344,28 +373,19 @@ qp_status qp_group_attend(const qp_layout* L, const void* q_g, const void* k_g, 
   if (!aligned16(q_g) || !aligned16(k_g) || !aligned16(v_g) || !aligned16(out_g)) return QP_ERR_INVALID_ARG;
   if (lse && (((uintptr_t)lse) & 3u)) return QP_ERR_INVALID_ARG;
 
-  qp::AttendArgs a{};
+  qp::AttendArgs a = attend_sizes(L, n_g, cache);
   a.q = q_g;
   a.k = k_g;
   a.v = v_g;
-  a.c = cache ? cache->len : 0;
-  a.cap = cache ? cache->capacity : 0;
   a.ck = a.c > 0 ? cache->k : nullptr;
   a.cv = a.c > 0 ? cache->v : nullptr;
   a.out = out_g;
   a.lse = lse;
-  a.n_g = n_g;
-  a.h_q = L->n_q_heads;
-  a.h_kv = L->n_kv_heads;
-  a.d = L->head_dim;
-  a.scale_log2 = scale_log2_of(L);
-  a.cache_fp8 = cache != nullptr && cache->format == QP_CACHE_FP8_E4M3 && a.c > 0;
 
   hipStream_t s = (hipStream_t)hip_stream;
-  const bool mfma_ok = qp::attend_mfma_supported(a, L->dtype);
   const int which = g_attend_kernel.load(std::memory_order_relaxed);
-  if (which == QP_ATTEND_MFMA && !mfma_ok) return QP_ERR_UNSUPPORTED;
-  if (a.cache_fp8 && (!mfma_ok || which == QP_ATTEND_SCALAR)) return QP_ERR_UNSUPPORTED;  // only the MFMA kernel reads it
+  bool mfma_ok = false;
+  if ((st = check_attend_kernel(a, L->dtype, which, &mfma_ok)) != QP_OK) return st;
   const size_t ws_bytes = workspace ? workspace_bytes : 0;
   if (mfma_ok && which == QP_ATTEND_AUTO && qp::attend_decode_applies(a, L->dtype))
     qp::launch_attend_decode(a, workspace, ws_bytes, s);

@@ -183,6 +183,8 @@ void note_hip_error(int e);  // what qp_last_hip_error() reports on this thread
 // return holds the library's enqueue mutex until side_join(main), which makes `main` wait for the side stream.
 hipStream_t side_fork(hipStream_t main);
 void side_join(hipStream_t main);
+// The checks of qp_group_attend that do not need its tensors, for callers that launch something before it.
+qp_status check_group_attend(const qp_layout* L, int32_t n_g, const qp_cache* cache);
 
 // Scoring and selection take runs of groups too: `count` consecutive groups of the call's n_g tokens, the last one of
 // n_last; group i's scores are at scores + i * score_stride (floats). One launch serves all of them (a grid dimension).

@@ -70,6 +70,37 @@ def test_forced_mfma_kernel_refuses_a_cache_beyond_its_offsets(frames):
         B.select_attend_kernel(B.QP_ATTEND_AUTO)
 
 
+@pytest.mark.skipif(__import__("torch").cuda.is_available(), reason="needs a machine WITHOUT a GPU: there every launch fails")
+@pytest.mark.parametrize("case,status", [("scalar_fp8", B.QP_ERR_UNSUPPORTED), ("mfma_offsets", B.QP_ERR_UNSUPPORTED),
+                                          ("window_rows", B.QP_ERR_UNSUPPORTED), ("scale", B.QP_ERR_INVALID_ARG)])
+@pytest.mark.parametrize("keep", [16, 9])
+def test_layer_group_refuses_before_its_first_launch(case, status, keep):
+    """What the attention or the scoring of a layer refuses is refused before the QKV projection, which appends kept tokens
+    to the cache, has run: a pinned kernel that cannot serve the cache, too many window rows, a softmax scale that is none.
+    Without a GPU any launch fails, and the call would say that instead."""
+    L, S = B.make_layout(8, 2, 128, "bf16"), B.make_layer_shape(256, 512)
+    fake = 1 << 20
+    c = B.qp_cache(fake, fake, fake, 1 << 23 if case == "mfma_offsets" else 64, 5, B.QP_CACHE_SAME)
+    n_window = 65536 if case == "window_rows" else 16
+    ws = 1 << 40
+    if case == "scalar_fp8":
+        c.format = B.QP_CACHE_FP8_E4M3
+        B.select_attend_kernel(B.QP_ATTEND_SCALAR)
+    elif case == "mfma_offsets":
+        B.select_attend_kernel(B.QP_ATTEND_MFMA)
+    elif case == "scale":
+        L = B.make_layout(8, 2, 128, "bf16", softmax_scale=-1.0)
+    elif keep == 16:
+        status = B.QP_ERR_HIP                        # every token kept: the window is not looked at, such calls are served
+    W = B.qp_layer_weights(*[fake] * 7)
+    try:
+        st = B.lib().qp_layer_group(ctypes.byref(L), ctypes.byref(S), ctypes.byref(W), fake, fake, 16, 16, 0, fake, n_window,
+                                    B.RULES["window_attn"], keep, ctypes.byref(c), fake, None, fake, ws, None)
+    finally:
+        B.select_attend_kernel(B.QP_ATTEND_AUTO)
+    assert st == status and c.len == 5
+
+
 def test_debug_fail_after_arguments():
     assert B.lib().qp_debug_fail_after(-1) == B.QP_ERR_INVALID_ARG
     assert B.lib().qp_debug_fail_after(0) == B.QP_OK

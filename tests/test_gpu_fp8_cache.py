@@ -7,6 +7,7 @@ import torch
 from helpers import assert_attn_close, compare_kept
 from oracle import qp_oracle as O
 from paper_2505_16175_amd import binding as B
+from paper_2505_16175_amd import workload as W
 from paper_2505_16175_amd.workload import CONFIGS, make_layer, scaled, to_f64
 
 pytestmark = pytest.mark.gpu
@@ -177,6 +178,32 @@ def test_e4m3_cache_is_refused_where_no_kernel_reads_it():
     with pytest.raises(B.QPError) as e:
         B.group_attend(layout, q, kv, kv, bad, torch.empty_like(q))
     assert e.value.status == B.QP_ERR_INVALID_ARG
+
+
+def test_refused_layer_call_leaves_cache_and_indices_alone():
+    """An 8-bit cache that the pinned kernel does not read, every token kept: nothing behind the cache's length is written."""
+    dims = W.LayerDims(256, 512, 8, 2)
+    layout = B.make_layout(8, 2, 128, "bf16")
+    shape = B.make_layer_shape(256, 512, dims.rms_eps, dims.rope_theta, dims.mrope_section)
+    wt = {k_: v_.to(DEV) for k_, v_ in W.make_decoder_layer(dims, 0, seed=3).items()}
+    cache = B.Cache(layout, 40, fmt=FP8)
+    for t in (cache.k, cache.v):
+        t.view(torch.uint8).fill_(0x2a)
+    cache.c.len = 5
+    for n_t in (1, 16):
+        x = W.make_hidden(1, n_t, 256, seed=8).to(DEV)
+        kept = torch.full((2, n_t), -3, dtype=torch.int32, device=DEV)
+        B.select_attend_kernel(B.QP_ATTEND_SCALAR)
+        try:
+            with pytest.raises(B.QPError) as e:
+                B.layer_group(layout, shape, B.LayerWeights(**wt), x, W.text_positions(n_t, 90).to(DEV), 0, 70, None,
+                              "key_norm_small", n_t, cache, torch.empty_like(x), kept, B.make_layer_workspace(layout, shape, n_t, 0))
+        finally:
+            B.select_attend_kernel(B.QP_ATTEND_AUTO)
+        torch.cuda.synchronize()
+        assert e.value.status == B.QP_ERR_UNSUPPORTED and cache.len == 5
+        assert (cache.k.view(torch.uint8) == 0x2a).all() and (cache.v.view(torch.uint8) == 0x2a).all()
+        assert (cache.pos == -1).all() and (kept == -3).all()
 
 
 @pytest.mark.parametrize("n_g,h_q,h_kv,c", [(1, 28, 4, 1), (4, 28, 4, 31), (2, 64, 8, 32), (1, 28, 4, 33), (3, 6, 3, 255), (4, 28, 4, 257),
