@@ -69,6 +69,10 @@ __device__ __forceinline__ void wait_vmcnt() {
   asm volatile("s_waitcnt vmcnt(%0)" : : "n"(N) : "memory");
 }
 
+// The wavefront's LDS reads so far have their results. Direct loads into a buffer are not ordered behind reads of it, and the
+// compiler, which sees no dependence between the two, may put its own wait for a read's result behind the request.
+__device__ __forceinline__ void wait_lds_reads() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }
+
 // 8 E4M3 bytes -> 8 bf16 (exact)
 __device__ __forceinline__ bf16x8 widen8(uint2 p) {
   u32x4 o;
@@ -259,7 +263,7 @@ __global__ __launch_bounds__(dc_waves(F8) * 64) void attend_decode_kernel(Attend
 #pragma unroll
     for (int n = 0; n < 4; ++n) v_addr8[n] = v_key8 * DC_D + (((2 * n + (grp & 1)) ^ ((v_key8 >> 1) & 7)) << 4) + 8 * (l16 & 1);
     auto request8 = [&](int b_, int buf_, bool is_v_) {
-      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // the buffer's last reads are not ordered before direct loads into it
+      wait_lds_reads();
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
         const int kl = 8 * i + (lane >> 3);
@@ -341,13 +345,19 @@ __global__ __launch_bounds__(dc_waves(F8) * 64) void attend_decode_kernel(Attend
       bf16x8 pf[2];
       decode_qk_softmax<false>(buf, k_addr, qf, b == n_cb, b == n_cb ? a.n_g : min(DC_BK, a.c - b * DC_BK), t_lane, g, c2, lazy,
                         m_run, l_run, o, pf);
-      if (has2) QP_DC_REQUEST(b + 2 * NW, buf, false)  // the K fragments of block i are in registers
+      if (has2) {
+        wait_lds_reads();
+        QP_DC_REQUEST(b + 2 * NW, buf, false)
+      }
       // V(i) has landed: block i+1 and K(i+2) may still be in flight
       if (has2) wait_vmcnt<24>();
       else if (has1) wait_vmcnt<16>();
       else wait_vmcnt<0>();
       decode_pv<false>(buf + DC_TILE, v_addr, pf, o);
-      if (has2) QP_DC_REQUEST(b + 2 * NW, buf, true)
+      if (has2) {
+        wait_lds_reads();
+        QP_DC_REQUEST(b + 2 * NW, buf, true)
+      }
       b += NW;
       cur ^= 1;
     }
