@@ -488,15 +488,22 @@ __global__ __launch_bounds__(MF_NT, 2) void attend_mfma_kernel(AttendArgs a) {
     if (n > 1) store_v(t_begin + 1, p1, 1);
   } else {
     request(0);
+    if (my_split == 1) {
+      request(1);
+      request(2);
+    }
   }
   // Everything requested so far has to be here: from now on the only vector-memory operations in flight are the tile
   // requests, which the compiler does not see.
   __builtin_amdgcn_s_waitcnt(MF_VMCNT0);
   __syncthreads();
-  // The first products need no more than that, and at the start of a launch all workgroups ask at once; the next pairs are
-  // awaited in the loop. us with all pairs awaited here / now: 64 tokens of the 7B heads over 46,125 entries 59.6 / 58.5, 10
-  // over 100,000 40.4 / 39.7, 77 over 9,840 31.3 / 31.0, 64 of the 72B heads over 5,000 28.7 / 28.3; long launches the same.
-  if (!F8) {
+  // The first products need no more than that. In a chunk of a split launch, which is short and starts together with all
+  // others, the next pairs are requested behind the wait and awaited in the loop; a whole row block has them requested in
+  // front of it, where the requests hold no products up. us requested in front / behind: chunks, 64 tokens of the 7B heads over
+  // 46,125 entries 59.6 / 58.5, 10 over 100,000 40.4 / 39.7, 77 over 9,840 31.3 / 31.0, 64 of the 72B heads over 5,000 28.7 /
+  // 28.3; whole row blocks, 3600 frames of 128 tokens in groups of 64 150660 / 150980, 512 of 256 in groups of 16, 72B heads,
+  // 66540 / 66650.
+  if (!F8 && my_split > 1) {
     request(1);
     request(2);
   }
