@@ -503,7 +503,6 @@ __device__ __forceinline__ void gemm_tile_product(const GemmArgs& a, const TileG
       }
     }
     settle();
-    const bool appends = a.append.k != nullptr && head >= a.h_q;
     bf16_t* const col = dst + (size_t)head_dst * 128 + dim0 + 8 * s_chunk;
 #pragma unroll
     for (int i = 0; i < T::MI; ++i)
@@ -512,15 +511,22 @@ __device__ __forceinline__ void gemm_tile_product(const GemmArgs& a, const TileG
         const int r = u * (64 / SC) + s_row, m = mw + 32 * i + r;
         if (m < a.m) {
           bf16_t* const at = col + (size_t)m * heads_dst * 128;
-          const u32x4 lo = chunk_of(2 * i, r), hi = chunk_of(2 * i + 1, r);
-          *(u32x4*)at = lo;
-          *(u32x4*)(at + 64) = hi;
-          if (appends) {
-            const int dim = dim0 + 8 * s_chunk;
-            append_chunk(a.append, !rotate, head_dst, m, dim, lo);
-            append_chunk(a.append, !rotate, head_dst, m, dim + 64, hi);
-            if (rotate && dim == 0) append_index(a.append, head_dst, m, a.m);
-          }
+          *(u32x4*)at = chunk_of(2 * i, r);
+          *(u32x4*)(at + 64) = chunk_of(2 * i + 1, r);
+        }
+      }
+    if (a.append.k == nullptr || head < a.h_q) return;
+    // the same rows into the cache; in the loop above the question cost the launches that append nothing 0.5 %
+    const int dim = dim0 + 8 * s_chunk;
+#pragma unroll
+    for (int i = 0; i < T::MI; ++i)
+#pragma unroll
+      for (int u = 0; u < 32 * SC / 64; ++u) {
+        const int r = u * (64 / SC) + s_row, m = mw + 32 * i + r;
+        if (m < a.m) {
+          append_chunk(a.append, !rotate, head_dst, m, dim, chunk_of(2 * i, r));
+          append_chunk(a.append, !rotate, head_dst, m, dim + 64, chunk_of(2 * i + 1, r));
+          if (rotate && dim == 0) append_index(a.append, head_dst, m, a.m);
         }
       }
   }
@@ -551,7 +557,7 @@ __global__ __launch_bounds__(T::NW * 64) void gemm_mixed_kernel(GemmArgs a, Tile
 // One thread per token and run of 4 outputs (QKV_ROPE: per run of 4 dims of a head's first half and their rotary
 // partners).
 constexpr int RD_BATCH = 4;  // chunks whose loads are in flight together
-template <int MODE>
+template <int MODE, bool APPEND>
 __global__ __launch_bounds__(256) void gemm_reduce_kernel(GemmArgs a) {
   const long id = (long)blockIdx.x * 256 + threadIdx.x;
   const int runs = MODE == GEMM_QKV_ROPE ? a.n / 8 : a.n / 4;  // per token
@@ -626,7 +632,7 @@ __global__ __launch_bounds__(256) void gemm_reduce_kernel(GemmArgs a) {
     bf16_t* row = dst + ((size_t)m * heads_dst + head_dst) * 128;
     *(uint2*)(row + f) = __builtin_bit_cast(uint2, p0);
     *(uint2*)(row + 64 + f) = __builtin_bit_cast(uint2, p1);
-    if (a.append.k != nullptr && head >= a.h_q) {
+    if (APPEND && head >= a.h_q) {
       const bool is_v = head >= a.h_q + a.h_kv;
       append_run(a.append, is_v, head_dst, m, f, __builtin_bit_cast(uint2, p0));
       append_run(a.append, is_v, head_dst, m, f + 64, __builtin_bit_cast(uint2, p1));
@@ -899,7 +905,9 @@ static hipError_t launch_mode(GemmArgs& a, void* scratch, size_t scratch_bytes, 
   }
   if (e != hipSuccess || a.split_k == 1 || !reduce) return e;
   const long threads = (long)a.m * (MODE == GEMM_QKV_ROPE ? a.n / 8 : a.n / 4);
-  hipLaunchKernelGGL(gemm_reduce_kernel<MODE>, dim3((unsigned)((threads + 255) / 256)), dim3(256), 0, s, a);
+  const dim3 grid((unsigned)((threads + 255) / 256));
+  if (MODE == GEMM_QKV_ROPE && a.append.k != nullptr) hipLaunchKernelGGL((gemm_reduce_kernel<MODE, MODE == GEMM_QKV_ROPE>), grid, dim3(256), 0, s, a);
+  else hipLaunchKernelGGL((gemm_reduce_kernel<MODE, false>), grid, dim3(256), 0, s, a);
   return hipSuccess;
 }
 
