@@ -54,7 +54,7 @@ __device__ __forceinline__ float dot8(const uint4& w, const uint4& x, float acc)
   return acc;
 }
 
-// 1 / rms of row t of x, as one wavefront of rms_norm_kernel takes it: the same sums in the same order
+// 1 / rms of a row, as one wavefront of rms_norm_kernel takes it: the same sums in the same order
 template <typename First>
 __device__ __forceinline__ float gemv_inv_rms(const uint4* x, int chunks, int k, float eps, int lane, const First& first) {
   float ss = 0.f;
@@ -96,9 +96,11 @@ struct AppendFusion {};
 template <int MODE, int M, typename F>
 __global__ __launch_bounds__(GV_WAVES * 64) void gemv_bf16_kernel(GemmArgs a, F fuse) {
   constexpr bool FUSED = std::is_same<F, GemvFusion>::value, APPEND = FUSED || std::is_same<F, AppendFusion>::value;
+  static_assert(!APPEND || MODE == GEMM_QKV_ROPE, "keys and values are appended");
+  static_assert(!FUSED || M == 1, "one wavefront takes the norm of the one row");
   __shared__ float part[GV_WAVES][4][M];
-  __shared__ float inv_rms[M];
-  __shared__ float2 angles[M][2];  // QKV_ROPE: (cos, sin) of this workgroup's two frequencies
+  __shared__ float inv_rms;
+  __shared__ float2 angles[2];  // FUSED: (cos, sin) of this workgroup's two frequencies
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int quad = blockIdx.x;  // < n / 4
@@ -127,13 +129,11 @@ __global__ __launch_bounds__(GV_WAVES * 64) void gemv_bf16_kernel(GemmArgs a, F 
 #pragma unroll
     for (int t = 0; t < M; ++t) acc[e][t] = 0.f;
   constexpr int STEP = GV_WAVES * 64;
-  uint4 ahead[GV_NORM];  // FUSED: wavefront t < M takes token t's norm; its row is requested before anything else
+  uint4 ahead[GV_NORM];  // FUSED: wavefront 0 takes the norm; the row is requested before anything else
   if constexpr (FUSED) {
-    if (wave < M) {
-      const uint4* xr = x[0];
-      if (M > 1 && wave > 0) xr = x[M - 1];
+    if (wave == 0) {
 #pragma unroll
-      for (int i = 0; i < GV_NORM; ++i) ahead[i] = xr[min(lane + 64 * i, chunks - 1)];
+      for (int i = 0; i < GV_NORM; ++i) ahead[i] = x[0][min(lane + 64 * i, chunks - 1)];
     }
   }
   uint4 w0[4], w1[4], x0[M], x1[M], n0, n1;
@@ -150,31 +150,28 @@ __global__ __launch_bounds__(GV_WAVES * 64) void gemv_bf16_kernel(GemmArgs a, F 
     if constexpr (FUSED) n0 = ((const uint4*)fuse.norm_w)[c], n1 = ((const uint4*)fuse.norm_w)[c1];
   };
   int c = wave * 64 + lane;
-  float inv[M];
+  float inv = 0.f;
   if constexpr (FUSED) {
     request(min(c, chunks - 1));
-    if (wave < M) {
-      const float v = gemv_inv_rms(wave == 0 ? x[0] : x[M - 1], chunks, a.k, fuse.eps, lane, ahead);
-      if (lane == 0) inv_rms[wave] = v;
-    } else if (MODE == GEMM_QKV_ROPE && wave == M + quad % (GV_WAVES - M)) {
+    if (wave == 0) {
+      const float v = gemv_inv_rms(x[0], chunks, a.k, fuse.eps, lane, ahead);
+      if (lane == 0) inv_rms = v;
+    } else if (wave == 1 + quad % (GV_WAVES - 1)) {
       // the double-precision chain goes to another SIMD from workgroup to workgroup
-      const int f0 = 2 * (quad & 31);
-      const float2 cs = rope_cos_sin(fuse.rope, min(lane >> 1, a.m - 1), f0 + (lane & 1));
-      if (lane < 2 * M) angles[lane >> 1][lane & 1] = cs;
+      const float2 cs = rope_cos_sin(fuse.rope, 0, 2 * (quad & 31) + (lane & 1));
+      if (lane < 2) angles[lane] = cs;
     }
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // not for the weights under way
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
-#pragma unroll
-    for (int t = 0; t < M; ++t) inv[t] = inv_rms[t];
+    inv = inv_rms;
   }
   for (; c < chunks; c += 2 * STEP) {
     const bool has1 = c + STEP < chunks;
     if constexpr (!FUSED) {
       request(c);  // not at the end of the trip before, as below: 72B QKV of two tokens 32.3 us so, 31.3 here
     } else {
-#pragma unroll
-      for (int t = 0; t < M; ++t) x0[t] = scale8(x0[t], n0, inv[t]), x1[t] = scale8(x1[t], n1, inv[t]);
+      x0[0] = scale8(x0[0], n0, inv), x1[0] = scale8(x1[0], n1, inv);
     }
 #pragma unroll
     for (int e = 0; e < 4; ++e)
@@ -227,7 +224,7 @@ __global__ __launch_bounds__(GV_WAVES * 64) void gemv_bf16_kernel(GemmArgs a, F 
     else dst = (bf16_t*)a.v_out, heads_dst = a.h_kv, head_dst = head - a.h_q - a.h_kv;
     if (head < a.h_q + a.h_kv) {
       float4 cs;  // (cos, sin) of f0 and f0 + 1
-      if constexpr (FUSED) cs = make_float4(angles[t][0].x, angles[t][0].y, angles[t][1].x, angles[t][1].y);
+      if constexpr (FUSED) cs = make_float4(angles[0].x, angles[0].y, angles[1].x, angles[1].y);
       else cs = *(const float4*)(a.cos_sin + ((size_t)t * 64 + f0) * 2);
       const float c[2] = {cs.x, cs.z}, sn[2] = {cs.y, cs.w};
 #pragma unroll
@@ -289,8 +286,8 @@ hipError_t launch_gemv_bf16(const GemmArgs& a, int mode, hipStream_t s) {
   return hipErrorInvalidValue;
 }
 
-hipError_t launch_gemv_fused(const GemmArgs& a, const GemvFusion& f, int mode, hipStream_t s) {
-  if (a.m != 1 || a.append.k == nullptr || mode != GEMM_QKV_ROPE || !gemv_applies(a) || !gemm_supported(a, mode)) return hipErrorInvalidValue;
+hipError_t launch_gemv_fused(const GemmArgs& a, const GemvFusion& f, hipStream_t s) {
+  if (a.m != 1 || a.append.k == nullptr || !gemm_supported(a, GEMM_QKV_ROPE)) return hipErrorInvalidValue;
   hipLaunchKernelGGL((gemv_bf16_kernel<GEMM_QKV_ROPE, 1, GemvFusion>), dim3((unsigned)(a.n / 4)), dim3(GV_WAVES * 64), 0, s, a, f);
   return hipSuccess;
 }

@@ -233,17 +233,18 @@ qp_status qp_layer_group(const qp_layout* layout, const qp_layer_shape* shape, c
   void* split_ws = ws + c.path + (path_bytes - kSplit) / 256 * 256;
   // Where every token is kept (the stages after the video) the projection appends to the cache itself: the append's launch
   // is short, but a side stream forked and joined around it held the caller's up (7B layer, 64 tokens over 46,125 entries
-  // 212.5 us, 202.5 without). A token or two (decoding): the weight-streaming kernel takes the norms and the rotary angles into its own launches.
+  // 212.5 us, 202.5 without). One token (decoding, always kept): the weight-streaming QKV launch also takes the first norm and
+  // the rotary angles.
   const bool appended = keep == n_g, streamed = n_g == 1 && qp::gemm_uses_gemv(qkv);
   if (appended)
     qkv.append = qp::CacheAppend{cache->k, cache->v, cache->pos, kept_idx_or_null, cache->capacity, cache->len,
                                  group_token_base, cache->format == QP_CACHE_FP8_E4M3};
-  qp::GemvFusion fuse{};  // one token: the weight-streaming projection takes the norm and the angles
+  qp::GemvFusion fuse{};
   if (streamed) {
     fuse.norm_w = weights->ln1_w, fuse.eps = shape->rms_eps;
     fuse.rope = qp::RopeArgs{pos, (long)axis_stride, n_g, shape->rope_theta, shape->mrope_section[0], shape->mrope_section[1], nullptr};
     qkv.x = x_g;
-    st = finish(qp::launch_gemv_fused(qkv, fuse, qp::GEMM_QKV_ROPE, s));
+    st = finish(qp::launch_gemv_fused(qkv, fuse, s));
   } else {
     qp::launch_norm_rope(x_g, weights->ln1_w, ws + c.h, n_g, dm, shape->rms_eps, pos, (long)axis_stride, shape->rope_theta,
                          shape->mrope_section[0], shape->mrope_section[1], (float*)(ws + c.cs), s);

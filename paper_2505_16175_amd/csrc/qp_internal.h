@@ -277,13 +277,13 @@ GemmSplit gemm_plan_split(const GemmArgs& a, int mode, size_t scratch_bytes);  /
 bool gemv_applies(const GemmArgs& a);
 bool gemm_uses_gemv(const GemmArgs& a);   // gemv_applies and no tiling is forced
 hipError_t launch_gemv_bf16(const GemmArgs& a, int mode, hipStream_t s);
-// Such a call of one token with the layer's steps before it taken into the launch (QKV_ROPE).
+// The QKV projection of one token with the layer's steps before it taken into the launch, and appended to the cache.
 struct GemvFusion {
   const void* norm_w;  // x is RMSNormed on the way (weights [k], eps)
   float eps;
-  RopeArgs rope;       // QKV_ROPE: the angles themselves instead of a table of them
+  RopeArgs rope;       // the angles themselves instead of a table of them
 };
-hipError_t launch_gemv_fused(const GemmArgs& a, const GemvFusion& f, int mode, hipStream_t s);
+hipError_t launch_gemv_fused(const GemmArgs& a, const GemvFusion& f, hipStream_t s);
 int gemm_tile_rows(const GemmArgs& a);    // token rows per workgroup tile the launcher would use: 128 or 256
 int gemm_tile_cols(const GemmArgs& a);    // outputs per workgroup tile of an unsplit launch: 128 or 256
 int gemm_tile_blocks(const GemmArgs& a);  // workgroups of an unsplit launch, padding of the XCD mapping included
