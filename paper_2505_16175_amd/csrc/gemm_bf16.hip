@@ -489,11 +489,7 @@ __device__ __forceinline__ void gemm_tile_product(const GemmArgs& a, const TileG
         if (rotate) {
           const float c[4] = {cs0[i].x, cs0[i].z, cs1[i].x, cs1[i].z}, s[4] = {cs0[i].y, cs0[i].w, cs1[i].y, cs1[i].w};
 #pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            const float x0 = lo[e], x1 = hi[e];
-            lo[e] = fmaf(x0, c[e], -(x1 * s[e]));  // spelled out: every tiling and kind of launch rounds alike
-            hi[e] = fmaf(x1, c[e], x0 * s[e]);
-          }
+          for (int e = 0; e < 4; ++e) rotate_pair(lo[e], hi[e], c[e], s[e]);
         }
         bf16x4 p0, p1;
 #pragma unroll
@@ -620,11 +616,7 @@ __global__ __launch_bounds__(256) void gemm_reduce_kernel(GemmArgs a) {
       const float4 cs1 = *(const float4*)(a.cos_sin + ((size_t)m * 64 + f + 2) * 2);
       const float c[4] = {cs0.x, cs0.z, cs1.x, cs1.z}, sn[4] = {cs0.y, cs0.w, cs1.y, cs1.w};
 #pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const float x0 = lo[e], x1 = hi[e];
-        lo[e] = x0 * c[e] - x1 * sn[e];
-        hi[e] = x1 * c[e] + x0 * sn[e];
-      }
+      for (int e = 0; e < 4; ++e) rotate_pair(lo[e], hi[e], c[e], sn[e]);
     }
     bf16x4 p0, p1;
 #pragma unroll

@@ -228,11 +228,7 @@ __global__ __launch_bounds__(GV_WAVES * 64) void gemv_bf16_kernel(GemmArgs a, F 
       else cs = *(const float4*)(a.cos_sin + ((size_t)t * 64 + f0) * 2);
       const float c[2] = {cs.x, cs.z}, sn[2] = {cs.y, cs.w};
 #pragma unroll
-      for (int e = 0; e < 2; ++e) {
-        const float x0 = lo[e], x1 = hi[e];
-        lo[e] = x0 * c[e] - x1 * sn[e];
-        hi[e] = x1 * c[e] + x0 * sn[e];
-      }
+      for (int e = 0; e < 2; ++e) rotate_pair(lo[e], hi[e], c[e], sn[e]);
     }
     bf16_t* out_row = dst + ((size_t)t * heads_dst + head_dst) * 128;
     const uint32_t p0 = (uint32_t)f32_to_bf16_rne(lo[0]) | ((uint32_t)f32_to_bf16_rne(lo[1]) << 16);

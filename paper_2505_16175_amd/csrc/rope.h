@@ -24,4 +24,12 @@ __device__ __forceinline__ float2 rope_cos_sin(const RopeArgs& a, int t, int i) 
   return make_float2((float)cs, (float)sn);
 }
 
+// A rotary pair turned by its angle. The roundings are spelled out, not left to the compiler's contraction: every store of
+// the QKV projection (tiles, split product, weight streaming) rounds alike.
+__device__ __forceinline__ void rotate_pair(float& lo, float& hi, float c, float s) {
+  const float x0 = lo, x1 = hi;
+  lo = fmaf(x0, c, -__fmul_rn(x1, s));
+  hi = fmaf(x1, c, __fmul_rn(x0, s));
+}
+
 }  // namespace qp

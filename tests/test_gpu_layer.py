@@ -276,6 +276,37 @@ def test_linear_is_the_same_in_every_tiling(m, n, k):
     assert_stored_close(to_f64(outs[0]), LO.bf16_round(LO.linear(to_f64(x), to_f64(w)) + to_f64(r)), "linear")
 
 
+def test_rotation_rounds_alike_in_every_kind_of_launch():
+    """Products and biases of small whole numbers have exact sums in any order, so what is left is the rotation: streamed
+    weights (one and two tokens), split products of both tile widths, and whole tiles give the same bits."""
+    n, d_model, h_q, h_kv = 400, 4096, 12, 2
+    layout = B.make_layout(h_q, h_kv, 128, "bf16")
+    rows = (h_q + 2 * h_kv) * 128
+    g = torch.Generator(device=DEV).manual_seed(31)
+    whole = lambda lim, *s: torch.randint(-lim, lim + 1, s, generator=g, device=DEV).to(torch.bfloat16)
+    x, w, b = whole(3, n, d_model), whole(2, rows, d_model), whole(5, rows)
+    ang = torch.rand(n, 64, generator=g, device=DEV) * 6.28
+    cs = torch.stack((ang.cos(), ang.sin()), -1).contiguous()
+    scratch = torch.empty(32 << 20, dtype=torch.uint8, device=DEV)
+
+    def qkv(step, ws):
+        out = [torch.full((n, h, 128), float("nan"), dtype=torch.bfloat16, device=DEV) for h in (h_q, h_kv, h_kv)]
+        for t in range(0, n, step):
+            B.qkv_rope(layout, x[t:t + step], w, b, cs[t:t + step], *(o[t:t + step] for o in out), ws)
+        torch.cuda.synchronize()
+        return out
+
+    want = qkv(n, None)
+    assert torch.equal(want[2].view(n, -1), (x.double() @ w.double().T + b.double())[:, -h_kv * 128:].to(torch.bfloat16))
+    for step, tiles in ((1, 0), (2, 0), (64, 32), (200, 64), (400, 32)):       # 64-wide tiles, and 256-wide ones at 400 tokens
+        ws = scratch if tiles else None
+        if tiles:
+            p = B.linear_plan(step, rows, d_model, scratch.numel())
+            assert p["k_chunks"] > 1 and p["workgroups"] == tiles
+        for a, c in zip(qkv(step, ws), want):
+            assert torch.equal(a, c), f"{step} tokens per call"
+
+
 @pytest.mark.parametrize("bias", [False, True])
 @pytest.mark.parametrize("m,n,k", [(130, 1000, 640), (257, 520, 64), (700, 3584, 256)])
 def test_linear_without_a_residual_in_every_tiling(m, n, k, bias):
