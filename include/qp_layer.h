@@ -57,7 +57,9 @@ qp_status qp_rms_norm(const void* x, const void* w, void* out, int32_t n_tokens,
  *   workspace: optional device scratch (256-byte aligned), may be NULL. A call whose output tiles would occupy at
  *     most a quarter of the compute units (few tokens against long rows: text chunks, decode steps, where streaming
  *     the weights once is the bound) deals the contraction to k chunks, about one workgroup per compute unit in
- *     all; their f32 partial sums ([chunks][m][n], as many chunks as fit) live in this scratch and a second launch
+ *     all; so does a larger one of a long contraction where two or three chunks of 128 x 256 tiles fill the compute
+ *     units in one round and that is estimated to be a tenth faster (some 400 to 1100 tokens of a down projection).
+ *     The chunks' f32 partial sums ([chunks][m][n], as many chunks as fit) live in this scratch and a second launch
  *     adds them in chunk order and applies bias / residual. Without scratch nothing is split. Same inputs, same
  *     scratch size: bit-identical results.
  * UNSUPPORTED unless k is a multiple of 64 and n a multiple of 8. */
@@ -82,7 +84,8 @@ qp_status qp_swiglu_gate_up(const void* h, const void* w_gate_up, void* act, int
                             int32_t d_ff, void* hip_stream);
 
 /* The projections run 256 x 256 output tiles per workgroup, or 128 (tokens) x 256 or 128 x 128 when the larger tiles
- * would leave compute units idle; a split call of few outputs runs 64-wide tiles of 128 or, up to 64 tokens, 64 rows. The
+ * would leave compute units idle; whole rounds of 256 x 256 tiles may be followed by smaller ones over the last outputs,
+ * in the same launch, to the same bits; a split call of few outputs runs 64-wide tiles of 128 or, up to 64 tokens, 64 rows. The
  * launcher chooses per call. This pins 256-wide tiles of so many token rows for later calls of this process (tests cover
  * both; the 128- and 64-wide tiles cannot be pinned): 0 = choose per call, 128 or 256. INVALID_ARG for any other value. */
 qp_status qp_select_linear_tile(int32_t token_rows);
@@ -94,7 +97,7 @@ qp_status qp_select_linear_tile(int32_t token_rows);
  * token_rows_per_tile is then 1 or 2 (the tokens it computes) and workgroups = n / 4; a tiling pinned with
  * qp_select_linear_tile keeps such calls on the tiled kernel. */
 typedef struct {
-  int32_t token_rows_per_tile; /* 128 or 256; 1 or 2 for the weight-streaming kernel. A split call of at most 64 tokens
+  int32_t token_rows_per_tile; /* 128 or 256 (also where tiles of 128 rows follow the whole rounds of those); 1 or 2 for the weight-streaming kernel. A split call of at most 64 tokens
                                   on 64-wide tiles leaves out the upper 64 rows of its one tile */
   int32_t workgroups;
   int32_t k_chunks;

@@ -99,6 +99,9 @@ __device__ __forceinline__ int weight_row(int j, int n0, int d_ff) {
   return n0 + j;
 }
 
+// Whether a split contraction on 256-wide tiles deals its tiles' chunks to the XCDs instead of its tiles (see launch_tile).
+__device__ __forceinline__ bool deals_items(int split_k, int tiles) { return split_k > 1 && tiles % 8 != 0; }
+
 // A grid of tiles of one kind: block `block` of `blocks` (a multiple of 8) per k chunk, over outputs n_first and up.
 struct TileGrid {
   int block, blocks;
@@ -119,12 +122,14 @@ __device__ __forceinline__ void gemm_tile_product(const GemmArgs& a, const TileG
   // side, its L2 then fetches 8 + 4 operand tiles per k-step for 32 products. (Weight tiles dealt to the XCDs in turn
   // left them unequal: 18 weight tiles x 12 token tiles put 36 workgroups on two XCDs of 32 CUs, 166 us for QKV of 3000
   // tokens at 7B sizes, 99 now.)
-  // A split contraction has a grid row per k chunk, or (a grid of one row) its items are the chunks of its tiles, tile by
-  // tile, and those are dealt to the XCDs.
-  const bool by_item = gridDim.y < a.split_k;
-  const int per_xcd = grid.blocks >> 3;
-  int id = (grid.block & 7) * per_xcd + (grid.block >> 3), chunk = blockIdx.y;
-  if (id >= grid.tiles_m * grid.tiles_n * (by_item ? a.split_k : 1)) return;  // padding of the mapping (whole workgroup, before any barrier)
+  // A split contraction has a grid row per k chunk, and its tiles are dealt row by row, or (deals_items) the chunks of its
+  // tiles, tile by tile, over the whole grid.
+  const int tiles = grid.tiles_m * grid.tiles_n;
+  const bool by_item = T::BN == GM_BN && deals_items(a.split_k, tiles);
+  const int block = by_item ? blockIdx.y * grid.blocks + grid.block : grid.block;
+  const int items = by_item ? tiles * a.split_k : tiles, per_xcd = (items + 7) >> 3;
+  int id = (block & 7) * per_xcd + (block >> 3), chunk = blockIdx.y;
+  if ((block >> 3) >= per_xcd || id >= items) return;  // padding of the mapping (whole workgroup, before any barrier)
   if (by_item) {
     const int tile = id / a.split_k;
     chunk = id - tile * a.split_k;
@@ -845,8 +850,8 @@ static hipError_t launch_tile(GemmArgs a, hipStream_t s) {
   // 257 / 300 / 384 tokens 90 / 95 / 106 -> 55 / 59 / 66; 4608 x 3584 at 160 / 256 32 / 38 -> 22 / 26. Narrow tiles, two and
   // three to a CU, have the room: 4608 x 3584 at 128 tokens 24.0, by items 25.1. Chunk by chunk an XCD would read one range
   // of k of all rows, and rows 16 KB apart then meet in few memory channels: 8192 x 8192 at 3 tokens 29.5 -> 32.7.
-  const bool by_item = a.split_k > 1 && T::BN == GM_BN && tiles % 8 != 0;
-  const dim3 grid = by_item ? dim3((unsigned)((tiles * a.split_k + 7) / 8 * 8)) : dim3((unsigned)((tiles + 7) / 8 * 8), a.split_k);
+  // So deals_items deals the items; the grid is the same either way, and what it has too much ends at once.
+  const dim3 grid((unsigned)((tiles + 7) / 8 * 8), a.split_k);
   hipLaunchKernelGGL((gemm_bf16_kernel<MODE, T>), grid, dim3(T::NW * 64), lds, s, a);
   return hipSuccess;
 }

@@ -1,4 +1,6 @@
 """GPU parity of the decoder layer around the path (include/qp_layer.h) against the fp64 layer oracle."""
+import ctypes
+
 import numpy as np
 import pytest
 import torch
@@ -371,6 +373,44 @@ def test_split_where_chunks_fill_the_chip(m, n, k, chunks):
     B.linear(x.to(DEV), w.to(DEV), b.to(DEV), r.to(DEV), out, scratch)
     torch.cuda.synchronize()
     assert_stored_close(to_f64(out), LO.bf16_round(LO.linear(to_f64(x), to_f64(w), to_f64(b)) + to_f64(r)), "split in halves")
+
+
+def _launched_grids(call):
+    """Grids (x, y) of the kernels that `call` launches, in order, from a stream capture of it."""
+    class Params(ctypes.Structure):    # hipKernelNodeParams
+        _fields_ = [("block", ctypes.c_uint * 3), ("extra", ctypes.c_void_p), ("func", ctypes.c_void_p),
+                    ("grid", ctypes.c_uint * 3), ("args", ctypes.c_void_p), ("lds", ctypes.c_uint)]
+
+    path = next(line.split()[-1] for line in open("/proc/self/maps") if "libamdhip64" in line)
+    hip = ctypes.CDLL(path)
+    graph = torch.cuda.CUDAGraph(keep_graph=True)
+    with torch.cuda.graph(graph):
+        call()
+    handle, count = ctypes.c_void_p(graph.raw_cuda_graph()), ctypes.c_size_t(0)
+    assert hip.hipGraphGetNodes(handle, None, ctypes.byref(count)) == 0
+    nodes = (ctypes.c_void_p * count.value)()
+    assert hip.hipGraphGetNodes(handle, nodes, ctypes.byref(count)) == 0
+    grids = []
+    for node in nodes:
+        p = Params()
+        assert hip.hipGraphKernelNodeGetParams(ctypes.c_void_p(node), ctypes.byref(p)) == 0
+        grids.append((p.grid[0], p.grid[1]))
+    return grids
+
+
+@pytest.mark.parametrize("m,n,k", [(513, 3592, 4160), (900, 3584, 18944), (300, 3584, 18944), (200, 4608, 3584), (64, 10240, 8192),
+                                   (64, 3584, 18944), (128, 3584, 3584), (512, 37888, 64), (4090, 10240, 128), (700, 3584, 256),
+                                   (2048, 3584, 192), (2, 3584, 256)])
+def test_linear_plan_is_what_is_launched(m, n, k):
+    """Split products whose tiles are dealt to the XCDs and whose items are, 64-wide tiles, whole tiles, two tilings in one
+    launch, streamed weights: the first launch has the plan's workgroups in every k chunk, and a split one a second launch."""
+    x, w = (torch.zeros(*s, dtype=torch.bfloat16, device=DEV) for s in ((m, k), (n, k)))
+    out = torch.empty(m, n, dtype=torch.bfloat16, device=DEV)
+    scratch = torch.empty(32 << 20, dtype=torch.uint8, device=DEV)
+    p = B.linear_plan(m, n, k, scratch.numel())
+    B.linear(x, w, None, None, out, scratch)
+    grids = _launched_grids(lambda: B.linear(x, w, None, None, out, scratch))
+    assert grids[0] == (p["workgroups"], p["k_chunks"]) and len(grids) == (2 if p["k_chunks"] > 1 else 1)
 
 
 @pytest.mark.parametrize("n,d_model,h_q,h_kv", [(1, 3584, 28, 4), (9, 1024, 4, 2), (64, 3584, 28, 4),
