@@ -149,10 +149,16 @@ def _ptr(t: Optional[torch.Tensor]):
     return ctypes.c_void_p(t.data_ptr())
 
 
+# The current stream's handle alone: torch.cuda.current_stream() builds a Stream object and looks its device up again, 3 of the
+# 11 us that the host spends on a tiny video. Neither name is public: a torch without them takes the long way.
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+_device = getattr(torch._C, "_cuda_getDevice", None)
+
+
 def _stream():
-    # the handle alone: torch.cuda.current_stream() builds a Stream object and looks its device up again, 3 of the 11 us
-    # that the host spends on a tiny video
-    return ctypes.c_void_p(torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice()))
+    if _raw_stream is None or _device is None:
+        return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    return ctypes.c_void_p(_raw_stream(_device()))
 
 
 def _check(status, where):

@@ -101,6 +101,18 @@ def test_layer_group_refuses_before_its_first_launch(case, status, keep):
     assert st == status and c.len == 5
 
 
+@pytest.mark.parametrize("missing", ["_cuda_getCurrentRawStream", "_cuda_getDevice"])
+def test_binding_takes_the_stream_from_a_torch_without_the_raw_handle(monkeypatch, missing):
+    import importlib.util
+    import torch
+    monkeypatch.delattr(torch._C, missing, raising=False)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda *a: type("S", (), {"cuda_stream": 0x1230})())
+    spec = importlib.util.spec_from_file_location(B.__package__ + ".binding_of_another_torch", B.__file__)
+    mod = importlib.util.module_from_spec(spec)
+    spec.loader.exec_module(mod)
+    assert mod._stream().value == 0x1230
+
+
 def test_debug_fail_after_arguments():
     assert B.lib().qp_debug_fail_after(-1) == B.QP_ERR_INVALID_ARG
     assert B.lib().qp_debug_fail_after(0) == B.QP_OK
