@@ -748,9 +748,9 @@ def test_decode_step_equals_its_parts_bit_for_bit(dims, n_t):
 @pytest.mark.parametrize("fp8", [False, True])
 @pytest.mark.parametrize("d_model", [64, 4160, 8192, 8256])
 def test_decode_step_takes_norms_angles_and_append_with_it(d_model, fp8, n_t, keep):
-    """The launches of a token or two norm their rows, take the rotary angles and append to the cache (not where a token is
-    pruned): rows of less than a wavefront's chunks, of several trips, of more than the norm has in flight, over both cache
-    formats. Bit for bit what the separate calls give, the cache rows those of qp_topk_compact."""
+    """The QKV launch of one token norms its row, takes the rotary angles and appends to the cache; that of two appends (not
+    where a token is pruned). Rows of less than a wavefront's chunks, of several trips, of more than the norm has in flight,
+    over both cache formats. Bit for bit what the separate calls give, the cache rows those of qp_topk_compact."""
     dims = W.LayerDims(d_model, 256, 6, 2)
     layout = B.make_layout(6, 2, 128, "bf16")
     shape = B.make_layer_shape(d_model, 256, dims.rms_eps, dims.rope_theta, dims.mrope_section)
@@ -795,11 +795,11 @@ def test_decode_step_takes_norms_angles_and_append_with_it(d_model, fp8, n_t, ke
 
 @pytest.mark.parametrize("fp8", [False, True])
 @pytest.mark.parametrize("n_t,d_model", [(3, 512), (65, 2048), (130, 2048), (300, 64), (257, 4096)])
-def test_kept_tokens_are_appended_by_the_projection(n_t, d_model, fp8):
-    """Every token kept: the QKV projection writes the cache rows too, from the reduction of a split product and from whole
-    tiles. Codes, positions and kept indices are those of qp_topk_compact on the layer's own K and V."""
-    dims = W.LayerDims(d_model, 256, 6, 2)
-    layout = B.make_layout(6, 2, 128, "bf16")
+def test_kept_tokens_are_appended_by_the_projection(n_t, d_model, fp8, h_q=6, h_kv=2):
+    """Every token kept: the QKV projection writes the cache rows too, from the reduction of a split product and from tiles of
+    128 x 128. Codes, positions and kept indices are those of qp_topk_compact on the layer's own K and V."""
+    dims = W.LayerDims(d_model, 256, h_q, h_kv)
+    layout = B.make_layout(h_q, h_kv, 128, "bf16")
     shape = B.make_layer_shape(d_model, 256, dims.rms_eps, dims.rope_theta, dims.mrope_section)
     wt = {k_: v_.to(DEV) for k_, v_ in W.make_decoder_layer(dims, 0, seed=3).items()}
     x = W.make_hidden(1, n_t, d_model, seed=8).to(DEV)
@@ -808,23 +808,33 @@ def test_kept_tokens_are_appended_by_the_projection(n_t, d_model, fp8):
     caches = [B.Cache(layout, n_t + 9, fmt=fmt) for _ in range(2)]
     for cache in caches:
         cache.c.len = 5
-    kept = torch.full((2, 2, n_t), -1, dtype=torch.int32, device=DEV)
+    kept = torch.full((2, h_kv, n_t), -1, dtype=torch.int32, device=DEV)
     B.layer_group(layout, shape, B.LayerWeights(**wt), x, pos, 0, 700, None, "key_norm_small", n_t, caches[0],
                   torch.empty_like(x), kept[0], B.make_layer_workspace(layout, shape, n_t, 0))
     h = torch.empty_like(x)
     cs = torch.empty(n_t, 64, 2, dtype=torch.float32, device=DEV)
-    q = torch.empty(n_t, 6, 128, dtype=torch.bfloat16, device=DEV)
-    k = torch.empty(n_t, 2, 128, dtype=torch.bfloat16, device=DEV)
+    q = torch.empty(n_t, h_q, 128, dtype=torch.bfloat16, device=DEV)
+    k = torch.empty(n_t, h_kv, 128, dtype=torch.bfloat16, device=DEV)
     v = torch.empty_like(k)
     B.rms_norm(x, wt["ln1_w"], h, dims.rms_eps)
     B.rope_table(pos, 0, n_t, dims.rope_theta, dims.mrope_section, cs)
     B.qkv_rope(layout, h, wt["w_qkv"], wt["b_qkv"], cs, q, k, v, torch.empty(32 << 20, dtype=torch.uint8, device=DEV))
-    B.topk_compact(layout, torch.zeros(2, n_t, device=DEV), k, v, n_t, 700, caches[1], kept[1])
+    B.topk_compact(layout, torch.zeros(h_kv, n_t, device=DEV), k, v, n_t, 700, caches[1], kept[1])
     torch.cuda.synchronize()
     assert caches[0].len == caches[1].len == 5 + n_t
     assert torch.equal(kept[0], kept[1]) and torch.equal(caches[0].pos, caches[1].pos)
     for a, b in ((caches[0].k, caches[1].k), (caches[0].v, caches[1].v)):
         assert torch.equal(a.view(torch.uint8), b.view(torch.uint8))
+
+
+@pytest.mark.parametrize("fp8", [False, True])
+@pytest.mark.parametrize("n_t,h_q,h_kv,rows,workgroups", [(4100, 6, 2, 128, 168), (8200, 6, 2, 256, 168),
+                                                           (13400, 6, 2, 256, 216 + 216), (17900, 4, 2, 256, 216 + 144)])
+def test_kept_tokens_are_appended_from_every_tiling(n_t, h_q, h_kv, rows, workgroups, fp8):
+    """The QKV tiles of large groups: 128 x 256, 256 x 256, and those followed by 128 x 128 or 128 x 256 in one launch."""
+    plan = B.linear_plan(n_t, (h_q + 2 * h_kv) * 128, 64, 0)
+    assert (plan["token_rows_per_tile"], plan["workgroups"]) == (rows, workgroups)
+    test_kept_tokens_are_appended_by_the_projection(n_t, 64, fp8, h_q, h_kv)
 
 
 @pytest.mark.parametrize("n_t,dims", [(7, SMALL), (3, W.LayerDims(2112, 256, 4, 2)), (64, W.LayerDims(8192, 256, 8, 2)),
@@ -918,6 +928,8 @@ def test_layer_stack_replays_from_a_hip_graph():
 
 def test_qkv_rope_split_in_wide_tiles():
     """36 tiles of 128 x 256 in 7 chunks, dealt to the XCDs as 252 items."""
+    plan = B.linear_plan(200, 4608, 3584, 32 << 20)
+    assert (plan["token_rows_per_tile"], plan["workgroups"], plan["k_chunks"]) == (128, 40, 7)
     test_qkv_rope_split_contraction(200, 3584, 28, 4)
 
 

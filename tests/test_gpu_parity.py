@@ -896,6 +896,7 @@ RUNS = [  # layout (H_q, H_kv, d, dtype), frames, tokens per frame, frames per g
     ((28, 4, 128, "bf16"), 41, 128, 2, 1.0, "key_norm_small", 0, True, 77),     # everything kept, entries from before
     ((28, 4, 128, "bf16"), 321, 128, 16, 0.1, "window_attn", 1170, False, 0),   # more window scratch than one run holds
     ((28, 4, 128, "bf16"), 515, 128, 16, 0.1, "window_attn", 1170, False, 0),   # three runs, the last of one short group
+    ((28, 4, 128, "bf16"), 146, 121, 9, 0.3, "window_attn", 64, False, 0),      # 18 key chunks, the last of one key, four per workgroup
     ((64, 64, 64, "bf16"), 203, 4, 100, 0.1, "window_attn", 37600, False, 0),   # scratch for one group: a run each
     ((28, 4, 128, "bf16"), 67, 121, 4, 0.3, "window_attn+shared", 64, False, 0),  # summed over heads, short last group
     ((12, 3, 128, "bf16"), 250, 64, 3, 0.5, "value_norm+shared", 0, False, 0),
