@@ -466,6 +466,7 @@ __global__ __launch_bounds__(MF_NT, 2) void attend_mfma_kernel(AttendArgs a) {
     const int lim = tile < n_ct ? a.c - 1 - tile * MF_BN : t_lane - (tile - n_ct) * MF_BN;
     mask_block(st, lim - 32 * kb - 4 * g);
   };
+  const bool late = my_split > 1 && a.split_tiles > 2;  // the second and third pair are requested behind the first wait
   // this wavefront's last tile (relative; -1: no rows)
   const int last = wave_live ? min(n, n_ct + t_w_max / MF_BN + 1 - t_begin) - 1 : -1;
 
@@ -488,7 +489,7 @@ __global__ __launch_bounds__(MF_NT, 2) void attend_mfma_kernel(AttendArgs a) {
     if (n > 1) store_v(t_begin + 1, p1, 1);
   } else {
     request(0);
-    if (my_split == 1) {
+    if (!late) {
       request(1);
       request(2);
     }
@@ -501,9 +502,9 @@ __global__ __launch_bounds__(MF_NT, 2) void attend_mfma_kernel(AttendArgs a) {
   // others, the next pairs are requested behind the wait and awaited in the loop; a whole row block has them requested in
   // front of it, where the requests hold no products up. us requested in front / behind: chunks, 64 tokens of the 7B heads over
   // 46,125 entries 59.6 / 58.5, 10 over 100,000 40.4 / 39.7, 77 over 9,840 31.3 / 31.0, 64 of the 72B heads over 5,000 28.7 /
-  // 28.3; whole row blocks, 3600 frames of 128 tokens in groups of 64 150660 / 150980, 512 of 256 in groups of 16, 72B heads,
+  // 28.3; chunks of two tiles, which need them at once, 5 over 600 11.3 / 11.7; whole row blocks, 3600 frames of 128 tokens in groups of 64 150660 / 150980, 512 of 256 in groups of 16, 72B heads,
   // 66540 / 66650.
-  if (!F8 && my_split > 1) {
+  if (!F8 && late) {
     request(1);
     request(2);
   }
