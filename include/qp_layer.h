@@ -74,7 +74,8 @@ qp_status qp_rope_table(const int32_t* pos, int64_t axis_stride, int32_t n_token
 
 /* q, k, v = h w_qkv^T + b_qkv split into heads, rotary embedding applied to q and k (pairs (i, i+64) of a head),
  * written token-major: q [n_tokens][H_q][128], k, v [n_tokens][H_kv][128]. h [n_tokens][d_model].
- * workspace: as in qp_linear (the rotary embedding then runs in the second launch). */
+ * workspace: as in qp_linear, but split only where the tiles occupy at most a quarter of the compute units: other sums
+ * would round otherwise and near-tied keys be kept in place of others (the rotary embedding then runs in the second launch). */
 qp_status qp_qkv_rope(const qp_layout* layout, const void* h, const void* w_qkv, const void* b_qkv,
                       const float* cos_sin, int32_t n_tokens, int32_t d_model, void* q, void* k, void* v,
                       void* workspace, size_t workspace_bytes, void* hip_stream);
@@ -85,9 +86,10 @@ qp_status qp_swiglu_gate_up(const void* h, const void* w_gate_up, void* act, int
 
 /* The projections run 256 x 256 output tiles per workgroup, or 128 (tokens) x 256 or 128 x 128 when the larger tiles
  * would leave compute units idle; whole rounds of 256 x 256 tiles may be followed by smaller ones over the last outputs,
- * in the same launch, to the same bits; a split call of few outputs runs 64-wide tiles of 128 or, up to 64 tokens, 64 rows. The
- * launcher chooses per call. This pins 256-wide tiles of so many token rows for later calls of this process (tests cover
- * both; the 128- and 64-wide tiles cannot be pinned): 0 = choose per call, 128 or 256. INVALID_ARG for any other value. */
+ * in the same launch, to the same bits; a split call of few outputs runs 64-wide tiles of 128 or, up to 64 tokens, 64
+ * rows. The launcher chooses per call. This pins 256-wide tiles of so many token rows for later calls of this process
+ * (tests cover both; the 128- and 64-wide tiles cannot be pinned): 0 = choose per call, 128 or 256. INVALID_ARG for any
+ * other value. */
 qp_status qp_select_linear_tile(int32_t token_rows);
 
 /* How qp_linear would lay out a call (host arithmetic only, nothing is launched): token rows per workgroup tile,
@@ -97,8 +99,9 @@ qp_status qp_select_linear_tile(int32_t token_rows);
  * token_rows_per_tile is then 1 or 2 (the tokens it computes) and workgroups = n / 4; a tiling pinned with
  * qp_select_linear_tile keeps such calls on the tiled kernel. */
 typedef struct {
-  int32_t token_rows_per_tile; /* 128 or 256 (also where tiles of 128 rows follow the whole rounds of those); 1 or 2 for the weight-streaming kernel. A split call of at most 64 tokens
-                                  on 64-wide tiles leaves out the upper 64 rows of its one tile */
+  int32_t token_rows_per_tile; /* 128 or 256 (also where tiles of 128 rows follow whole rounds of those); 1 or 2 for the
+                                  weight-streaming kernel. A split call of at most 64 tokens on 64-wide tiles leaves out
+                                  the upper 64 rows of its one tile */
   int32_t workgroups;
   int32_t k_chunks;
   int32_t k_steps_per_chunk;   /* the last chunk may have fewer */
@@ -125,8 +128,8 @@ size_t qp_layer_workspace_bytes(const qp_layout* layout, const qp_layer_shape* s
  * projection and joined back into it before the call returns, so they run beside the attention and the
  * projections. Tokens that are all kept are appended by the QKV projection itself, without that stream.
  * Calls from several host threads are serialised while they enqueue on it.
- * Errors: INVALID_ARG, UNSUPPORTED (shape), CAPACITY (cache or workspace too small); on any error nothing is
- * launched and the cache is untouched. */
+ * Errors: INVALID_ARG, UNSUPPORTED (shape, or a cache that the selected attention kernel does not read), CAPACITY (cache
+ * or workspace too small); on any of these nothing is launched and the cache is untouched. */
 qp_status qp_layer_group(const qp_layout* layout, const qp_layer_shape* shape, const qp_layer_weights* weights,
                          const void* x_g, const int32_t* pos, int64_t axis_stride, int32_t n_group_tokens,
                          int32_t group_token_base, const void* q_win, int32_t n_window, qp_score_rule rule,

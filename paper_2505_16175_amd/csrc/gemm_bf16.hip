@@ -197,15 +197,16 @@ __device__ __forceinline__ void gemm_tile_product(const GemmArgs& a, const TileG
   // loop the barrier sits before the LAST k-step's products of a step: by then every wavefront has read all its
   // fragments of the step (its slots can be refilled), the next step's tiles have landed, and the wait at the
   // barrier and the latency of the next step's first fragment reads run under those products.
-  // With equal rings of the smaller tilings all refill requests are issued there too. At 256 x 256 that is 64 of them per step within a quarter
-  // of its products: the address path takes 16 cycles for each, falls behind, and holds up the products behind the
-  // requests. So that tiling (rings of 2 and 3) spreads them: a step t issues, two per k-step and wavefront, the second
+  // With equal rings of the smaller tilings all refill requests are issued there too. At 256 x 256 that is 64 of them per
+  // step within a quarter of its products: the address path takes 16 cycles for each, falls behind, and holds up the
+  // products behind the requests. So that tiling (rings of 2 and 3) spreads them: a step t issues, two per k-step and wavefront, the second
   // half of X(t + 1), then W(t + 2) into the slot that step t - 1 left, then, behind the barrier, the first half of
   // X(t + 2). PFLOP/s at 4096 x 59136 x 8192 / 4096 x 8192 x 29568 / 2048 x 37888 x 3584: 1.25 / 1.23 / 1.17 all behind
   // the barrier (with or without the third weight slot), 1.35 / 1.31 / 1.25 spread. The 128 x 256 tiling (equal rings of 3)
   // spreads them too: a step t issues step t + 2 into the slot that step t - 1 left, a request behind every other product
   // before the barrier. us behind the barrier / spread: 2048 x 3584 x 18944 262 / 257, 300 x 37888 x 3584 112 / 105, 257
-  // tokens of it 100 / 96, 300 x 59136 x 8192 365 / 340; 300 x 4608 x 3584 in 4 chunks 27.9 / 28.4.
+  // tokens of it 100 / 96, 300 x 59136 x 8192 365 / 340; in chunks 520 x 3584 x 18944 95 / 92, 900 tokens of it 139 / 132, 400
+  // x 8192 x 29568 242 / 227, 1024 x 3584 x 18944 147 / 149, 300 x 4608 x 3584 27.9 / 28.4.
   // Requests complete in order: when step t + 1 is awaited at the end of step t, what may stay in flight is, with equal
   // rings, the XS - 2 steps after it, and with rings of 2 and 3 the weights of step t + 2.
   const int n_steps = min(a.steps_per_split, a.k / BK - step_begin);
@@ -785,8 +786,8 @@ int gemm_tile_blocks(const GemmArgs& a) {
 // Above a quarter of the CUs a product without fused steps is still split where two or three chunks of its 128 x 256 tiles
 // fill the chip (at least 4/5 of it, one round) and the estimate, with the tile times above and the partial sums at 4.5 TB/s,
 // is a tenth below the unsplit one: long contractions whose tiles leave CUs idle or are small ones. us unsplit / split:
-// 3584 x 18944 at 520 tokens 137 / 91, 640 167 / 105, 768 166 / 110, 900 148 / 130, 1024 170 / 148, 1100 163 / 149; 8192 x
-// 29568 at 400 275 / 221, 512 290 / 253. At k = 3584 (o_proj) there is nothing to gain.
+// 3584 x 18944 at 520 tokens 134 / 92, 640 166 / 105, 768 166 / 110, 900 146 / 132, 1024 169 / 149, 1100 163 / 149; 8192 x
+// 29568 at 400 278 / 227, 512 287 / 253. At k = 3584 (o_proj) there is nothing to gain.
 constexpr int NARROW_ABOVE = 8;
 GemmSplit gemm_plan_split(const GemmArgs& a, int mode, size_t scratch_bytes) {
   GemmSplit p{1, a.k / GM_BK, 0, 0, 0};
@@ -847,7 +848,7 @@ static hipError_t launch_tile(GemmArgs a, hipStream_t s) {
   const long tiles = (long)a.tiles_m * a.tiles_n;
   // Tiles of one workgroup per CU that are few and no multiple of 8 leave XCDs short if only they are dealt: 42 tiles x 6
   // chunks were 36 workgroups on seven XCDs of 32 CUs and none on the last. us dealt by tiles / by items: 3584 x 18944 at
-  // 257 / 300 / 384 tokens 90 / 95 / 106 -> 55 / 59 / 66; 4608 x 3584 at 160 / 256 32 / 38 -> 22 / 26. Narrow tiles, two and
+  // 257 / 300 / 384 tokens 90 / 96 / 107 -> 59 / 62 / 69; 4608 x 3584 at 160 / 256 32 / 38 -> 23 / 26. Narrow tiles, two and
   // three to a CU, have the room: 4608 x 3584 at 128 tokens 24.0, by items 25.1. Chunk by chunk an XCD would read one range
   // of k of all rows, and rows 16 KB apart then meet in few memory channels: 8192 x 8192 at 3 tokens 29.5 -> 32.7.
   // So deals_items deals the items; the grid is the same either way, and what it has too much ends at once.

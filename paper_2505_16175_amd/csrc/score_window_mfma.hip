@@ -55,9 +55,9 @@ static int win_chunk_keys(int n_g) {
 // PASS 2: scores[h][j] for the chunk's keys from the merged partials.
 // A group's key chunks decide which partials there are, and so the bits of its scores; how many of them a workgroup takes
 // does not. A workgroup is a chain of latencies (keys, window rows, in pass 2 the partials of all chunks of its rows), so it
-// takes 2 or 4 chunks, up to 256 keys, as long as that leaves one workgroup per CU. 16 groups of 2048 tokens, 7B heads, 64
-// window rows: pass 1 42.4 -> 25.0 us, pass 2 56.7 -> 27.0; 13 groups of 1152, 72B heads, 128 rows: the whole video 1204 ->
-// 1172, with two workgroups per CU left 1188.
+// takes 2 or 4 chunks, up to 256 keys, as long as that leaves one workgroup per CU. 16 groups of 1100 tokens, 7B heads, 64
+// window rows, both passes alone on the card (kernel trace): pass 1 28.8 -> 26.2 us, pass 2 37.7 -> 26.0; 13 groups of 1152,
+// 72B heads, 128 rows: the whole video 1204 -> 1172, with two workgroups per CU left 1188.
 struct WinChunks {
   int keys, n, per_wg;  // keys per chunk, chunks of the group, chunks per workgroup
 };
