@@ -42,7 +42,7 @@
 //     then formed again around the new max, of both blocks of a tile if it is the first. The row's first tile sets it. The
 //     range of bf16 and f32 would allow a reference far below the max, but the max itself is then rounded to bf16, where
 //     around itself it is an exact 1, and of a sharp row it is most of the sum: see MF_RESCALE.
-//   * The row sum of the bf16-rounded numerators is taken with shifts and adds (pack_pair).
+//   * The row sum of the bf16-rounded numerators is taken by four small products with ones (add_four).
 // 8192 tokens of the 7B heads over 24,576 entries, random (all-zero, which leaves the clock alone) inputs: 2945 us (2000);
 // one tile after the other with max, numerators and v_dot2 sum between the two products 3240 (2590); this pipeline with the
 // v_dot2 sum and all requests behind the barrier 3220 (2500). Products in fours per kind: alternating one by one costs 1 %.
@@ -68,7 +68,9 @@ typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8;
 typedef __attribute__((__vector_size__(4 * sizeof(__bf16)))) __bf16 bf16x4;
 typedef __attribute__((__vector_size__(2 * sizeof(__bf16)))) __bf16 bf16x2;
 typedef __attribute__((__vector_size__(16 * sizeof(float)))) float f32x16;
+typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4;
 typedef __attribute__((__vector_size__(4 * sizeof(short)))) short s16x4;
+typedef __attribute__((__vector_size__(8 * sizeof(short)))) short s16x8;
 typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) u32x4 lds_u32x4;
@@ -103,21 +105,23 @@ __device__ __forceinline__ void mask_block(f32x16& st, int lim) {
   for (int r = 0; r < 16; ++r) st[r] = 8 * (r >> 2) + (r & 3) > lim ? -INFINITY : st[r];
 }
 
-// Two numerators, rounded to bf16, as elements i and i + 1 of a P^T operand; their rounded values are added to s0 and s1.
-// The sum is taken with shifts and adds: v_dot2_f32_bf16 would do it in one instruction, but that runs on the matrix pipe
-// and holds it for 16 cycles.
-__device__ __forceinline__ void pack_pair(float e0, float e1, bf16x8& p, int i, float& s0, float& s1) {
-  bf16x2 pr;
-  pr[0] = (__bf16)e0;
-  pr[1] = (__bf16)e1;
-  unsigned u = __builtin_bit_cast(unsigned, pr);
-  asm("" : "+v"(u));  // one conversion for the operand and the sum
-  pr = __builtin_bit_cast(bf16x2, u);
-  p[i] = pr[0];
-  p[i + 1] = pr[1];
-  const float lo = __uint_as_float(u << 16), hi = __uint_as_float(u & 0xffff0000u);
-  s0 += lo;
-  s1 += hi;
+// Two numerators, rounded to bf16, as elements i and i + 1 of a P^T operand.
+__device__ __forceinline__ void pack_pair(float e0, float e1, bf16x8& p, int i) {
+  p[i] = (__bf16)e0;
+  p[i + 1] = (__bf16)e1;
+}
+// Adds four rounded numerators of this lane (elements 4 hi .. 4 hi + 3 of a P^T operand) to sum, in every element of it. Of
+// the 4x4x4 product's 16 independent blocks, lane l holds all four contraction elements of column l & 3 of block l >> 2 and
+// gets that column of the result: with ones as the other operand, its own sum. It takes the matrix pipe 8 cycles; shifts
+// and adds took 16 of the vector pipe for each pair of numerators, and 44 % of a step's vector instructions. At full
+// occupancy the kernel is bound by power, so instructions that are gone are time: 512 frames of 256 tokens through the 72B heads
+// 62150 -> 60920 us, 1024 of 128 through the 7B heads 22580 -> 22080, 256 of them 2348 -> 2294, 99 of 121 tokens over an 8-bit
+// cache 520 -> 503. (v_dot2_f32_bf16, two numerators each, holds the matrix pipe for 16 cycles.)
+__device__ __forceinline__ f32x4 add_four(const bf16x8& p, int hi, f32x4 sum) {
+  const s16x8 all = __builtin_bit_cast(s16x8, p);
+  const s16x4 part = hi ? __builtin_shufflevector(all, all, 4, 5, 6, 7) : __builtin_shufflevector(all, all, 0, 1, 2, 3);
+  const s16x4 ones = {0x3f80, 0x3f80, 0x3f80, 0x3f80};
+  return __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(ones, part, sum, 0, 0, 0);
 }
 
 struct Pieces {
@@ -360,13 +364,13 @@ __global__ __launch_bounds__(MF_NT, 2) void attend_mfma_kernel(AttendArgs a) {
     for (int n = 0; n < 4; ++n)
 #pragma unroll
       for (int r = 0; r < 16; ++r) o[n][r] *= alpha;
-    float ps0 = 0.f, ps1 = 0.f;
+    f32x4 ps = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int r = 0; r < 16; r += 2) {
-      pack_pair(__builtin_amdgcn_exp2f(fmaf(st[r], c2, nmc)), __builtin_amdgcn_exp2f(fmaf(st[r + 1], c2, nmc)), pf[r >> 3],
-                r & 7, ps0, ps1);
+      pack_pair(__builtin_amdgcn_exp2f(fmaf(st[r], c2, nmc)), __builtin_amdgcn_exp2f(fmaf(st[r + 1], c2, nmc)), pf[r >> 3], r & 7);
+      if (r & 2) ps = add_four(pf[r >> 3], (r >> 2) & 1, ps);
     }
-    psum = ps0 + ps1;
+    psum = ps[0];
   };
 
   bf16x8 kf[4], vf[4];  // fragments under way: three ahead of the products
@@ -380,14 +384,12 @@ __global__ __launch_bounds__(MF_NT, 2) void attend_mfma_kernel(AttendArgs a) {
                   unsigned turn_mask, bool cut, auto extra) {
     constexpr bool QK = decltype(qk)::value, SECOND = decltype(second)::value;
     constexpr int CUR = SECOND ? 32 * 256 : 0, NEXT = SECOND ? 0 : 32 * 256;
-    float ps0 = 0.f, ps1 = 0.f, e0 = 0.f, e1 = 0.f;
+    float e0 = 0.f, e1 = 0.f;
     f32x16 sn;
 #pragma unroll
     for (int r = 0; r < 16; ++r) sn[r] = 0.f;
     float t0 = fmaf(s_cur[0], c2, nmc), t1 = fmaf(s_cur[1], c2, nmc);
-    auto pack = [&](int s) {
-      pack_pair(e0, e1, p_cur[s >> 2], 2 * (s & 3), ps0, ps1);
-    };
+    auto pack = [&](int s) { pack_pair(e0, e1, p_cur[s >> 2], 2 * (s & 3)); };
     auto do_qk = [&](int s) {
       if (QK) {
         sn = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[s & 3], qf[s], sn, 0, 0, 0);
@@ -423,7 +425,13 @@ __global__ __launch_bounds__(MF_NT, 2) void attend_mfma_kernel(AttendArgs a) {
     }
     pack(7);
     if (QK) s_next = sn;
-    float psum = ps0 + ps1;
+    // behind the step's products: as soon as four were ready, the sums cost 0.3-1 % more
+    f32x4 ps0 = {0.f, 0.f, 0.f, 0.f}, ps1 = ps0;
+    ps0 = add_four(p_cur[0], 0, ps0);
+    ps1 = add_four(p_cur[0], 1, ps1);
+    ps0 = add_four(p_cur[1], 0, ps0);
+    ps1 = add_four(p_cur[1], 1, ps1);
+    float psum = ps0[0] + ps1[0];
     if (__any(psum > MF_RESCALE)) move_reference(s_cur, sn, QK && SECOND && !cut, p_cur, psum);
     l_run += psum;
   };
