@@ -10,18 +10,22 @@
 // Tiling. A workgroup of 8 wavefronts owns a 256 x 256 output tile and walks K in steps of 64. Both operand
 // tiles (256 rows x 128 bytes each) go global -> LDS with global_load_lds_dwordx4 into rings of buffers (two for
 // activations, three for weights), the next steps' tiles in flight while this step's are multiplied; one barrier per
-// step, placed before the step's last quarter of products so that the matrix pipe stays busy across it. Rows are
+// step, placed in the middle of the step's products so that the matrix pipe stays busy across it. Rows are
 // unpadded; the
 // 16-byte chunk c of row r sits at position c ^ ((r >> 1) & 7), which makes both the 1 KB stores of the loads
-// and the fragment reads (32 rows x 16 bytes per half wavefront) conflict-free.
-// Wavefront (wm, wn) of the 2 x 4 arrangement computes 128 tokens x 64 outputs as 4 x 2 blocks of
-// v_mfma_f32_32x32x16_bf16 with the WEIGHT rows as the A operand and the token rows as B, so that a lane ends
-// up with one token (m = lane & 31) and, per block, 16 outputs in runs of 4: the fused steps below
+// and the fragment reads (16 rows x 16 bytes per quarter wavefront) conflict-free.
+// Wavefront (wm, wn) of the 2 x 4 arrangement computes 128 tokens x 64 outputs as 8 x 4 blocks of
+// v_mfma_f32_16x16x32_bf16 with the WEIGHT rows as the A operand and the token rows as B, so that a lane ends
+// up with one token (m = lane & 15) and, per block, a run of 4 outputs: the fused steps below
 // only ever combine values of the same lane:
 //   * QKV_ROPE: the 256 tile columns are two heads; wavefront wn serves head wn >> 1 and, of its 128 dims, the
-//     32 dims [32 (wn & 1), +32) in block 0 and their rotary partners (+64) in block 1. The weight rows are
+//     32 dims [32 (wn & 1), +32) in blocks 0 and 1 and their rotary partners (+64) in blocks 2 and 3. The weight rows are
 //     fetched into LDS in that order (a permutation inside the tile, contiguous in runs of 32 rows).
-//   * SWIGLU: block 0 holds gate columns [n0/2 + 32 wn, +32), block 1 the up columns of the same outputs.
+//   * SWIGLU: blocks 0 and 1 hold gate columns [n0/2 + 32 wn, +32), blocks 2 and 3 the up columns of the same outputs.
+// The shape of the product: at full occupancy the chip is bound by power, and a product of 16 x 16 x 32 costs less of it than
+// half of one of 32 x 32 x 16, whose accumulators pass through the registers every 16 k instead of every 32. Register-only
+// loops on random operands reach 2.07-2.19 PFLOP/s with the former and 1.81 with the latter (2.44 both on zeros). Both add
+// k in runs of 8, one after the other, so the results are the same bits.
 // Workgroup ids are dealt round-robin over the 8 XCDs; the workgroups an XCD runs side by side cover a block of
 // token tiles x weight tiles, which bounds what its L2 has to fetch per k-step.
 #include <atomic>
@@ -33,7 +37,7 @@ namespace qp {
 
 typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8;
 typedef __attribute__((__vector_size__(4 * sizeof(__bf16)))) __bf16 bf16x4;
-typedef __attribute__((__vector_size__(16 * sizeof(float)))) float f32x16;
+typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4;
 
 constexpr int GM_BK = 64;   // k per ring slot
 constexpr int GM_BN = 256;  // weight rows per tile of the wide tilings
@@ -49,7 +53,7 @@ struct Tile {
   static constexpr int CPR = ROWB / 16;                     // 16-byte chunks per row
   static constexpr int RPI = 64 / CPR;                      // rows one load instruction covers
   static constexpr int RPL = 256 / ROWB;                    // rows per 256 bytes of LDS (one sweep of the banks)
-  static constexpr int KS = BK / 16;                        // k-steps of the MFMA per slot
+  static constexpr int KS = BK / 32;                        // k-steps of the MFMA per slot
   static constexpr int XT = BM * ROWB;                      // bytes of the activation tile
   static constexpr int WT = BN * ROWB;                      // ... of the weight tile
   static constexpr int XS = XS_, WS = WS_;
@@ -83,6 +87,14 @@ __device__ __forceinline__ void gm_dma16(const unsigned char* base, unsigned byt
 }
 #pragma clang diagnostic pop
 
+// acc += w x, in place. The builtin leaves it to the allocator where the sum goes, and that moved accumulators around and
+// spilled. What the compiler does not know of an instruction in inline assembly is how long its result takes: the accumulators
+// meet no other instruction from their clearing to the end of the products, and there the wait is spelled out (the fragments
+// come from LDS reads, whose counter the compiler minds as for any operand).
+__device__ __forceinline__ void gm_product(f32x4& acc, const u32x4& w, const u32x4& x) {
+  asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+v"(acc) : "v"(w), "v"(x));
+}
+
 template <int N>
 __device__ __forceinline__ void gm_wait_vmcnt() {
   asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
@@ -114,7 +126,7 @@ __device__ __forceinline__ void gemm_tile_product(const GemmArgs& a, const TileG
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int l32 = lane & 31, g = lane >> 5;
+  const int l16 = lane & 15, g = lane >> 4;
   const int wm = wave / T::WN, wn = wave % T::WN;
 
   // workgroup id -> (weight tile, token tile). Ids go round-robin over the 8 XCDs; each XCD takes an equal run of the
@@ -178,35 +190,41 @@ __device__ __forceinline__ void gemm_tile_product(const GemmArgs& a, const TileG
 #define GM_ISSUE_X(p_, step_, slot_) gm_dma16(x_base, x_off[p_] + (unsigned)(step_) * ROWB, x_lds + (slot_)*T::XT + 1024 * (p_));
 #define GM_ISSUE_W(p_, step_, slot_) gm_dma16(w_base, w_off[p_] + (unsigned)(step_) * ROWB, w_lds + (slot_)*T::WT + 1024 * (p_));
 
-  // fragment addresses inside a slot: row (l32 + 32 block), chunk 2 s + g of k-step s
+  // fragment addresses inside a slot: row (l16 + 16 block), chunk 4 s + g of k-step s
   int f_off[T::KS];
 #pragma unroll
-  for (int s = 0; s < T::KS; ++s) f_off[s] = l32 * ROWB + (((2 * s + g) ^ T::swizzle(l32)) << 4);
+  for (int s = 0; s < T::KS; ++s) f_off[s] = l16 * ROWB + (((4 * s + g) ^ T::swizzle(l16)) << 4);
   const int x_frag = wm * (32 * T::MI) * ROWB;
   const int w_frag = T::XS * T::XT + wn * 64 * ROWB;
 
-  f32x16 acc[2][T::MI];
+  constexpr int NJ = 4, NI = 2 * T::MI;  // 16 x 16 blocks per wavefront across the outputs / the tokens
+  f32x4 acc[NJ][NI];
 #pragma unroll
-  for (int j = 0; j < 2; ++j)
+  for (int j = 0; j < NJ; ++j)
 #pragma unroll
-    for (int i = 0; i < T::MI; ++i)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) acc[j][i][r] = 0.f;
+    for (int i = 0; i < NI; ++i) {
+      acc[j][i] = f32x4{0.f, 0.f, 0.f, 0.f};
+      asm volatile("" : "+v"(acc[j][i]));
+    }
 
   // Ring schedule. All slots are free at the start, so the first steps are requested at once. Inside the
-  // loop the barrier sits before the LAST k-step's products of a step: by then every wavefront has read all its
+  // loop the barrier sits between the two k-steps of a step: by then every wavefront has read all its
   // fragments of the step (its slots can be refilled), the next step's tiles have landed, and the wait at the
-  // barrier and the latency of the next step's first fragment reads run under those products.
-  // With equal rings of the smaller tilings all refill requests are issued there too. At 256 x 256 that is 64 of them per
-  // step within a quarter of its products: the address path takes 16 cycles for each, falls behind, and holds up the
-  // products behind the requests. So that tiling (rings of 2 and 3) spreads them: a step t issues, two per k-step and wavefront, the second
-  // half of X(t + 1), then W(t + 2) into the slot that step t - 1 left, then, behind the barrier, the first half of
-  // X(t + 2). PFLOP/s at 4096 x 59136 x 8192 / 4096 x 8192 x 29568 / 2048 x 37888 x 3584: 1.25 / 1.23 / 1.17 all behind
-  // the barrier (with or without the third weight slot), 1.35 / 1.31 / 1.25 spread. The 128 x 256 tiling (equal rings of 3)
+  // barrier and the latency of the next step's first fragment reads run under the second k-step's products.
+  // With equal rings of the smaller tilings all refill requests are issued there too. At 256 x 256 that is 64 of them, and
+  // the address path takes 16 cycles for each, falls behind, and holds up the
+  // products behind the requests. So that tiling (rings of 2 and 3) spreads them: a step t issues W(t + 2) in its first half,
+  // into the slot that step t - 1 left, and behind the barrier X(t + 2), which is awaited there a step later: half of it
+  // in the first half of step t + 1 left it half a step and cost 5-8 %. The 128 x 256 tiling (equal rings of 3)
   // spreads them too: a step t issues step t + 2 into the slot that step t - 1 left, a request behind every other product
   // before the barrier. us behind the barrier / spread: 2048 x 3584 x 18944 262 / 257, 300 x 37888 x 3584 112 / 105, 257
   // tokens of it 100 / 96, 300 x 59136 x 8192 365 / 340; in chunks 520 x 3584 x 18944 95 / 92, 900 tokens of it 139 / 132, 400
   // x 8192 x 29568 242 / 227, 1024 x 3584 x 18944 147 / 149, 300 x 4608 x 3584 27.9 / 28.4.
+  // PFLOP/s of products of 32 x 32 x 16 with the barrier behind three quarters of a step / of this loop, random inputs:
+  // 4096 x 59136 x 8192 1.38 / 1.46, 4096 x 8192 x 29568 1.36 / 1.48, 2048 x 37888 x 3584 1.24 / 1.33, 8192 x 8192 x 8192 1.35 /
+  // 1.47, 2048 x 3584 x 18944 1.22 / 1.25, 1024 x 8192 x 8192 1.19 / 1.29. On zeros, which leave the clock alone, 8192 x 8192 x
+  // 8192 runs at 1.80, and at 1.98 with the lines of later steps touched ahead of the requests, so that these find them in the
+  // L2; on random inputs that cost 1 %.
   // Requests complete in order: when step t + 1 is awaited at the end of step t, what may stay in flight is, with equal
   // rings, the XS - 2 steps after it, and with rings of 2 and 3 the weights of step t + 2.
   const int n_steps = min(a.steps_per_split, a.k / BK - step_begin);
@@ -224,71 +242,51 @@ __device__ __forceinline__ void gemm_tile_product(const GemmArgs& a, const TileG
   else if (n_steps >= 2) gm_wait_vmcnt<PW>();
   else gm_wait_vmcnt<0>();
   __syncthreads();
-  u32x4 wf[2][2], xf[2][T::MI];  // fragments of k-step s+1 are read while the products of k-step s run (two sets)
-#define GM_READ(xst_, wst_, s_, b_)                                                                            \
+  // Fragments: two sets of the weights', and of the activations' too where registers allow it; otherwise one, each refilled
+  // for the next k-step behind its last product (128 x 256: 2048 x 3584 x 18944 222 us with two sets, 227 with one; two sets
+  // for the last of the eight of 256 x 256, so that no read is issued right in front of the barrier, changed nothing).
+  constexpr int XSETS = NI > 4 ? 1 : 2;
+  u32x4 wf[2][NJ], xf[XSETS][NI];
+#define GM_READ_W(wst_, s_, j_) wf[s_][j_] = *(const u32x4*)((wst_) + w_frag + (j_) * 16 * ROWB + f_off[s_]);
+#define GM_READ_X(xst_, s_, i_) xf[(s_) % XSETS][i_] = *(const u32x4*)((xst_) + x_frag + (i_) * 16 * ROWB + f_off[s_]);
+  // behind product mf of a k-step: the fragments of the next one, k-step s_
+#define GM_READ_AHEAD(xst_, wst_, s_, mf_)                                                                     \
   {                                                                                                            \
-    _Pragma("unroll") for (int j = 0; j < 2; ++j) wf[b_][j] = *(const u32x4*)((wst_) + w_frag + j * 32 * ROWB + f_off[s_]); \
-    _Pragma("unroll") for (int i = 0; i < T::MI; ++i) xf[b_][i] = *(const u32x4*)((xst_) + x_frag + i * 32 * ROWB + f_off[s_]); \
+    if ((mf_) < NJ) GM_READ_W(wst_, s_, (mf_) < NJ ? (mf_) : 0)                                                \
+    if (XSETS == 1 ? (mf_) % NJ == NJ - 1 : (mf_) < NI) GM_READ_X(xst_, s_, XSETS == 1 ? (mf_) / NJ : (mf_) < NI ? (mf_) : 0)  \
   }
-#define GM_MFMA(b_)                                                                                            \
-  _Pragma("unroll") for (int i = 0; i < T::MI; ++i) _Pragma("unroll") for (int j = 0; j < 2; ++j) acc[j][i] =  \
-      __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, wf[b_][j]), __builtin_bit_cast(bf16x8, xf[b_][i]), acc[j][i], 0, 0, 0);
-  // one product / one fragment read, by index, so that the work after the barrier can be interleaved by hand
-#define GM_MFMA_ONE(b_, mf_)                                                                                   \
-  acc[(mf_) & 1][(mf_) >> 1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(                                        \
-      __builtin_bit_cast(bf16x8, wf[b_][(mf_) & 1]), __builtin_bit_cast(bf16x8, xf[b_][(mf_) >> 1]), acc[(mf_) & 1][(mf_) >> 1], 0, 0, 0);
-#define GM_READ_ONE(xst_, wst_, r_)                                                                            \
-  {                                                                                                            \
-    if ((r_) < 2) wf[0][(r_) < 2 ? (r_) : 0] = *(const u32x4*)((wst_) + w_frag + (r_) * 32 * ROWB + f_off[0]);  \
-    else xf[0][(r_) >= 2 ? (r_) - 2 : 0] = *(const u32x4*)((xst_) + x_frag + ((r_) - 2) * 32 * ROWB + f_off[0]); \
-  }
-  constexpr int NM = 2 * T::MI;                       // products per k-step
-  constexpr int PIECES = PW + 2 + T::MI;              // refill requests + first fragment reads of the next step
-  constexpr int PER = (PIECES + NM - 1) / NM;         // of them behind each product
-  GM_READ(smem, smem, 0, 0)
+  // one product of k-step s by index: NJ in a row share the activations' fragment
+#define GM_MFMA_ONE(s_, mf_)                                                                                   \
+  gm_product(acc[(mf_) % NJ][(mf_) / NJ], wf[s_][(mf_) % NJ], xf[(s_) % XSETS][(mf_) / NJ]);
+  constexpr int NM = NJ * NI;              // products per k-step
+  constexpr int PER = (PW + NM - 1) / NM;  // refill requests behind each
+#pragma unroll
+  for (int j = 0; j < NJ; ++j) GM_READ_W(smem, 0, j)
+#pragma unroll
+  for (int i = 0; i < NI; ++i) GM_READ_X(smem, 0, i)
   int xslot = 0, wslot = 0;
   constexpr bool SPREAD = XS == WS && T::MI == 2 && T::BN == 256;
-  static_assert(!SPREAD || PW <= (T::KS - 1) * NM / 2, "a request behind every other product");
-  static_assert(XS == WS || (T::XQ == 4 && T::WQ == 4 && T::MI == 4 && T::KS == 4), "spread of the requests");
-  // One step that has a successor; refill_x / refill_w: there is a step left to request into the freed slots, refill_x0:
-  // the second half of the next step's activations is still to be requested (rings of 2 and 3).
-  auto step_and_next = [&](int step, bool refill_x0, bool refill_x, bool refill_w, auto wait) {
+  static_assert(T::KS == 2, "two k-steps of the products per slot");
+  static_assert(!SPREAD || PW <= NM / 2, "a request behind every other product");
+  static_assert(XS == WS || (T::XQ == 4 && T::WQ == 4 && T::MI == 4), "spread of the requests");
+  // One step that has a successor; refill_x / refill_w: there is a step left to request into the freed slots.
+  auto step_and_next = [&](int step, bool refill_x, bool refill_w, auto wait) {
     const unsigned char *xst = smem + xslot * T::XT, *wst = smem + wslot * T::WT;
+    const int wfree = wslot == 0 ? WS - 1 : wslot - 1;  // the slot that the step before left
+    const int free = xslot == 0 ? XS - 1 : xslot - 1;
 #pragma unroll
-    for (int s = 0; s < T::KS - 1; ++s) {
-      GM_READ(xst, wst, s + 1, (s + 1) & 1)
+    for (int mf = 0; mf < NM; ++mf) {
+      GM_MFMA_ONE(0, mf)
+      GM_READ_AHEAD(xst, wst, 1, mf)
       __builtin_amdgcn_sched_barrier(0);
       if (XS != WS) {
-        const int wfree = wslot == 0 ? WS - 1 : wslot - 1;  // the slot that the step before left
-#pragma unroll
-        for (int mf = 0; mf < NM; ++mf) {
-          GM_MFMA_ONE(s & 1, mf)
-          __builtin_amdgcn_sched_barrier(0);
-          if ((mf & 3) == 1) {  // NM = 8: two requests per k-step
-            const int q = 2 * s + (mf >> 2);
-            if (q < T::XQ / 2) {
-              if (refill_x0) GM_ISSUE_X(T::XQ / 2 + q, step + 1, xslot ^ 1)
-            } else if (refill_w) {
-              GM_ISSUE_W(q - T::XQ / 2, step + 2, wfree)
-            }
-          }
-          __builtin_amdgcn_sched_barrier(0);
-        }
+        if (mf % 8 == 4 && refill_w) GM_ISSUE_W(mf / 8, step + 2, wfree)
       } else if (SPREAD) {
-        const int free = xslot == 0 ? XS - 1 : xslot - 1;  // the slot that the step before left
-#pragma unroll
-        for (int mf = 0; mf < NM; ++mf) {
-          GM_MFMA_ONE(s & 1, mf)
-          __builtin_amdgcn_sched_barrier(0);
-          const int at = s * NM + mf, q = at / 2;
-          if ((at & 1) && q < PW && refill_w) {
-            if (q < T::XQ) GM_ISSUE_X(q, step + XS - 1, free)
-            else GM_ISSUE_W(q - T::XQ, step + XS - 1, free)
-          }
-          __builtin_amdgcn_sched_barrier(0);
+        const int q = mf / 2;
+        if ((mf & 1) && q < PW && refill_w) {
+          if (q < T::XQ) GM_ISSUE_X(q, step + XS - 1, free)
+          else GM_ISSUE_W(q - T::XQ, step + XS - 1, free)
         }
-      } else {
-        GM_MFMA(s & 1)
       }
       __builtin_amdgcn_sched_barrier(0);
     }
@@ -299,16 +297,19 @@ __device__ __forceinline__ void gemm_tile_product(const GemmArgs& a, const TileG
 #pragma unroll
     for (int mf = 0; mf < NM; ++mf) {
       GM_MFMA_ONE(1, mf)
+      GM_READ_AHEAD(xst_next, wst_next, 0, mf)
       __builtin_amdgcn_sched_barrier(0);
+      if (XS != WS) {
+        if (mf % 4 == 2 && mf / 4 < T::XQ && refill_x) GM_ISSUE_X(mf / 4, step + XS, xslot)
+      } else if (!SPREAD) {
 #pragma unroll
-      for (int u = 0; u < PER; ++u) {
-        const int p = mf * PER + u;
-        if (p < T::XQ) {
-          if (!SPREAD && refill_x && (XS == WS || p < T::XQ / 2)) GM_ISSUE_X(p, step + XS, xslot)
-        } else if (p < PW) {
-          if (!SPREAD && refill_w && XS == WS) GM_ISSUE_W(p - T::XQ, step + WS, wslot)
-        } else if (p < PIECES) {
-          GM_READ_ONE(xst_next, wst_next, p - PW)
+        for (int u = 0; u < PER; ++u) {
+          const int p = mf * PER + u;
+          if (p < T::XQ) {
+            if (refill_x) GM_ISSUE_X(p, step + XS, xslot)
+          } else if (p < PW) {
+            if (refill_w) GM_ISSUE_W(p - T::XQ, step + WS, wslot)
+          }
         }
       }
       __builtin_amdgcn_sched_barrier(0);
@@ -317,67 +318,68 @@ __device__ __forceinline__ void gemm_tile_product(const GemmArgs& a, const TileG
   };
   int step = 0;
   for (; step + XS < n_steps; ++step)
-    step_and_next(step, step > 0, true, !SPREAD || step > 0, [] { gm_wait_vmcnt<XS != WS ? T::WQ : (XS - 2) * PW>(); });
+    step_and_next(step, true, !SPREAD || step > 0, [] { gm_wait_vmcnt<XS != WS ? T::WQ : (XS - 2) * PW>(); });
   for (; step + 1 < n_steps; ++step)
-    step_and_next(step, step > 0 && step + 1 < n_steps, false, SPREAD && step > 0 && step + XS - 1 < n_steps, [&] {
+    step_and_next(step, false, SPREAD && step > 0 && step + XS - 1 < n_steps, [&] {
       if (XS == WS && XS >= 3 && step + 2 < n_steps) gm_wait_vmcnt<PW>();
       else gm_wait_vmcnt<0>();
     });
   {  // last step: nothing left to request or to wait for
     const unsigned char *xst = smem + xslot * T::XT, *wst = smem + wslot * T::WT;
 #pragma unroll
-    for (int s = 0; s < T::KS - 1; ++s) {
-      GM_READ(xst, wst, s + 1, (s + 1) & 1)
-      __builtin_amdgcn_sched_barrier(0);
-      GM_MFMA(s & 1)
+    for (int mf = 0; mf < NM; ++mf) {
+      GM_MFMA_ONE(0, mf)
+      GM_READ_AHEAD(xst, wst, 1, mf)
       __builtin_amdgcn_sched_barrier(0);
     }
-    GM_MFMA(1)
+#pragma unroll
+    for (int mf = 0; mf < NM; ++mf) GM_MFMA_ONE(1, mf)
   }
 #undef GM_MFMA_ONE
-#undef GM_READ_ONE
+#undef GM_READ_AHEAD
+#undef GM_READ_W
+#undef GM_READ_X
 #undef GM_ISSUE_X
 #undef GM_ISSUE_W
-#undef GM_READ
-#undef GM_MFMA
 
-  // ---- store: lane owns token m = m0 + (BM/2) wm + 32 i + l32 and, in block j, outputs 8 (r >> 2) + 4 g + (r & 3)
+  __builtin_amdgcn_sched_barrier(0);
+  asm volatile("s_nop 15\n\ts_nop 7");  // the last products' results
+  __builtin_amdgcn_sched_barrier(0);
+  // ---- store: lane owns token m = m0 + (32 MI) wm + 16 i + l16 and, in block j, outputs 4 g + 0..3
   const int u64 = (n0 >> 6) + wn;  // QKV_ROPE: which run of 64 outputs (half a head's rotary pairs) this wavefront has
+  const int mw = m0 + wm * (32 * T::MI);  // this wavefront's first token
   if (a.split_k > 1) {
     // partial sums of this k chunk, f32 [chunk][m][n] with n the output's logical column (for QKV: head * 128 + dim);
     // gemm_reduce_kernel adds the chunks in order and applies the mode's store
     float* part = a.partial + (size_t)chunk * a.m * a.n;
 #pragma unroll
-    for (int j = 0; j < 2; ++j)
+    for (int j = 0; j < NJ; ++j) {
+      int n;
+      if (MODE == GEMM_QKV_ROPE) n = (u64 >> 1) * 128 + (u64 & 1) * 32 + (j >> 1) * 64 + 16 * (j & 1) + 4 * g;
+      else n = n0 + wn * 64 + j * 16 + 4 * g;
+      if (n >= a.n) continue;
 #pragma unroll
-      for (int q4 = 0; q4 < 4; ++q4) {
-        int n;
-        if (MODE == GEMM_QKV_ROPE) n = (u64 >> 1) * 128 + (u64 & 1) * 32 + j * 64 + 8 * q4 + 4 * g;
-        else n = n0 + wn * 64 + j * 32 + 8 * q4 + 4 * g;
-        if (n >= a.n) continue;
-#pragma unroll
-        for (int i = 0; i < T::MI; ++i) {
-          const int m = m0 + wm * (32 * T::MI) + i * 32 + l32;
-          if (m >= a.m) continue;
-          *(float4*)(part + (size_t)m * a.n + n) =
-              make_float4(acc[j][i][4 * q4], acc[j][i][4 * q4 + 1], acc[j][i][4 * q4 + 2], acc[j][i][4 * q4 + 3]);
-        }
+      for (int i = 0; i < NI; ++i) {
+        const int m = mw + i * 16 + l16;
+        if (m >= a.m) continue;
+        *(float4*)(part + (size_t)m * a.n + n) = make_float4(acc[j][i][0], acc[j][i][1], acc[j][i][2], acc[j][i][3]);
       }
+    }
     return;
   }
   if (MODE == GEMM_SWIGLU) {  // half as many outputs: 64-byte runs of rows staged as below gained nothing (7.5 us per tile)
     bf16_t* out = (bf16_t*)a.out;
 #pragma unroll
-    for (int q4 = 0; q4 < 4; ++q4) {
-      const int n = (n0 >> 1) + wn * 32 + 8 * q4 + 4 * g;
+    for (int j = 0; j < NJ / 2; ++j) {
+      const int n = (n0 >> 1) + wn * 32 + 16 * j + 4 * g;
 #pragma unroll
-      for (int i = 0; i < T::MI; ++i) {
-        const int m = m0 + wm * (32 * T::MI) + i * 32 + l32;
+      for (int i = 0; i < NI; ++i) {
+        const int m = mw + i * 16 + l16;
         if (m >= a.m) continue;
         bf16x4 pk;
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-          const float gate = acc[0][i][4 * q4 + e], up = acc[1][i][4 * q4 + e];
+          const float gate = acc[j][i][e], up = acc[j + 2][i][e];
           pk[e] = (__bf16)(gate / (1.f + __expf(-gate)) * up);
         }
         *(uint2*)(out + (size_t)m * d_ff + n) = __builtin_bit_cast(uint2, pk);
@@ -403,12 +405,14 @@ __device__ __forceinline__ void gemm_tile_product(const GemmArgs& a, const TileG
   static_assert(T::NW * SREG <= T::LDS, "staging fits the rings");
   unsigned char* const stage = smem + wave * SREG;
   auto swizzled = [](int r, int c) { return c ^ (SC == 8 ? r & 7 : (r >> 2) & 3); };
-  // this lane's run of 4 outputs at chunk c (half g) of its token in block `blk`
-  auto staged = [&](int blk, int c) { return (uint2*)(stage + blk * SBLK + l32 * SROW + swizzled(l32, c) * 16 + g * 8); };
+  // this lane's run of 4 outputs in block j16 of 16 (chunk 2 j16 + g / 2, half g & 1) of its token of block i in region `blk`
+  auto staged = [&](int blk, int i, int j16) {
+    const int r = 16 * (i & 1) + l16;
+    return (uint2*)(stage + blk * SBLK + r * SROW + swizzled(r, 2 * j16 + (g >> 1)) * 16 + (g & 1) * 8);
+  };
   auto settle = [] { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); };  // the wavefront's writes before its reads
   const int s_row = lane / SC, s_chunk = lane % SC;  // where this lane reads and stores
   auto chunk_of = [&](int blk, int r) { return *(const u32x4*)(stage + blk * SBLK + r * SROW + swizzled(r, s_chunk) * 16); };
-  const int mw = m0 + wm * (32 * T::MI);  // this wavefront's first token
   if (MODE == GEMM_PLAIN) {
     const bf16_t* bias = (const bf16_t*)a.bias;
     bf16_t* out = (bf16_t*)a.out;
@@ -431,26 +435,24 @@ __device__ __forceinline__ void gemm_tile_product(const GemmArgs& a, const TileG
       settle();
     }
 #pragma unroll
-    for (int i = 0; i < T::MI; ++i)
+    for (int i = 0; i < NI; ++i)
 #pragma unroll
-      for (int j = 0; j < 2; ++j)
-#pragma unroll
-        for (int q4 = 0; q4 < 4; ++q4) {
-          float b[4] = {0.f, 0.f, 0.f, 0.f}, r[4] = {0.f, 0.f, 0.f, 0.f};
-          if (bias != nullptr) {
-            const uint2 raw = *(const uint2*)(bias + min(nw0 + j * 32 + 8 * q4 + 4 * g, a.n - 4));
-            b[0] = bf16lo_to_f32(raw.x), b[1] = bf16hi_to_f32(raw.x), b[2] = bf16lo_to_f32(raw.y), b[3] = bf16hi_to_f32(raw.y);
-          }
-          uint2* const at = staged(i, 4 * j + q4);
-          if (has_res) {
-            const uint2 raw = *at;
-            r[0] = bf16lo_to_f32(raw.x), r[1] = bf16hi_to_f32(raw.x), r[2] = bf16lo_to_f32(raw.y), r[3] = bf16hi_to_f32(raw.y);
-          }
-          bf16x4 pk;
-#pragma unroll
-          for (int e = 0; e < 4; ++e) pk[e] = (__bf16)((acc[j][i][4 * q4 + e] + b[e]) + r[e]);
-          *at = __builtin_bit_cast(uint2, pk);
+      for (int j = 0; j < NJ; ++j) {
+        float b[4] = {0.f, 0.f, 0.f, 0.f}, r[4] = {0.f, 0.f, 0.f, 0.f};
+        if (bias != nullptr) {
+          const uint2 raw = *(const uint2*)(bias + min(nw0 + j * 16 + 4 * g, a.n - 4));
+          b[0] = bf16lo_to_f32(raw.x), b[1] = bf16hi_to_f32(raw.x), b[2] = bf16lo_to_f32(raw.y), b[3] = bf16hi_to_f32(raw.y);
         }
+        uint2* const at = staged(i >> 1, i, j);
+        if (has_res) {
+          const uint2 raw = *at;
+          r[0] = bf16lo_to_f32(raw.x), r[1] = bf16hi_to_f32(raw.x), r[2] = bf16lo_to_f32(raw.y), r[3] = bf16hi_to_f32(raw.y);
+        }
+        bf16x4 pk;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) pk[e] = (__bf16)((acc[j][i][e] + b[e]) + r[e]);
+        *at = __builtin_bit_cast(uint2, pk);
+      }
     settle();
 #pragma unroll
     for (int i = 0; i < T::MI; ++i)
@@ -471,13 +473,13 @@ __device__ __forceinline__ void gemm_tile_product(const GemmArgs& a, const TileG
     else if (head < a.h_q + a.h_kv) dst = (bf16_t*)a.k_out, heads_dst = a.h_kv, head_dst = head - a.h_q;
     else dst = (bf16_t*)a.v_out, heads_dst = a.h_kv, head_dst = head - a.h_q - a.h_kv, rotate = false;
 #pragma unroll
-    for (int q4 = 0; q4 < 4; ++q4) {
-      const int f = dim0 + 8 * q4 + 4 * g;  // rotary frequency index of the run's first element
-      float4 cs0[T::MI], cs1[T::MI];
+    for (int j = 0; j < NJ / 2; ++j) {
+      const int f = dim0 + 16 * j + 4 * g;  // rotary frequency index of the run's first element
+      float4 cs0[NI], cs1[NI];
       if (rotate) {
 #pragma unroll
-        for (int i = 0; i < T::MI; ++i) {
-          const float* cs = a.cos_sin + ((size_t)min(mw + i * 32 + l32, a.m - 1) * 64 + f) * 2;
+        for (int i = 0; i < NI; ++i) {
+          const float* cs = a.cos_sin + ((size_t)min(mw + i * 16 + l16, a.m - 1) * 64 + f) * 2;
           cs0[i] = *(const float4*)cs, cs1[i] = *(const float4*)(cs + 4);
         }
       }
@@ -488,10 +490,10 @@ __device__ __forceinline__ void gemm_tile_product(const GemmArgs& a, const TileG
         b1[0] = bf16lo_to_f32(r1.x), b1[1] = bf16hi_to_f32(r1.x), b1[2] = bf16lo_to_f32(r1.y), b1[3] = bf16hi_to_f32(r1.y);
       }
 #pragma unroll
-      for (int i = 0; i < T::MI; ++i) {
+      for (int i = 0; i < NI; ++i) {
         float lo[4], hi[4];
 #pragma unroll
-        for (int e = 0; e < 4; ++e) lo[e] = acc[0][i][4 * q4 + e] + b0[e], hi[e] = acc[1][i][4 * q4 + e] + b1[e];
+        for (int e = 0; e < 4; ++e) lo[e] = acc[j][i][e] + b0[e], hi[e] = acc[j + 2][i][e] + b1[e];
         if (rotate) {
           const float c[4] = {cs0[i].x, cs0[i].z, cs1[i].x, cs1[i].z}, s[4] = {cs0[i].y, cs0[i].w, cs1[i].y, cs1[i].w};
 #pragma unroll
@@ -500,8 +502,8 @@ __device__ __forceinline__ void gemm_tile_product(const GemmArgs& a, const TileG
         bf16x4 p0, p1;
 #pragma unroll
         for (int e = 0; e < 4; ++e) p0[e] = (__bf16)lo[e], p1[e] = (__bf16)hi[e];
-        *staged(2 * i, q4) = __builtin_bit_cast(uint2, p0);
-        *staged(2 * i + 1, q4) = __builtin_bit_cast(uint2, p1);
+        *staged(2 * (i >> 1), i, j) = __builtin_bit_cast(uint2, p0);
+        *staged(2 * (i >> 1) + 1, i, j) = __builtin_bit_cast(uint2, p1);
       }
     }
     settle();
