@@ -255,9 +255,12 @@ __device__ __forceinline__ void gemm_tile_product(const GemmArgs& a, const TileG
     if ((mf_) < NJ) GM_READ_W(wst_, s_, (mf_) < NJ ? (mf_) : 0)                                                \
     if (XSETS == 1 ? (mf_) % NJ == NJ - 1 : (mf_) < NI) GM_READ_X(xst_, s_, XSETS == 1 ? (mf_) / NJ : (mf_) < NI ? (mf_) : 0)  \
   }
-  // one product of k-step s by index: NJ in a row share the activations' fragment
+  // One product of k-step s by index: NJ in a row share the activations' fragment, and the last of them and the next one the
+  // weights', back and forth: every operand that stays saves power (4096 x 59136 x 8192 2655 -> 2630 us, 2048 x 37888 x 3584
+  // 409 -> 406, 2048 x 3584 x 18944 212 -> 210).
+#define GM_J(mf_) ((((mf_) / NJ) & 1) ? NJ - 1 - (mf_) % NJ : (mf_) % NJ)
 #define GM_MFMA_ONE(s_, mf_)                                                                                   \
-  gm_product(acc[(mf_) % NJ][(mf_) / NJ], wf[s_][(mf_) % NJ], xf[(s_) % XSETS][(mf_) / NJ]);
+  gm_product(acc[GM_J(mf_)][(mf_) / NJ], wf[s_][GM_J(mf_)], xf[(s_) % XSETS][(mf_) / NJ]);
   constexpr int NM = NJ * NI;              // products per k-step
   constexpr int PER = (PW + NM - 1) / NM;  // refill requests behind each
 #pragma unroll
@@ -336,6 +339,7 @@ __device__ __forceinline__ void gemm_tile_product(const GemmArgs& a, const TileG
     for (int mf = 0; mf < NM; ++mf) GM_MFMA_ONE(1, mf)
   }
 #undef GM_MFMA_ONE
+#undef GM_J
 #undef GM_READ_AHEAD
 #undef GM_READ_W
 #undef GM_READ_X
