@@ -99,6 +99,38 @@ def test_group_attend_key_split_matches_oracle(h_q, h_kv, n_g, c):
 
 
 @pytest.mark.gpu
+@pytest.mark.parametrize("h_q,h_kv,n_g,c,chunks", [
+    (28, 4, 64, 20480, 32),    # two row blocks, the second half full; chunks of 10 tiles: both of a chunk on one XCD
+    (28, 4, 40, 20700, 30),    # 24 rows in the second block, a cut-off cache tile
+    (28, 4, 73, 41000, 31),    # an odd number of chunks: dealt one by one
+    (28, 4, 64, 18000, 32),    # chunks of 9 tiles: dealt one by one
+    (16, 2, 40, 61440, 64),    # four XCDs per KV head
+])
+def test_group_attend_two_row_blocks_of_a_chunk_on_one_xcd(h_q, h_kv, n_g, c, chunks):
+    """Every (row block, key chunk) is served exactly once on either side of the rule that deals them to the XCDs."""
+    print(f"case heads={h_q}/{h_kv} n_g={n_g} c={c}", flush=True)
+    d = 128
+    g = torch.Generator().manual_seed(n_g + c + h_q)
+    mk = lambda *s: torch.randn(*s, generator=g).to(torch.bfloat16)
+    q, k, v = mk(n_g, h_q, d), mk(n_g, h_kv, d), mk(n_g, h_kv, d)
+    ck, cv = mk(h_kv, c, d), mk(h_kv, c, d)
+    want, want_lse = O.attend_group(_f64(q), _f64(k), _f64(v), _f64(ck), _f64(cv), return_lse=True)
+    layout = B.make_layout(h_q, h_kv, d, "bf16")
+    cache = B.Cache(layout, c)
+    cache.k.copy_(ck)
+    cache.v.copy_(cv)
+    cache.c.len = c
+    ws = B.make_workspace(layout, n_g, 0)
+    assert B.attend_plan(layout, n_g, c, ws.numel())["key_chunks"] == chunks
+    out = torch.full((n_g, h_q, d), float("nan"), dtype=torch.bfloat16, device=DEV)
+    lse = torch.full((h_q, n_g), float("nan"), dtype=torch.float32, device=DEV)
+    B.group_attend(layout, q.to(DEV), k.to(DEV), v.to(DEV), cache, out, lse, ws)
+    torch.cuda.synchronize()
+    assert_attn_close(_f64(out), want, "bf16", "split")
+    np.testing.assert_allclose(_f64(lse), want_lse, rtol=2e-5, atol=2e-3)
+
+
+@pytest.mark.gpu
 @pytest.mark.parametrize("h_q,h_kv,n_g,c,fp8", [(28, 4, 2400, 2100, False), (64, 8, 1100, 2100, False),
                                                 (16, 16, 4400, 2100, False), (28, 4, 8192, 24000, False),
                                                 (28, 4, 4096, 24000, False), (28, 4, 2400, 2100, True),
