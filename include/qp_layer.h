@@ -100,7 +100,7 @@ qp_status qp_select_linear_tile(int32_t token_rows);
  * qp_select_linear_tile keeps such calls on the tiled kernel. */
 typedef struct {
   int32_t token_rows_per_tile; /* 128 or 256 (also where tiles of 128 rows follow whole rounds of those); 1 or 2 for the
-                                  weight-streaming kernel. A split call of at most 64 tokens on 64-wide tiles leaves out
+                                  weight-streaming kernel. A split call of at most 64 tokens on tiles of 64 or 128 outputs leaves out
                                   the upper 64 rows of its one tile */
   int32_t workgroups;
   int32_t k_chunks;

@@ -28,6 +28,7 @@
 // k in runs of 8, one after the other, so the results are the same bits.
 // Workgroup ids are dealt round-robin over the 8 XCDs; the workgroups an XCD runs side by side cover a block of
 // token tiles x weight tiles, which bounds what its L2 has to fetch per k-step.
+#include <algorithm>
 #include <atomic>
 
 #include "append.h"
@@ -71,6 +72,9 @@ typedef Tile<128, 256, 2, 3> Tile128;
 typedef Tile<128, 128, 1, 3> Mid;
 typedef Tile<128, 64, 2, 3> Narrow128;    // 2 wavefronts, two workgroups per CU
 typedef Tile<64, 64, 1, 3> Narrow64;      // ... three
+typedef Tile<64, 64, 1, 5> Deep64;        // two
+typedef Tile<64, 128, 1, 3> Mid64;        // 4 wavefronts, two workgroups per CU
+typedef Tile<64, 256, 1, 4> Wide64;       // 8 wavefronts, all of a CU's LDS
 
 // 64 lanes x 16 bytes global -> LDS at the wave-uniform LDS byte address lds_addr (lane L lands at lds_addr + 16 L);
 // m0 is clobbered on purpose (see lds_dma16)
@@ -111,7 +115,7 @@ __device__ __forceinline__ int weight_row(int j, int n0, int d_ff) {
   return n0 + j;
 }
 
-// Whether a split contraction on 256-wide tiles deals its tiles' chunks to the XCDs instead of its tiles (see launch_tile).
+// Whether a split contraction on tiles of 128 or 256 outputs deals its tiles' chunks to the XCDs instead of its tiles (see launch_tile).
 __device__ __forceinline__ bool deals_items(int split_k, int tiles) { return split_k > 1 && tiles % 8 != 0; }
 
 // A grid of tiles of one kind: block `block` of `blocks` (a multiple of 8) per k chunk, over outputs n_first and up.
@@ -137,7 +141,7 @@ __device__ __forceinline__ void gemm_tile_product(const GemmArgs& a, const TileG
   // A split contraction has a grid row per k chunk, and its tiles are dealt row by row, or (deals_items) the chunks of its
   // tiles, tile by tile, over the whole grid.
   const int tiles = grid.tiles_m * grid.tiles_n;
-  const bool by_item = T::BN == GM_BN && deals_items(a.split_k, tiles);
+  const bool by_item = T::BN >= 128 && deals_items(a.split_k, tiles);
   const int block = by_item ? blockIdx.y * grid.blocks + grid.block : grid.block;
   const int items = by_item ? tiles * a.split_k : tiles, per_xcd = (items + 7) >> 3;
   int id = (block & 7) * per_xcd + (block >> 3), chunk = blockIdx.y;
@@ -238,7 +242,8 @@ __device__ __forceinline__ void gemm_tile_product(const GemmArgs& a, const TileG
       for (int q = 0; q < T::WQ; ++q) GM_ISSUE_W(q, p, p)
     }
   // the first step's tiles have landed: all but the later requests are complete
-  if (XS >= 3 && n_steps >= 3) gm_wait_vmcnt<2 * PW>();
+  if (XS > 3 && n_steps >= XS) gm_wait_vmcnt<(XS - 1) * PW>();
+  else if (XS >= 3 && n_steps >= 3) gm_wait_vmcnt<2 * PW>();
   else if (n_steps >= 2) gm_wait_vmcnt<PW>();
   else gm_wait_vmcnt<0>();
   __syncthreads();
@@ -269,6 +274,7 @@ __device__ __forceinline__ void gemm_tile_product(const GemmArgs& a, const TileG
   for (int i = 0; i < NI; ++i) GM_READ_X(smem, 0, i)
   int xslot = 0, wslot = 0;
   constexpr bool SPREAD = XS == WS && T::MI == 2 && T::BN == 256;
+  static_assert(XS <= 5 && (XS - 1) * PW <= 63, "the waits spelled out, and what vmcnt counts");
   static_assert(T::KS == 2, "two k-steps of the products per slot");
   static_assert(!SPREAD || PW <= NM / 2, "a request behind every other product");
   static_assert(XS == WS || (T::XQ == 4 && T::WQ == 4 && T::MI == 4), "spread of the requests");
@@ -324,7 +330,9 @@ __device__ __forceinline__ void gemm_tile_product(const GemmArgs& a, const TileG
     step_and_next(step, true, !SPREAD || step > 0, [] { gm_wait_vmcnt<XS != WS ? T::WQ : (XS - 2) * PW>(); });
   for (; step + 1 < n_steps; ++step)
     step_and_next(step, false, SPREAD && step > 0 && step + XS - 1 < n_steps, [&] {
-      if (XS == WS && XS >= 3 && step + 2 < n_steps) gm_wait_vmcnt<PW>();
+      if (XS == WS && XS >= 5 && step + 4 < n_steps) gm_wait_vmcnt<3 * PW>();
+      else if (XS == WS && XS >= 4 && step + 3 < n_steps) gm_wait_vmcnt<2 * PW>();
+      else if (XS == WS && XS >= 3 && step + 2 < n_steps) gm_wait_vmcnt<PW>();
       else gm_wait_vmcnt<0>();
     });
   {  // last step: nothing left to request or to wait for
@@ -794,7 +802,19 @@ int gemm_tile_blocks(const GemmArgs& a) {
 // is a tenth below the unsplit one: long contractions whose tiles leave CUs idle or are small ones. us unsplit / split:
 // 3584 x 18944 at 520 tokens 134 / 92, 640 166 / 105, 768 166 / 110, 900 146 / 132, 1024 169 / 149, 1100 163 / 149; 8192 x
 // 29568 at 400 278 / 227, 512 287 / 253. At k = 3584 (o_proj) there is nothing to gain.
+//
+// Of these products of few outputs, long contractions take tiles of 128 outputs instead (64 or 128 token rows), one workgroup
+// per CU, dealt to the XCDs by items as the 256-wide ones are: an activation fragment read meets twice the outputs and a
+// request brings twice the weights, and a chunk of a long contraction still has the steps to hide its start. us 64 outputs /
+// 128, weights from HBM: 3584 x 18944 at 16 tokens 28.8 / 28.1, 64 35.7 / 31.1, 100 42.5 / 35.1, 128 46.3 / 37.8, 200 61.0 /
+// 50.2, 250 70.8 / 55.7; 5120 x 13824 at 64 and 128 44.0 / 32.7 and 58.7 / 38.6; 3584 x 5120 at 64 and 128 16.0 / 15.1 and 21.6 /
+// 19.5. They need at least 5/8 of the CUs: 2560 outputs at 64 tokens, 160 workgroups, 16.9 / 15.8; 2048, 128 of them, 14.2 / 15.7.
+// With shorter contractions 64 outputs stay: at k = 3584 8 chunks of 28 tiles of 128 take 13.5 and of 56 tiles of 64 13.5-13.8.
+// There, up to 64 tokens, half as many chunks fill the chip if 4 of them make 7/8 to all of a workgroup per CU, with a ring of
+// 5 slots in the room of the second one, and leave half the partial sums: 3584 x 3584 at 64 and 16 tokens 13.8 / 12.2 and 11.5 /
+// 10.1 (with 3 slots no gain). 4 chunks of fewer tiles lose (2048 x 8192, 128 workgroups, 14.2 / 16.9).
 constexpr int NARROW_ABOVE = 8;
+constexpr int MID_STEPS = 80;  // k-steps from which a contraction is long
 GemmSplit gemm_plan_split(const GemmArgs& a, int mode, size_t scratch_bytes) {
   GemmSplit p{1, a.k / GM_BK, 0, 0, 0};
   if (mode == GEMM_SWIGLU || scratch_bytes == 0 || gemm_uses_gemv(a)) return p;
@@ -824,10 +844,19 @@ GemmSplit gemm_plan_split(const GemmArgs& a, int mode, size_t scratch_bytes) {
   if (want > cus / tiles) want = cus / tiles;
   const size_t per_chunk = (size_t)a.m * a.n * sizeof(float);
   if (few_outputs && rows == 128 && g_forced_tile_rows.load(std::memory_order_relaxed) == 0) {
-    const long narrow = tiles_m * ((a.n + Narrow64::BN - 1) / Narrow64::BN);
-    want = NARROW_ABOVE;
-    while (want > 1 && narrow * want > 2 * cus + cus / 4) want /= 2;  // a quarter of a chip above: 72 tiles x 8 measured better than x 4
-    p.narrow = 1;
+    const long mid = tiles_m * ((a.n + Mid::BN - 1) / Mid::BN);
+    long mid_want = std::min<long>(NARROW_ABOVE, cus / mid);
+    if ((size_t)mid_want * per_chunk > scratch_bytes) mid_want = (long)(scratch_bytes / per_chunk);
+    if (steps >= MID_STEPS && mid_want >= 2 && mid * mid_want * 8 >= (long)cus * 5) {
+      want = mid_want;
+      p.narrow = Mid::BN;
+    } else {
+      const long narrow = tiles_m * ((a.n + Narrow64::BN - 1) / Narrow64::BN);
+      want = NARROW_ABOVE;
+      while (want > 1 && narrow * want > 2 * cus + cus / 4) want /= 2;  // a quarter of a chip above: 72 tiles x 8 measured better than x 4
+      if (want == 8 && a.m <= 64 && narrow * 4 <= cus && narrow * 4 * 8 >= (long)cus * 7) want = 4;
+      p.narrow = Narrow64::BN;
+    }
   }
   if ((size_t)want * per_chunk > scratch_bytes) want = (long)(scratch_bytes / per_chunk);
   if (want < 2) return GemmSplit{1, steps, 0, 0, 0};
@@ -897,13 +926,26 @@ static hipError_t launch_mode(GemmArgs& a, void* scratch, size_t scratch_bytes, 
   a.split_k = sp.split_k, a.steps_per_split = sp.steps_per_split, a.partial = (float*)scratch;
   hipError_t e;
   if (sp.narrow) {  // never for SWIGLU, which is not split
-    if constexpr (MODE != GEMM_SWIGLU) e = a.m <= 64 ? launch_tile<MODE, Narrow64>(a, s) : launch_tile<MODE, Narrow128>(a, s);
-    else e = hipErrorInvalidValue;
+    if constexpr (MODE != GEMM_SWIGLU) {
+      if (sp.narrow == Mid::BN) e = a.m <= 64 ? launch_tile<MODE, Mid64>(a, s) : launch_tile<MODE, Mid>(a, s);
+      else if (a.m > 64) e = launch_tile<MODE, Narrow128>(a, s);
+      // up to one workgroup per CU there is room for a deeper ring
+      else if ((a.n + Deep64::BN - 1) / Deep64::BN * a.split_k <= device_cu_count()) e = launch_tile<MODE, Deep64>(a, s);
+      else e = launch_tile<MODE, Narrow64>(a, s);
+    } else {
+      e = hipErrorInvalidValue;
+    }
   } else if (a.split_k == 1 && gemm_tile(a).wide > 0) {
     const TileChoice t = gemm_tile(a);
     e = t.rest_cols == 128 ? launch_mixed<MODE, Mid>(a, t.wide, s) : launch_mixed<MODE, Tile128>(a, t.wide, s);
   } else if (a.split_k == 1 && gemm_tile_cols(a) == 128) {
     e = launch_tile<MODE, Mid>(a, s);
+  } else if (MODE == GEMM_SWIGLU && a.m <= 64 && gemm_tile_rows(a) == 128 && g_forced_tile_rows.load(std::memory_order_relaxed) == 0) {
+    // 64 token rows instead of 128 that are half padding, a slot more in the ring. us 128 / 64 rows, weights from HBM: 37888 x
+    // 3584 at 5, 16, 40 and 64 tokens 53.4 / 50.7, 53.7 / 51.5, 55.9 / 54.1, 57.7 / 56.5 (tiles of 128 outputs 58-66, of 64 52-62:
+    // more requests for the same activations); 59136 x 8192 at 30 and 64 171.4 / 169.9, 173.6 / 172.2.
+    if constexpr (MODE == GEMM_SWIGLU) e = launch_tile<MODE, Wide64>(a, s);
+    else e = hipErrorInvalidValue;
   } else {
     e = sp.halves || gemm_tile_rows(a) == 128 ? launch_tile<MODE, Tile128>(a, s) : launch_tile<MODE, Tile256>(a, s);
   }

@@ -146,7 +146,7 @@ qp_status qp_linear_plan(int32_t m, int32_t n, int32_t k, size_t workspace_bytes
     return QP_OK;
   }
   const int rows = sp.halves ? 128 : qp::gemm_tile_rows(a);
-  const int cols = sp.narrow ? 64 : sp.split_k > 1 ? 256 : qp::gemm_tile_cols(a);
+  const int cols = sp.narrow ? sp.narrow : sp.split_k > 1 ? 256 : qp::gemm_tile_cols(a);
   const int tiles_m = (m + rows - 1) / rows, tiles_n = (n + cols - 1) / cols;
   out->token_rows_per_tile = rows;
   out->workgroups = sp.split_k > 1 ? (tiles_m * tiles_n + 7) / 8 * 8 : qp::gemm_tile_blocks(a);

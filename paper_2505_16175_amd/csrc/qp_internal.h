@@ -269,7 +269,7 @@ hipError_t launch_gemm_norm(const GemmArgs& a, const void* norm_w, void* norm_ou
 struct GemmSplit {
   int split_k, steps_per_split;
   size_t scratch_bytes;
-  int narrow;  // 1: tiles of 64 outputs (and of 64 token rows for at most 64 tokens) instead of 256
+  int narrow;  // 0, or tiles of 64 or 128 outputs (and of 64 token rows for at most 64 tokens) instead of 256
   int halves;  // 1: tiles of 128 x 256 whatever an unsplit product would take
 };
 GemmSplit gemm_plan_split(const GemmArgs& a, int mode, size_t scratch_bytes);  // host arithmetic only

@@ -343,6 +343,64 @@ def test_narrow_split_tiles(m, n, k):
     assert_stored_close(to_f64(out), LO.bf16_round(LO.linear(to_f64(x), to_f64(w), to_f64(b)) + to_f64(r)), "narrow tiles")
 
 
+@pytest.mark.parametrize("m,n,k,chunks", [(3, 2568, 5120, 8), (64, 3584, 5184, 8), (63, 5112, 5120, 6),    # 64 token rows
+                                          (65, 3584, 5120, 8), (129, 2560, 6976, 6), (128, 5120, 5120, 6)])  # 128
+def test_split_tiles_of_128_outputs(m, n, k, chunks):
+    """Few outputs against a long k: tiles of 128 outputs, dealt by items and (a multiple of 8 of them) by tiles; token rows,
+    outputs and the last chunk's steps that end inside them. Offered less scratch than 5/8 of the chip needs, or a step less
+    to contract, a call keeps the 64-wide tiles."""
+    p = B.linear_plan(m, n, k, 32 << 20)
+    tiles = -(-m // 128) * -(-n // 128)
+    assert p["k_chunks"] == chunks and p["workgroups"] == (tiles + 7) // 8 * 8
+    narrow = (-(-m // 128) * -(-n // 64) + 7) // 8 * 8
+    assert B.linear_plan(m, n, k, 3 * m * n * 4)["workgroups"] == narrow == B.linear_plan(m, n, 79 * 64, 32 << 20)["workgroups"]
+    g = torch.Generator().manual_seed(m + n + k)
+    x, w, b, r = _bf(m, k, gen=g), _bf(n, k, gen=g, scale=k ** -0.5), _bf(n, gen=g), _bf(m, n, gen=g)
+    scratch = torch.empty(32 << 20, dtype=torch.uint8, device=DEV).fill_(0xff)
+    out = torch.full((m, n), float("nan"), dtype=torch.bfloat16, device=DEV)
+    B.linear(x.to(DEV), w.to(DEV), b.to(DEV), r.to(DEV), out, scratch)
+    torch.cuda.synchronize()
+    assert_stored_close(to_f64(out), LO.bf16_round(LO.linear(to_f64(x), to_f64(w), to_f64(b)) + to_f64(r)), "128 outputs")
+
+
+@pytest.mark.parametrize("m,n,k,chunks", [(5, 504, 2304, 8), (64, 512, 2432, 8), (33, 3600, 2368, 4), (64, 3584, 3648, 4)])
+def test_narrow_split_tiles_with_a_deep_ring(m, n, k, chunks):
+    """At most one workgroup per compute unit: a ring of five slots, chunks shorter and longer than it (the last of one, three
+    or seven steps)."""
+    p = B.linear_plan(m, n, k, 32 << 20)
+    assert p["k_chunks"] == chunks and p["workgroups"] * chunks <= 256 and p["workgroups"] >= n // 64
+    g = torch.Generator().manual_seed(m + n + k)
+    x, w, r = _bf(m, k, gen=g), _bf(n, k, gen=g, scale=k ** -0.5), _bf(m, n, gen=g)
+    scratch = torch.empty(32 << 20, dtype=torch.uint8, device=DEV).fill_(0xff)
+    out = torch.full((m, n), float("nan"), dtype=torch.bfloat16, device=DEV)
+    B.linear(x.to(DEV), w.to(DEV), None, r.to(DEV), out, scratch)
+    torch.cuda.synchronize()
+    assert_stored_close(to_f64(out), LO.bf16_round(LO.linear(to_f64(x), to_f64(w)) + to_f64(r)), "deep ring")
+
+
+@pytest.mark.parametrize("m,d_ff,k", [(3, 16512, 64), (64, 16640, 128), (33, 18944, 192), (63, 16512, 256), (17, 16512, 320), (64, 32768, 704)])
+def test_swiglu_in_tiles_of_64_tokens(m, d_ff, k):
+    """Up to 64 tokens: contractions shorter and longer than the ring of four slots. A pinned tiling of 128 rows, which adds in
+    the same order, gives the same bits."""
+    g = torch.Generator(device=DEV).manual_seed(m + d_ff + k)
+    x = torch.randn(m, k, generator=g, device=DEV).to(torch.bfloat16)
+    w = (torch.randn(2 * d_ff, k, generator=g, device=DEV) * k ** -0.5).to(torch.bfloat16)
+    outs = []
+    for rows in (0, 128):
+        B.select_linear_tile(rows)
+        try:
+            out = torch.full((m, d_ff), float("nan"), dtype=torch.bfloat16, device=DEV)
+            B.swiglu_gate_up(x, w, out)
+            torch.cuda.synchronize()
+        finally:
+            B.select_linear_tile(0)
+        outs.append(out)
+    assert torch.equal(*outs)
+    y = x.double() @ w.double().T
+    gate, up = y[:, :d_ff], y[:, d_ff:]
+    assert_stored_close(to_f64(outs[0]), to_f64((gate * torch.sigmoid(gate) * up).to(torch.bfloat16)), "swiglu")
+
+
 @pytest.mark.parametrize("m,n,k", [(63, 3584, 1088), (65, 4600, 2048), (200, 3584, 2112), (100, 10240, 1024)])
 def test_wide_split_tiles(m, n, k):
     """The split of 256-wide tiles at the same kind of edges: too short a k for the 64-wide ones, or many outputs."""
