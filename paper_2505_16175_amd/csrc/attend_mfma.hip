@@ -619,12 +619,18 @@ __global__ __launch_bounds__(MF_NT, 2) void attend_mfma_kernel(AttendArgs a) {
 #pragma unroll
   for (int n = 0; n < 4; ++n)
 #pragma unroll
-    for (int q4 = 0; q4 < 4; ++q4) {
-      // registers 4*q4 .. 4*q4+3 hold d = 32 n + 8 q4 + 4 g + 0..3
-      bf16x4 pk;
+    for (int q4 = 0; q4 < 4; q4 += 2) {
+      // Registers 4 q4 .. 4 q4 + 3 hold d = 32 n + 8 q4 + 4 g + 0..3: the row's two lanes swap, so that one has 8 outputs of
+      // q4 and the other of q4 + 1, and a store writes 32 bytes of each of its rows instead of 16. No barrier here: wavefronts
+      // end at their rows' horizons, and the stores of those that end early cost nothing. us before / after: 99 frames over an
+      // 8-bit cache 486.2 / 478.2, 256 frames of the 7B heads 2222 / 2208, 1500 tokens of the 72B heads over 600 74.8 / 71.8.
+      bf16x4 pk[2];
 #pragma unroll
-      for (int e = 0; e < 4; ++e) pk[e] = (__bf16)(o[n][4 * q4 + e] * inv);
-      *(uint2*)(orow + 32 * n + 8 * q4 + 4 * g) = __builtin_bit_cast(uint2, pk);
+      for (int e = 0; e < 4; ++e) pk[0][e] = (__bf16)(o[n][4 * q4 + e] * inv), pk[1][e] = (__bf16)(o[n][4 * q4 + 4 + e] * inv);
+      const uint2 even = __builtin_bit_cast(uint2, pk[0]), odd = __builtin_bit_cast(uint2, pk[1]);
+      const auto x = __builtin_amdgcn_permlane32_swap(even.x, odd.x, false, false);
+      const auto y = __builtin_amdgcn_permlane32_swap(even.y, odd.y, false, false);
+      *(uint4*)(orow + 32 * n + 8 * (q4 + g)) = make_uint4(x[0], y[0], x[1], y[1]);
     }
   if (a.lse != nullptr && g == 0)
     a.lse[(size_t)(h * r_heads + j_lane) * a.n_g + t_lane] = (m_run * c2 + log2f(l_tot)) * 0.6931471805599453f;
