@@ -99,6 +99,40 @@ def test_group_attend_key_split_matches_oracle(h_q, h_kv, n_g, c):
 
 
 @pytest.mark.gpu
+@pytest.mark.parametrize("fp8", [False, True])
+@pytest.mark.parametrize("h_q,h_kv,n_g,c", [(28, 4, 7, 600), (28, 4, 41, 2000), (64, 8, 64, 1500), (14, 2, 333, 1100), (28, 4, 256, 700)])
+def test_group_attend_split_partial_rows(h_q, h_kv, n_g, c, fp8):
+    """Every row of the key split's partial results is written, and nothing beside them: row counts that end inside a
+    wavefront's 32 rows and that fill row blocks, last chunks of one group tile and of several, where wavefronts end apart."""
+    print(f"case heads={h_q}/{h_kv} n_g={n_g} c={c} fp8={fp8}", flush=True)
+    d = 128
+    g = torch.Generator().manual_seed(n_g + c + h_q)
+    mk = lambda *s: torch.randn(*s, generator=g).to(torch.bfloat16)
+    q, k, v = mk(n_g, h_q, d), mk(n_g, h_kv, d), mk(n_g, h_kv, d)
+    ck, cv = mk(h_kv, c, d), mk(h_kv, c, d)
+    if fp8:
+        ck, cv = (t.float().to(torch.float8_e4m3fn).to(torch.bfloat16) for t in (ck, cv))
+    want, want_lse = O.attend_group(_f64(q), _f64(k), _f64(v), _f64(ck), _f64(cv), return_lse=True)
+    layout = B.make_layout(h_q, h_kv, d, "bf16")
+    cache = B.Cache(layout, c, fmt=B.QP_CACHE_FP8_E4M3 if fp8 else B.QP_CACHE_SAME)
+    cache.k.copy_(ck)
+    cache.v.copy_(cv)
+    cache.c.len = c
+    size = B.make_workspace(layout, n_g, 0).numel()
+    plan = B.attend_plan(layout, n_g, c, size)
+    assert plan["key_chunks"] > 1
+    guard = 1 << 20
+    ws = torch.full((size + guard,), 0xff, dtype=torch.uint8, device=DEV)      # NaN patterns: every partial read must have been written
+    out = torch.full((n_g, h_q, d), float("nan"), dtype=torch.bfloat16, device=DEV)
+    lse = torch.full((h_q, n_g), float("nan"), dtype=torch.float32, device=DEV)
+    B.group_attend(layout, q.to(DEV), k.to(DEV), v.to(DEV), cache, out, lse, ws[:size])
+    torch.cuda.synchronize()
+    assert (ws[size:] == 0xff).all()
+    assert_attn_close(_f64(out), want, "bf16", "split")
+    np.testing.assert_allclose(_f64(lse), want_lse, rtol=2e-5, atol=2e-3)
+
+
+@pytest.mark.gpu
 @pytest.mark.parametrize("h_q,h_kv,n_g,c,chunks", [
     (28, 4, 64, 20480, 32),    # two row blocks, the second half full; chunks of 10 tiles: both of a chunk on one XCD
     (28, 4, 40, 20700, 30),    # 24 rows in the second block, a cut-off cache tile
