@@ -813,6 +813,7 @@ int gemm_tile_blocks(const GemmArgs& a) {
 // There, up to 64 tokens, half as many chunks fill the chip if 4 of them make 7/8 to all of a workgroup per CU, with a ring of
 // 5 slots in the room of the second one, and leave half the partial sums: 3584 x 3584 at 64 and 16 tokens 13.8 / 12.2 and 11.5 /
 // 10.1 (with 3 slots no gain). 4 chunks of fewer tiles lose (2048 x 8192, 128 workgroups, 14.2 / 16.9).
+// Both rules are for PLAIN: other chunks add in another order, and QKV's sums decide which near-tied keys are kept.
 constexpr int NARROW_ABOVE = 8;
 constexpr int MID_STEPS = 80;  // k-steps from which a contraction is long
 GemmSplit gemm_plan_split(const GemmArgs& a, int mode, size_t scratch_bytes) {
@@ -847,14 +848,14 @@ GemmSplit gemm_plan_split(const GemmArgs& a, int mode, size_t scratch_bytes) {
     const long mid = tiles_m * ((a.n + Mid::BN - 1) / Mid::BN);
     long mid_want = std::min<long>(NARROW_ABOVE, cus / mid);
     if ((size_t)mid_want * per_chunk > scratch_bytes) mid_want = (long)(scratch_bytes / per_chunk);
-    if (steps >= MID_STEPS && mid_want >= 2 && mid * mid_want * 8 >= (long)cus * 5) {
+    if (mode == GEMM_PLAIN && steps >= MID_STEPS && mid_want >= 2 && mid * mid_want * 8 >= (long)cus * 5) {
       want = mid_want;
       p.narrow = Mid::BN;
     } else {
       const long narrow = tiles_m * ((a.n + Narrow64::BN - 1) / Narrow64::BN);
       want = NARROW_ABOVE;
       while (want > 1 && narrow * want > 2 * cus + cus / 4) want /= 2;  // a quarter of a chip above: 72 tiles x 8 measured better than x 4
-      if (want == 8 && a.m <= 64 && narrow * 4 <= cus && narrow * 4 * 8 >= (long)cus * 7) want = 4;
+      if (mode == GEMM_PLAIN && want == 8 && a.m <= 64 && narrow * 4 <= cus && narrow * 4 * 8 >= (long)cus * 7) want = 4;
       p.narrow = Narrow64::BN;
     }
   }
@@ -925,10 +926,12 @@ static hipError_t launch_mode(GemmArgs& a, void* scratch, size_t scratch_bytes, 
   const GemmSplit sp = gemm_plan_split(a, MODE, scratch != nullptr ? scratch_bytes : 0);
   a.split_k = sp.split_k, a.steps_per_split = sp.steps_per_split, a.partial = (float*)scratch;
   hipError_t e;
-  if (sp.narrow) {  // never for SWIGLU, which is not split
+  if (sp.narrow == Mid::BN) {  // PLAIN only
+    if constexpr (MODE == GEMM_PLAIN) e = a.m <= 64 ? launch_tile<MODE, Mid64>(a, s) : launch_tile<MODE, Mid>(a, s);
+    else e = hipErrorInvalidValue;
+  } else if (sp.narrow) {  // never for SWIGLU, which is not split
     if constexpr (MODE != GEMM_SWIGLU) {
-      if (sp.narrow == Mid::BN) e = a.m <= 64 ? launch_tile<MODE, Mid64>(a, s) : launch_tile<MODE, Mid>(a, s);
-      else if (a.m > 64) e = launch_tile<MODE, Narrow128>(a, s);
+      if (a.m > 64) e = launch_tile<MODE, Narrow128>(a, s);
       // up to one workgroup per CU there is room for a deeper ring
       else if ((a.n + Deep64::BN - 1) / Deep64::BN * a.split_k <= device_cu_count()) e = launch_tile<MODE, Deep64>(a, s);
       else e = launch_tile<MODE, Narrow64>(a, s);

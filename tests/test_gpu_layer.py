@@ -501,6 +501,31 @@ def test_qkv_rope_split_contraction(n, d_model, h_q, h_kv):
         assert_stored_close(to_f64(got), ref, name)
 
 
+@pytest.mark.parametrize("n,d_model,h_q,h_kv,per_chunk", [(64, 5120, 32, 8, 20), (100, 5120, 32, 8, 20), (64, 5120, 28, 4, 10),
+                                                           (128, 5120, 28, 4, 10), (64, 3584, 24, 4, 7), (64, 3584, 28, 4, 7)])
+def test_qkv_chunks_are_those_of_64_wide_tiles(n, d_model, h_q, h_kv, per_chunk):
+    """The order of QKV's sums decides which near-tied keys are kept: it stays that of 64-wide tiles in the largest power of
+    two of chunks, at most 8, that gives a CU at most 2.25 of them, where a plain product of the sizes is dealt otherwise.
+    Weight row t of V has 2^24 at the end of k-step t and 1 and -2^24 in step t + 1: 2^24 + 1 is 2^24 in f32, so the sum is 1
+    where a chunk starts with step t + 1, and 0 elsewhere."""
+    layout = B.make_layout(h_q, h_kv, 128, "bf16")
+    rows, steps = (h_q + 2 * h_kv) * 128, d_model // 64
+    w = torch.zeros(rows, d_model, dtype=torch.bfloat16)
+    v_rows = w[-h_kv * 128:]
+    for t in range(steps - 1):
+        v_rows[t, 64 * t + 63], v_rows[t, 64 * t + 64], v_rows[t, 64 * t + 127] = 2.0 ** 24, 1.0, -2.0 ** 24
+    x = torch.ones(n, d_model, dtype=torch.bfloat16, device=DEV)
+    cs = torch.zeros(n, 64, 2, dtype=torch.float32, device=DEV)
+    scratch = torch.empty(32 << 20, dtype=torch.uint8, device=DEV).fill_(0xff)
+    q, k, v = (torch.full((n, h, 128), float("nan"), dtype=torch.bfloat16, device=DEV) for h in (h_q, h_kv, h_kv))
+    B.qkv_rope(layout, x, w.to(DEV), torch.zeros(rows, dtype=torch.bfloat16, device=DEV), cs, q, k, v, scratch)
+    torch.cuda.synchronize()
+    want = torch.zeros(h_kv * 128, dtype=torch.bfloat16)
+    want[per_chunk - 1:steps - 1:per_chunk] = 1.0
+    for row in v.view(n, -1).cpu():
+        assert torch.equal(row, want), f"chunks start with steps {(row.nonzero().flatten() + 1).tolist()}"
+
+
 def test_unsupported_shapes_are_refused_before_launch():
     x = torch.zeros(4, 72, dtype=torch.bfloat16, device=DEV)
     w = torch.zeros(8, 72, dtype=torch.bfloat16, device=DEV)
