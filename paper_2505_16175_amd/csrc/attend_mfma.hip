@@ -90,6 +90,11 @@ constexpr int MF_LDS = 2 * MF_STAGES * MF_TILE;
 // 2.23 / 1.82 / 1.71. What it costs: 4096 tokens over 24,576 entries 1293 / 1328 / 1384 / 1420 us, with 2^12 1294 / 1316 /
 // 1348 / 1388; 77 tokens over 9840 29.0 / 30.2 / 32.3 / 33.0 and 29.1 / 28.9 / 30.2 / 32.9.
 constexpr float MF_RESCALE = 64.f;
+// Up to so many rows of a KV head a chunk's partial rows are stored from the accumulators: for one to three live wavefronts the
+// barrier and the way through LDS take longer than what whole rows save. us of the call from the accumulators / through LDS:
+// 7B heads, 5 tokens (35 rows) over 600, 5,000 and 20,000 entries 11.9 / 12.6, 12.5 / 13.1, 16.4 / 17.1; 9 tokens over 5,000
+// 13.8 / 14.1, 11 tokens 15.2 / 15.4, 14 (98 rows) 16.4 / 16.2, 18 17.5 / 17.1; 72B heads, 5 tokens (40 rows) over 5,000 14.4 / 15.0.
+constexpr int MF_DIRECT_ROWS = 96;
 constexpr int MF_VMCNT0 = 0x0f70;       // s_waitcnt vmcnt(0), other counters untouched
 constexpr int MF_VMCNT4 = 0x0f74;       // s_waitcnt vmcnt(4)
 constexpr int MF_LGKM0 = 0xc07f;        // s_waitcnt lgkmcnt(0)
@@ -600,11 +605,24 @@ __global__ __launch_bounds__(MF_NT, 2) void attend_mfma_kernel(AttendArgs a) {
 
   if (my_split > 1) {
     // partial result of this chunk: every chunk starts on a cache tile, whose keys all rows see, so l_tot > 0
-    __syncthreads();  // the ring's last readers (its last requests have landed, see turn)
+    const bool staged = n_rows > MF_DIRECT_ROWS;
+    if (staged) __syncthreads();  // the ring's last readers (its last requests have landed, see turn)
     if (!wave_live) return;
     const float l_tot = sum_halves(l_run);
     const float inv = 1.f / l_tot;
     const size_t prow0 = (size_t)chunk * ((size_t)a.h_kv * a.part_rows) + (size_t)h * a.part_rows + row0;
+    float* const po = a.part_o + prow0 * MF_D;
+    if (g == 0 && row_ok) a.part_lse[prow0 + l32] = m_run * c2 + log2f(l_tot);
+    if (!staged) {
+      if (!row_ok) return;
+#pragma unroll
+      for (int n = 0; n < 4; ++n)
+#pragma unroll
+        for (int q4 = 0; q4 < 4; ++q4)
+          *(float4*)(po + l32 * MF_D + 32 * n + 8 * q4 + 4 * g) =
+              make_float4(o[n][4 * q4] * inv, o[n][4 * q4 + 1] * inv, o[n][4 * q4 + 2] * inv, o[n][4 * q4 + 3] * inv);
+      return;
+    }
     // Through LDS, 16-byte chunk c of row r at c ^ (r & 15), which keeps both sides free of bank conflicts: a store then
     // writes two whole rows. Stored from the accumulators an instruction touched 32 rows in pieces of 32 bytes, 4096 of
     // them per workgroup and all at once at the launch's end. The workgroups' rows lie powers of two apart in many calls, so
@@ -620,9 +638,7 @@ __global__ __launch_bounds__(MF_NT, 2) void attend_mfma_kernel(AttendArgs a) {
       for (int q4 = 0; q4 < 4; ++q4)
         *(float4*)(stage + l32 * (MF_D * 4) + ((8 * n + 2 * q4 + g) ^ (l32 & 15)) * 16) =
             make_float4(o[n][4 * q4] * inv, o[n][4 * q4 + 1] * inv, o[n][4 * q4 + 2] * inv, o[n][4 * q4 + 3] * inv);
-    if (g == 0 && row_ok) a.part_lse[prow0 + l32] = m_run * c2 + log2f(l_tot);
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // the wavefront's writes before its reads
-    float* const po = a.part_o + prow0 * MF_D;
 #pragma unroll
     for (int u = 0; u < 16; ++u) {
       const int r = 2 * ((u + rot) & 15) + g;

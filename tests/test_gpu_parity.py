@@ -133,6 +133,15 @@ def test_group_attend_split_partial_rows(h_q, h_kv, n_g, c, fp8):
 
 
 @pytest.mark.gpu
+@pytest.mark.parametrize("fp8", [False, True])
+@pytest.mark.parametrize("h_q,h_kv,n_g,c", [(28, 4, 3, 600), (28, 4, 5, 1000), (14, 2, 9, 3000), (64, 8, 12, 1500), (12, 2, 16, 900),
+                                            (28, 4, 14, 2000), (64, 8, 13, 1500)])
+def test_group_attend_split_partial_rows_of_few_tokens(h_q, h_kv, n_g, c, fp8):
+    """Up to 96 rows of a KV head leave from the accumulators, more through LDS: 21 to 96 rows, whole wavefronts and not, 98, 104."""
+    test_group_attend_split_partial_rows(h_q, h_kv, n_g, c, fp8)
+
+
+@pytest.mark.gpu
 @pytest.mark.parametrize("h_q,h_kv,n_g,c,chunks", [
     (28, 4, 64, 20480, 32),    # two row blocks, the second half full; chunks of 10 tiles: both of a chunk on one XCD
     (28, 4, 40, 20700, 30),    # 24 rows in the second block, a cut-off cache tile
