@@ -178,9 +178,11 @@ __global__ __launch_bounds__(MF_NT, 2) void attend_mfma_kernel(AttendArgs a) {
       // Dealt one by one, the two row blocks of a text chunk each took a copy of the cache through an L2 of their own: both
       // of a key chunk go to one XCD, whose L2 then fetches its keys once. us before / after, 7B heads: 64 tokens over 60,000
       // entries 69.6 / 66.5, 50 tokens 64.8 / 60.1, 64 over 30,000 45.0 / 43.6, over 20,000 (chunks of 10 tiles) 36.5 / 34.8.
-      // Shorter chunks are not bound by the fetch (64 over 9,840, 5 tiles: 28.6 / 28.8), and of three row blocks and more,
+      // Shorter chunks are not bound by the fetch (64 over 9,840, 5 tiles: 28.6 / 28.8), nor are those of an 8-bit cache, half
+      // as large, up to 13 tiles (40 and 50 tokens over 20,000, 10 tiles: 31.4 / 33.0 and 33.7 / 34.4; 50 over 25,000, 13 tiles:
+      // 37.5 / 37.5; 50 over 30,000 and 46,125: 40.7 / 40.0 and 51.3 / 50.3), and of three row blocks and more,
       // side by side, chunks got slower (200 over 5,000 31.4 / 34.1, 128 over 9,840 33.5 / 34.2).
-      if (n_whole == 0 && n_rb == 2 && a.split_tiles >= 10 && a.n_split % per == 0) item = (idx / 2 * per + xcd % per) * 2 + idx % 2;
+      if (n_whole == 0 && n_rb == 2 && a.split_tiles >= (F8 ? 14 : 10) && a.n_split % per == 0) item = (idx / 2 * per + xcd % per) * 2 + idx % 2;
     } else if (a.h_kv % 8 == 0) {
       const int hp = a.h_kv / 8;  // KV heads per XCD
       h = (idx % hp) * 8 + xcd;

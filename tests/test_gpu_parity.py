@@ -174,6 +174,16 @@ def test_group_attend_two_row_blocks_of_a_chunk_on_one_xcd(h_q, h_kv, n_g, c, ch
 
 
 @pytest.mark.gpu
+@pytest.mark.parametrize("n_g,c,tiles", [(64, 26624, 13), (64, 28672, 14), (40, 28650, 14)])
+def test_group_attend_two_row_blocks_of_a_chunk_of_an_8_bit_cache(n_g, c, tiles):
+    """Chunks of 13 tiles are dealt one by one, of 14 in pairs."""
+    layout = B.make_layout(28, 4, 128, "bf16")
+    plan = B.attend_plan(layout, n_g, c, B.workspace_bytes(layout, n_g, 0))
+    assert (plan["key_chunks"], plan["tiles_per_chunk"]) == (32, tiles)
+    test_group_attend_split_partial_rows(28, 4, n_g, c, True)
+
+
+@pytest.mark.gpu
 @pytest.mark.parametrize("h_q,h_kv,n_g,c,fp8", [(28, 4, 2400, 2100, False), (64, 8, 1100, 2100, False),
                                                 (16, 16, 4400, 2100, False), (28, 4, 8192, 24000, False),
                                                 (28, 4, 4096, 24000, False), (28, 4, 2400, 2100, True),
