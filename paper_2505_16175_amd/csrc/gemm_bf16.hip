@@ -220,10 +220,12 @@ __device__ __forceinline__ void gemm_tile_product(const GemmArgs& a, const TileG
   // products behind the requests. So that tiling (rings of 2 and 3) spreads them: a step t issues W(t + 2) in its first half,
   // into the slot that step t - 1 left, and behind the barrier X(t + 2), which is awaited there a step later: half of it
   // in the first half of step t + 1 left it half a step and cost 5-8 %. The 128 x 256 tiling (equal rings of 3)
-  // spreads them too: a step t issues step t + 2 into the slot that step t - 1 left, a request behind every other product
-  // before the barrier. us behind the barrier / spread: 2048 x 3584 x 18944 262 / 257, 300 x 37888 x 3584 112 / 105, 257
-  // tokens of it 100 / 96, 300 x 59136 x 8192 365 / 340; in chunks 520 x 3584 x 18944 95 / 92, 900 tokens of it 139 / 132, 400
-  // x 8192 x 29568 242 / 227, 1024 x 3584 x 18944 147 / 149, 300 x 4608 x 3584 27.9 / 28.4.
+  // puts its requests behind every other product behind the barrier, two steps ahead of their wait. us, weights from HBM, in the
+  // first half of the next step / there: 2048 x 3584 x 18944 255.6 / 251.8, 2048 x 4096 x 14336 204.1 / 200.4, 1024 x 6144 x 5120
+  // 76.9 / 75.9, 768 x 8192 x 29568 421 / 416; in chunks 520 x 3584 x 18944 92.4 / 89.9, 400 x 8192 x 29568 236 / 230. Behind
+  // every product they are all under way a little sooner, but ragged or short launches lose: every other / every product 1024 x
+  // 6144 x 5120 76.7 / 74.9, 1920 x 3584 x 18944 256 / 250, but 1024 x 8192 x 8192 121.5 / 125.4, 2048 x 4096 x 4096 62.1 / 63.9, 300
+  // x 59136 x 8192 342 / 357, 520 x 3584 x 18944 91.5 / 95.4, 900 tokens of it 132 / 139.
   // PFLOP/s of products of 32 x 32 x 16 with the barrier behind three quarters of a step / of this loop, random inputs:
   // 4096 x 59136 x 8192 1.38 / 1.46, 4096 x 8192 x 29568 1.36 / 1.48, 2048 x 37888 x 3584 1.24 / 1.33, 8192 x 8192 x 8192 1.35 /
   // 1.47, 2048 x 3584 x 18944 1.22 / 1.25, 1024 x 8192 x 8192 1.19 / 1.29. On zeros, which leave the clock alone, 8192 x 8192 x
@@ -267,36 +269,27 @@ __device__ __forceinline__ void gemm_tile_product(const GemmArgs& a, const TileG
 #define GM_MFMA_ONE(s_, mf_)                                                                                   \
   gm_product(acc[GM_J(mf_)][(mf_) / NJ], wf[s_][GM_J(mf_)], xf[(s_) % XSETS][(mf_) / NJ]);
   constexpr int NM = NJ * NI;              // products per k-step
-  constexpr int PER = (PW + NM - 1) / NM;  // refill requests behind each
+  constexpr int PER = (PW + NM - 1) / NM;  // refill requests behind each of them
 #pragma unroll
   for (int j = 0; j < NJ; ++j) GM_READ_W(smem, 0, j)
 #pragma unroll
   for (int i = 0; i < NI; ++i) GM_READ_X(smem, 0, i)
   int xslot = 0, wslot = 0;
-  constexpr bool SPREAD = XS == WS && T::MI == 2 && T::BN == 256;
+  constexpr int EVERY = T::MI == 2 && T::BN == 256 ? 2 : 1;  // ... or one behind every other product
   static_assert(XS <= 5 && (XS - 1) * PW <= 63, "the waits spelled out, and what vmcnt counts");
   static_assert(T::KS == 2, "two k-steps of the products per slot");
-  static_assert(!SPREAD || PW <= NM / 2, "a request behind every other product");
-  static_assert(XS == WS || (T::XQ == 4 && T::WQ == 4 && T::MI == 4), "spread of the requests");
-  // One step that has a successor; refill_x / refill_w: there is a step left to request into the freed slots.
-  auto step_and_next = [&](int step, bool refill_x, bool refill_w, auto wait) {
+  static_assert(XS != WS || EVERY == 1 || (PER == 1 && PW <= NM / EVERY), "all requests within a k-step");
+  static_assert(XS == WS || (T::XQ == 4 && T::WQ == 4 && T::MI == 4), "where rings of 2 and 3 put their requests");
+  // One step that has a successor; refill: there is a step left to request into the freed slots.
+  auto step_and_next = [&](int step, bool refill, auto wait) {
     const unsigned char *xst = smem + xslot * T::XT, *wst = smem + wslot * T::WT;
     const int wfree = wslot == 0 ? WS - 1 : wslot - 1;  // the slot that the step before left
-    const int free = xslot == 0 ? XS - 1 : xslot - 1;
 #pragma unroll
     for (int mf = 0; mf < NM; ++mf) {
       GM_MFMA_ONE(0, mf)
       GM_READ_AHEAD(xst, wst, 1, mf)
       __builtin_amdgcn_sched_barrier(0);
-      if (XS != WS) {
-        if (mf % 8 == 4 && refill_w) GM_ISSUE_W(mf / 8, step + 2, wfree)
-      } else if (SPREAD) {
-        const int q = mf / 2;
-        if ((mf & 1) && q < PW && refill_w) {
-          if (q < T::XQ) GM_ISSUE_X(q, step + XS - 1, free)
-          else GM_ISSUE_W(q - T::XQ, step + XS - 1, free)
-        }
-      }
+      if (XS != WS && mf % 8 == 4 && refill) GM_ISSUE_W(mf / 8, step + 2, wfree)
       __builtin_amdgcn_sched_barrier(0);
     }
     const int xnext = xslot == XS - 1 ? 0 : xslot + 1, wnext = wslot == WS - 1 ? 0 : wslot + 1;
@@ -309,16 +302,13 @@ __device__ __forceinline__ void gemm_tile_product(const GemmArgs& a, const TileG
       GM_READ_AHEAD(xst_next, wst_next, 0, mf)
       __builtin_amdgcn_sched_barrier(0);
       if (XS != WS) {
-        if (mf % 4 == 2 && mf / 4 < T::XQ && refill_x) GM_ISSUE_X(mf / 4, step + XS, xslot)
-      } else if (!SPREAD) {
+        if (mf % 4 == 2 && mf / 4 < T::XQ && refill) GM_ISSUE_X(mf / 4, step + XS, xslot)
+      } else if (refill && mf % EVERY == EVERY - 1) {
 #pragma unroll
         for (int u = 0; u < PER; ++u) {
-          const int p = mf * PER + u;
-          if (p < T::XQ) {
-            if (refill_x) GM_ISSUE_X(p, step + XS, xslot)
-          } else if (p < PW) {
-            if (refill_w) GM_ISSUE_W(p - T::XQ, step + WS, wslot)
-          }
+          const int p = mf / EVERY * PER + u;
+          if (p < T::XQ) GM_ISSUE_X(p, step + XS, xslot)
+          else if (p < PW) GM_ISSUE_W(p - T::XQ, step + WS, wslot)
         }
       }
       __builtin_amdgcn_sched_barrier(0);
@@ -327,9 +317,9 @@ __device__ __forceinline__ void gemm_tile_product(const GemmArgs& a, const TileG
   };
   int step = 0;
   for (; step + XS < n_steps; ++step)
-    step_and_next(step, true, !SPREAD || step > 0, [] { gm_wait_vmcnt<XS != WS ? T::WQ : (XS - 2) * PW>(); });
+    step_and_next(step, true, [] { gm_wait_vmcnt<XS != WS ? T::WQ : (XS - 2) * PW>(); });
   for (; step + 1 < n_steps; ++step)
-    step_and_next(step, false, SPREAD && step > 0 && step + XS - 1 < n_steps, [&] {
+    step_and_next(step, false, [&] {
       if (XS == WS && XS >= 5 && step + 4 < n_steps) gm_wait_vmcnt<3 * PW>();
       else if (XS == WS && XS >= 4 && step + 3 < n_steps) gm_wait_vmcnt<2 * PW>();
       else if (XS == WS && XS >= 3 && step + 2 < n_steps) gm_wait_vmcnt<PW>();
