@@ -315,16 +315,45 @@ __device__ __forceinline__ void gemm_tile_product(const GemmArgs& a, const TileG
     }
     xslot = xnext, wslot = wnext;
   };
-  int step = 0;
-  for (; step + XS < n_steps; ++step)
-    step_and_next(step, true, [] { gm_wait_vmcnt<XS != WS ? T::WQ : (XS - 2) * PW>(); });
-  for (; step + 1 < n_steps; ++step)
-    step_and_next(step, false, [&] {
-      if (XS == WS && XS >= 5 && step + 4 < n_steps) gm_wait_vmcnt<3 * PW>();
-      else if (XS == WS && XS >= 4 && step + 3 < n_steps) gm_wait_vmcnt<2 * PW>();
-      else if (XS == WS && XS >= 3 && step + 2 < n_steps) gm_wait_vmcnt<PW>();
-      else gm_wait_vmcnt<0>();
-    });
+  // A wavefront whose tokens all lie past the end multiplies nothing: it requests its part of the tiles and keeps the barriers.
+  // Its products cost power, and with the other wavefronts of its SIMD the matrix pipe. us with them / without: 900 x 3584 x 18944
+  // 135 / 129, 260 and 300 x 59136 x 8192 338 / 322 and 345 / 335, 258 x 3584 x 18944 60.7 / 57.9, 16 x 8192 x 8192 36.2 / 32.6, QKV
+  // of 3 tokens 1536 -> 2048 10.0 / 9.3 and 2048 -> 2560 10.8 / 10.3; full tiles do not change.
+  auto idle_and_next = [&](int step, bool refill, auto wait) {
+    if (XS != WS && refill) {
+      const int wfree = wslot == 0 ? WS - 1 : wslot - 1;
+#pragma unroll
+      for (int q = 0; q < T::WQ; ++q) GM_ISSUE_W(q, step + 2, wfree)
+    }
+    wait();
+    __syncthreads();
+    if (refill) {
+#pragma unroll
+      for (int q = 0; q < T::XQ; ++q) GM_ISSUE_X(q, step + XS, xslot)
+      if (XS == WS)
+#pragma unroll
+        for (int q = 0; q < T::WQ; ++q) GM_ISSUE_W(q, step + WS, wslot)
+    }
+    xslot = xslot == XS - 1 ? 0 : xslot + 1, wslot = wslot == WS - 1 ? 0 : wslot + 1;
+  };
+  auto walk = [&](auto and_next) {  // every step but the last
+    int step = 0;
+    for (; step + XS < n_steps; ++step) and_next(step, true, [] { gm_wait_vmcnt<XS != WS ? T::WQ : (XS - 2) * PW>(); });
+    for (; step + 1 < n_steps; ++step)
+      and_next(step, false, [&] {
+        if (XS == WS && XS >= 5 && step + 4 < n_steps) gm_wait_vmcnt<3 * PW>();
+        else if (XS == WS && XS >= 4 && step + 3 < n_steps) gm_wait_vmcnt<2 * PW>();
+        else if (XS == WS && XS >= 3 && step + 2 < n_steps) gm_wait_vmcnt<PW>();
+        else gm_wait_vmcnt<0>();
+      });
+  };
+  const int mw = m0 + wm * (32 * T::MI);  // this wavefront's first token
+  if (mw >= a.m) {
+    walk(idle_and_next);
+    if (MODE != GEMM_SWIGLU && a.split_k == 1) __syncthreads();  // the one in front of the staging
+    return;
+  }
+  walk(step_and_next);
   {  // last step: nothing left to request or to wait for
     const unsigned char *xst = smem + xslot * T::XT, *wst = smem + wslot * T::WT;
 #pragma unroll
@@ -349,7 +378,6 @@ __device__ __forceinline__ void gemm_tile_product(const GemmArgs& a, const TileG
   __builtin_amdgcn_sched_barrier(0);
   // ---- store: lane owns token m = m0 + (32 MI) wm + 16 i + l16 and, in block j, outputs 4 g + 0..3
   const int u64 = (n0 >> 6) + wn;  // QKV_ROPE: which run of 64 outputs (half a head's rotary pairs) this wavefront has
-  const int mw = m0 + wm * (32 * T::MI);  // this wavefront's first token
   if (a.split_k > 1) {
     // partial sums of this k chunk, f32 [chunk][m][n] with n the output's logical column (for QKV: head * 128 + dim);
     // gemm_reduce_kernel adds the chunks in order and applies the mode's store

@@ -343,6 +343,56 @@ def test_narrow_split_tiles(m, n, k):
     assert_stored_close(to_f64(out), LO.bf16_round(LO.linear(to_f64(x), to_f64(w), to_f64(b)) + to_f64(r)), "narrow tiles")
 
 
+@pytest.mark.parametrize("rows,k", [(128, 64), (128, 192), (128, 448), (256, 64), (256, 192), (256, 448), (0, 320)])
+@pytest.mark.parametrize("m", [257, 289, 320, 353, 385, 449])
+def test_wavefronts_past_the_last_token(m, rows, k):
+    """Wavefronts of the last token tile that have no token only request and wait: rows of 32, 64 and 128 tokens per
+    wavefront, contractions shorter and longer than the rings, all three stores. The rows equal those of a full tile, bit for
+    bit, and what lies behind them is left alone."""
+    n, full, h_q, h_kv = 1024, 512, 4, 2
+    g = torch.Generator(device=DEV).manual_seed(m + rows + k)
+    rnd = lambda *s: torch.randn(*s, generator=g, device=DEV).to(torch.bfloat16)
+    x, w, b, r = rnd(full, k), rnd(n, k), rnd(n), rnd(full, n)
+    cs = torch.randn(full, 64, 2, generator=g, device=DEV)
+    layout = B.make_layout(h_q, h_kv, 128, "bf16")
+
+    def outputs(t):
+        o = [torch.full((full, *s), float("nan"), dtype=torch.bfloat16, device=DEV)
+             for s in ((n,), (n // 2,), (h_q, 128), (h_kv, 128), (h_kv, 128))]
+        B.linear(x[:t], w, b, r[:t], o[0][:t])
+        B.swiglu_gate_up(x[:t], w, o[1][:t])
+        B.qkv_rope(layout, x[:t], w, b, cs[:t], o[2][:t], o[3][:t], o[4][:t])
+        torch.cuda.synchronize()
+        return o
+
+    B.select_linear_tile(rows)
+    try:
+        some, whole = outputs(m), outputs(full)
+    finally:
+        B.select_linear_tile(0)
+    for a, c in zip(some, whole):
+        assert torch.equal(a[:m], c[:m]) and torch.isfinite(c.float()).all() and torch.isnan(a[m:].float()).all()
+    want = LO.linear(to_f64(x[:m]), to_f64(w), to_f64(b)) + to_f64(r[:m])
+    assert_stored_close(to_f64(some[0][:m]), LO.bf16_round(want), "linear")
+
+
+@pytest.mark.parametrize("m", [3, 32, 33, 65, 96, 129, 160, 193])
+@pytest.mark.parametrize("n,k", [(3584, 640), (1024, 2112), (2560, 5184), (4608, 1088), (6144, 1024)])
+def test_wavefronts_past_the_last_token_of_a_split_product(m, n, k):
+    """The same in chunks: tiles of 64 outputs with both rings, of 128 and of 256."""
+    g = torch.Generator(device=DEV).manual_seed(m + n + k)
+    rnd = lambda *s: torch.randn(*s, generator=g, device=DEV).to(torch.bfloat16)
+    x, w, r = rnd(m, k), rnd(n, k), rnd(m, n)
+    assert B.linear_plan(m, n, k, 32 << 20)["k_chunks"] > 1
+    scratch = torch.empty(32 << 20, dtype=torch.uint8, device=DEV).fill_(0xff)
+    out = torch.full((m + 1, n), float("nan"), dtype=torch.bfloat16, device=DEV)
+    B.linear(x, w, None, r, out[:m], scratch)
+    torch.cuda.synchronize()
+    assert torch.isnan(out[m].float()).all()
+    want = (x.double() @ w.double().T + r.double()).to(torch.bfloat16)
+    assert_stored_close(to_f64(out[:m]), to_f64(want), "split product")
+
+
 @pytest.mark.parametrize("m,n,k,chunks", [(3, 2568, 5120, 8), (64, 3584, 5184, 8), (63, 5112, 5120, 6),    # 64 token rows
                                           (65, 3584, 5120, 8), (129, 2560, 6976, 6), (128, 5120, 5120, 6)])  # 128
 def test_split_tiles_of_128_outputs(m, n, k, chunks):
