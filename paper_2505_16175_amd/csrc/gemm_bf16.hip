@@ -827,6 +827,8 @@ int gemm_tile_blocks(const GemmArgs& a) {
 // 128, weights from HBM: 3584 x 18944 at 16 tokens 28.8 / 28.1, 64 35.7 / 31.1, 100 42.5 / 35.1, 128 46.3 / 37.8, 200 61.0 /
 // 50.2, 250 70.8 / 55.7; 5120 x 13824 at 64 and 128 44.0 / 32.7 and 58.7 / 38.6; 3584 x 5120 at 64 and 128 16.0 / 15.1 and 21.6 /
 // 19.5. They need at least 5/8 of the CUs: 2560 outputs at 64 tokens, 160 workgroups, 16.9 / 15.8; 2048, 128 of them, 14.2 / 15.7.
+// Up to 32 tokens, where fewer requests are for activations, they need more than 160 of 256: 2560 x 9728 at 3, 16, 32 and 48 tokens
+// 17.9 / 18.4, 18.6 / 19.1, 19.7 / 19.7, 21.0 / 20.6; 2816 x 18944, 176 workgroups, at 3 and 16 28.8 / 28.4, 29.7 / 29.3.
 // With shorter contractions 64 outputs stay: at k = 3584 8 chunks of 28 tiles of 128 take 13.5 and of 56 tiles of 64 13.5-13.8.
 // There, up to 64 tokens, half as many chunks fill the chip if 4 of them make 7/8 to all of a workgroup per CU, with a ring of
 // 5 slots in the room of the second one, and leave half the partial sums: 3584 x 3584 at 64 and 16 tokens 13.8 / 12.2 and 11.5 /
@@ -866,7 +868,7 @@ GemmSplit gemm_plan_split(const GemmArgs& a, int mode, size_t scratch_bytes) {
     const long mid = tiles_m * ((a.n + Mid::BN - 1) / Mid::BN);
     long mid_want = std::min<long>(NARROW_ABOVE, cus / mid);
     if ((size_t)mid_want * per_chunk > scratch_bytes) mid_want = (long)(scratch_bytes / per_chunk);
-    if (mode == GEMM_PLAIN && steps >= MID_STEPS && mid_want >= 2 && mid * mid_want * 8 >= (long)cus * 5) {
+    if (mode == GEMM_PLAIN && steps >= MID_STEPS && mid_want >= 2 && mid * mid_want * 8 >= (long)cus * 5 + (a.m <= 32 ? 1 : 0)) {
       want = mid_want;
       p.narrow = Mid::BN;
     } else {

@@ -413,6 +413,13 @@ def test_split_tiles_of_128_outputs(m, n, k, chunks):
     assert_stored_close(to_f64(out), LO.bf16_round(LO.linear(to_f64(x), to_f64(w), to_f64(b)) + to_f64(r)), "128 outputs")
 
 
+@pytest.mark.parametrize("m,n,width", [(32, 2560, 64), (33, 2560, 128), (32, 2568, 128), (64, 2560, 128), (64, 2432, 64)])
+def test_tiles_of_128_outputs_need_more_of_the_chip_for_few_tokens(m, n, width):
+    """160 workgroups serve more than 32 tokens, 168 any number."""
+    p = B.linear_plan(m, n, 5120, 32 << 20)
+    assert (p["workgroups"], p["k_chunks"]) == ((-(-n // width) + 7) // 8 * 8, 8)
+
+
 @pytest.mark.parametrize("m,n,k,chunks", [(5, 504, 2304, 8), (64, 512, 2432, 8), (33, 3600, 2368, 4), (64, 3584, 3648, 4)])
 def test_narrow_split_tiles_with_a_deep_ring(m, n, k, chunks):
     """At most one workgroup per compute unit: a ring of five slots, chunks shorter and longer than it (the last of one, three
