@@ -94,7 +94,7 @@ __device__ __forceinline__ void gm_dma16(const unsigned char* base, unsigned byt
 // acc += w x, in place. The builtin leaves it to the allocator where the sum goes, and that moved accumulators around and
 // spilled. What the compiler does not know of an instruction in inline assembly is how long its result takes: the accumulators
 // meet no other instruction from their clearing to the end of the products, and there the wait is spelled out (the fragments
-// come from LDS reads, whose counter the compiler minds as for any operand).
+// come from LDS reads, whose counter the compiler minds as for any operand). tests/test_product_waits.py reads the assembly for it.
 __device__ __forceinline__ void gm_product(f32x4& acc, const u32x4& w, const u32x4& x) {
   asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+v"(acc) : "v"(w), "v"(x));
 }
@@ -374,7 +374,11 @@ __device__ __forceinline__ void gemm_tile_product(const GemmArgs& a, const TileG
 #undef GM_ISSUE_W
 
   __builtin_amdgcn_sched_barrier(0);
-  asm volatile("s_nop 15\n\ts_nop 7");  // the last products' results
+  asm volatile("s_nop 15\n\ts_nop 7");  // the last products' results, which nothing may take from in front of here
+#pragma unroll
+  for (int j = 0; j < NJ; ++j)
+#pragma unroll
+    for (int i = 0; i < NI; ++i) asm volatile("" : "+v"(acc[j][i]));
   __builtin_amdgcn_sched_barrier(0);
   // ---- store: lane owns token m = m0 + (32 MI) wm + 16 i + l16 and, in block j, outputs 4 g + 0..3
   const int u64 = (n0 >> 6) + wn;  // QKV_ROPE: which run of 64 outputs (half a head's rotary pairs) this wavefront has
