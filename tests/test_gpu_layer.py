@@ -343,6 +343,23 @@ def test_narrow_split_tiles(m, n, k):
     assert_stored_close(to_f64(out), LO.bf16_round(LO.linear(to_f64(x), to_f64(w), to_f64(b)) + to_f64(r)), "narrow tiles")
 
 
+@pytest.mark.parametrize("m,n,k,chunks", [(64, 4608, 3584, 8), (33, 3080, 4096, 8), (3, 4616, 2368, 4), (17, 4360, 2432, 8), (64, 7176, 4672, 4)])
+def test_narrow_split_tiles_with_three_slots(m, n, k, chunks):
+    """Up to 64 tokens and more than a workgroup per compute unit: 64 x 64 tiles with a ring of three slots, chunks shorter and
+    longer than it, outputs that end inside a tile."""
+    p = B.linear_plan(m, n, k, 32 << 20)
+    assert p["k_chunks"] == chunks and p["workgroups"] == (-(-n // 64) + 7) // 8 * 8 and -(-n // 64) * chunks > 256
+    g = torch.Generator(device=DEV).manual_seed(m + n + k)
+    rnd = lambda *s: torch.randn(*s, generator=g, device=DEV).to(torch.bfloat16)
+    x, w, b, r = rnd(m, k), rnd(n, k), rnd(n), rnd(m, n)
+    scratch = torch.empty(32 << 20, dtype=torch.uint8, device=DEV).fill_(0xff)
+    out = torch.full((m, n), float("nan"), dtype=torch.bfloat16, device=DEV)
+    B.linear(x, w, b, r, out, scratch)
+    torch.cuda.synchronize()
+    want = (x.double() @ w.double().T + b.double() + r.double()).to(torch.bfloat16)
+    assert_stored_close(to_f64(out), to_f64(want), "three slots")
+
+
 @pytest.mark.parametrize("rows,k", [(128, 64), (128, 192), (128, 448), (256, 64), (256, 192), (256, 448), (0, 320)])
 @pytest.mark.parametrize("m", [257, 289, 320, 353, 385, 449])
 def test_wavefronts_past_the_last_token(m, rows, k):
