@@ -249,10 +249,13 @@ __device__ __forceinline__ void gemm_tile_product(const GemmArgs& a, const TileG
   else if (n_steps >= 2) gm_wait_vmcnt<PW>();
   else gm_wait_vmcnt<0>();
   __syncthreads();
-  // Fragments: two sets of the weights', and of the activations' too where registers allow it; otherwise one, each refilled
-  // for the next k-step behind its last product (128 x 256: 2048 x 3584 x 18944 222 us with two sets, 227 with one; two sets
-  // for the last of the eight of 256 x 256, so that no read is issued right in front of the barrier, changed nothing).
-  constexpr int XSETS = NI > 4 ? 1 : 2;
+  // Fragments: two sets of the weights', and of the activations' in the small tilings; the 128 x 256 and 256 x 256 ones have one
+  // of these, each refilled for the next k-step behind its last product. 256 x 256 has no registers for two (two for the last of
+  // the eight, so that no read is issued right in front of the barrier, changed nothing). 128 x 256, us with two sets / one, weights
+  // from HBM: 2048 x 3584 x 18944 249.9 / 244.6, 2048 x 4096 x 14336 198.6 / 194.1, 1024 x 6144 x 5120 75.6 / 74.6, 768 x 8192 x 29568
+  // 414 / 409, 300 x 59136 x 8192 323 / 322 (one weight, from the caches: 2048 x 3584 x 18944 222 / 227); 128 x 64: 256 x 1024 x
+  // 4096 13.6 / 13.8, 100 x 4608 x 3584 21.7 / 21.7.
+  constexpr int XSETS = T::BN == 256 && T::MI >= 2 ? 1 : 2;
   u32x4 wf[2][NJ], xf[XSETS][NI];
 #define GM_READ_W(wst_, s_, j_) wf[s_][j_] = *(const u32x4*)((wst_) + w_frag + (j_) * 16 * ROWB + f_off[s_]);
 #define GM_READ_X(xst_, s_, i_) xf[(s_) % XSETS][i_] = *(const u32x4*)((xst_) + x_frag + (i_) * 16 * ROWB + f_off[s_]);
