@@ -75,7 +75,8 @@ qp_status qp_rope_table(const int32_t* pos, int64_t axis_stride, int32_t n_token
 /* q, k, v = h w_qkv^T + b_qkv split into heads, rotary embedding applied to q and k (pairs (i, i+64) of a head),
  * written token-major: q [n_tokens][H_q][128], k, v [n_tokens][H_kv][128]. h [n_tokens][d_model].
  * workspace: as in qp_linear, but split only where the tiles occupy at most a quarter of the compute units: other sums
- * would round otherwise and near-tied keys be kept in place of others (the rotary embedding then runs in the second launch). */
+ * would round otherwise and near-tied keys be kept in place of others; its chunks are its own, not those that qp_linear_plan
+ * reports for the sizes (the rotary embedding then runs in the second launch). */
 qp_status qp_qkv_rope(const qp_layout* layout, const void* h, const void* w_qkv, const void* b_qkv,
                       const float* cos_sin, int32_t n_tokens, int32_t d_model, void* q, void* k, void* v,
                       void* workspace, size_t workspace_bytes, void* hip_stream);
@@ -86,10 +87,11 @@ qp_status qp_swiglu_gate_up(const void* h, const void* w_gate_up, void* act, int
 
 /* The projections run 256 x 256 output tiles per workgroup, or 128 (tokens) x 256 or 128 x 128 when the larger tiles
  * would leave compute units idle; whole rounds of 256 x 256 tiles may be followed by smaller ones over the last outputs,
- * in the same launch, to the same bits; a split call of few outputs runs 64-wide tiles of 128 or, up to 64 tokens, 64
- * rows. The launcher chooses per call. This pins 256-wide tiles of so many token rows for later calls of this process
- * (tests cover both; the 128- and 64-wide tiles cannot be pinned): 0 = choose per call, 128 or 256. INVALID_ARG for any
- * other value. */
+ * in the same launch, to the same bits. A split call of few outputs runs tiles of 64 outputs, or of 128 where the
+ * contraction is long (qp_linear only), with 128 token rows or, up to 64 tokens, 64; SwiGLU of up to 64 tokens and many
+ * outputs runs 64 x 256, to the same bits. The launcher chooses per call. This pins 256-wide tiles of so many token rows
+ * for later calls of this process (tests cover both; the 128- and 64-wide tiles and those of 64 token rows cannot be
+ * pinned): 0 = choose per call, 128 or 256. INVALID_ARG for any other value. */
 qp_status qp_select_linear_tile(int32_t token_rows);
 
 /* How qp_linear would lay out a call (host arithmetic only, nothing is launched): token rows per workgroup tile,

@@ -32,8 +32,8 @@
 // each 16-key step go to lane half g) so that the accumulator layout of S^T is already the
 // operand layout of P^T; V^T is read with the same permutation.
 //
-// Schedule. What bounds the loop is the matrix pipe (64 products of 32 cycles per SIMD and tile) and, at full occupancy, the
-// power that the products and their operands cost: the chip lowers its clock. The loop is software-pipelined over three
+// Schedule. What bounds the loop is the matrix pipe (64 products of 32 cycles per SIMD and tile, and 16 small ones of 8 for the
+// row sums, 6 % more) and, at full occupancy, the power that the products and their operands cost: the chip lowers its clock. The loop is software-pipelined over three
 // consecutive blocks: one step issues S^T of block j+1, the numerators of block j and O^T += V^T P^T of block j-1, none
 // of which waits for another, in a fixed order of 16 products with two vector operations and an exponential or so behind
 // each, and fragments read three products ahead. For that the numerators must not wait for the block's max:
@@ -43,8 +43,9 @@
 //     range of bf16 and f32 would allow a reference far below the max, but the max itself is then rounded to bf16, where
 //     around itself it is an exact 1, and of a sharp row it is most of the sum: see MF_RESCALE.
 //   * The row sum of the bf16-rounded numerators is taken by four small products with ones (add_four).
-// 8192 tokens of the 7B heads over 24,576 entries, random (all-zero, which leaves the clock alone) inputs: 2945 us (2000);
-// one tile after the other with max, numerators and v_dot2 sum between the two products 3240 (2590); this pipeline with the
+// 8192 tokens of the 7B heads over 24,576 entries, random (all-zero, which leaves the clock alone) inputs: 2727 us (1967), with
+// the row sums by vector adds on the same card 2764 (1952). With those, on an earlier card: 2945 us (2000);
+// one tile after the other with max, numerators and v_dot2 sum between the two products 3240 (2590); that pipeline with the
 // v_dot2 sum and all requests behind the barrier 3220 (2500). Products in fours per kind: alternating one by one costs 1 %.
 //   * K/V tiles go global -> LDS with global_load_lds_dwordx4 (no staging registers, no ds_write):
 //     one instruction moves 64 lanes x 16 bytes into 1 KB of LDS, lane L landing at base + 16 L.
@@ -121,7 +122,8 @@ __device__ __forceinline__ void pack_pair(float e0, float e1, bf16x8& p, int i) 
 // and adds took 16 of the vector pipe for each pair of numerators, and 44 % of a step's vector instructions. At full
 // occupancy the kernel is bound by power, so instructions that are gone are time: 512 frames of 256 tokens through the 72B heads
 // 62150 -> 60920 us, 1024 of 128 through the 7B heads 22580 -> 22080, 256 of them 2348 -> 2294, 99 of 121 tokens over an 8-bit
-// cache 520 -> 503. (v_dot2_f32_bf16, two numerators each, holds the matrix pipe for 16 cycles.)
+// cache 520 -> 503; but 77 tokens of 32 heads (8 of keys) over 46,000 and 100,000 entries, three half blocks of rows, 77.8 -> 78.8 and
+// 168 -> 173: the lone one runs further ahead of its partner than the L2 holds. (v_dot2_f32_bf16, two numerators each, holds the matrix pipe for 16 cycles.)
 __device__ __forceinline__ f32x4 add_four(const bf16x8& p, int hi, f32x4 sum) {
   const s16x8 all = __builtin_bit_cast(s16x8, p);
   const s16x4 part = hi ? __builtin_shufflevector(all, all, 4, 5, 6, 7) : __builtin_shufflevector(all, all, 0, 1, 2, 3);
@@ -182,6 +184,7 @@ __global__ __launch_bounds__(MF_NT, 2) void attend_mfma_kernel(AttendArgs a) {
       // as large, up to 13 tiles (40 and 50 tokens over 20,000, 10 tiles: 31.4 / 33.0 and 33.7 / 34.4; 50 over 25,000, 13 tiles:
       // 37.5 / 37.5; 50 over 30,000 and 46,125: 40.7 / 40.0 and 51.3 / 50.3), and of three row blocks and more,
       // side by side, chunks got slower (200 over 5,000 31.4 / 34.1, 128 over 9,840 33.5 / 34.2).
+      // Chunks that do not divide among the head's XCDs would need a larger grid, which has not been tried: one by one, as before.
       if (n_whole == 0 && n_rb == 2 && a.split_tiles >= (F8 ? 14 : 10) && a.n_split % per == 0) item = (idx / 2 * per + xcd % per) * 2 + idx % 2;
     } else if (a.h_kv % 8 == 0) {
       const int hp = a.h_kv / 8;  // KV heads per XCD

@@ -24,7 +24,7 @@
 //   * SWIGLU: blocks 0 and 1 hold gate columns [n0/2 + 32 wn, +32), blocks 2 and 3 the up columns of the same outputs.
 // The shape of the product: at full occupancy the chip is bound by power, and a product of 16 x 16 x 32 costs less of it than
 // half of one of 32 x 32 x 16, whose accumulators pass through the registers every 16 k instead of every 32. Register-only
-// loops on random operands reach 2.07-2.19 PFLOP/s with the former and 1.81 with the latter (2.44 both on zeros). Both add
+// loops (mfma_peak_probe.hip) on random operands reach 2.14 PFLOP/s with the former and 1.85 with the latter (2.47 both on zeros). Both add
 // k in runs of 8, one after the other, so the results are the same bits.
 // Workgroup ids are dealt round-robin over the 8 XCDs; the workgroups an XCD runs side by side cover a block of
 // token tiles x weight tiles, which bounds what its L2 has to fetch per k-step.
@@ -226,9 +226,10 @@ __device__ __forceinline__ void gemm_tile_product(const GemmArgs& a, const TileG
   // every product they are all under way a little sooner, but ragged or short launches lose: every other / every product 1024 x
   // 6144 x 5120 76.7 / 74.9, 1920 x 3584 x 18944 256 / 250, but 1024 x 8192 x 8192 121.5 / 125.4, 2048 x 4096 x 4096 62.1 / 63.9, 300
   // x 59136 x 8192 342 / 357, 520 x 3584 x 18944 91.5 / 95.4, 900 tokens of it 132 / 139.
-  // PFLOP/s of products of 32 x 32 x 16 with the barrier behind three quarters of a step / of this loop, random inputs:
+  // PFLOP/s of products of 32 x 32 x 16 with the barrier behind three quarters of a step / of this loop, random inputs, one weight:
   // 4096 x 59136 x 8192 1.38 / 1.46, 4096 x 8192 x 29568 1.36 / 1.48, 2048 x 37888 x 3584 1.24 / 1.33, 8192 x 8192 x 8192 1.35 /
-  // 1.47, 2048 x 3584 x 18944 1.22 / 1.25, 1024 x 8192 x 8192 1.19 / 1.29. On zeros, which leave the clock alone, 8192 x 8192 x
+  // 1.47, 1024 x 8192 x 8192 1.19 / 1.29. Launches of 128 x 256 tiles with weights from HBM gained little by the shape: 2048 x 3584 x
+  // 18944 259 us / 257, x 3584 55.3 / 54.8, 1024 x 8192 x 29568 434 / 433. On zeros, which leave the clock alone, 8192 x 8192 x
   // 8192 runs at 1.80, and at 1.98 with the lines of later steps touched ahead of the requests, so that these find them in the
   // L2; on random inputs that cost 1 %.
   // Requests complete in order: when step t + 1 is awaited at the end of step t, what may stay in flight is, with equal
@@ -266,8 +267,8 @@ __device__ __forceinline__ void gemm_tile_product(const GemmArgs& a, const TileG
     if (XSETS == 1 ? (mf_) % NJ == NJ - 1 : (mf_) < NI) GM_READ_X(xst_, s_, XSETS == 1 ? (mf_) / NJ : (mf_) < NI ? (mf_) : 0)  \
   }
   // One product of k-step s by index: NJ in a row share the activations' fragment, and the last of them and the next one the
-  // weights', back and forth: every operand that stays saves power (4096 x 59136 x 8192 2655 -> 2630 us, 2048 x 37888 x 3584
-  // 409 -> 406, 2048 x 3584 x 18944 212 -> 210).
+  // weights', back and forth: every operand that stays saves power. us forth only / back and forth, weights from HBM: 8192 x 8192 x
+  // 8192 756 / 746, 4096 x 8192 x 29568 1326 / 1311, 4096 x 59136 x 8192 2760 / 2747; launches of 128 x 256 tiles do not change.
 #define GM_J(mf_) ((((mf_) / NJ) & 1) ? NJ - 1 - (mf_) % NJ : (mf_) % NJ)
 #define GM_MFMA_ONE(s_, mf_)                                                                                   \
   gm_product(acc[GM_J(mf_)][(mf_) / NJ], wf[s_][GM_J(mf_)], xf[(s_) % XSETS][(mf_) / NJ]);
@@ -431,9 +432,9 @@ __device__ __forceinline__ void gemm_tile_product(const GemmArgs& a, const TileG
   // x 3584 437 (457), now 376 (400); 4096 x 4096 x 512 31 (47), now 26 (30).
   // Each wavefront stages its own tokens x outputs, so one barrier (the ring's last readers) is all it takes. Row r's
   // 16-byte chunk c sits at c ^ (r & 7) (128-byte rows) or c ^ ((r >> 2) & 3) (64-byte rows), which keeps the 16-byte accesses
-  // free of bank conflicts. The 8-byte ones of the accumulator layout have them (a half wavefront touches one half of its
-  // chunks): counted, 4 cycles per write, 12 % of the LDS cycles at k = 512 and 2 % at k = 3584, and with a residual, which
-  // is also read 8 bytes at a time, 22 % at k = 512.
+  // free of bank conflicts. The 8-byte ones of the accumulator layout have them in 128-byte rows, where rows r and r + 8 of a
+  // half wavefront's 16 meet: counted at 8192 x 8192, 4 cycles per write, 12 % of the LDS cycles at k = 512 and 2 % at k = 3584, and
+  // 2 per read of a residual, 14 and 3 % in all.
   __syncthreads();
   constexpr int SROW = MODE == GEMM_PLAIN ? 128 : 64;  // bytes of a staged row
   constexpr int SC = SROW / 16;                         // its chunks
@@ -750,16 +751,17 @@ static std::atomic<int> g_forced_tile_rows{0};  // 0: choose per launch; 128 / 2
 void gemm_force_tile_rows(int rows) { g_forced_tile_rows.store(rows, std::memory_order_relaxed); }
 
 // The tiling that finishes soonest: a launch lasts ceil(tiles / CUs) rounds of one tile each. A tile's time by its size,
-// measured per 64-wide k-step with one workgroup per CU: 256 x 256 1.55 us, 128 x 256 0.96, 128 x 128 0.60 (fewer
+// measured per 64-wide k-step with one workgroup per CU and weights from HBM: 256 x 256 1.36 us, 128 x 256 0.82, 128 x 128 0.54
+// (one weight: 1.39, 0.76, 0.44; the costs below are of a loop of 32 x 32 x 16 products, 1.55, 0.96 and 0.60 us, and still fit). Fewer
 // products per fragment read and per request, so small tiles pay only where they fill CUs that the larger leave idle:
-// 7B o_proj at 700 tokens, 84 / 168 tiles, 48 -> 30 us; 72B down at 512, 128 / 256 tiles, 420 -> 289 us).
+// 7B o_proj at 700 tokens, 84 / 168 tiles, 47 -> 31 us; 72B down at 512, 128 / 256 tiles, 413 -> 281 us.
 //
 // Whole rounds of the large tile may be followed by a round of a smaller one instead of one that is mostly empty: the first
 // `wide` weight tiles of 256 outputs then make the whole rounds and the others take the smaller tile, in the same launch.
-// A tile's products walk k in the same order in every tiling, so the results are the same bits. us one tiling / mixed: 512 x
-// 37888 x 3584 (1 round and 160 tiles of 128 x 128) 170 / 138, 1500 360 / 342, 4096 892 / 863; 4096 x 59136 x 8192 (14 and 224 of
-// 128 x 256) 3054 / 2945; 2048 / 4096 x 10240 x 8192 315 / 281 and 574 / 522; 5000 x 3584 x 18944 739 / 605; 4096 x 4608 x 3584
-// 145 / 129. An estimate within 1.5 % keeps one tiling.
+// A tile's products walk k in the same order in every tiling, so the results are the same bits. us one tiling (the better of 256
+// and 128 token rows) / mixed, weights from HBM: SwiGLU 512 x 37888 x 3584 (1 round and 160 tiles of 128 x 128) 162 / 126, 1500 324 /
+// 310, 4096 824 / 778; 4096 x 59136 x 8192 (14 and 224 of 128 x 256) 2738 / 2644; plain 2048 / 4096 x 10240 x 8192 302 / 256 and
+// 511 / 473; 5000 x 3584 x 18944 697 / 545; 4096 x 4608 x 3584 137 / 116. An estimate within 1.5 % keeps one tiling.
 struct TileChoice {
   int rows, cols;
   double cost;  // of the launch, in 256 x 256 tiles one after the other
@@ -824,9 +826,10 @@ int gemm_tile_blocks(const GemmArgs& a) {
 //
 // Above a quarter of the CUs a product without fused steps is still split where two or three chunks of its 128 x 256 tiles
 // fill the chip (at least 4/5 of it, one round) and the estimate, with the tile times above and the partial sums at 4.5 TB/s,
-// is a tenth below the unsplit one: long contractions whose tiles leave CUs idle or are small ones. us unsplit / split:
-// 3584 x 18944 at 520 tokens 134 / 92, 640 166 / 105, 768 166 / 110, 900 146 / 132, 1024 169 / 149, 1100 163 / 149; 8192 x
-// 29568 at 400 278 / 227, 512 287 / 253. At k = 3584 (o_proj) there is nothing to gain.
+// is a tenth below the unsplit one: long contractions whose tiles leave CUs idle or are small ones. (The estimate's 1.55 and 0.95
+// us per step are those of the loop of 32 x 32 x 16 products, both about 1.15 times the present ones.) us unsplit / split, weights from HBM:
+// 3584 x 18944 at 520 tokens 136 / 89, 640 160 / 104, 768 157 / 105, 900 137 / 122, 1024 158 / 142, 1100 155 / 143; 8192 x
+// 29568 at 400 268 / 211, 512 276 / 243. At k = 3584 (o_proj) there is nothing to gain.
 //
 // Of these products of few outputs, long contractions take tiles of 128 outputs instead (64 or 128 token rows), one workgroup
 // per CU, dealt to the XCDs by items as the 256-wide ones are: an activation fragment read meets twice the outputs and a

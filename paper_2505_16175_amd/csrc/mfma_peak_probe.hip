@@ -1,11 +1,12 @@
 // Stand-alone probe: what the bf16 matrix pipe of this GPU sustains with nothing else going on.
 //
 // 512 workgroups x 8 wavefronts run v_mfma_f32_32x32x16_bf16 back to back on four independent
-// accumulators, operands held in registers (no LDS, no memory traffic in the loop). The operand
-// bits are taken from memory once: all 1.0, all zeros, or random bf16 values. The published peak
-// (2.5 PFLOP/s dense bf16) is reached with constant operands; with random operands the chip lowers
-// its clock (power management), which bounds any real kernel: attention roofline fractions in this
-// repository are quoted against the published peak, and this probe says how much of it is reachable.
+// accumulators, or v_mfma_f32_16x16x32_bf16 on eight, operands held in registers (no LDS, no memory
+// traffic in the loop). The operand bits are taken from memory once: all 1.0, all zeros, or random bf16
+// values. The published peak (2.5 PFLOP/s dense bf16) is nearly reached with constant operands; with random
+// operands the chip lowers its clock (power management), less so for the second shape, which bounds any
+// real kernel: attention roofline fractions in this repository are quoted against the published peak, and
+// this probe says how much of it is reachable.
 // A second part (overlap_loop below) measures how far vector work hides under another wavefront's MFMAs.
 #include <hip/hip_runtime.h>
 #include <stdio.h>
@@ -13,6 +14,7 @@
 
 typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8;
 typedef __attribute__((__vector_size__(16 * sizeof(float)))) float f32x16;
+typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4;
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 
 __global__ __launch_bounds__(512) void mfma_loop(const u32x4* src, float* out, int iters) {
@@ -33,6 +35,27 @@ __global__ __launch_bounds__(512) void mfma_loop(const u32x4* src, float* out, i
   float s = 0;
   for (int n = 0; n < 4; ++n)
     for (int r = 0; r < 16; ++r) s += acc[n][r];
+  out[blockIdx.x * blockDim.x + threadIdx.x] = s;
+}
+
+// The same flops per iteration in products of 16 x 16 x 32.
+__global__ __launch_bounds__(512) void mfma_loop16(const u32x4* src, float* out, int iters) {
+  bf16x8 a[8], b[8];
+  for (int i = 0; i < 8; ++i) {
+    a[i] = __builtin_bit_cast(bf16x8, src[(threadIdx.x * 16 + i) & 8191]);
+    b[i] = __builtin_bit_cast(bf16x8, src[(threadIdx.x * 16 + 8 + i) & 8191]);
+  }
+  f32x4 acc[8];
+  for (int n = 0; n < 8; ++n) acc[n] = f32x4{0.f, 0.f, 0.f, 0.f};
+  for (int it = 0; it < iters; ++it) {
+#pragma unroll
+    for (int i = 0; i < 8; ++i)
+#pragma unroll
+      for (int n = 0; n < 8; ++n) acc[n] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[(i + n) & 7], b[i], acc[n], 0, 0, 0);
+  }
+  float s = 0;
+  for (int n = 0; n < 8; ++n)
+    for (int r = 0; r < 4; ++r) s += acc[n][r];
   out[blockIdx.x * blockDim.x + threadIdx.x] = s;
 }
 
@@ -127,22 +150,28 @@ int main() {
       }
     }
     CHECK(hipMemcpy(src, h, 8192 * 16, hipMemcpyHostToDevice));
-    const int iters = 4000;  // 32 MFMAs per iteration and wavefront
-    hipEvent_t e0, e1;
-    CHECK(hipEventCreate(&e0));
-    CHECK(hipEventCreate(&e1));
-    hipLaunchKernelGGL(mfma_loop, dim3(512), dim3(512), 0, 0, src, out, iters);
-    CHECK(hipDeviceSynchronize());
-    CHECK(hipEventRecord(e0));
-    for (int r = 0; r < 5; ++r) hipLaunchKernelGGL(mfma_loop, dim3(512), dim3(512), 0, 0, src, out, iters);
-    CHECK(hipEventRecord(e1));
-    CHECK(hipEventSynchronize(e1));
-    float ms;
-    CHECK(hipEventElapsedTime(&ms, e0, e1));
-    ms /= 5;
-    const double flops = 512.0 * 8 * iters * 32 * 32768.0;
-    printf("operands %s: %.3f ms per launch, %.1f TFLOP/s (%.1f %% of 2500)\n", names[mode], ms, flops / ms / 1e9,
-           flops / ms / 1e9 / 25.0);
+    const int iters = 4000;  // 32 (64) products per iteration and wavefront
+    const struct {
+      const char* name;
+      void (*loop)(const u32x4*, float*, int);
+    } shapes[] = {{"32x32x16", mfma_loop}, {"16x16x32", mfma_loop16}};
+    for (const auto& shape : shapes) {
+      hipEvent_t e0, e1;
+      CHECK(hipEventCreate(&e0));
+      CHECK(hipEventCreate(&e1));
+      hipLaunchKernelGGL(shape.loop, dim3(512), dim3(512), 0, 0, src, out, iters);
+      CHECK(hipDeviceSynchronize());
+      CHECK(hipEventRecord(e0));
+      for (int r = 0; r < 5; ++r) hipLaunchKernelGGL(shape.loop, dim3(512), dim3(512), 0, 0, src, out, iters);
+      CHECK(hipEventRecord(e1));
+      CHECK(hipEventSynchronize(e1));
+      float ms;
+      CHECK(hipEventElapsedTime(&ms, e0, e1));
+      ms /= 5;
+      const double flops = 512.0 * 8 * iters * 32 * 32768.0;
+      printf("products %s, operands %s: %.3f ms per launch, %.1f TFLOP/s (%.1f %% of 2500)\n", shape.name, names[mode], ms,
+             flops / ms / 1e9, flops / ms / 1e9 / 25.0);
+    }
   }
   // co-execution of MFMA and vector work on one SIMD
   const int modes[] = {1, 2, 3, 5, 10, 9, 15, 15 | 32, 15 | 32 | 64, 15 | 32 | 128, 15 | 16, 15 | 16 | 32, 15 | 16 | 32 | 64};
