@@ -95,6 +95,9 @@ constexpr float MF_RESCALE = 64.f;
 // barrier and the way through LDS take longer than what whole rows save. us of the call from the accumulators / through LDS:
 // 7B heads, 5 tokens (35 rows) over 600, 5,000 and 20,000 entries 11.9 / 12.6, 12.5 / 13.1, 16.4 / 17.1; 9 tokens over 5,000
 // 13.8 / 14.1, 11 tokens 15.2 / 15.4, 14 (98 rows) 16.4 / 16.2, 18 17.5 / 17.1; 72B heads, 5 tokens (40 rows) over 5,000 14.4 / 15.0.
+// With more than a tile of tokens, which so few rows have only where every query head has keys of its own, four live wavefronts
+// are stored so too: of the last chunk they end at their horizons, and the barrier would hold them until the last has ended. 16 such
+// heads, 100 tokens over 600 and 5,000 entries 14.7 / 15.5, 21.0 / 21.7, 128 over 600 15.3 / 15.7, over 20,000 39.1 / 38.7.
 constexpr int MF_DIRECT_ROWS = 96;
 constexpr int MF_VMCNT0 = 0x0f70;       // s_waitcnt vmcnt(0), other counters untouched
 constexpr int MF_VMCNT4 = 0x0f74;       // s_waitcnt vmcnt(4)
@@ -610,7 +613,7 @@ __global__ __launch_bounds__(MF_NT, 2) void attend_mfma_kernel(AttendArgs a) {
 
   if (my_split > 1) {
     // partial result of this chunk: every chunk starts on a cache tile, whose keys all rows see, so l_tot > 0
-    const bool staged = n_rows > MF_DIRECT_ROWS;
+    const bool staged = n_rows > (a.n_g > MF_BN ? MF_HB : MF_DIRECT_ROWS);
     if (staged) __syncthreads();  // the ring's last readers (its last requests have landed, see turn)
     if (!wave_live) return;
     const float l_tot = sum_halves(l_run);

@@ -135,9 +135,10 @@ def test_group_attend_split_partial_rows(h_q, h_kv, n_g, c, fp8):
 @pytest.mark.gpu
 @pytest.mark.parametrize("fp8", [False, True])
 @pytest.mark.parametrize("h_q,h_kv,n_g,c", [(28, 4, 3, 600), (28, 4, 5, 1000), (14, 2, 9, 3000), (64, 8, 12, 1500), (12, 2, 16, 900),
-                                            (28, 4, 14, 2000), (64, 8, 13, 1500)])
+                                            (28, 4, 14, 2000), (64, 8, 13, 1500), (16, 16, 100, 600), (8, 8, 128, 1300), (8, 8, 130, 1300)])
 def test_group_attend_split_partial_rows_of_few_tokens(h_q, h_kv, n_g, c, fp8):
-    """Up to 96 rows of a KV head leave from the accumulators, more through LDS: 21 to 96 rows, whole wavefronts and not, 98, 104."""
+    """Up to 96 rows of a KV head leave from the accumulators, 128 where their tokens make two tiles, more through LDS: 21 to 96
+    rows, whole wavefronts and not, 98, 104; 100, 128 and 130 tokens of one row each."""
     test_group_attend_split_partial_rows(h_q, h_kv, n_g, c, fp8)
 
 
