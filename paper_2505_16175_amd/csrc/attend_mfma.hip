@@ -620,7 +620,6 @@ __global__ __launch_bounds__(MF_NT, 2) void attend_mfma_kernel(AttendArgs a) {
     const float inv = 1.f / l_tot;
     const size_t prow0 = (size_t)chunk * ((size_t)a.h_kv * a.part_rows) + (size_t)h * a.part_rows + row0;
     float* const po = a.part_o + prow0 * MF_D;
-    if (g == 0 && row_ok) a.part_lse[prow0 + l32] = m_run * c2 + log2f(l_tot);
     if (!staged) {
       if (!row_ok) return;
 #pragma unroll
@@ -629,6 +628,7 @@ __global__ __launch_bounds__(MF_NT, 2) void attend_mfma_kernel(AttendArgs a) {
         for (int q4 = 0; q4 < 4; ++q4)
           *(float4*)(po + l32 * MF_D + 32 * n + 8 * q4 + 4 * g) =
               make_float4(o[n][4 * q4] * inv, o[n][4 * q4 + 1] * inv, o[n][4 * q4 + 2] * inv, o[n][4 * q4 + 3] * inv);
+      if (g == 0) a.part_lse[prow0 + l32] = m_run * c2 + log2f(l_tot);
       return;
     }
     // Through LDS, 16-byte chunk c of row r at c ^ (r & 15), which keeps both sides free of bank conflicts: a store then
@@ -646,6 +646,7 @@ __global__ __launch_bounds__(MF_NT, 2) void attend_mfma_kernel(AttendArgs a) {
       for (int q4 = 0; q4 < 4; ++q4)
         *(float4*)(stage + l32 * (MF_D * 4) + ((8 * n + 2 * q4 + g) ^ (l32 & 15)) * 16) =
             make_float4(o[n][4 * q4] * inv, o[n][4 * q4 + 1] * inv, o[n][4 * q4 + 2] * inv, o[n][4 * q4 + 3] * inv);
+    if (g == 0 && row_ok) a.part_lse[prow0 + l32] = m_run * c2 + log2f(l_tot);
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // the wavefront's writes before its reads
 #pragma unroll
     for (int u = 0; u < 16; ++u) {
